@@ -2,11 +2,13 @@
 //
 //   learned_sample   kSamples evenly spaced (key, rank) pairs of the sorted
 //                    keys -> inputs x = top 24 key bits / 2^24, targets rank/n.
-//   learned_train    one workgroup: quantile initialisation of the ramps, then
-//                    Adam steps on the mean squared error over batches of 128
-//                    samples (forward and backward written out below), with
-//                    w1, W2, w3 projected onto >= 0 after every step so that
-//                    the router stays monotone.
+//   learned_init     quantile initialisation of the ramps.
+//   learned_train    one workgroup: Adam steps on the mean squared error over
+//                    batches of 128 samples (forward and backward written out
+//                    below), with w1, W2, w3 projected onto >= 0 after every
+//                    step so that the router stays monotone.
+//   learned_errors   every sample's squared error and their mean, before and
+//   learned_loss     after the training.
 //   learned_xbounds  tabulation of the trained router: the first input X of
 //   learned_radix    every leaf (a binary search over X per leaf, valid
 //                    because routing is monotone) and the leaf at every
@@ -27,119 +29,196 @@ namespace sfc {
 namespace {
 
 constexpr int kBatch = 128;
-constexpr int kTrainThreads = 256;
+constexpr int kTrainWaves = 8;
+constexpr int kTrainThreads = kTrainWaves * kWave;
 
 __device__ __forceinline__ float clip01(float v) { return fminf(fmaxf(v, 0.f), 1.f); }
 __device__ __forceinline__ float inside01(float v) { return (v > 0.f && v < 1.f) ? 1.f : 0.f; }
 
-// Gradient of the batch's mean squared error, written into G (kParams, LDS),
-// for parameters P (LDS).  Threads 0..cnt-1 hold one sample each (x, t);
-// sh1 and sd2 are LDS scratch [kBatch][kHidden + 1].  Returns the batch loss
-// in every thread.  The summation order is fixed, so the result does not
-// depend on timing.
-__device__ float batch_gradient(const float* P, float* G, float x, float t, int cnt,
-                                float (*sh1)[kHidden + 1], float (*sd2)[kHidden + 1],
-                                float* s_red) {
-  const int tid = threadIdx.x;
-  const bool mine = tid < cnt;
-  float a1[kHidden], a2[kHidden];
-  float g = 0.f, y = 0.f;
-  if (mine) {
+// ---- one training step on the matrix cores -----------------------------------
+//
+// A step is three products over the batch of 128 samples (the second layer's
+// forward, its transpose backward, and the weight gradient) and five column
+// sums, 4 * 10^5 multiply-adds in a chain of 256 steps: one workgroup, bound
+// by the length of a step's dependent chain.  The products run as
+// v_mfma_f32_16x16x4_f32, which adds its four terms one after another, each
+// a fused multiply-add rounded once (checked bit for bit against fmaf), so a
+// chain of them is the plain loop over k, and the parameters are those that
+// loop gives, bit for bit.
+//
+// Wave w holds samples 16 w .. 16 w + 15, sample l % 16 in lane l, and of each
+// sample's 32 units those with index 4 s + l / 16 (s = 0..7).  The rows of a
+// product are numbered so that its result (unit 4 (4 t + v) + l / 16 in
+// register v of tile t) is the next product's operand as it stands: hidden
+// values, output and back-propagated errors never leave the registers.  Only
+// the weight gradient, whose sum runs over the samples, goes through LDS:
+// waves 0..3 take one 16x16 tile of it each, waves 4..6 the column sums, and
+// each lane updates (Adam) the parameters whose gradients it holds.
+// 256 steps over 2^16 samples take 0.94 ms; 26.1 ms with one sample per lane
+// and every weight read from LDS for each multiply-add.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kWStride = 36;             // LDS row of 32 weights
+constexpr int kQStride = 36;             // samples of equal b % 4, by b / 4
+constexpr int kBStride = 4 * kQStride + 4;   // LDS row of 128 samples
+constexpr int kOwned = 4;                // parameters a lane owns at most
+
+// Rows of 128 samples in LDS, one per unit.
+enum { kRowD2 = 0, kRowH1 = 32, kRowE3 = 64, kRowD1X = 96, kRowD1 = 128, kRowG = 160, kRows = 161 };
+
+struct TrainLds {
+  float w2[kHidden * kWStride];    // [i][unit_pos(j)]
+  float w2t[kHidden * kWStride];   // [j][unit_pos(i)]
+  float w1[kHidden], b1[kHidden], b2[kHidden], w3[kHidden];   // [unit_pos(unit)]
+  float b3[4];
+  float rows[kRows * kBStride];    // [row][sample_pos(b)]
+};
+
+// Units of equal index % 4 are neighbours, so that a lane's eight are two
+// 16-byte loads; samples likewise.
+__device__ __forceinline__ int unit_pos(int k) { return (k & 3) * 8 + (k >> 2); }
+__device__ __forceinline__ int sample_pos(int b) { return (b & 3) * kQStride + (b >> 2); }
+
+// Eight consecutive LDS words (16-byte aligned).
+__device__ __forceinline__ void load8(const float* p, float v[8]) {
+  const f32x4 a = *(const f32x4*)p, b = *(const f32x4*)(p + 4);
 #pragma unroll
-    for (int j = 0; j < kHidden; ++j) a1[j] = __fmaf_rn(P[kOffW1 + j], x, P[kOffB1 + j]);
-    y = P[kOffB3];
-#pragma unroll
-    for (int i = 0; i < kHidden; ++i) {
-      float a = P[kOffB2 + i];
-#pragma unroll
-      for (int j = 0; j < kHidden; ++j)
-        a = __fmaf_rn(P[kOffW2 + i * kHidden + j], clip01(a1[j]), a);
-      a2[i] = a;
-      y = __fmaf_rn(P[kOffW3 + i], clip01(a), y);
-    }
-    g = 2.f * (y - t) / (float)cnt;
-#pragma unroll
-    for (int j = 0; j < kHidden; ++j) sh1[tid][j] = clip01(a1[j]);
-#pragma unroll
-    for (int i = 0; i < kHidden; ++i) sd2[tid][i] = g * P[kOffW3 + i] * inside01(a2[i]);
+  for (int i = 0; i < 4; ++i) {
+    v[i] = a[i];
+    v[4 + i] = b[i];
   }
-  // Batch loss (fixed tree over LDS).
-  s_red[tid] = mine ? (y - t) * (y - t) : 0.f;
-  __syncthreads();
-  for (int o = kTrainThreads / 2; o > 0; o >>= 1) {
-    if (tid < o) s_red[tid] += s_red[tid + o];
-    __syncthreads();
+}
+
+// Parameter r of the ones this lane owns (r < kOwned; -1: none): waves 0..3
+// the second layer's weights (tile (w & 1, w >> 1) of the matrix, rows
+// 4 (l / 16) + r, column l % 16), wave 4 its biases and the output weights,
+// wave 5 the first layer's weights and biases, wave 6's first lane the output
+// bias.
+__device__ __forceinline__ int owned_param(int r) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  if (w < 4) {
+    const int i = 16 * (w & 1) + 4 * (l >> 4) + r, j = 16 * (w >> 1) + (l & 15);
+    return kOffW2 + i * kHidden + j;
   }
-  const float loss = s_red[0] / (float)(cnt > 0 ? cnt : 1);
+  if (r > 0) return -1;
+  if (w == 4) return l < kHidden ? kOffB2 + l : kOffW3 + l - kHidden;
+  if (w == 5) return l < kHidden ? kOffW1 + l : kOffB1 + l - kHidden;
+  return w == 6 && l == 0 ? kOffB3 : -1;
+}
+
+// Puts parameter `at` into its places in LDS.
+__device__ __forceinline__ void store_param(TrainLds& S, int at, float v) {
+  if (at >= kOffW2 && at < kOffB2) {
+    const int i = (at - kOffW2) / kHidden, j = (at - kOffW2) % kHidden;
+    S.w2[i * kWStride + unit_pos(j)] = v;
+    S.w2t[j * kWStride + unit_pos(i)] = v;
+  } else if (at >= kOffB3) {
+    S.b3[0] = v;
+  } else if (at >= kOffW3) {
+    S.w3[unit_pos(at - kOffW3)] = v;
+  } else if (at >= kOffB2) {
+    S.b2[unit_pos(at - kOffB2)] = v;
+  } else if (at >= kOffB1) {
+    S.b1[unit_pos(at - kOffB1)] = v;
+  } else if (at >= 0) {
+    S.w1[unit_pos(at)] = v;
+  }
+}
+
+// Gradient of the mean squared error over samples 0..cnt - 1 of a batch for
+// the parameters in S: G[r] is that of owned_param(r).  x, t: the sample of
+// this lane, 16 w + l % 16 (zeros from cnt on).  Returns the sample's error
+// y - t.  One barrier; the caller's next one ends the reads of S.
+__device__ __forceinline__ float batch_gradient(TrainLds& S, float x, float t, int cnt,
+                                                float G[kOwned]) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, c = l & 15, grp = l >> 4;
+  const bool mine = 16 * w + c < cnt;
+  // Forward.  Row r of tile t stands for unit 16 t + 4 (r % 4) + r / 4.
+  const int row0 = 4 * (c & 3) + (c >> 2);
+  float w1[8], b1[8], w3[8], a1[8], h1[8], a2[8], h2[8];
+  load8(S.w1 + 8 * grp, w1);
+  load8(S.b1 + 8 * grp, b1);
+  f32x4 acc[2];
+  acc[0] = *(const f32x4*)(S.b2 + 8 * grp);
+  acc[1] = *(const f32x4*)(S.b2 + 8 * grp + 4);
+  float m0[8], m1[8];
+  load8(S.w2 + row0 * kWStride + 8 * grp, m0);
+  load8(S.w2 + (row0 + 16) * kWStride + 8 * grp, m1);
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    a1[s] = __fmaf_rn(w1[s], x, b1[s]);
+    h1[s] = clip01(a1[s]);
+    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(m0[s], h1[s], acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(m1[s], h1[s], acc[1], 0, 0, 0);
+  }
+  load8(S.w3 + 8 * grp, w3);
+  load8(S.w2t + row0 * kWStride + 8 * grp, m0);
+  load8(S.w2t + (row0 + 16) * kWStride + 8 * grp, m1);
+  const float b3 = S.b3[0];
+  f32x4 yv = {b3, b3, b3, b3};   // every row of this product is the output
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    a2[s] = acc[s >> 2][s & 3];
+    h2[s] = clip01(a2[s]);
+    yv = __builtin_amdgcn_mfma_f32_16x16x4f32(w3[s], h2[s], yv, 0, 0, 0);
+  }
+  const float err = yv[0] - t;
+  const float g = mine ? 2.f * err / (float)cnt : 0.f;
+  // Backward through the second layer.
+  float* at = S.rows + grp * kBStride + sample_pos(16 * w + c);   // unit 4 s + grp: row 4 s + grp
+  acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const float d2 = mine ? g * w3[s] * inside01(a2[s]) : 0.f;
+    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(m0[s], d2, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(m1[s], d2, acc[1], 0, 0, 0);
+    at[(kRowD2 + 4 * s) * kBStride] = d2;
+    at[(kRowH1 + 4 * s) * kBStride] = h1[s];
+    at[(kRowE3 + 4 * s) * kBStride] = mine ? g * h2[s] : 0.f;
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const float d1 = mine ? acc[s >> 2][s & 3] * inside01(a1[s]) : 0.f;
+    at[(kRowD1X + 4 * s) * kBStride] = d1 * x;
+    at[(kRowD1 + 4 * s) * kBStride] = d1;
+  }
+  if (grp == 0) at[kRowG * kBStride] = g;
   __syncthreads();
 
-  // dW2[i][j] = sum_b d2[b][i] h1[b][j]; db2[i] = sum_b d2[b][i].
-  for (int e = tid; e < kHidden * kHidden; e += kTrainThreads) {
-    const int i = e / kHidden, j = e % kHidden;
-    float acc = 0.f;
-    for (int b = 0; b < cnt; ++b) acc = __fmaf_rn(sd2[b][i], sh1[b][j], acc);
-    G[kOffW2 + e] = acc;
-  }
-  if (tid < kHidden) {
-    float acc = 0.f;
-    for (int b = 0; b < cnt; ++b) acc += sd2[b][tid];
-    G[kOffB2 + tid] = acc;
-  }
-  __syncthreads();
-
-  // Second phase: reuse the scratch for d1 = (W2^T d2) * clip'(a1) and
-  // e = g * h2 (for dw3).
-  float d1[kHidden], e3[kHidden];
-  if (mine) {
+  if (w < 4) {
+    // dW2[i][j] = sum over the samples, in order, of d2[i] h1[j].
+    const float* pa = S.rows + (kRowD2 + 16 * (w & 1) + c) * kBStride + grp * kQStride;
+    const float* pb = S.rows + (kRowH1 + 16 * (w >> 1) + c) * kBStride + grp * kQStride;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < kHidden; ++j) d1[j] = 0.f;
+    for (int q = 0; q < kBatch / 4; q += 4) {
+      const f32x4 va = *(const f32x4*)(pa + q), vb = *(const f32x4*)(pb + q);
 #pragma unroll
-    for (int i = 0; i < kHidden; ++i) {
-      const float di = sd2[tid][i];
-#pragma unroll
-      for (int j = 0; j < kHidden; ++j) d1[j] = __fmaf_rn(di, P[kOffW2 + i * kHidden + j], d1[j]);
-      e3[i] = g * clip01(a2[i]);
+      for (int i = 0; i < 4; ++i)
+        sum = __builtin_amdgcn_mfma_f32_16x16x4f32(va[i], vb[i], sum, 0, 0, 0);
     }
 #pragma unroll
-    for (int j = 0; j < kHidden; ++j) d1[j] *= inside01(a1[j]);
-  }
-  __syncthreads();
-  if (mine) {
+    for (int r = 0; r < kOwned; ++r) G[r] = sum[r];
+  } else if (w < 7) {
+    // The row's sum over the samples, in order.
+    const int row = w == 4 ? (l < kHidden ? kRowD2 + l : kRowE3 + l - kHidden)
+                    : w == 5 ? (l < kHidden ? kRowD1X + l : kRowD1 + l - kHidden)
+                             : kRowG;
+    const float* p = S.rows + row * kBStride;
+    float sum = 0.f;
 #pragma unroll
-    for (int j = 0; j < kHidden; ++j) {
-      sh1[tid][j] = d1[j] * x;   // contribution to dw1
-      sd2[tid][j] = d1[j];       // contribution to db1
-    }
-  }
-  __syncthreads();
-  if (tid < kHidden) {
-    float aw = 0.f, ab = 0.f;
-    for (int b = 0; b < cnt; ++b) {
-      aw += sh1[b][tid];
-      ab += sd2[b][tid];
-    }
-    G[kOffW1 + tid] = aw;
-    G[kOffB1 + tid] = ab;
-  }
-  __syncthreads();
-  if (mine) {
+    for (int q = 0; q < kBatch / 4; q += 4) {
+      f32x4 v[4];
 #pragma unroll
-    for (int i = 0; i < kHidden; ++i) sh1[tid][i] = e3[i];
-    sd2[tid][0] = g;
+      for (int k = 0; k < 4; ++k) v[k] = *(const f32x4*)(p + k * kQStride + q);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum += v[k][i];
+    }
+    G[0] = sum;
   }
-  __syncthreads();
-  if (tid < kHidden) {
-    float acc = 0.f;
-    for (int b = 0; b < cnt; ++b) acc += sh1[b][tid];
-    G[kOffW3 + tid] = acc;
-  }
-  if (tid == kHidden) {
-    float acc = 0.f;
-    for (int b = 0; b < cnt; ++b) acc += sd2[b][0];
-    G[kOffB3] = acc;
-  }
-  __syncthreads();
-  return loss;
+  return err;
 }
 
 __global__ __launch_bounds__(kTrainThreads) void learned_grad_kernel(const float* __restrict__ p_in,
@@ -148,16 +227,27 @@ __global__ __launch_bounds__(kTrainThreads) void learned_grad_kernel(const float
                                                                      int cnt,
                                                                      float* __restrict__ g_out,
                                                                      float* __restrict__ loss_out) {
-  __shared__ float P[kParams], G[kParams];
-  __shared__ float sh1[kBatch][kHidden + 1], sd2[kBatch][kHidden + 1];
-  __shared__ float s_red[kTrainThreads];
-  for (int i = threadIdx.x; i < kParams; i += kTrainThreads) P[i] = p_in[i];
+  __shared__ TrainLds S;
+  __shared__ float s_red[kBatch];
+  for (int i = threadIdx.x; i < kParams; i += kTrainThreads) store_param(S, i, p_in[i]);
   __syncthreads();
-  const int tid = threadIdx.x;
-  const float x = tid < cnt ? xs[tid] : 0.f, t = tid < cnt ? ts[tid] : 0.f;
-  const float loss = batch_gradient(P, G, x, t, cnt, sh1, sd2, s_red);
-  for (int i = tid; i < kParams; i += kTrainThreads) g_out[i] = G[i];
-  if (tid == 0) loss_out[0] = loss;
+  const int b = 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
+  const float x = b < cnt ? xs[b] : 0.f, t = b < cnt ? ts[b] : 0.f;
+  float G[kOwned];
+  const float err = batch_gradient(S, x, t, cnt, G);
+#pragma unroll
+  for (int r = 0; r < kOwned; ++r) {
+    const int at = owned_param(r);
+    if (at >= 0) g_out[at] = G[r];
+  }
+  // Batch loss (fixed tree over LDS).
+  if ((threadIdx.x & 63) < 16) s_red[b] = b < cnt ? err * err : 0.f;
+  __syncthreads();
+  for (int o = kBatch / 2; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) s_red[threadIdx.x] += s_red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) loss_out[0] = s_red[0] / (float)(cnt > 0 ? cnt : 1);
 }
 
 __global__ __launch_bounds__(256) void learned_sample(const uint64_t* __restrict__ keys, uint64_t n,
@@ -170,47 +260,20 @@ __global__ __launch_bounds__(256) void learned_sample(const uint64_t* __restrict
   ts[s] = (float)((double)i / (double)n);
 }
 
-// Mean squared error of the router over all samples (one workgroup).
-__device__ float sample_loss(const float* P, const float* __restrict__ xs,
-                             const float* __restrict__ ts, uint32_t S, float* s_red) {
-  float acc = 0.f;
-  for (uint32_t s = threadIdx.x; s < S; s += kTrainThreads) {
-    const float d = router_output(P, xs[s]) - ts[s];
-    acc += d * d;
-  }
-  s_red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int o = kTrainThreads / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) s_red[threadIdx.x] += s_red[threadIdx.x + o];
-    __syncthreads();
-  }
-  const float r = s_red[0] / (float)S;
-  __syncthreads();
-  return r;
-}
-
-__global__ __launch_bounds__(kTrainThreads) void learned_train(const float* __restrict__ xs,
-                                                               const float* __restrict__ ts,
-                                                               uint32_t S, uint32_t steps, float lr,
-                                                               float* __restrict__ p_out,
-                                                               float* __restrict__ losses) {
-  __shared__ float P[kParams], G[kParams], Mo[kParams], Vo[kParams];
-  __shared__ float sh1[kBatch][kHidden + 1], sd2[kBatch][kHidden + 1];
-  __shared__ float s_red[kTrainThreads];
+// Quantile initialisation: ramp j rises from quantile j/32 to (j+1)/32 of the
+// sample inputs; identity second layer; output = mean of the ramps.
+__global__ __launch_bounds__(256) void learned_init(const float* __restrict__ xs, uint32_t S,
+                                                    float* __restrict__ P) {
   const int tid = threadIdx.x;
-  // Quantile initialisation: ramp j rises from quantile j/32 to (j+1)/32 of
-  // the sample inputs; identity second layer; output = mean of the ramps.
-  for (int i = tid; i < kParams; i += kTrainThreads) {
+  for (int i = kOffW2 + tid; i < kParams; i += 256) {
     float v = 0.f;
-    if (i >= kOffW2 && i < kOffB2) {
+    if (i < kOffB2) {
       const int e = i - kOffW2;
       v = (e / kHidden == e % kHidden) ? 1.f : 0.f;
     } else if (i >= kOffW3 && i < kOffB3) {
       v = 1.f / (float)kHidden;
     }
     P[i] = v;
-    Mo[i] = 0.f;
-    Vo[i] = 0.f;
   }
   if (tid < kHidden) {
     const float q0 = xs[(uint64_t)tid * S / kHidden];
@@ -220,42 +283,99 @@ __global__ __launch_bounds__(kTrainThreads) void learned_train(const float* __re
     P[kOffW1 + tid] = 1.f / span;
     P[kOffB1 + tid] = -q0 / span;
   }
-  __syncthreads();
-  const float loss0 = sample_loss(P, xs, ts, S, s_red);
+}
 
+// Squared error of the router at every sample.
+__global__ __launch_bounds__(256) void learned_errors(const float* __restrict__ P,
+                                                      const float* __restrict__ xs,
+                                                      const float* __restrict__ ts, uint32_t S,
+                                                      float* __restrict__ sq) {
+  const uint32_t s = blockIdx.x * 256 + threadIdx.x;
+  if (s >= S) return;
+  const float d = router_output(P, xs[s]) - ts[s];
+  sq[s] = d * d;
+}
+
+// Mean of the S squared errors (one workgroup): 256 strided sums, then a tree.
+__global__ __launch_bounds__(256) void learned_loss(const float* __restrict__ sq, uint32_t S,
+                                                    float* __restrict__ loss) {
+  __shared__ float s_red[256];
+  float acc = 0.f;
+  // Eight loads in flight per thread, added in order (positions past the end
+  // load the last one and add nothing).
+  for (uint32_t s0 = threadIdx.x; s0 < S; s0 += 256 * 8) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = sq[s0 + 256 * k < S ? s0 + 256 * k : S - 1];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (s0 + 256 * k < S) acc += v[k];
+  }
+  s_red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) s_red[threadIdx.x] += s_red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) loss[0] = s_red[0] / (float)S;
+}
+
+// Adam over `steps` batches, in place on the parameters (one workgroup).
+// Batch st: samples (odd multiplier) * (st * kBatch + b) mod S, a permutation
+// of the samples within every pass over them.
+__global__ __launch_bounds__(kTrainThreads) void learned_train(const float* __restrict__ xs,
+                                                               const float* __restrict__ ts,
+                                                               uint32_t S, uint32_t steps, float lr,
+                                                               float* __restrict__ params) {
+  __shared__ TrainLds L;
+  const int b = 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
+  float P[kOwned], Mo[kOwned], Vo[kOwned];
+#pragma unroll
+  for (int r = 0; r < kOwned; ++r) {
+    const int at = owned_param(r);
+    P[r] = at >= 0 ? params[at] : 0.f;
+    Mo[r] = Vo[r] = 0.f;
+    if (at >= 0) store_param(L, at, P[r]);
+  }
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   float b1t = 1.f, b2t = 1.f;
   const uint32_t mask = S - 1;   // S is a power of two
+  // A step's samples are loaded during the step before it.
+  uint32_t s = (uint32_t)((uint64_t)b * 2654435761ull) & mask;
+  float x = xs[s], t = ts[s];
+  const int owned = (threadIdx.x >> 6) < 4 ? kOwned : (threadIdx.x >> 6) < 7 ? 1 : 0;
+  __syncthreads();
   for (uint32_t st = 0; st < steps; ++st) {
-    // Batch st: samples (odd multiplier) * (st * kBatch + tid) mod S, a
-    // permutation of the samples within every pass over them.
-    const int cnt = kBatch;
-    float x = 0.f, t = 0.f;
-    if (tid < cnt) {
-      const uint32_t s = (uint32_t)(((uint64_t)st * kBatch + tid) * 2654435761ull) & mask;
-      x = xs[s];
-      t = ts[s];
-    }
-    batch_gradient(P, G, x, t, cnt, sh1, sd2, s_red);
+    s = (uint32_t)(((uint64_t)(st + 1) * kBatch + b) * 2654435761ull) & mask;
+    const float nx = xs[s], nt = ts[s];
+    float G[kOwned] = {0.f, 0.f, 0.f, 0.f};
+    batch_gradient(L, x, t, kBatch, G);
     b1t *= b1;
     b2t *= b2;
-    for (int i = tid; i < kParams; i += kTrainThreads) {
-      const float gi = G[i];
-      Mo[i] = b1 * Mo[i] + (1.f - b1) * gi;
-      Vo[i] = b2 * Vo[i] + (1.f - b2) * gi * gi;
-      const float mh = Mo[i] / (1.f - b1t), vh = Vo[i] / (1.f - b2t);
-      float v = P[i] - lr * mh / (sqrtf(vh) + eps);
-      const bool nonneg = (i < kOffB1) || (i >= kOffW2 && i < kOffB2) || (i >= kOffW3 && i < kOffB3);
+#pragma unroll
+    for (int r = 0; r < kOwned; ++r) {
+      if (r >= owned) break;
+      const int at = owned_param(r);
+      if (at < 0) break;
+      const float gi = G[r];
+      Mo[r] = b1 * Mo[r] + (1.f - b1) * gi;
+      Vo[r] = b2 * Vo[r] + (1.f - b2) * gi * gi;
+      const float mh = Mo[r] / (1.f - b1t), vh = Vo[r] / (1.f - b2t);
+      float v = P[r] - lr * mh / (sqrtf(vh) + eps);
+      const bool nonneg =
+          (at < kOffB1) || (at >= kOffW2 && at < kOffB2) || (at >= kOffW3 && at < kOffB3);
       if (nonneg) v = fmaxf(v, 0.f);
-      P[i] = v;
+      P[r] = v;
+      store_param(L, at, v);
     }
+    x = nx;
+    t = nt;
     __syncthreads();
   }
-  const float loss1 = sample_loss(P, xs, ts, S, s_red);
-  for (int i = tid; i < kParams; i += kTrainThreads) p_out[i] = P[i];
-  if (tid == 0) {
-    losses[0] = loss0;
-    losses[1] = loss1;
+#pragma unroll
+  for (int r = 0; r < kOwned; ++r) {
+    const int at = owned_param(r);
+    if (at >= 0) params[at] = P[r];
   }
 }
 
@@ -442,7 +562,7 @@ hipError_t fit_pieces(const uint64_t* keys, uint64_t n, const LearnedArrays& a, 
 
 }  // namespace
 
-size_t learned_scratch_bytes() { return align256(kSamples * 4) * 2 + 256; }
+size_t learned_scratch_bytes() { return align256(kSamples * 4) * 3 + 256; }
 
 uint32_t learned_max_pieces(uint64_t n) { return (uint32_t)(n / kPiece + kLeaves + 1); }
 
@@ -475,18 +595,31 @@ hipError_t learned_fit(const uint64_t* keys, uint64_t n, uint32_t steps, float l
   while ((uint64_t)S > n) S >>= 1;
   char* p = (char*)scratch;
   float* xs = (float*)p;          p += align256(kSamples * 4);
-  float* ts = (float*)p;
+  float* ts = (float*)p;          p += align256(kSamples * 4);
+  float* sq = (float*)p;
   hipError_t e;
   {
     ProfScope ps("learned_sample", s);
     learned_sample<<<(S + 255) / 256, 256, 0, s>>>(keys, n, S, xs, ts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  {
-    ProfScope ps("learned_train", s);
-    learned_train<<<1, kTrainThreads, 0, s>>>(xs, ts, S, steps, lr, params, losses);
+    learned_init<<<1, 256, 0, s>>>(xs, S, params);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
+  auto loss = [&](float* out) {
+    ProfScope ps("learned_loss", s);
+    learned_errors<<<(S + 255) / 256, 256, 0, s>>>(params, xs, ts, S, sq);
+    hipError_t le = hipGetLastError();
+    if (le != hipSuccess) return le;
+    learned_loss<<<1, 256, 0, s>>>(sq, S, out);
+    return hipGetLastError();
+  };
+  if ((e = loss(losses)) != hipSuccess) return e;
+  {
+    ProfScope ps("learned_train", s);
+    learned_train<<<1, kTrainThreads, 0, s>>>(xs, ts, S, steps, lr, params);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if ((e = loss(losses + 1)) != hipSuccess) return e;
   {
     ProfScope ps("learned_tabulate", s);
     learned_xbounds<<<(kLeaves + 1 + 255) / 256, 256, 0, s>>>(params, a.xb);
