@@ -9,10 +9,10 @@
 //                    step so that the router stays monotone.
 //   learned_errors   every sample's squared error and their mean, before and
 //   learned_loss     after the training.
-//   learned_xbounds  tabulation of the trained router: the first input X of
-//   learned_radix    every leaf (a binary search over X per leaf, valid
-//                    because routing is monotone) and the leaf at every
-//                    2^8-th input.
+//   learned_radix    tabulation of the trained router: the leaf at every
+//   learned_xbounds  2^8-th input, and the first input X of every leaf (a
+//                    binary search per leaf, valid because routing is
+//                    monotone).
 //   learned_keybounds first key index of every leaf.
 //   learned_piece_offsets  pieces per leaf (ceil(size / kPiece)) and their
 //                    exclusive scan (one workgroup).
@@ -379,15 +379,48 @@ __global__ __launch_bounds__(kTrainThreads) void learned_train(const float* __re
   }
 }
 
-__global__ __launch_bounds__(256) void learned_xbounds(const float* __restrict__ P,
-                                                       uint32_t* __restrict__ xb) {
-  const uint32_t l = blockIdx.x * 256 + threadIdx.x;
+// rt[t] = the leaf of input t << 8 (t < 2^16), and of the last input.
+__global__ __launch_bounds__(256) void learned_radix(const float* __restrict__ P,
+                                                     uint32_t* __restrict__ rt) {
+  const uint32_t t = blockIdx.x * 256 + threadIdx.x;
+  if (t > kRouteSlots) return;
+  const uint32_t X = t < kRouteSlots ? t << (kXBits - kRouteBits) : (1u << kXBits) - 1;
+  rt[t] = router_leaf_x(P, X);
+}
+
+// xb[l] = the first X with leaf(X) >= l, 2^24 if none.  The table rt (every
+// 2^8-th input's leaf) brackets it: routing is monotone, so the search of the
+// table leaves at most eight evaluations of the network, a chain of 10^3
+// multiply-adds each (all 24 steps by evaluation took 0.09 ms with the table,
+// against 0.04 ms).  One wave per workgroup, so that the 65 waves spread over
+// the CUs.
+__global__ __launch_bounds__(64) void learned_xbounds(const float* __restrict__ P,
+                                                      const uint32_t* __restrict__ rt,
+                                                      uint32_t* __restrict__ xb) {
+  constexpr int kStep = kXBits - kRouteBits;
+  const uint32_t l = blockIdx.x * 64 + threadIdx.x;
   if (l > (uint32_t)kLeaves) return;
   if (l == 0 || l == (uint32_t)kLeaves) {
     xb[l] = l == 0 ? 0u : (1u << kXBits);
     return;
   }
-  uint32_t lo = 0, len = 1u << kXBits;   // first X with leaf(X) >= l, 2^24 if none
+  uint32_t t = 0, tl = kRouteSlots;   // first t with rt[t] >= l, kRouteSlots if none
+  while (tl > 0) {
+    const uint32_t h = tl >> 1;
+    if (rt[t + h] < l) {
+      t += h + 1;
+      tl -= h + 1;
+    } else {
+      tl = h;
+    }
+  }
+  // leaf((t - 1) << 8) < l <= leaf(t << 8): the first X lies past the former,
+  // at most the latter.
+  if (t == 0) {
+    xb[l] = 0;
+    return;
+  }
+  uint32_t lo = ((t - 1) << kStep) + 1, len = (1u << kStep) - 1;
   while (len > 0) {
     const uint32_t h = len >> 1;
     if (router_leaf_x(P, lo + h) < l) {
@@ -398,14 +431,6 @@ __global__ __launch_bounds__(256) void learned_xbounds(const float* __restrict__
     }
   }
   xb[l] = lo;
-}
-
-__global__ __launch_bounds__(256) void learned_radix(const float* __restrict__ P,
-                                                     uint32_t* __restrict__ rt) {
-  const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-  if (t > kRouteSlots) return;
-  const uint32_t X = t < kRouteSlots ? t << (kXBits - kRouteBits) : (1u << kXBits) - 1;
-  rt[t] = router_leaf_x(P, X);
 }
 
 // lp[l].x = first index whose key routes to a leaf >= l: keys route by their
@@ -622,9 +647,9 @@ hipError_t learned_fit(const uint64_t* keys, uint64_t n, uint32_t steps, float l
   if ((e = loss(losses + 1)) != hipSuccess) return e;
   {
     ProfScope ps("learned_tabulate", s);
-    learned_xbounds<<<(kLeaves + 1 + 255) / 256, 256, 0, s>>>(params, a.xb);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     learned_radix<<<(kRouteSlots + 1 + 255) / 256, 256, 0, s>>>(params, a.rt);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    learned_xbounds<<<(kLeaves + 1 + 63) / 64, 64, 0, s>>>(params, a.rt, a.xb);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return fit_pieces(keys, n, a, a.max_pieces, s);
