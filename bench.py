@@ -41,7 +41,7 @@ def kernel_source_hash(name: str) -> str:
 # Kernels whose algorithmic bytes the bench states (candidates for the
 # roofline's dominant kernel).
 ROOFLINE_KERNELS = ("keygen_tiles", "tile_hist", "scatter_pass", "chunk_sort", "ranges_search",
-                    "compact_test", "query_filters", "compact_write")
+                    "compact_test", "compact_write")
 
 
 def timed_calls(fn, steps: int):
@@ -726,16 +726,16 @@ def main():
     cand, rep = stats["candidates"], total
     passes = round(kern["scatter_pass"][0] / args.steps)   # radix passes per build
     tiles = math.ceil(cand / 4096)
-    slots = 8 * m   # refined layout: eight slots (begin u32, count u32, offset u64) per query
+    slots = 8 * m   # refined layout: eight slots (begin u32, count u32) per query
     algo = {
         "keygen_tiles": 16 * n + 8 * n + 16 * n,            # points in, keys and input-order copy out
         "tile_hist": (passes - 1) * 8 * n,                  # passes 2.. read the keys
         "scatter_pass": passes * 24 * n,                    # (key+id) in and out per pass
-        "ranges_search": 24 * m + 8 * slots,                # queries in; begin+count per slot
+        # queries in; begin+count per slot and the 32-byte record per query
+        "ranges_search": 24 * m + 8 * slots + 32 * m,
         # default: each candidate's 8-byte grid cell, the 32-byte filter record
         # of its query per row (the rare undecided candidates read 16 B more)
         "compact_test": 8 * cand + 32 * m + 12 * slots + cand // 8 + 4 * tiles,
-        "query_filters": 24 * m + 32 * m,
         "compact_write": cand // 8 + 8 * tiles + 4 * rep + 4 * rep + 8 * (m + 1) + 12 * slots,
     }
     if "chunk_sort" in kern:

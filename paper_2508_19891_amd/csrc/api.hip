@@ -181,6 +181,13 @@ int tuned(TuneOp op, uint64_t size) {
   return it == g_tune.end() ? -1 : it->second;
 }
 
+bool tuned_any(TuneOp op) {
+  std::lock_guard<std::mutex> g(g_tune_mu);
+  for (const auto& t : g_tune)
+    if (t.first.first == (int)op && t.second >= 0) return true;
+  return false;
+}
+
 void set_tuned(TuneOp op, uint64_t size, int value) {
   std::lock_guard<std::mutex> g(g_tune_mu);
   g_tune[{(int)op, bucket(size)}] = value;
@@ -215,6 +222,7 @@ struct sfc_index {
   size_t ws_bytes = 0;
   void* cws = nullptr;         // compaction scratch (grow-only)
   size_t cws_bytes = 0;
+  uint64_t cws_rows = 0;       // candidate rows cws holds
   sfc_query_stats last{};
   // learned index
   float* lparams = nullptr;        // device, sfc::kParams
@@ -237,8 +245,6 @@ struct sfc_index {
   bool stree_ready = false;
   // early termination: occupancy bits of the quadtree nodes (null: off)
   uint32_t* occ = nullptr;
-  uint64_t last_pruned = 0;
-  int last_coarse = -1;   // the last batch's ranges: some radius past the cell shift limit
   // updates (sfc_insert / sfc_erase); ins == null until the first update
   uint32_t* ins = nullptr;         // device, insert epoch per stored entry
   uint32_t* era = nullptr;         // device, erase epoch per stored entry
@@ -259,7 +265,9 @@ struct sfc_index {
   // larger ids buffer reruns only the write pass.
   struct Pending {
     bool valid = false;
-    uint64_t m = 0, rows = 0, total = 0, generation = 0;
+    uint64_t m = 0, total = 0, generation = 0;
+    uint64_t max_rows = 0;      // as the batch was compacted
+    bool device_sized = false;
     sfc::QueryScratch qs{};
   } pending;
   uint64_t merges = 0, compactions = 0;
@@ -364,6 +372,7 @@ void release_arrays(sfc_index* h) {
   h->alloc.put(h->cws);
   h->cws = nullptr;
   h->cws_bytes = 0;
+  h->cws_rows = 0;
   h->alloc.put(h->lparams);
   h->alloc.put(h->lmodel);
   h->alloc.put(h->set_off);
@@ -490,65 +499,103 @@ sfc_status points_for_test(sfc_index* h) {
 // four runs for each of eight cubes).
 uint32_t slots_of(const sfc_index* h) { return dim_of(h) == 3 && h->refine ? 32 : 8; }
 
-// Runs ranges + searches + scan; on SFC_OK *total_rows holds the number of
-// candidate rows and *total_cand the number of candidates.
-// The same into query scratch at ws (query_scratch_bytes(m, slots_of(h))
-// bytes), reading the counts back through rb (host, 8 words).
-sfc_status run_ranges_into(sfc_index* h, void* ws, uint64_t* rb, const double* q,
-                           const double* delta, const uint32_t* qset, uint64_t m,
-                           sfc::QueryScratch* qs, uint64_t* total_rows, uint64_t* total_cand,
-                           uint64_t* dbg_lo, uint64_t* dbg_hi, uint64_t* dbg_b, uint64_t* dbg_e,
-                           uint32_t* dbg_nr, const uint32_t* qepoch);
-
-sfc_status run_ranges(sfc_index* h, const double* q, const double* delta, const uint32_t* qset,
-                      uint64_t m, sfc::QueryScratch* qs, uint64_t* total_rows, uint64_t* total_cand,
-                      uint64_t* dbg_lo, uint64_t* dbg_hi, uint64_t* dbg_b, uint64_t* dbg_e,
-                      uint32_t* dbg_nr, const uint32_t* qepoch = nullptr) {
-  h->pending.valid = false;   // the scratch is about to be reused
-  sfc_status st = ensure_ws(h, sfc::query_scratch_bytes(m, slots_of(h)));
-  if (st != SFC_OK) return st;
-  uint64_t* pin = sfc::pinned_scratch();
-  if (!pin) return SFC_ERR_NOMEM;
-  return run_ranges_into(h, h->ws, pin, q, delta, qset, m, qs, total_rows, total_cand, dbg_lo,
-                         dbg_hi, dbg_b, dbg_e, dbg_nr, qepoch);
+// The compaction scratch holds at least `rows` candidate rows.
+sfc_status ensure_cws(sfc_index* h, uint64_t rows) {
+  if (h->cws && h->cws_rows >= rows) return SFC_OK;
+  const size_t bytes = sfc::compact_scratch_bytes(rows);
+  h->cws_rows = 0;
+  sfc_status st = grow(h, &h->cws, &h->cws_bytes, bytes);
+  if (st == SFC_OK) h->cws_rows = rows;
+  return st;
 }
 
-sfc_status run_ranges_into(sfc_index* h, void* ws, uint64_t* rb, const double* q,
-                           const double* delta, const uint32_t* qset, uint64_t m,
-                           sfc::QueryScratch* qs, uint64_t* total_rows, uint64_t* total_cand,
-                           uint64_t* dbg_lo, uint64_t* dbg_hi, uint64_t* dbg_b, uint64_t* dbg_e,
-                           uint32_t* dbg_nr, const uint32_t* qepoch) {
-  sfc::query_scratch_carve(ws, m, qs, slots_of(h));
-  const bool learned = h->search == SFC_SEARCH_LEARNED && h->linfo.fitted && !qset;
-  const sfc::LearnedView lv = h->larr.view();
-  const sfc::StreeView sv = sfc::stree_view(h->keys, h->n, h->stree);
-  if (dim_of(h) == 3)
-    SFC_TRY(sfc::launch_ranges3(q, delta, m, h->keys, h->n, h->refine != 0, h->refine_min,
-                                stree_on(h) ? &sv : nullptr, *qs,
-                                h->stream));
-  else
-    SFC_TRY(sfc::launch_ranges(q, delta, m, h->keys, h->n, h->curve, h->refine != 0,
-                               h->refine_min, h->metric == SFC_METRIC_L2,
-                               learned ? &lv : nullptr,
-                               stree_on(h) ? &sv : nullptr, h->occ, qset,
-                               qset ? h->set_off : nullptr, h->n_sets, *qs, dbg_lo, dbg_hi, dbg_b,
-                               dbg_e, dbg_nr, h->stream));
-  if (qepoch)
-    SFC_TRY(sfc::validate_epochs(qepoch, m, h->oldest, h->epoch, qs->counters + 2, h->stream));
-  uint64_t* pin = rb;
-  SFC_TRY(hipMemcpyAsync(pin, qs->row_off + m, 8, hipMemcpyDeviceToHost, h->stream));
-  SFC_TRY(hipMemcpyAsync(pin + 1, qs->counters, 56, hipMemcpyDeviceToHost, h->stream));
-  SFC_TRY(hipStreamSynchronize(h->stream));
-  const uint32_t err = ((const uint32_t*)(pin + 1))[2];
-  if (err & sfc::kErrInvalidQuery) return SFC_ERR_INVALID;
-  if (err & (sfc::kErrLookback | sfc::kErrInternal)) return SFC_ERR_DEVICE;
-  *total_rows = pin[0];
-  *total_cand = pin[3];   // counters[4..5]
-  h->linfo.endpoints_last = learned ? pin[4] : 0;
-  h->linfo.fallbacks_last = learned ? pin[5] : 0;
-  h->last_pruned = pin[6];   // counters[10..11]
-  h->last_coarse = (pin[7] >> 32) != 0 ? 1 : 0;   // counters[13]: radii past the shift limit
+// Whether updates left tombstones or entries newer than the oldest queryable
+// epoch: then a query sees only the entries visible at its epoch.
+bool epoch_filtered(const sfc_index* h) {
+  return h->ins && !(h->dead == 0 && h->max_ins <= h->oldest);
+}
+
+// The search of a batch over h.  qepoch: the queries' epochs (null: the
+// current one).  The views the plan points to live in *v.
+struct Views {
+  sfc::LearnedView learned;
+  sfc::StreeView stree;
+};
+sfc::RangePlan range_plan(const sfc_index* h, Views* v, const double* q, const double* delta,
+                          const uint32_t* qset, const uint32_t* qepoch) {
+  sfc::RangePlan p;
+  p.q = q;
+  p.delta = delta;
+  p.dim = dim_of(h);
+  p.keys = h->keys;
+  p.n = h->n;
+  p.curve = h->curve;
+  p.refine = h->refine != 0;
+  p.refine_min = h->refine_min;
+  p.ball = h->metric == SFC_METRIC_L2;
+  v->learned = h->larr.view();
+  v->stree = sfc::stree_view(h->keys, h->n, h->stree);
+  if (h->search == SFC_SEARCH_LEARNED && h->linfo.fitted && !qset) p.lview = &v->learned;
+  if (stree_on(h)) p.sview = &v->stree;
+  p.occ = h->occ;
+  p.qset = qset;
+  p.set_off = qset ? h->set_off : nullptr;
+  p.n_sets = h->n_sets;
+  p.record.mode = test_cells(h) ? sfc::kRecordFilter : sfc::kRecordExact;
+  p.record.window = h->metric == SFC_METRIC_LINF;
+  p.record.qepoch = qepoch;
+  p.record.oldest = h->oldest;
+  p.record.epoch = h->epoch;
+  return p;
+}
+
+// The compaction of that batch; the row count or capacity, the scratch and
+// the outputs are the caller's to set.
+sfc::CompactPlan compact_plan(const sfc_index* h, const double* q, const double* delta,
+                              uint64_t* offsets, uint32_t* ids, uint64_t ids_cap) {
+  sfc::CompactPlan p;
+  p.q = q;
+  p.delta = delta;
+  p.pts = h->xy;
+  p.pts_in = h->xy_in;
+  p.cells = test_cells(h);
+  p.ids = h->ids;
+  p.keys = h->n_sets ? nullptr : h->keys;
+  p.n = h->n;
+  p.curve = h->curve;
+  p.offsets = offsets;
+  p.out_ids = ids;
+  p.cap = ids_cap;
+  p.window = h->metric == SFC_METRIC_LINF;
+  p.dim = dim_of(h);
+  if (epoch_filtered(h)) {
+    p.ins = h->ins;
+    p.era = h->era;
+  }
+  return p;
+}
+
+sfc_status status_of(const sfc::BatchStatus& st) {
+  if (st.err & sfc::kErrInvalidQuery) return SFC_ERR_INVALID;
+  if (st.err & (sfc::kErrLookback | sfc::kErrInternal)) return SFC_ERR_DEVICE;
   return SFC_OK;
+}
+
+// What the handle keeps of a batch's counters.
+void keep_stats(sfc_index* h, uint64_t m, const sfc::BatchStatus& st) {
+  h->linfo.endpoints_last = st.endpoints;
+  h->linfo.fallbacks_last = st.fallbacks;
+  h->last.queries = m;
+  h->last.rows = st.rows;
+  h->last.candidates = st.candidates;
+  h->last.reported = st.total;
+  h->last.pruned = st.pruned;
+}
+
+// The pinned words of this thread as a batch's counters.
+sfc::BatchStatus* pinned_status() {
+  static_assert(sizeof(sfc::BatchStatus) <= 4096, "fits the pinned scratch");
+  return (sfc::BatchStatus*)sfc::pinned_scratch();
 }
 
 // Size and window statistics of the fitted leaves and pieces (read back).
@@ -893,15 +940,21 @@ sfc_status sfc_build_sets(const double* xy, const uint64_t* set_off, uint32_t n_
 }  // extern "C"
 
 namespace {
-// The entries a query of h sees: all stored ones unless updates left
-// tombstones or entries newer than the oldest queryable epoch.
-bool epoch_view(const sfc_index* h, const uint32_t* qepoch, sfc::EpochView* ev) {
-  if (!h->ins || (h->dead == 0 && h->max_ins <= h->oldest)) return false;
-  ev->ins = h->ins;
-  ev->era = h->era;
-  ev->qepoch = qepoch;
-  ev->epoch = h->epoch;
-  return true;
+
+// Batches of up to this many queries run without reading their row count
+// first: their compaction is sized for expected_rows, and only a batch with
+// more rows than that (then nothing was tested) is compacted again at its exact
+// size.  A handle whose last batch had more rows a query reads the count.  The
+// read costs a synchronisation in the middle of a batch: over 2^20 points 16
+// queries take 45 us without and 60 with it, 2^16 96 and 110, 2^17 146 and 165,
+// 2^19 348 and 358.  Beyond 2^17 the gain is a few percent and the capacity's
+// scratch (450 bytes a query) grows large.
+constexpr uint64_t kUnreadMax = 1u << 17;
+uint64_t expected_rows(uint64_t m) { return m <= 1024 ? (1u << 16) : 16 * m; }
+bool rows_expected(const sfc_index* h, uint64_t m) {
+  const sfc_query_stats& l = h->last;
+  return l.queries == 0 ||
+         (double)l.rows * (double)m <= (double)expected_rows(m) * (double)l.queries;
 }
 
 sfc_status query_impl(sfc_index* h, const double* q, const double* delta, const uint32_t* qset,
@@ -910,50 +963,66 @@ sfc_status query_impl(sfc_index* h, const double* q, const double* delta, const 
   if (!h || !offsets || !total_out || (m > 0 && (!q || !delta)) || (ids_cap > 0 && !ids))
     return SFC_ERR_INVALID;
   if (m > (1ull << 36)) return SFC_ERR_INVALID;
-  {
-    sfc_status st = points_for_test(h);
+  sfc_status st = points_for_test(h);
+  if (st != SFC_OK) return st;
+  h->pending.valid = false;   // the scratch is about to be reused
+  if (m == 0) {
+    SFC_TRY(sfc::fill_u64(offsets, 0, 1, h->stream));
+    SFC_TRY(hipStreamSynchronize(h->stream));
+    keep_stats(h, 0, sfc::BatchStatus{});
+    *total_out = 0;
+    return SFC_OK;
+  }
+  st = ensure_ws(h, sfc::query_scratch_bytes(m, slots_of(h)));
+  if (st != SFC_OK) return st;
+  sfc::BatchStatus* host = pinned_status();
+  if (!host) return SFC_ERR_NOMEM;
+  sfc::QueryScratch qs;
+  if (!sfc::query_scratch_carve(h->ws, m, &qs, slots_of(h))) return SFC_ERR_DEVICE;
+  // A capacity within one chunk only (a batch of one chunk has its own
+  // contract), and no launch shape chosen by the exact row count.
+  uint64_t cap_rows = 0;
+  if (m <= kUnreadMax && rows_expected(h, m) && !sfc::tuned_any(sfc::kTuneTestShape)) {
+    cap_rows = expected_rows(m);
+    if (!sfc::compact_single_chunk(cap_rows) || ensure_cws(h, cap_rows) != SFC_OK) cap_rows = 0;
+  }
+  Views views;
+  sfc::RangePlan rp = range_plan(h, &views, q, delta, qset, qepoch);
+  sfc::CompactPlan cp = compact_plan(h, q, delta, offsets, ids, ids_cap);
+  cp.host = host;
+  rp.need_rows = cap_rows == 0;
+  rp.host = cap_rows == 0 ? host : nullptr;
+  SFC_TRY(sfc::launch_ranges(rp, qs, h->stream));
+  if (cap_rows) {
+    cp.max_rows = cap_rows;
+    cp.device_sized = true;
+    cp.scratch = h->cws;
+    SFC_TRY(sfc::launch_compact(cp, qs, h->stream));
+  }
+  SFC_TRY(hipStreamSynchronize(h->stream));
+  st = status_of(*host);
+  if (st != SFC_OK) return st;
+  if (host->rows > cap_rows || cap_rows == 0) {   // the exact count is known now
+    cp.max_rows = host->rows;
+    cp.device_sized = false;
+    cp.coarse = host->coarse ? 1 : 0;
+    st = ensure_cws(h, cp.max_rows);
+    if (st != SFC_OK) return st;
+    cp.scratch = h->cws;
+    SFC_TRY(sfc::launch_compact(cp, qs, h->stream));
+    SFC_TRY(hipStreamSynchronize(h->stream));
+    st = status_of(*host);
     if (st != SFC_OK) return st;
   }
-  sfc::QueryScratch qs{};
-  uint64_t total_rows = 0, total_cand = 0;
-  sfc::EpochView ev;
-  const bool filtered = epoch_view(h, qepoch, &ev);
-  h->pending.valid = false;
-  if (m > 0) {
-    sfc_status st = run_ranges(h, q, delta, qset, m, &qs, &total_rows, &total_cand, nullptr,
-                               nullptr, nullptr, nullptr, nullptr, qepoch);
-    if (st != SFC_OK) return st;
-  } else {
-    sfc_status st = ensure_ws(h, sfc::query_scratch_bytes(0));
-    if (st != SFC_OK) return st;
-    sfc::query_scratch_carve(h->ws, 0, &qs);
-  }
-  {
-    sfc_status st = grow(h, &h->cws, &h->cws_bytes, sfc::compact_scratch_bytes(total_rows));
-    if (st != SFC_OK) return st;
-  }
-  SFC_TRY(sfc::launch_compact(q, delta, m, h->xy, h->xy_in, test_cells(h), h->ids, h->n, qs,
-                              total_rows, false, h->cws, offsets, ids, ids_cap,
-                              h->metric == SFC_METRIC_LINF, dim_of(h), h->stream,
-                              filtered ? &ev : nullptr, false, m > 0 ? h->last_coarse : 0));
-  uint64_t total = 0;
-  SFC_TRY(read_words(offsets + m, &total, 1, h->stream));
-  if (m > 0) {
-    uint64_t cw[2];
-    SFC_TRY(read_words(qs.counters, cw, 2, h->stream));
-    if (((const uint32_t*)cw)[2] & (sfc::kErrLookback | sfc::kErrInternal)) return SFC_ERR_DEVICE;
-  }
-  h->last.queries = m;
-  h->last.candidates = total_cand;
-  h->last.reported = total;
-  h->last.rows = total_rows;
-  h->last.pruned = m > 0 ? h->last_pruned : 0;
+  const uint64_t total = host->total;
+  keep_stats(h, m, *host);
   *total_out = total;
-  if (total > ids_cap && m > 0 && sfc::compact_single_chunk(total_rows)) {
+  if (total > ids_cap && sfc::compact_single_chunk(host->rows)) {
     sfc_index::Pending& p = h->pending;
     p.valid = true;
     p.m = m;
-    p.rows = total_rows;
+    p.max_rows = cp.max_rows;
+    p.device_sized = cp.device_sized;
     p.total = total;
     p.generation = h->generation;
     p.qs = qs;
@@ -982,32 +1051,18 @@ sfc_status sfc_query_async(sfc_index* h, const double* q, const double* delta,
   // Growing a scratch buffer waits for the work queued on it first.
   sfc_status st = points_for_test(h);
   if (st == SFC_OK) st = ensure_ws(h, sfc::query_scratch_bytes(m, slots_of(h)));
-  if (st == SFC_OK) st = grow(h, &h->cws, &h->cws_bytes, sfc::compact_scratch_bytes(max_rows));
+  if (st == SFC_OK) st = ensure_cws(h, max_rows);
   if (st != SFC_OK) return st;
-  sfc::QueryScratch qs{};
-  sfc::query_scratch_carve(h->ws, m, &qs, slots_of(h));
-  const bool learned = h->search == SFC_SEARCH_LEARNED && h->linfo.fitted;
-  const sfc::LearnedView lv = h->larr.view();
-  const sfc::StreeView sv = sfc::stree_view(h->keys, h->n, h->stree);
-  sfc::EpochView ev;
-  const bool filtered = epoch_view(h, qepoch, &ev);
-  if (dim_of(h) == 3)
-    SFC_TRY(sfc::launch_ranges3(q, delta, m, h->keys, h->n, h->refine != 0, h->refine_min,
-                                stree_on(h) ? &sv : nullptr, qs,
-                                h->stream));
-  else
-    SFC_TRY(sfc::launch_ranges(q, delta, m, h->keys, h->n, h->curve, h->refine != 0,
-                               h->refine_min, h->metric == SFC_METRIC_L2,
-                               learned ? &lv : nullptr,
-                               stree_on(h) ? &sv : nullptr, h->occ, nullptr, nullptr, 0, qs,
-                               nullptr, nullptr, nullptr, nullptr, nullptr, h->stream));
-  if (qepoch)
-    SFC_TRY(sfc::validate_epochs(qepoch, m, h->oldest, h->epoch, qs.counters + 2, h->stream));
-  SFC_TRY(sfc::launch_compact(q, delta, m, h->xy, h->xy_in, test_cells(h), h->ids, h->n, qs,
-                              max_rows, true, h->cws, offsets, ids, ids_cap,
-                              h->metric == SFC_METRIC_LINF, dim_of(h), h->stream,
-                              filtered ? &ev : nullptr));
-  SFC_TRY(hipMemcpyAsync(flags, qs.counters + 2, 4, hipMemcpyDeviceToDevice, h->stream));
+  sfc::QueryScratch qs;
+  if (!sfc::query_scratch_carve(h->ws, m, &qs, slots_of(h))) return SFC_ERR_DEVICE;
+  Views views;
+  SFC_TRY(sfc::launch_ranges(range_plan(h, &views, q, delta, nullptr, qepoch), qs, h->stream));
+  sfc::CompactPlan cp = compact_plan(h, q, delta, offsets, ids, ids_cap);
+  cp.max_rows = max_rows;
+  cp.device_sized = true;
+  cp.scratch = h->cws;
+  cp.flags_out = flags;
+  SFC_TRY(sfc::launch_compact(cp, qs, h->stream));
   return SFC_OK;
 }
 
@@ -1041,29 +1096,18 @@ sfc_status sfc_query_async_on(sfc_index* h, void* stream, void* scratch, uint64_
   SFC_TRY(hipEventRecord(ready, h->stream));
   SFC_TRY(hipStreamWaitEvent(s, ready, 0));
   SFC_TRY(take_sync_event(h, &done));
-  sfc::QueryScratch qs{};
-  sfc::query_scratch_carve(scratch, m, &qs, slots_of(h));
-  const bool learned = h->search == SFC_SEARCH_LEARNED && h->linfo.fitted;
-  const sfc::LearnedView lv = h->larr.view();
-  const sfc::StreeView sv = sfc::stree_view(h->keys, h->n, h->stree);
-  sfc::EpochView ev;
-  const bool filtered = epoch_view(h, qepoch, &ev);
-  hipError_t e =
-      dim_of(h) == 3
-          ? sfc::launch_ranges3(q, delta, m, h->keys, h->n, h->refine != 0, h->refine_min,
-                                stree_on(h) ? &sv : nullptr, qs, s)
-          : sfc::launch_ranges(q, delta, m, h->keys, h->n, h->curve, h->refine != 0,
-                               h->refine_min, h->metric == SFC_METRIC_L2,
-                               learned ? &lv : nullptr, stree_on(h) ? &sv : nullptr, h->occ,
-                               nullptr, nullptr, 0, qs, nullptr, nullptr, nullptr, nullptr,
-                               nullptr, s);
-  if (e == hipSuccess && qepoch)
-    e = sfc::validate_epochs(qepoch, m, h->oldest, h->epoch, qs.counters + 2, s);
+  sfc::QueryScratch qs;
+  hipError_t e = sfc::query_scratch_carve(scratch, m, &qs, slots_of(h)) ? hipSuccess
+                                                                        : hipErrorInvalidValue;
+  Views views;
   if (e == hipSuccess)
-    e = sfc::launch_compact(q, delta, m, h->xy, h->xy_in, test_cells(h), h->ids, h->n, qs,
-                            max_rows, true, (char*)scratch + qbytes, offsets, ids, ids_cap,
-                            h->metric == SFC_METRIC_LINF, dim_of(h), s, filtered ? &ev : nullptr);
-  if (e == hipSuccess) e = hipMemcpyAsync(flags, qs.counters + 2, 4, hipMemcpyDeviceToDevice, s);
+    e = sfc::launch_ranges(range_plan(h, &views, q, delta, nullptr, qepoch), qs, s);
+  sfc::CompactPlan cp = compact_plan(h, q, delta, offsets, ids, ids_cap);
+  cp.max_rows = max_rows;
+  cp.device_sized = true;
+  cp.scratch = (char*)scratch + qbytes;
+  cp.flags_out = flags;
+  if (e == hipSuccess) e = sfc::launch_compact(cp, qs, s);
   if (e == hipSuccess) e = hipEventRecord(done, s);
   if (e != hipSuccess) {
     h->idle_events.push_back(done);
@@ -1096,11 +1140,17 @@ sfc_status sfc_query_retry(sfc_index* h, uint64_t* offsets, uint32_t* ids, uint6
     return SFC_ERR_CAPACITY;
   }
   h->pending.valid = false;
-  SFC_TRY(sfc::launch_compact(nullptr, nullptr, p.m, h->xy, h->xy_in, nullptr, h->ids, h->n,
-                              p.qs, p.rows, false, h->cws, offsets, ids, ids_cap, false, dim_of(h),
-                              h->stream, nullptr, true));
-  uint64_t total = 0;
-  SFC_TRY(read_words(offsets + p.m, &total, 1, h->stream));
+  sfc::BatchStatus* host = pinned_status();
+  if (!host) return SFC_ERR_NOMEM;
+  sfc::CompactPlan cp = compact_plan(h, nullptr, nullptr, offsets, ids, ids_cap);
+  cp.max_rows = p.max_rows;
+  cp.device_sized = p.device_sized;
+  cp.scratch = h->cws;
+  cp.write_only = true;
+  cp.host = host;
+  SFC_TRY(sfc::launch_compact(cp, p.qs, h->stream));
+  SFC_TRY(hipStreamSynchronize(h->stream));
+  const uint64_t total = host->total;
   if (total != p.total) return SFC_ERR_DEVICE;
   h->last.reported = total;
   *total_out = total;
@@ -1162,38 +1212,35 @@ sfc_status sfc_query_batch_static(sfc_index* h, const double* q, const double* d
     if (st != SFC_OK) return st;
   }
   h->pending.valid = false;   // the handle's kept batch is not this one
-  sfc::QueryScratch qs{};
-  uint64_t total_rows = 0, total_cand = 0;
-  if (m > 0) {
-    uint64_t rb[8];
-    sfc_status st = run_ranges_into(h, base, rb, q, delta, nullptr, m, &qs, &total_rows,
-                                    &total_cand, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                    nullptr);
-    if (st != SFC_OK) return st;
-  } else {
-    sfc::query_scratch_carve(base, 0, &qs, slots_of(h));
+  if (m == 0) {
+    SFC_TRY(sfc::fill_u64(offsets, 0, 1, h->stream));
+    SFC_TRY(hipStreamSynchronize(h->stream));
+    keep_stats(h, 0, sfc::BatchStatus{});
+    *total_out = 0;
+    return SFC_OK;
   }
-  if (qbytes + sfc::compact_scratch_bytes(total_rows) > kStaticScratchBytes)
-    return SFC_ERR_SCRATCH;
-  sfc::EpochView ev;
-  const bool filtered = epoch_view(h, nullptr, &ev);
-  SFC_TRY(sfc::launch_compact(q, delta, m, h->xy, h->xy_in, test_cells(h), h->ids, h->n, qs,
-                              total_rows, false, (char*)base + qbytes, offsets, ids, ids_cap,
-                              h->metric == SFC_METRIC_LINF, dim_of(h), h->stream,
-                              filtered ? &ev : nullptr, false, m > 0 ? h->last_coarse : 0));
-  uint64_t tail[3] = {0, 0, 0};   // the total, then the error word's doubleword
-  SFC_TRY(hipMemcpyAsync(&tail[0], offsets + m, 8, hipMemcpyDeviceToHost, h->stream));
-  if (m > 0)
-    SFC_TRY(hipMemcpyAsync(&tail[1], qs.counters, 16, hipMemcpyDeviceToHost, h->stream));
+  sfc::QueryScratch qs;
+  if (!sfc::query_scratch_carve(base, m, &qs, slots_of(h))) return SFC_ERR_DEVICE;
+  Views views;
+  sfc::RangePlan rp = range_plan(h, &views, q, delta, nullptr, nullptr);
+  rp.need_rows = true;
+  SFC_TRY(sfc::launch_ranges(rp, qs, h->stream));
+  sfc::BatchStatus bs;
+  SFC_TRY(hipMemcpyAsync(&bs, qs.status, sizeof(bs), hipMemcpyDeviceToHost, h->stream));
   SFC_TRY(hipStreamSynchronize(h->stream));
-  if (m > 0 && (((const uint32_t*)&tail[1])[2] & (sfc::kErrLookback | sfc::kErrInternal)))
-    return SFC_ERR_DEVICE;
-  const uint64_t total = tail[0];
-  h->last.queries = m;
-  h->last.candidates = total_cand;
-  h->last.reported = total;
-  h->last.rows = total_rows;
-  h->last.pruned = m > 0 ? h->last_pruned : 0;
+  sfc_status st = status_of(bs);
+  if (st != SFC_OK) return st;
+  if (qbytes + sfc::compact_scratch_bytes(bs.rows) > kStaticScratchBytes) return SFC_ERR_SCRATCH;
+  sfc::CompactPlan cp = compact_plan(h, q, delta, offsets, ids, ids_cap);
+  cp.max_rows = bs.rows;
+  cp.scratch = (char*)base + qbytes;
+  cp.coarse = bs.coarse ? 1 : 0;
+  SFC_TRY(sfc::launch_compact(cp, qs, h->stream));
+  uint64_t total = 0;
+  SFC_TRY(hipMemcpyAsync(&total, offsets + m, 8, hipMemcpyDeviceToHost, h->stream));
+  SFC_TRY(hipStreamSynchronize(h->stream));
+  bs.total = total;
+  keep_stats(h, m, bs);
   *total_out = total;
   return total > ids_cap ? SFC_ERR_CAPACITY : SFC_OK;
 }
@@ -1219,10 +1266,29 @@ sfc_status sfc_query_ranges(sfc_index* h, const double* q, const double* delta, 
     return SFC_ERR_INVALID;
   if (dim_of(h) == 3) return SFC_ERR_UNSUPPORTED;   // eight ranges per query, not four
   if (m == 0) return SFC_OK;
-  sfc::QueryScratch qs{};
-  uint64_t total_rows = 0, total_cand = 0;
-  return run_ranges(h, q, delta, nullptr, m, &qs, &total_rows, &total_cand, key_lo, key_hi, begin,
-                    end, nranges);
+  h->pending.valid = false;   // the scratch is about to be reused
+  sfc_status st = ensure_ws(h, sfc::query_scratch_bytes(m, slots_of(h)));
+  if (st != SFC_OK) return st;
+  sfc::BatchStatus* host = pinned_status();
+  if (!host) return SFC_ERR_NOMEM;
+  sfc::QueryScratch qs;
+  if (!sfc::query_scratch_carve(h->ws, m, &qs, slots_of(h))) return SFC_ERR_DEVICE;
+  Views views;
+  sfc::RangePlan rp = range_plan(h, &views, q, delta, nullptr, nullptr);
+  rp.need_rows = true;
+  rp.host = host;
+  rp.dbg_lo = key_lo;
+  rp.dbg_hi = key_hi;
+  rp.dbg_b = begin;
+  rp.dbg_e = end;
+  rp.dbg_nr = nranges;
+  SFC_TRY(sfc::launch_ranges(rp, qs, h->stream));
+  SFC_TRY(hipStreamSynchronize(h->stream));
+  st = status_of(*host);
+  if (st != SFC_OK) return st;
+  h->linfo.endpoints_last = host->endpoints;
+  h->linfo.fallbacks_last = host->fallbacks;
+  return SFC_OK;
 }
 
 uint64_t sfc_size(const sfc_index* h) { return h ? h->n : 0; }
@@ -1414,8 +1480,8 @@ struct sfc_graph {
   void* cscratch = nullptr;     // compaction scratch (queries)
   uint32_t* err = nullptr;      // construction error word
   sfc::QueryScratch qs{};
-  uint64_t m = 0, max_rows = 0, cap_ids = 0;
-  uint64_t* offsets = nullptr;
+  sfc::BatchStatus* host = nullptr;   // query batch: pinned, the replay's counters
+  uint64_t cap_ids = 0;
   uint64_t generation = 0;      // h's generation at recording
 };
 
@@ -1426,6 +1492,7 @@ void graph_release(sfc_graph* g) {
   if (g->exec) (void)hipGraphExecDestroy(g->exec);
   if (g->graph) (void)hipGraphDestroy(g->graph);
   if (g->cap) (void)hipStreamDestroy(g->cap);
+  if (g->host) (void)hipHostFree(g->host);
   if (g->h) {
     g->h->alloc.put(g->scratch);
     g->h->alloc.put(g->cscratch);
@@ -1511,40 +1578,33 @@ sfc_status sfc_graph_query(sfc_index* h, const double* q, const double* delta,
   g->h = h;
   g->kind = 1;
   g->generation = h->generation;
-  g->m = m;
-  g->max_rows = max_rows;
   g->cap_ids = ids_cap;
-  g->offsets = offsets;
   g->scratch = h->alloc.get(sfc::query_scratch_bytes(m, slots_of(h)));
   g->cscratch = h->alloc.get(sfc::compact_scratch_bytes(max_rows));
-  if (!g->scratch || !g->cscratch) {
+  if (hipHostMalloc((void**)&g->host, sizeof(sfc::BatchStatus), hipHostMallocDefault) !=
+      hipSuccess) {
+    (void)hipGetLastError();
+    g->host = nullptr;
+  }
+  if (!g->scratch || !g->cscratch || !g->host) {
     graph_release(g);
     return SFC_ERR_NOMEM;
   }
-  sfc::query_scratch_carve(g->scratch, m, &g->qs, slots_of(h));
-  const bool learned = h->search == SFC_SEARCH_LEARNED && h->linfo.fitted && !qset;
-  const sfc::LearnedView lv = h->larr.view();
-  const sfc::StreeView sv = sfc::stree_view(h->keys, h->n, h->stree);
-  sfc::EpochView ev;
-  const bool filtered = epoch_view(h, nullptr, &ev);
+  std::memset(g->host, 0, sizeof(*g->host));
+  if (!sfc::query_scratch_carve(g->scratch, m, &g->qs, slots_of(h))) {
+    graph_release(g);
+    return SFC_ERR_DEVICE;
+  }
+  Views views;
+  const sfc::RangePlan rp = range_plan(h, &views, q, delta, qset, nullptr);
+  sfc::CompactPlan cp = compact_plan(h, q, delta, offsets, ids, ids_cap);
+  cp.max_rows = max_rows;
+  cp.device_sized = true;
+  cp.scratch = g->cscratch;
+  cp.host = g->host;
   sfc_status st = graph_capture(g, [&](hipStream_t s) {
-    hipError_t e =
-        dim_of(h) == 3
-            ? sfc::launch_ranges3(q, delta, m, h->keys, h->n, h->refine != 0, h->refine_min,
-                                stree_on(h) ? &sv : nullptr, g->qs,
-                                  s)
-            : sfc::launch_ranges(q, delta, m, h->keys, h->n, h->curve, h->refine != 0,
-                                 h->refine_min, h->metric == SFC_METRIC_L2,
-                                 learned ? &lv : nullptr,
-                                 stree_on(h) ? &sv : nullptr, h->occ, qset,
-                                 qset ? h->set_off : nullptr, h->n_sets, g->qs, nullptr, nullptr,
-                                 nullptr, nullptr, nullptr, s);
-    if (e == hipSuccess)
-      e = sfc::launch_compact(q, delta, m, h->xy, h->xy_in, test_cells(h), h->ids, h->n,
-                              g->qs, max_rows, true, g->cscratch, offsets, ids, ids_cap,
-                              h->metric == SFC_METRIC_LINF, dim_of(h), s,
-                              filtered ? &ev : nullptr);
-    return e;
+    hipError_t e = sfc::launch_ranges(rp, g->qs, s);
+    return e == hipSuccess ? sfc::launch_compact(cp, g->qs, s) : e;
   });
   if (st != SFC_OK) {
     graph_release(g);
@@ -1572,14 +1632,12 @@ sfc_status sfc_graph_wait(sfc_graph* g, uint64_t* total_out) {
     if ((uint32_t)w & (sfc::kErrLookback | sfc::kErrInternal)) return SFC_ERR_DEVICE;
     return SFC_OK;
   }
-  uint64_t cw[2];
-  uint64_t total = 0;
-  SFC_TRY(read_words(g->qs.counters, cw, 2, h->stream));
-  SFC_TRY(read_words(g->offsets + g->m, &total, 1, h->stream));
-  const uint32_t err = ((const uint32_t*)cw)[2];
-  if (err & sfc::kErrInvalidQuery) return SFC_ERR_INVALID;
-  if (err & (sfc::kErrLookback | sfc::kErrInternal)) return SFC_ERR_DEVICE;
-  if (err & sfc::kErrOverflow) return SFC_ERR_CAPACITY;   // more candidate rows than max_rows
+  SFC_TRY(hipStreamSynchronize(h->stream));
+  const sfc_status st = status_of(*g->host);
+  if (st != SFC_OK) return st;
+  // more candidate rows than max_rows
+  if (g->host->err & sfc::kErrOverflow) return SFC_ERR_CAPACITY;
+  const uint64_t total = g->host->total;
   if (total_out) *total_out = total;
   return total > g->cap_ids ? SFC_ERR_CAPACITY : SFC_OK;
 }
@@ -1658,11 +1716,7 @@ sfc_status sfc_autotune_query(sfc_index* h, const double* q, const double* delta
   sfc_status st = query_impl(h, q, delta, qset, m, offsets, ids, ids_cap, &total);
   if (st != SFC_OK && st != SFC_ERR_CAPACITY) return st;
   // The test kernel's shape is chosen per bucket of the batch's candidate rows.
-  sfc::QueryScratch qs{};
-  uint64_t rows = 0, cand = 0;
-  st = run_ranges(h, q, delta, qset, m, &qs, &rows, &cand, nullptr, nullptr, nullptr, nullptr,
-                  nullptr);
-  if (st != SFC_OK) return st;
+  const uint64_t rows = h->last.rows;
   double t[5] = {0, 0, 0, 0, 0};
   int pick = 0;
   double tb = 1e30;

@@ -27,6 +27,7 @@ constexpr uint64_t kOccWords = (kOccBits + 31) / 32;
 // tuned(op, size) returns -1 when the bucket has no entry.
 enum TuneOp { kTuneSortItems = 0, kTuneTestShape = 1 };
 int tuned(TuneOp op, uint64_t size);
+bool tuned_any(TuneOp op);   // whether any bucket has an entry
 void set_tuned(TuneOp op, uint64_t size, int value);
 
 // Fill kernel (used instead of hipMemsetAsync so that every step of a batch
@@ -83,12 +84,13 @@ hipError_t sort_build_sets_chunked(const double* xy, uint64_t n, int curve, uint
 // out[i] = xy[ids[i]] for points of dim (2 or 3) doubles.
 hipError_t gather_sorted(const uint32_t* ids, const double* xy, double* out, uint64_t n, int dim,
                          hipStream_t s);
-// Order of a batch of m queries (centres clamped into the square) by the
-// top 16 bits of their curve keys, stable: perm[i] = the i-th query in that
-// order.  scratch holds order_scratch_bytes(m); err: device error word.
+// Order of a batch of m queries (centres clamped into the domain) along the
+// curve, as far as the places of their keys among the n >= 1 sorted ones, taken
+// to 11 bits, tell: perm[i] = the i-th query in that order.  scratch holds
+// order_scratch_bytes(m).
 size_t order_scratch_bytes(uint64_t m);
-hipError_t order_queries(const double* q, uint64_t m, int curve, uint32_t* perm, void* scratch,
-                         uint32_t* err, hipStream_t s);
+hipError_t order_queries(const double* q, uint64_t m, int curve, const uint64_t* keys, uint64_t n,
+                         uint32_t* perm, void* scratch, hipStream_t s);
 // Early-termination occupancy bitmap (kOccWords words) of n sorted keys.
 hipError_t build_occupancy(const uint64_t* keys, uint64_t n, uint32_t* occ, hipStream_t s);
 
@@ -100,20 +102,63 @@ hipError_t scan_excl(const uint32_t* in, uint64_t* out, uint64_t count, const ui
                      uint64_t* partial, hipStream_t s);
 
 // ---- queries (query.hip) ----
+// The counters of a batch, in device memory; the compaction's last kernel
+// copies them to host memory when asked to.
+struct BatchStatus {
+  uint64_t rows;         // candidate rows of 64
+  uint64_t total;        // reported ids (host copy only)
+  uint64_t candidates;
+  uint64_t endpoints;    // learned lower bounds
+  uint64_t fallbacks;    // of which fell back to binary search
+  uint64_t pruned;       // cells skipped by early termination
+  uint32_t err;          // kErr* bits
+  uint32_t coarse;       // some radius lies past the cell filter's shift limit
+  uint32_t units;        // compaction units of the current chunk
+  uint32_t pad;
+};
+
+// What the search leaves of each query for the test pass: nothing, the cell
+// filter's limits, or the query itself (tests that read every point); for
+// queries at epochs also their epoch (qepoch[j], valid in [oldest, epoch], or
+// `epoch` when qepoch is null).
+enum { kRecordNone = 0, kRecordFilter = 1, kRecordExact = 2 };
+struct RecordPlan {
+  void* rec = nullptr;
+  int mode = kRecordNone;
+  bool window = false;
+  const uint32_t* qepoch = nullptr;
+  uint32_t oldest = 0, epoch = 0;
+};
+
+// Scratch of one batch of m queries.  Places are positions in the order that
+// the rows are processed in: the queries' own, or the curve order of perm.
 struct QueryScratch {
-  uint32_t* slot_begin;   // per query slot: first sorted index of its range
-  uint32_t* slot_count;   // per query slot: its number of candidates
-  uint32_t* slot_rows;    // per query slot: rows of 64 candidates
-  uint64_t* row_off;      // per query: its first row (+ the total at [m])
-  uint64_t* scan_tmp;     // scan partials
-  uint32_t* counters;     // [2] error word; u64 at [4]: candidates, [6]: learned
-                          // endpoints, [8]: learned fallbacks
-  int ss;                 // log2 of the slots per query (2: method's ranges, 3: refined)
-  uint64_t* pairs;        // dense (query, cell) work list: 4 * query + cell
-  void* qfilt;            // per query: its grid cell and the cell filter's limits (32 B)
-  uint32_t* perm;         // queries in curve order (the search's lane order)
-  uint32_t* qrows;        // per query: the rows of its slots
-  void* order_scratch;    // order_scratch_bytes(m)
+  uint64_t m = 0;
+  BatchStatus* status;
+  uint2* slots;            // per query and slot: first sorted index, candidates
+  uint64_t* row_off;       // per place: its first row (+ the total at [m])
+  uint64_t* blk_rows;      // per workgroup of places: its rows,
+  uint64_t* blk_off;       //   its first row,
+  uint64_t* blk_stat;      // per search workgroup: its candidates and flags,
+  uint32_t* blk_learned;   //   its learned endpoints and fallbacks
+  void* rec;               // per query: the test pass's record (32 B)
+  uint32_t* perm;          // the queries in curve order
+  uint64_t* out_base;      // per query: added to the hits before a row gives its output
+  uint32_t* qhits;         // per query: its reports
+  uint64_t* scan_tmp;      // scan partials
+  void* order_scratch;     // order_scratch_bytes(m)
+  uint64_t* pairs;         // early termination: dense (query, cell) list, 4 * query + cell
+  uint64_t* regions;       //   the same, by workgroup
+  uint32_t* pack_cnt;      //   per workgroup: its pairs,
+  uint32_t* pack_pre;      //   those before it (+ the total),
+  uint32_t* pack_pruned;   //   its pruned cells,
+  uint64_t* pack_flags;    //   its flags
+  int ss;                  // log2 of the slots per query
+  int block_queries;       // queries per search workgroup
+  uint32_t stats_ns, stats_np;   // workgroups whose counters are summed
+  bool learned;            // blk_learned is filled
+  bool perm_made;          // perm holds the queries in curve order
+  bool fused;              // expand_rows scans blk_rows and sums the counters itself
 };
 constexpr uint64_t kCompactTileRows = 64;           // rows of 64 candidates per tile
 constexpr uint64_t kCompactChunkTiles = 1ull << 19; // tiles per launch
@@ -122,63 +167,80 @@ uint64_t compact_chunk_tiles();
 void set_compact_chunk_tiles(uint64_t tiles);
 // Query scratch for m queries of up to `slots` slots each (8: the plane,
 // either layout, and three dimensions unrefined; 32: three dimensions
-// refined).
+// refined).  The carving returns false if the layout needs more than that.
 size_t query_scratch_bytes(uint64_t m, uint32_t slots = 8);
-void query_scratch_carve(void* base, uint64_t m, QueryScratch* qs, uint32_t slots = 8);
+bool query_scratch_carve(void* base, uint64_t m, QueryScratch* qs, uint32_t slots = 8);
 size_t compact_scratch_bytes(uint64_t total_rows);
 
-// Ranges and searches per query slot, then the scan of candidate counts into
-// segment offsets; optionally records the ranges (dbg_* may be null).  ball:
-// the Euclidean metric (the refinement may then also drop sub-cells outside
-// the disc).
-// lview non-null: searches go through the learned index; else sview
-// non-null: through the static search tree (both only without point sets).
-// occ non-null: cells whose occupancy bit is clear are skipped (early
-// termination; not applied when the ranges are recorded for inspection).
-// qset/set_off non-null: query j searches only set qset[j] (positions
-// [set_off[s], set_off[s+1]) of the sorted arrays).
-hipError_t launch_ranges(const double* q, const double* delta, uint64_t m, const uint64_t* keys,
-                         uint64_t n, int curve, bool refine, uint32_t refine_min, bool ball,
-                         const LearnedView* lview, const StreeView* sview, const uint32_t* occ,
-                         const uint32_t* qset, const uint64_t* set_off, uint32_t n_sets,
-                         QueryScratch& qs, uint64_t* dbg_lo, uint64_t* dbg_hi, uint64_t* dbg_b,
-                         uint64_t* dbg_e, uint32_t* dbg_nr, hipStream_t s);
-// Three dimensions (points and queries of three doubles, d = 3 Morton keys):
-// the at most 8 cube ranges of every query and their searches (binary, or the
-// static search tree when sview is non-null; refine: crowded cubes split once
-// into at most four runs of children, 32 slots per query), then the scan, as
-// launch_ranges.
-hipError_t launch_ranges3(const double* q, const double* delta, uint64_t m, const uint64_t* keys,
-                          uint64_t n, bool refine, uint32_t refine_min, const StreeView* sview,
-                          QueryScratch& qs, hipStream_t s);
-// Test-and-compact over the candidate rows.  device_sized = false: max_rows
-// is the exact row count (known on the host), processed in chunks.
-// device_sized = true: max_rows is a capacity, the count is read on the
-// device (a plan for graph capture); more rows raise kErrOverflow.  cscratch
-// holds compact_scratch_bytes(max_rows).  window: the square-window test
-// (half side delta) instead of the Euclidean ball.  dim: 2, or 3 for points
-// and queries of three doubles.  cells (may be null): the grid cells of the
-// sorted points (pack_cell2 / pack_cell3); with them most candidates are
-// decided from their cell and only the undecided ones read their coordinates,
-// from pts (the sorted points) when not null, else from pts_in (input order)
-// through their ids.  Without cells pts must not be null.  coarse: whether
-// some radius of the batch lies above the cell filter's shift limit (the
-// flag that launch_ranges sets in the counters: 1, 0 when the caller read
-// it, -1 when not; with 0 the test pass takes its shortest form).
-struct EpochView;
-hipError_t launch_compact(const double* q, const double* delta, uint64_t m, const double* pts,
-                          const double* pts_in, const uint64_t* cells, const uint32_t* ids,
-                          uint64_t npts, const QueryScratch& qs,
-                          uint64_t max_rows, bool device_sized, void* cscratch,
-                          uint64_t* offsets, uint32_t* out_ids, uint64_t cap, bool window,
-                          int dim, hipStream_t s,
-                          const EpochView* ev = nullptr, bool write_only = false,
-                          int coarse = -1);
-// Whether a batch of total_rows rows (host-sized) is compacted in one chunk:
-// then an output larger than the capacity leaves the ids untouched, and the
-// write pass can be rerun alone (write_only) for a larger buffer.
+// Ranges and searches of a batch (qs carved for its m queries), then the
+// rows and the batch's counters.
+struct RangePlan {
+  const double* q = nullptr;
+  const double* delta = nullptr;
+  int dim = 2;                         // 3: points and queries of three doubles, Morton keys
+  const uint64_t* keys = nullptr;
+  uint64_t n = 0;
+  int curve = 0;
+  bool refine = false;
+  uint32_t refine_min = 0;
+  bool ball = false;                   // Euclidean metric: the refinement may drop sub-cells
+                                       // outside the disc
+  const LearnedView* lview = nullptr;  // search through the learned index; else
+  const StreeView* sview = nullptr;    // through the static search tree (not with point sets)
+  const uint32_t* occ = nullptr;       // skip cells whose occupancy bit is clear
+  const uint32_t* qset = nullptr;      // query j searches only set qset[j] (positions
+  const uint64_t* set_off = nullptr;   // [set_off[s], set_off[s+1]) of the sorted arrays)
+  uint32_t n_sets = 0;
+  RecordPlan record;
+  bool need_rows = false;              // the caller reads the counters before the compaction
+  BatchStatus* host = nullptr;         // receives them then (host memory), if not null
+  // Inspection (all or none): the method's key and index ranges, four per
+  // query, and their number; no early termination, refinement or records.
+  uint64_t* dbg_lo = nullptr;
+  uint64_t* dbg_hi = nullptr;
+  uint64_t* dbg_b = nullptr;
+  uint64_t* dbg_e = nullptr;
+  uint32_t* dbg_nr = nullptr;
+};
+hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s);
+
+// Test-and-compact over the candidate rows of a batch whose ranges are in qs.
+struct CompactPlan {
+  const double* q = nullptr;
+  const double* delta = nullptr;
+  const double* pts = nullptr;       // the sorted points, or null: then
+  const double* pts_in = nullptr;    // the points in input order, read through their ids
+  const uint64_t* cells = nullptr;   // grid cells of the sorted points: with them most
+                                     // candidates are decided from their cell and only the
+                                     // others read their point; without, pts must be set
+  const uint32_t* ids = nullptr;
+  const uint64_t* keys = nullptr;    // the sorted keys, their number and the curve, to process
+  uint64_t n = 0;                    // the rows in curve order; null: in query order
+  int curve = 0;
+  uint64_t max_rows = 0;             // device_sized false: the exact row count, processed in
+  bool device_sized = false;         // chunks; true: a capacity, the count is read on the
+                                     // device and more rows raise kErrOverflow
+  void* scratch = nullptr;           // compact_scratch_bytes(max_rows)
+  uint64_t* offsets = nullptr;
+  uint32_t* out_ids = nullptr;
+  uint64_t cap = 0;
+  bool window = false;               // the square-window test instead of the ball
+  int dim = 2;
+  const uint32_t* ins = nullptr;     // with both: only entries with ins <= e < era are
+  const uint32_t* era = nullptr;     // visible to a query at epoch e
+  bool write_only = false;           // the write pass alone, on a batch still in scratch
+  int coarse = -1;                   // BatchStatus::coarse if the caller read it (1, 0), else
+                                     // -1; with 0 the test pass takes its shortest form
+  BatchStatus* host = nullptr;       // host memory: the final counters, if not null
+  uint32_t* flags_out = nullptr;     // device: the final error bits, if not null
+};
+hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs, hipStream_t s);
+// Whether a batch of total_rows rows is compacted in one chunk: then an output
+// larger than the capacity leaves the ids untouched, and the write pass can be
+// rerun alone (write_only) for a larger buffer.
 bool compact_single_chunk(uint64_t total_rows);
 // Scan with the element count in device memory (count_dev <= max_count).
+size_t scan_dev_scratch_bytes(uint64_t max_count);
 hipError_t scan_excl_dev(const uint32_t* in, uint64_t* out, const uint32_t* count_dev,
                          uint64_t max_count, const uint64_t* carry_in, uint64_t* partial,
                          hipStream_t s);
@@ -194,15 +256,6 @@ struct Run {
   uint32_t* ins = nullptr;
   uint32_t* era = nullptr;
   uint64_t* cells = nullptr;   // grid cells of the points (pack_cell2) if kept (may be null)
-};
-// Which stored entries a query sees: those with ins <= e < era, e = the
-// query's epoch (qepoch[j], or `epoch` when qepoch is null).  ins == null:
-// every entry is visible.
-struct EpochView {
-  const uint32_t* ins = nullptr;
-  const uint32_t* era = nullptr;
-  const uint32_t* qepoch = nullptr;
-  uint32_t epoch = 0;
 };
 // Merges the stored run (n entries) with a sorted batch (k entries, local
 // ids bids) into `out` (n + k entries).  The batch's entries are inserted at
@@ -223,10 +276,6 @@ size_t compact_entries_scratch(uint64_t n);
 hipError_t compact_entries(const Run& stored, uint64_t n, uint32_t oldest, const Run& out,
                            void* scratch, uint64_t** kept_total, hipStream_t s);
 hipError_t fill_iota(uint32_t* out, uint64_t k, uint32_t first, hipStream_t s);
-// Raises kErrInvalidQuery in *err for an epoch outside [oldest, epoch].
-hipError_t validate_epochs(const uint32_t* qe, uint64_t m, uint32_t oldest, uint32_t epoch,
-                           uint32_t* err, hipStream_t s);
-
 // ---- learned index (learned.hip) ----
 size_t learned_scratch_bytes();
 // Device arrays of a learned index sized for n keys (learned_model_bytes(n)

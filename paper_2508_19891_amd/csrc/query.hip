@@ -7,24 +7,41 @@
 //                  Observation gives each cell's interval); slot r then runs
 //                  the two searches of interval r over the sorted keys
 //                  (binary search or the learned index), optionally split
-//                  once into the cell's children that meet the box.
+//                  once into the cell's children that meet the box.  It also
+//                  writes what the test needs of each query (a record) and
+//                  each workgroup's candidate rows.
 //   cells_pack     with early termination: the cells whose quadtree node
 //                  holds a point, as a dense (query, cell) work list, so the
 //                  search spends lanes only on them.
-//   scan           candidate rows of every slot -> row offsets.
-//   expand_rows    rows -> (slot, first candidate) tiles.
-//   compact_test   a block tests its tiles' candidates (64-lane rows) with
-//                  the exact distance test and counts the hits per tile;
-//                  the hit counts are scanned on the device.
-//   compact_write  the same tiles again, one lane per reported id: the ids at
-//                  the scanned positions, in candidate order, and every
-//                  row's output position.
-//   query_offsets  the CSR offset of every query, from its first row.
+//   batch_scan     the workgroups' rows -> their first rows, and the batch's
+//                  counters (small batches: inside expand_rows).
+//   expand_rows    rows -> (slot, first candidate) tiles, and every query's
+//                  first row.
+//   compact_test   a wave tests 16 rows of 64 candidates each with the exact
+//                  distance test: a hit mask per row, the rows' hits before
+//                  it among the 16, and the 16 rows' hits, which are scanned
+//                  on the device.
+//   compact_write  the same tiles again: the ids of the hits at the scanned
+//                  positions, in candidate order; and the CSR offset of every
+//                  query, from its first row.
+//
+// A small batch is four launches: no counter is read by the host, scans are done
+// inside the kernels that need them, no memory is cleared, and the last kernel
+// stores the counters to host memory (16 queries over 2^16 points: 140 -> 39 us,
+// most of it the launches' own latency).
+//
+// A large batch's search takes its queries in curve order, and with many rows a
+// query the rows follow that order too: consecutive tiles then read the same
+// lines of the cells and ids and find them in the L2 of their XCD.  The reports
+// still leave in query order: the hits of every query (from the rows' prefixes)
+// are scanned in query order, and each row is written at its query's offset.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
 
 #include <cstdlib>
+#include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "curve.h"
@@ -37,29 +54,141 @@ namespace sfc {
 
 namespace {
 
+// ---- what the test pass needs of a query ------------------------------------
+//
+// A point p with grid cell u = floor(p * S) (S = 2^32 in the plane, 2^21 in
+// three dimensions) lies in [u, u + 1) quanta on each axis.  Measured in
+// quanta from the query's own cell c = floor(q S), its offset on an axis is
+// o = e + th with the integer e = u - c and |th| < 1, so o^2 lies within
+// 2|e| + 1 of e^2.  A candidate comes from the query's own cells, which meet
+// the box widened by one quantum, so |e| <= E = 6R + 10 with R = d S (exact
+// scalings): the sum of the squared offsets lies within the slack
+// s = DIM (2E + 1) of the sum of the e^2.  For the Euclidean test:
+//   * if sum e^2 <= R^2 (1 - 2^-16) - s, the rounded binary64 test accepts p;
+//   * if sum e^2 > R^2 (1 + 2^-16) + s, it rejects p;
+// for the square window, |e| <= R (1 - 2^-16) - 1 on every axis accepts and
+// |e| > R (1 + 2^-16) + 1 on some axis rejects.  Evaluated in binary32
+// (relative errors below 2^-20 all told) these verdicts equal the exact
+// test's, whose own rounding is a few 2^-53 relative, when R >= 16 (so the
+// slack is small beside R^2).  Other points read their coordinates and take
+// the exact test.  A query uses the filter when R >= 16 and its cell lies
+// within 2^30 quanta of the domain.  Above R = 2^28 (plane) / 2^17 (three
+// dimensions) the cells are compared 2^k quanta wide (u >> k against
+// floor(q S 2^-k), k the smallest shift that brings R 2^-k to that limit,
+// at most 24): the same bounds hold there with R 2^-k for R, since the
+// shifted offsets again differ from the exact ones by less than one.  Then
+// |e| < 2^31, exact in 32-bit arithmetic.  Cells sit in one word: x | y << 32,
+// or x | y << 21 | z << 42.
+struct QueryFilter {
+  float acc, rej;   // limits on sum e^2 (or per-axis |e|); filter off: acc = not a number
+                    // and rej = +inf, so that neither comparison decides a candidate
+  uint32_t c[3];    // the query's cell per axis (low 32 bits), 2^shift quanta wide
+  uint32_t shift;   // cells are compared 2^shift quanta wide
+  uint32_t pad[2];
+};
+// The record of a batch whose test reads every candidate's point.
+struct QueryExact2 {
+  double x, y, d;
+  uint32_t pad;
+  uint32_t epoch;   // the epoch it is answered at
+};
+struct QueryExact3 {
+  double x, y, z, d;
+};
+static_assert(sizeof(QueryFilter) == 32 && sizeof(QueryExact2) == 32 && sizeof(QueryExact3) == 32,
+              "a record is 32 bytes");
+
+template <int DIM>
+constexpr double grid_side() { return DIM == 2 ? 4294967296.0 : 2097152.0; }
+// The largest radius, in quanta, compared in whole quanta.
+template <int DIM>
+constexpr double filter_limit() { return DIM == 2 ? 0x1p28 : 0x1p17; }
+
+template <int DIM>
+__device__ __forceinline__ QueryFilter query_filter(const double (&q)[DIM], double d,
+                                                    bool window) {
+  constexpr double S = grid_side<DIM>(), kMaxR = filter_limit<DIM>();
+  const double R0 = d * S;
+  int k = 0;
+  while (k < 24 && R0 > kMaxR * __builtin_ldexp(1.0, k)) ++k;
+  const double R = __builtin_ldexp(R0, -k);   // exact
+  bool on = R0 >= 16.0 && R <= kMaxR;
+  QueryFilter f{};
+  f.shift = (uint32_t)k;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) {
+    const double qs = q[a] * S;
+    on = on && qs > -0x1p30 && qs < S + 0x1p30;
+    f.c[a] = (uint32_t)(int64_t)__builtin_floor(on ? __builtin_ldexp(qs, -k) : 0.0);
+  }
+  if (window) {
+    f.acc = (float)(R * (1.0 - 0x1p-16) - 1.0);
+    f.rej = (float)(R * (1.0 + 0x1p-16) + 1.0);
+  } else {
+    const double slack = DIM * (2.0 * (6.0 * R + 10.0) + 1.0);
+    f.acc = (float)(R * R * (1.0 - 0x1p-16) - slack);
+    f.rej = (float)(R * R * (1.0 + 0x1p-16) + slack);
+  }
+  if (!on) {   // undecided for every candidate: the exact test decides
+    f.acc = __uint_as_float(0xFFFFFFFFu);
+    f.rej = __builtin_inff();
+    f.shift = 0;
+  }
+  return f;
+}
+
+// Writes the record of query j.
+template <int DIM>
+__device__ __forceinline__ void put_record(const RecordPlan& R, uint64_t j,
+                                           const double (&q)[DIM], double d) {
+  if (R.mode == kRecordFilter) {
+    ((QueryFilter*)R.rec)[j] = query_filter<DIM>(q, d, R.window);
+  } else if (R.mode == kRecordExact) {
+    if constexpr (DIM == 2)
+      ((QueryExact2*)R.rec)[j] = QueryExact2{q[0], q[1], d, 0, R.qepoch ? R.qepoch[j] : R.epoch};
+    else
+      ((QueryExact3*)R.rec)[j] = QueryExact3{q[0], q[1], q[2], d};
+  }
+}
+
+// A workgroup's candidates and flags in one word (a workgroup's at most 64
+// queries have fewer than 2^39 candidates).
+constexpr int kStatShift = 48;
+constexpr uint64_t kStatInvalid = 1ull << kStatShift;         // an invalid query
+constexpr uint64_t kStatCoarse = 1ull << (kStatShift + 1);    // a radius past the filter limit
+
 // One lane per (query, slot): four slots per query (the method's ranges),
 // or eight (REFINE: two runs per cell of cells(Q)); the lane's work is the
-// body in query_lane.inc.
+// body in query_lane.inc.  perm non-null: the queries in curve order, so that
+// the searches of a workgroup meet in the same lines of the key array; slots
+// and records are laid out by query.  Each workgroup (64 queries) also sums
+// its counters, and its candidate rows if it holds 64 consecutive queries: one
+// word each per workgroup, no atomics (those of every workgroup on one address
+// serialise across the XCDs), and nothing to clear beforehand.
 // At least five waves per SIMD (at most 102 registers): the chains of
-// dependent probes need waves in flight.  The binary-search variants take 62
-// registers (eight waves) now that query_cells indexes its arrays statically;
-// the learned-index variants take 92.
+// dependent probes need waves in flight.
 template <int CURVE, bool REFINE, int SEARCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void ranges_search(
     const double2* __restrict__ q, const double* __restrict__ delta, uint64_t m,
     const uint64_t* __restrict__ keys, uint64_t n, LearnedView lv, StreeView sv,
     uint32_t refine_min, bool ball, const uint32_t* __restrict__ occ,
-    const uint64_t* __restrict__ pairs,
-    const uint64_t* __restrict__ pair_total, const uint32_t* __restrict__ qset,
-    const uint64_t* __restrict__ set_off, uint32_t n_sets, uint32_t* __restrict__ slot_begin, uint32_t* __restrict__ slot_count,
-    uint32_t* __restrict__ slot_rows, uint32_t* counters, unsigned long long* cand_total,
-    const uint32_t* __restrict__ perm,
-    uint64_t* __restrict__ dbg_lo, uint64_t* __restrict__ dbg_hi, uint64_t* __restrict__ dbg_b,
-    uint64_t* __restrict__ dbg_e, uint32_t* __restrict__ dbg_nr) {
+    const uint64_t* __restrict__ pairs, const uint32_t* __restrict__ pair_total,
+    const uint32_t* __restrict__ qset, const uint64_t* __restrict__ set_off, uint32_t n_sets,
+    const uint32_t* __restrict__ perm, RecordPlan record, uint2* __restrict__ slots,
+    uint64_t* __restrict__ blk_rows, uint64_t* __restrict__ blk_stat,
+    uint32_t* __restrict__ blk_learned, uint64_t* __restrict__ dbg_lo,
+    uint64_t* __restrict__ dbg_hi, uint64_t* __restrict__ dbg_b, uint64_t* __restrict__ dbg_e,
+    uint32_t* __restrict__ dbg_nr) {
   constexpr bool LEARNED = SEARCH == 1;
   __shared__ uint16_t lut[CURVE == SFC_CURVE_HILBERT ? 1024 : 1];
-  // Blocks past the listed pairs have nothing to do (uniform per block).
-  if (pairs && (uint64_t)blockIdx.x * 256 >= *pair_total) return;
+  // Workgroups past the listed pairs have nothing to do (uniform per block).
+  if (pairs && (uint64_t)blockIdx.x * 256 >= *pair_total) {
+    if (threadIdx.x == 0) {
+      blk_stat[blockIdx.x] = 0;
+      if (LEARNED) blk_learned[blockIdx.x] = 0;
+    }
+    return;
+  }
   if (CURVE == SFC_CURVE_HILBERT)
     for (int i = threadIdx.x; i < 1024; i += 256) lut[i] = kHilbertLutConst.v[i];
   __syncthreads();
@@ -67,27 +196,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   // cell that survived early termination, packed densely; idle lanes take
   // j = m.
   const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  uint64_t j, sidx;
-  int r;
-  if (pairs) {
-    const bool act = g < *pair_total;
-    const uint64_t pr = act ? pairs[g] : 0;
-    j = act ? pr >> 2 : m;
-    r = (int)(pr & 3);
-    sidx = pr;
-  } else {
-    // perm non-null: the queries in curve order, so that the searches of a
-    // workgroup meet in the same lines of the key array.
-    const uint64_t jj = g >> 2;
-    j = perm && jj < m ? perm[jj] : jj;
-    r = (int)(g & 3);
-    sidx = 4 * j + (uint64_t)r;
-  }
+  const bool act = pairs ? g < *pair_total : (g >> 2) < m;
+  const uint64_t pair = pairs ? (act ? pairs[g] : 0) : g;   // 4 * query + cell
+  const int r = (int)(pair & 3);
+  const uint64_t j = act ? (perm ? perm[pair >> 2] : pair >> 2) : m;
+  const uint64_t sidx = 4 * j + r;
 
   uint64_t b0 = 0, e0 = 0, b1 = 0, e1 = 0, klo = 0, khi = 0;
   int nr = 0;
-  bool bad = false;
+  bool bad = false, coarse = false;
   uint32_t fb = 0, ends = 0, pruned = 0;
+  if (!pairs && j < m && r == 0 && record.mode != kRecordNone) {
+    const double2 qq = q[j];
+    const double c[2] = {qq.x, qq.y}, d = delta[j];
+    put_record<2>(record, j, c, d);
+    coarse = d * grid_side<2>() > filter_limit<2>();
+    if (record.qepoch) {
+      const uint32_t qe = record.qepoch[j];
+      bad = qe < record.oldest || qe > record.epoch;
+    }
+  }
   // With point sets, a query searches only its own set's keys: positions
   // [base, base + nn) of the sorted arrays.
   uint64_t base = 0, nn = n;
@@ -102,40 +230,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     }
   }
 #include "query_lane.inc"
-  if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(&counters[2], kErrInvalidQuery);
-  // Candidates (and learned-index endpoints and fallbacks) of the block, for
-  // the statistics: one device atomic per counter and block (atomics on one
-  // address from every wave of the grid serialise).
-  __shared__ unsigned long long s_stat[4][4];
-  uint64_t wc = (e0 - b0) + (e1 - b1);
-  uint32_t wf = fb, we = ends, wp = pruned;
+  (void)pruned;   // counted where the work list is made
+  // Candidates, rows, flags (and learned-index endpoints and fallbacks) of
+  // the workgroup.
+  __shared__ uint64_t s_cand[4], s_rows[4];
+  __shared__ uint32_t s_learned[4];
+  const uint32_t r0 = (uint32_t)((e0 - b0 + 63) >> 6), r1 = (uint32_t)((e1 - b1 + 63) >> 6);
+  uint64_t wc = (e0 - b0) + (e1 - b1), wr = (uint64_t)r0 + r1;
+  uint32_t wl = (ends << 16) | fb;
+  const uint64_t flags = (__ballot(bad) != 0 ? kStatInvalid : 0) |
+                         (__ballot(coarse) != 0 ? kStatCoarse : 0);
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     wc += __shfl_xor(wc, o, 64);
-    wp += __shfl_xor(wp, o, 64);
-    if (LEARNED) {
-      wf += __shfl_xor(wf, o, 64);
-      we += __shfl_xor(we, o, 64);
-    }
+    wr += __shfl_xor(wr, o, 64);
+    if (LEARNED) wl += __shfl_xor(wl, o, 64);
   }
   const uint32_t wv = threadIdx.x >> 6;
   if (lane_id() == 0) {
-    s_stat[0][wv] = wc;
-    s_stat[1][wv] = we;
-    s_stat[2][wv] = wf;
-    s_stat[3][wv] = wp;
+    s_cand[wv] = wc | flags;
+    s_rows[wv] = wr;
+    if (LEARNED) s_learned[wv] = wl;
   }
   __syncthreads();
-  if (threadIdx.x < 4 && (threadIdx.x == 0 || threadIdx.x == 3 || LEARNED)) {
-    const unsigned long long t = s_stat[threadIdx.x][0] + s_stat[threadIdx.x][1] +
-                                 s_stat[threadIdx.x][2] + s_stat[threadIdx.x][3];
-    if (t) atomicAdd(cand_total + threadIdx.x, t);
+  if (threadIdx.x == 0) {
+    uint64_t c = 0, f = 0;
+    for (int w = 0; w < 4; ++w) {
+      c += s_cand[w] & (kStatInvalid - 1);
+      f |= s_cand[w] & ~(kStatInvalid - 1);
+    }
+    blk_stat[blockIdx.x] = c | f;
+    if (!pairs && !perm) blk_rows[blockIdx.x] = s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3];
+    if (LEARNED)
+      blk_learned[blockIdx.x] = s_learned[0] + s_learned[1] + s_learned[2] + s_learned[3];
   }
   if (j < m) {
     if (!REFINE) {
-      slot_begin[sidx] = (uint32_t)b0;
-      slot_count[sidx] = (uint32_t)(e0 - b0);
-      slot_rows[sidx] = (uint32_t)((e0 - b0 + 63) >> 6);
+      slots[sidx] = make_uint2((uint32_t)b0, (uint32_t)(e0 - b0));
       if (dbg_lo) {
         dbg_lo[sidx] = klo;
         dbg_hi[sidx] = khi;
@@ -144,12 +275,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
         if (r == 0) dbg_nr[j] = (uint32_t)nr;
       }
     } else {
-      slot_begin[2 * sidx] = (uint32_t)b0;
-      slot_count[2 * sidx] = (uint32_t)(e0 - b0);
-      slot_rows[2 * sidx] = (uint32_t)((e0 - b0 + 63) >> 6);
-      slot_begin[2 * sidx + 1] = (uint32_t)b1;
-      slot_count[2 * sidx + 1] = (uint32_t)(e1 - b1);
-      slot_rows[2 * sidx + 1] = (uint32_t)((e1 - b1 + 63) >> 6);
+      ((uint4*)slots)[sidx] =
+          make_uint4((uint32_t)b0, (uint32_t)(e0 - b0), (uint32_t)b1, (uint32_t)(e1 - b1));
     }
   }
 }
@@ -324,17 +451,26 @@ template <int SEARCH, bool REFINE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void ranges_search3(
     const double* __restrict__ q, const double* __restrict__ delta, uint64_t m,
     const uint64_t* __restrict__ keys, uint64_t n, LearnedView lv, StreeView sv,
-    uint32_t refine_min, uint32_t* __restrict__ slot_begin, uint32_t* __restrict__ slot_count,
-    uint32_t* __restrict__ slot_rows, uint32_t* counters, unsigned long long* cand_total) {
+    uint32_t refine_min, const uint32_t* __restrict__ perm, RecordPlan record,
+    uint2* __restrict__ slots, uint64_t* __restrict__ blk_rows,
+    uint64_t* __restrict__ blk_stat) {
   const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  const uint64_t j = g >> 3;
+  const uint64_t j = (g >> 3) < m ? (perm ? perm[g >> 3] : g >> 3) : m;
   const int r = (int)(g & 7);
   uint64_t B[4] = {0, 0, 0, 0}, E[4] = {0, 0, 0, 0};
   uint32_t fb = 0;
-  bool bad = false;
+  bool bad = false, coarse = false;
   if (j < m) {
     const double qx = q[3 * j], qy = q[3 * j + 1], qz = q[3 * j + 2], d = delta[j];
-    if (!(finite64(qx) && finite64(qy) && finite64(qz) && finite64(d) && d >= 0.0)) {
+    if (r == 0) {
+      const double c[3] = {qx, qy, qz};
+      put_record<3>(record, j, c, d);
+      coarse = d * grid_side<3>() > filter_limit<3>();
+    }
+    const bool bad_epoch = record.qepoch && (record.qepoch[j] < record.oldest ||
+                                             record.qepoch[j] > record.epoch);
+    if (bad_epoch ||
+        !(finite64(qx) && finite64(qy) && finite64(qz) && finite64(d) && d >= 0.0)) {
       bad = true;
     } else if (!REFINE) {
       uint64_t lo[8], hi[8];
@@ -412,89 +548,102 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
       }
     }
   }
-  if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(&counters[2], kErrInvalidQuery);
-  __shared__ unsigned long long s_c[4];
-  unsigned long long wc = (E[0] - B[0]) + (E[1] - B[1]) + (E[2] - B[2]) + (E[3] - B[3]);
+  // Candidates, rows and flags of the workgroup (32 queries).
+  __shared__ uint64_t s_cand[4], s_rows[4];
+  uint64_t wc = 0, wr = 0;
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) wc += __shfl_xor(wc, o, 64);
-  if (lane_id() == 0) s_c[threadIdx.x >> 6] = wc;
+  for (int t = 0; t < 4; ++t) {
+    wc += E[t] - B[t];
+    wr += (E[t] - B[t] + 63) >> 6;
+  }
+  const uint64_t flags = (__ballot(bad) != 0 ? kStatInvalid : 0) |
+                         (__ballot(coarse) != 0 ? kStatCoarse : 0);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    wc += __shfl_xor(wc, o, 64);
+    wr += __shfl_xor(wr, o, 64);
+  }
+  if (lane_id() == 0) {
+    s_cand[threadIdx.x >> 6] = wc | flags;
+    s_rows[threadIdx.x >> 6] = wr;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const unsigned long long t = s_c[0] + s_c[1] + s_c[2] + s_c[3];
-    if (t) atomicAdd(cand_total, t);
+    uint64_t c = 0, f = 0;
+    for (int w = 0; w < 4; ++w) {
+      c += s_cand[w] & (kStatInvalid - 1);
+      f |= s_cand[w] & ~(kStatInvalid - 1);
+    }
+    blk_stat[blockIdx.x] = c | f;
+    if (!perm) blk_rows[blockIdx.x] = s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3];
   }
   if (j < m) {
+    const uint64_t sidx = 8 * j + r;
     if (!REFINE) {
-      slot_begin[g] = (uint32_t)B[0];
-      slot_count[g] = (uint32_t)(E[0] - B[0]);
-      slot_rows[g] = (uint32_t)((E[0] - B[0] + 63) >> 6);
+      slots[sidx] = make_uint2((uint32_t)B[0], (uint32_t)(E[0] - B[0]));
     } else {
+      uint4* o = (uint4*)(slots + 4 * sidx);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        slot_begin[4 * g + t] = (uint32_t)B[t];
-        slot_count[4 * g + t] = (uint32_t)(E[t] - B[t]);
-        slot_rows[4 * g + t] = (uint32_t)((E[t] - B[t] + 63) >> 6);
-      }
+      for (int t = 0; t < 4; t += 2)
+        o[t / 2] = make_uint4((uint32_t)B[t], (uint32_t)(E[t] - B[t]), (uint32_t)B[t + 1],
+                              (uint32_t)(E[t + 1] - B[t + 1]));
     }
   }
 }
 
 // The cells of every query that survive early termination, as (query, cell)
-// pairs (4 * query + cell) for the search.  One thread per query; block b
-// lists its pairs at the start of its own region pairs[1024 b ..] and its
-// counts of pairs and of pruned cells in blk_cnt[b] and blk_pruned[b]
-// (pack_scan and pack_move then make the list dense, in query order).  No
-// atomic on a shared word: one per block, from every block of the grid,
-// serialises across the XCDs.  The slots of cells a query does not have are
-// cleared here; invalid queries (and bad set indices) raise the flag and
-// list no cell.
+// pairs (4 * query + cell) for the search.  One
+// thread per query; block b lists its pairs at the start of its own region
+// pairs[1024 b ..] and its counts of pairs and of pruned cells in blk_cnt[b]
+// and blk_pruned[b] (pack_scan and pack_move then make the list dense, in
+// query order), its flags in blk_flags[b].  No atomic on a shared word:
+// one per block, from every block of the grid, serialises across the XCDs.
+// The query's slots are cleared and its record is written here; invalid
+// queries (and epochs) raise the flag and list no cell.
 template <int CURVE, bool REFINE>
 __global__ __launch_bounds__(256) void cells_pack(
     const double2* __restrict__ q, const double* __restrict__ delta, uint64_t m,
-    const uint32_t* __restrict__ occ, const uint32_t* __restrict__ qset, uint32_t n_sets,
-    uint64_t* __restrict__ pairs, uint32_t* __restrict__ blk_cnt,
-    uint32_t* __restrict__ slot_rows, uint32_t* counters,
-    uint32_t* __restrict__ blk_pruned, const uint32_t* __restrict__ perm) {
+    const uint32_t* __restrict__ occ, uint64_t* __restrict__ pairs,
+    uint32_t* __restrict__ blk_cnt, uint32_t* __restrict__ blk_pruned,
+    uint64_t* __restrict__ blk_flags, RecordPlan record, uint2* __restrict__ slots) {
   __shared__ uint16_t lut[CURVE == SFC_CURVE_HILBERT ? 1024 : 1];
   __shared__ uint32_t s_cnt[4];
   __shared__ uint32_t s_pr[4];
+  __shared__ uint64_t s_fl[4];
   if (CURVE == SFC_CURVE_HILBERT)
     for (int i = threadIdx.x; i < 1024; i += 256) lut[i] = kHilbertLutConst.v[i];
   __syncthreads();
-  // perm non-null: queries in curve order, so that the listed pairs (and
-  // the searches that follow them) are too.
-  const uint64_t jj = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  const uint64_t j = perm && jj < m ? perm[jj] : jj;
+  const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   uint32_t nr = 0, pr = 0;
-  bool bad = false;
+  bool bad = false, coarse = false;
   if (j < m) {
-    if (qset && qset[j] >= n_sets) {
+    const double2 qq = q[j];
+    const double d = delta[j];
+    const double c[2] = {qq.x, qq.y};
+    put_record<2>(record, j, c, d);
+    coarse = d * grid_side<2>() > filter_limit<2>();
+    if (record.qepoch)
+      bad = record.qepoch[j] < record.oldest || record.qepoch[j] > record.epoch;
+    if (!(finite64(qq.x) && finite64(qq.y) && finite64(d) && d >= 0.0)) {
       bad = true;
+    } else if (REFINE) {
+      uint64_t lo[4], hi[4];
+      uint32_t cx[4], cy[4];
+      int64_t box[4];
+      int L = 0;
+      nr = (uint32_t)query_cells<CURVE>(lut, qq.x, qq.y, d, lo, hi, cx, cy, &L, box, occ, &pr);
     } else {
-      const double2 qq = q[j];
-      const double d = delta[j];
-      if (!(finite64(qq.x) && finite64(qq.y) && finite64(d) && d >= 0.0)) {
-        bad = true;
-      } else if (REFINE) {
-        uint64_t lo[4], hi[4];
-        uint32_t cx[4], cy[4];
-        int64_t box[4];
-        int L = 0;
-        nr = (uint32_t)query_cells<CURVE>(lut, qq.x, qq.y, d, lo, hi, cx, cy, &L, box, occ, &pr);
-      } else {
-        uint64_t lo[4], hi[4];
-        nr = (uint32_t)query_ranges<CURVE>(lut, qq.x, qq.y, d, lo, hi, occ, &pr);
-      }
+      uint64_t lo[4], hi[4];
+      nr = (uint32_t)query_ranges<CURVE>(lut, qq.x, qq.y, d, lo, hi, occ, &pr);
     }
-    // The rows of every slot of the query start at zero (one 16- or 32-byte
-    // store); the search then writes the slots of the listed cells.  The
-    // row scan and the row expansion read a slot's first index and count
-    // only when it has rows, so those need no clearing.
-    uint4* sr = (uint4*)(slot_rows + (REFINE ? 8 : 4) * j);
-    sr[0] = make_uint4(0, 0, 0, 0);
-    if (REFINE) sr[1] = make_uint4(0, 0, 0, 0);
+    // Every slot of the query starts empty; the search then writes the slots
+    // of the listed cells.
+    uint4* sl = (uint4*)(slots + (REFINE ? 8 : 4) * j);
+#pragma unroll
+    for (int i = 0; i < (REFINE ? 4 : 2); ++i) sl[i] = make_uint4(0, 0, 0, 0);
   }
-  if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(&counters[2], kErrInvalidQuery);
+  const uint64_t flags = (__ballot(bad) != 0 ? kStatInvalid : 0) |
+                         (__ballot(coarse) != 0 ? kStatCoarse : 0);
   // Block-exclusive offsets of the cell counts: wave prefix, then waves.
   const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
   uint32_t inc = nr, wp = pr;
@@ -506,34 +655,33 @@ __global__ __launch_bounds__(256) void cells_pack(
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) wp += __shfl_xor(wp, o, 64);
   if (lane == 63) s_cnt[wv] = inc;
-  if (lane == 0) s_pr[wv] = wp;
+  if (lane == 0) {
+    s_pr[wv] = wp;
+    s_fl[wv] = flags;
+  }
   __syncthreads();
   uint32_t before = 0;
   for (uint32_t w = 0; w < wv; ++w) before += s_cnt[w];
   if (threadIdx.x == 0) {
     blk_cnt[blockIdx.x] = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
     blk_pruned[blockIdx.x] = s_pr[0] + s_pr[1] + s_pr[2] + s_pr[3];
+    blk_flags[blockIdx.x] = s_fl[0] | s_fl[1] | s_fl[2] | s_fl[3];
   }
   const uint64_t o = (uint64_t)blockIdx.x * 1024 + before + inc - nr;
   for (uint32_t r = 0; r < nr; ++r) pairs[o + r] = 4 * j + r;
 }
 
 // One workgroup: the exclusive scan of the blocks' pair counts (blk_pre, and
-// the list's length in *pair_total) and the sum of their pruned cells.
+// the list's length in *pair_total).
 __global__ __launch_bounds__(1024) void pack_scan(const uint32_t* __restrict__ blk_cnt,
-                                                  const uint32_t* __restrict__ blk_pruned,
                                                   uint32_t nblk, uint32_t* __restrict__ blk_pre,
-                                                  unsigned long long* pair_total,
-                                                  unsigned long long* pruned_total) {
+                                                  uint32_t* pair_total) {
   __shared__ uint32_t s_w[16];
-  __shared__ unsigned long long s_p[16];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   uint32_t carry = 0;
-  unsigned long long pruned = 0;
   for (uint32_t b0 = 0; b0 < nblk; b0 += 1024) {
     const uint32_t b = b0 + tid;
     const uint32_t v = b < nblk ? blk_cnt[b] : 0u;
-    pruned += b < nblk ? blk_pruned[b] : 0u;
     uint32_t x = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -550,16 +698,7 @@ __global__ __launch_bounds__(1024) void pack_scan(const uint32_t* __restrict__ b
     carry += all;
     __syncthreads();
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) pruned += __shfl_xor(pruned, o, 64);
-  if (lane == 0) s_p[wv] = pruned;
-  __syncthreads();
-  if (tid == 0) {
-    unsigned long long p = 0;
-    for (int w = 0; w < 16; ++w) p += s_p[w];
-    *pair_total = carry;
-    *pruned_total = p;
-  }
+  if (tid == 0) *pair_total = carry;
 }
 
 // Block b moves its region's pairs to their place in the dense list.
@@ -582,53 +721,282 @@ constexpr int kIters = 2;                                 // iterations per wave
 constexpr int kTileRows = 4 * kRows * kIters;             // 64 rows per tile
 constexpr uint64_t kWaveRows = (uint64_t)kRows * kIters;  // rows per wave
 static_assert(kCompactTileRows == (uint64_t)kTileRows, "tile shape");
+// A wave's 16 rows: the unit whose hits are scanned.  Row r's hits come after
+// unit_off[r / 16] + unit_pre[r] others.
+constexpr uint32_t kTileUnits = 4;
+constexpr int kUnitShift = 4;
+static_assert(kWaveRows == 1u << kUnitShift, "a unit is a wave's rows");
 
-// Rows of each query: the sum over its 2^ss slots (the scan that follows
-// gives every query its first row).  One lane per slot, so the loads are
-// coalesced; a query's slots are 2^ss <= 64 consecutive lanes of one wave,
-// summed by shuffles.
-__global__ __launch_bounds__(256) void query_rows(const uint32_t* __restrict__ slot_rows,
-                                                  uint64_t nseg, int ss, uint32_t* __restrict__ qrows) {
-  const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  uint32_t t = g < nseg ? slot_rows[g] : 0u;
-  for (int o = 1; o < (1 << ss); o <<= 1) t += __shfl_xor(t, o, 64);
-  if (g < nseg && (g & ((1u << ss) - 1)) == 0) qrows[g >> ss] = t;
+// Tiles of a chunk's rows [rbase, row_end); none when the batch has more rows
+// than a capacity (only_whole): it is compacted again, or reported.
+__device__ __forceinline__ uint64_t chunk_tiles(uint64_t total_all, uint64_t rbase,
+                                                uint64_t row_end, bool only_whole) {
+  if (only_whole && total_all > row_end) return 0;
+  const uint64_t total = total_all < row_end ? total_all : row_end;
+  return total > rbase ? (total - rbase + kTileRows - 1) / kTileRows : 0;
+}
+
+// Tile of step i of workgroup b of a grid of a multiple of eight workgroups,
+// ~0 past the last: each XCD (the hardware deals workgroups to the eight XCDs
+// in turn) takes a contiguous range of the tiles, so that the lines that
+// consecutive tiles share are fetched into one L2.
+__device__ __forceinline__ uint64_t xcd_tile(uint64_t b, uint64_t grid, uint64_t i,
+                                             uint64_t ntiles) {
+  const uint64_t per = (ntiles + 7) / 8;
+  const uint64_t k = (b >> 3) + i * (grid >> 3);
+  const uint64_t t = (b & 7) * per + k;
+  return k < per && t < ntiles ? t : ~0ull;
+}
+
+// The batch's counters, from those of the workgroups: stat (ns words:
+// candidates and flags), learned (ns words or null: endpoints << 16 |
+// fallbacks), and with early termination flags and pruned (np words each, or
+// null).  Every thread of the workgroup calls it; thread 0 holds the result.
+struct BatchStats {
+  const uint64_t* stat;
+  const uint32_t* learned;
+  uint32_t ns;
+  const uint64_t* flags;
+  const uint32_t* pruned;
+  uint32_t np;
+};
+
+template <int WAVES>
+__device__ __forceinline__ void sum_stats(const BatchStats& B, uint64_t rows,
+                                          BatchStatus* status, BatchStatus* host) {
+  __shared__ uint64_t s_v[5][WAVES];
+  uint64_t v[5] = {0, 0, 0, 0, 0};   // candidates, endpoints, fallbacks, pruned, flags
+  // Eight words in flight per thread: those past the end load the last one
+  // and are not added.
+  for (uint32_t i0 = threadIdx.x; i0 < B.ns; i0 += WAVES * 64 * 8) {
+    uint64_t w[8];
+    uint32_t l[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+      const uint32_t i = i0 + k * WAVES * 64, ic = i < B.ns ? i : B.ns - 1;
+      w[k] = B.stat[ic];
+      l[k] = B.learned ? B.learned[ic] : 0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k)
+      if (i0 + k * WAVES * 64 < B.ns) {
+        v[0] += w[k] & (kStatInvalid - 1);
+        v[4] |= w[k] >> kStatShift;
+        v[1] += l[k] >> 16;
+        v[2] += l[k] & 0xFFFFu;
+      }
+  }
+  for (uint32_t i = threadIdx.x; i < B.np; i += WAVES * 64) {
+    v[3] += B.pruned[i];
+    v[4] |= B.flags[i] >> kStatShift;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] += __shfl_xor(v[k], o, 64);
+    v[4] |= __shfl_xor(v[4], o, 64);
+  }
+  if (lane_id() == 0)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) s_v[k][threadIdx.x >> 6] = v[k];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    BatchStatus st{};
+    st.rows = rows;
+    for (int w = 0; w < WAVES; ++w) {
+      st.candidates += s_v[0][w];
+      st.endpoints += s_v[1][w];
+      st.fallbacks += s_v[2][w];
+      st.pruned += s_v[3][w];
+      if (s_v[4][w] & 1) st.err |= kErrInvalidQuery;
+      if (s_v[4][w] & 2) st.coarse = 1;
+    }
+    *status = st;
+    if (host) *host = st;
+  }
+}
+
+// One workgroup: the exclusive scan of the workgroups' rows (blk_off, the
+// total in *rows_out), and the batch's counters in *status (and *host, host
+// memory, if not null); stats false: the counters stay, but for the rows.
+__global__ __launch_bounds__(1024) void batch_scan(const uint64_t* __restrict__ blk_rows,
+                                                   uint32_t nblk, uint64_t* __restrict__ blk_off,
+                                                   uint64_t* __restrict__ rows_out,
+                                                   BatchStats B, bool stats, BatchStatus* status,
+                                                   BatchStatus* host) {
+  constexpr uint32_t kPer = 8;
+  __shared__ uint64_t s_w[16];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  uint64_t carry = 0;
+  for (uint32_t b0 = 0; b0 < nblk; b0 += 1024 * kPer) {
+    const uint32_t f = b0 + tid * kPer;
+    uint64_t v[kPer], sum = 0;
+    // Every load in flight at once: entries past the end load the last one
+    // and count as zero.
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) v[i] = blk_rows[f + i < nblk ? f + i : nblk - 1];
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      if (f + i >= nblk) v[i] = 0;
+      sum += v[i];
+    }
+    uint64_t x = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint64_t y = __shfl_up(x, o, 64);
+      if (lane >= (uint32_t)o) x += y;
+    }
+    if (lane == 63) s_w[wv] = x;
+    __syncthreads();
+    uint64_t run = carry + x - sum, all = 0;
+    for (uint32_t w = 0; w < 16; ++w) {
+      if (w < wv) run += s_w[w];
+      all += s_w[w];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      if (f + i < nblk) blk_off[f + i] = run;
+      run += v[i];
+    }
+    carry += all;
+    __syncthreads();
+  }
+  if (tid == 0) *rows_out = carry;
+  if (stats)
+    sum_stats<16>(B, carry, status, host);
+  else if (tid == 0)
+    status->rows = carry;
+}
+
+// The K consecutive slots from `first` on, in the order of the places (perm:
+// the query of each, 2^ss slots; null: the queries' own), empty past nseg.
+template <int K>
+__device__ __forceinline__ void load_slots(const uint2* __restrict__ slots,
+                                           const uint32_t* __restrict__ perm, int ss,
+                                           uint64_t first, uint64_t nseg, uint2 (&v)[K]) {
+  // K divides 2^ss: a thread's slots are one query's, all there or none is.
+  if (first < nseg) {
+    if (perm) first = ((uint64_t)perm[first >> ss] << ss) + (first & ((1u << ss) - 1));
+    if constexpr (K == 1) {
+      v[0] = slots[first];
+    } else {
+#pragma unroll
+      for (int i = 0; i < K; i += 2) {
+        const uint4 t = ((const uint4*)(slots + first))[i / 2];
+        v[i] = make_uint2(t.x, t.y);
+        v[i + 1] = make_uint2(t.z, t.w);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < K; ++i) v[i] = make_uint2(0, 0);
+  }
+}
+
+__device__ __forceinline__ uint64_t rows_of(uint32_t count) { return ((uint64_t)count + 63) >> 6; }
+
+// Exclusive scan of one uint64 per thread over 256 threads; *total gets the
+// sum.
+__device__ __forceinline__ uint64_t scan256_u64(uint64_t v, uint64_t* s_w, uint64_t* total) {
+  const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
+  uint64_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_up(x, o, 64);
+    if (lane >= (uint32_t)o) x += y;
+  }
+  if (lane == 63) s_w[wv] = x;
+  __syncthreads();
+  uint64_t before = 0;
+  for (uint32_t w = 0; w < wv; ++w) before += s_w[w];
+  *total = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+  __syncthreads();
+  return before + x - v;
+}
+
+// Rows of each workgroup's K * 256 slots, from the slots (where the search
+// kernel's workgroups do not hold the queries of as many consecutive places).
+template <int K>
+__global__ __launch_bounds__(256) void slot_rows(const uint2* __restrict__ slots,
+                                                 const uint32_t* __restrict__ perm, int ss,
+                                                 uint64_t nseg, uint64_t* __restrict__ blk_rows) {
+  __shared__ uint64_t s_w[4];
+  uint2 v[K];
+  load_slots<K>(slots, perm, ss, ((uint64_t)blockIdx.x * 256 + threadIdx.x) * K, nseg, v);
+  uint64_t t = 0, total;
+#pragma unroll
+  for (int i = 0; i < K; ++i) t += rows_of(v[i].y);
+  scan256_u64(t, s_w, &total);
+  if (threadIdx.x == 0) blk_rows[blockIdx.x] = total;
 }
 
 // Row descriptors of a launch's rows [rbase, rend): for row r of slot s,
-// (first sorted index of the row, number of valid lanes, query index).  One
-// block per 256 slots (whole queries: 2^ss slots each); a slot's first row is
-// its query's first row (row_off, one entry per query) plus the rows of the
-// query's earlier slots.  The block's rows are spread over its threads and
-// each finds its slot by a binary search in LDS.
-__global__ __launch_bounds__(256) void expand_rows(const uint64_t* __restrict__ row_off,
-                                                   const uint32_t* __restrict__ slot_rows,
-                                                   const uint32_t* __restrict__ slot_begin,
-                                                   const uint32_t* __restrict__ slot_count,
-                                                   uint64_t nseg, int ss, uint64_t rbase,
-                                                   uint64_t row_end, uint4* __restrict__ row_meta) {
-  __shared__ uint64_t st[257];
-  const uint64_t m = nseg >> ss;
-  const uint64_t total = row_off[m];
-  const uint64_t rend = total < row_end ? total : row_end;
-  const uint64_t s0 = (uint64_t)blockIdx.x * 256;
+// (first sorted index of the row, number of valid lanes, the query), and the
+// first row of every place (row_off).  One block per K * 256 slots (whole
+// queries: 2^ss slots each), a thread's K slots consecutive; the block's
+// rows are spread over its threads and each finds its slot by a binary search
+// in LDS.  FUSED (at most kFusedBlocks blocks): the block sums the rows of the
+// blocks before it itself and block 0 gathers the batch's counters, so that a
+// small batch takes no batch_scan launch (5 us; with more blocks the repeated
+// sums would cost more).
+constexpr uint32_t kFusedBlocks = 1024;
+
+template <int K, bool FUSED>
+__global__ __launch_bounds__(256) void expand_rows(
+    uint64_t* __restrict__ row_off, const uint2* __restrict__ slots,
+    const uint32_t* __restrict__ perm, const uint64_t* __restrict__ blk_rows, const uint64_t* __restrict__ blk_off, BatchStats B,
+    BatchStatus* status, uint64_t m, int ss, uint64_t rbase, uint64_t row_end, bool flag_overflow,
+    uint4* __restrict__ row_meta) {
+  __shared__ uint64_t st[256 * K + 1];
+  __shared__ uint2 s_slot[256 * K];
+  __shared__ uint64_t s_w[4];
+  const uint64_t nseg = m << ss;
   const uint32_t tid = threadIdx.x;
-  // The rows of the query's earlier slots: an exclusive scan within each
-  // group of 2^ss lanes (a query's slots, inside one wave).
-  const uint32_t v = s0 + tid < nseg ? slot_rows[s0 + tid] : 0u;
-  const uint32_t gl = tid & ((1u << ss) - 1);
-  uint32_t x = v;
-  for (int o = 1; o < (1 << ss); o <<= 1) {
-    const uint32_t y = __shfl_up(x, o, 64);
-    if (gl >= (uint32_t)o) x += y;
+  uint64_t row0 = 0, total = 0;
+  if (FUSED) {
+    uint64_t before = 0, all = 0;
+    for (uint32_t i = tid; i < gridDim.x; i += 256) {
+      const uint64_t v = blk_rows[i];
+      all += v;
+      before += i < blockIdx.x ? v : 0;
+    }
+    scan256_u64(before, s_w, &row0);
+    scan256_u64(all, s_w, &total);
+    if (blockIdx.x == 0) {
+      sum_stats<4>(B, total, status, nullptr);
+      if (tid == 0) {
+        row_off[m] = total;
+        if (flag_overflow && total > row_end) status->err |= kErrOverflow;
+      }
+    }
+  } else {
+    row0 = blk_off[blockIdx.x];
+    total = row_off[m];
+    if (blockIdx.x == 0 && tid == 0 && flag_overflow && total > row_end)
+      status->err |= kErrOverflow;
   }
-  st[tid] = s0 + tid < nseg ? row_off[(s0 + tid) >> ss] + (x - v) : total;
-  if (tid == 0) st[256] = s0 + 256 < nseg ? row_off[(s0 + 256) >> ss] : total;
+  const uint64_t rend = total < row_end ? total : row_end;
+  const uint64_t s0 = (uint64_t)blockIdx.x * 256 * K;
+  const uint64_t first = s0 + (uint64_t)tid * K;
+  uint2 v[K];
+  load_slots<K>(slots, perm, ss, first, nseg, v);
+  uint64_t mine = 0, here;
+#pragma unroll
+  for (int i = 0; i < K; ++i) mine += rows_of(v[i].y);
+  uint64_t run = row0 + scan256_u64(mine, s_w, &here);
+  if (first < nseg && (first & ((1u << ss) - 1)) == 0) row_off[first >> ss] = run;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    st[tid * K + i] = run;
+    s_slot[tid * K + i] = v[i];
+    run += rows_of(v[i].y);
+  }
+  if (tid == 255) st[256 * K] = run;
   __syncthreads();
   const uint64_t r0 = st[0] > rbase ? st[0] : rbase;
-  const uint64_t r1 = st[256] < rend ? st[256] : rend;
+  const uint64_t r1 = st[256 * K] < rend ? st[256 * K] : rend;
   for (uint64_t r = r0 + tid; r < r1; r += 256) {
-    uint32_t lo = 0, len = 256;   // largest k with st[k] <= r
+    uint32_t lo = 0, len = 256 * K;   // largest k with st[k] <= r
     while (len > 0) {
       const uint32_t h = len >> 1;
       if (st[lo + h] <= r) {
@@ -639,108 +1007,21 @@ __global__ __launch_bounds__(256) void expand_rows(const uint64_t* __restrict__ 
       }
     }
     const uint32_t k = lo - 1;
-    const uint64_t sg = s0 + k;
     const uint64_t local = (r - st[k]) * kWave;
-    const uint64_t cnt = slot_count[sg];
-    const uint64_t nv = cnt - local < (uint64_t)kWave ? cnt - local : (uint64_t)kWave;
-    row_meta[r - rbase] = make_uint4((uint32_t)(slot_begin[sg] + local), (uint32_t)nv,
-                                     (uint32_t)(sg >> ss), 0u);
+    const uint2 sl = s_slot[k];
+    const uint64_t left = sl.y - local;
+    row_meta[r - rbase] = make_uint4((uint32_t)(sl.x + local),
+                                     (uint32_t)(left < (uint64_t)kWave ? left : (uint64_t)kWave),
+                                     perm ? perm[(s0 + k) >> ss] : (uint32_t)((s0 + k) >> ss),
+                                     0u);
   }
 }
 
-// ---- deciding the test from a point's grid cell ---------------------------------
-//
-// A point p with grid cell u = floor(p * S) (S = 2^32 in the plane, 2^21 in
-// three dimensions) lies in [u, u + 1) quanta on each axis.  Measured in
-// quanta from the query's own cell c = floor(q S), its offset on an axis is
-// o = e + th with the integer e = u - c and |th| < 1, so o^2 lies within
-// 2|e| + 1 of e^2.  A candidate comes from the query's own cells, which meet
-// the box widened by one quantum, so |e| <= E = 6R + 10 with R = d S (exact
-// scalings): the sum of the squared offsets lies within the slack
-// s = DIM (2E + 1) of the sum of the e^2.  For the Euclidean test:
-//   * if sum e^2 <= R^2 (1 - 2^-16) - s, the rounded binary64 test accepts p;
-//   * if sum e^2 > R^2 (1 + 2^-16) + s, it rejects p;
-// for the square window, |e| <= R (1 - 2^-16) - 1 on every axis accepts and
-// |e| > R (1 + 2^-16) + 1 on some axis rejects.  Evaluated in binary32
-// (relative errors below 2^-20 all told) these verdicts equal the exact
-// test's, whose own rounding is a few 2^-53 relative, when R >= 16 (so the
-// slack is small beside R^2).  Other points read their coordinates and take
-// the exact test.  A query uses the filter when R >= 16 and its cell lies
-// within 2^30 quanta of the domain.  Above R = 2^28 (plane) / 2^17 (three
-// dimensions) the cells are compared 2^k quanta wide (u >> k against
-// floor(q S 2^-k), k the smallest shift that brings R 2^-k to that limit,
-// at most 24): the same bounds hold there with R 2^-k for R, since the
-// shifted offsets again differ from the exact ones by less than one.  Then
-// |e| < 2^31, exact in 32-bit arithmetic.  Cells sit in one word: x | y << 32,
-// or x | y << 21 | z << 42.
-struct QueryFilter {
-  float acc, rej;   // limits on sum e^2 (or per-axis |e|); filter off: acc = not a number
-                    // and rej = +inf, so that neither comparison decides a candidate
-  uint32_t c[3];    // the query's cell per axis (low 32 bits), 2^shift quanta wide
-  uint32_t shift;   // cells are compared 2^shift quanta wide
-  uint32_t pad[2];
-};
-static_assert(sizeof(QueryFilter) == 32, "a record is 32 bytes");
-// The batch counter word that flag_coarse sets when some query may compare
-// coarser cells (the counters are cleared when the ranges are computed).
-constexpr int kShiftWord = 13;   // free: 2 errors, 4-11 statistics, 12 tiles, 14-15 total
-
-// Sets counters[kShiftWord] when some radius of the batch lies above the
-// filter's shift limit (delta S > limit): then the test pass reads the cell
-// shifts.  One atomic per workgroup that has such a radius.
-__global__ __launch_bounds__(256) void flag_coarse(const double* __restrict__ delta, uint64_t m,
-                                                   double S, double limit,
-                                                   uint32_t* __restrict__ counters) {
-  __shared__ uint32_t s_any;
-  if (threadIdx.x == 0) s_any = 0;
-  __syncthreads();
-  const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j < m && delta[j] * S > limit) s_any = 1;
-  __syncthreads();
-  if (threadIdx.x == 0 && s_any) atomicOr(&counters[kShiftWord], 1u);
-}
-
-template <int DIM>
-__global__ __launch_bounds__(256) void query_filters(const double* __restrict__ q,
-                                                     const double* __restrict__ delta, uint64_t m,
-                                                     bool window, QueryFilter* __restrict__ out) {
-  constexpr double S = DIM == 2 ? 4294967296.0 : 2097152.0;
-  constexpr double kMaxR = DIM == 2 ? 0x1p28 : 0x1p17;
-  const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j >= m) return;
-  const double R0 = delta[j] * S;
-  int k = 0;
-  while (k < 24 && R0 > kMaxR * __builtin_ldexp(1.0, k)) ++k;
-  const double R = __builtin_ldexp(R0, -k);   // exact
-  bool on = R0 >= 16.0 && R <= kMaxR;
-  QueryFilter f{};
-  f.shift = (uint32_t)k;
-#pragma unroll
-  for (int a = 0; a < DIM; ++a) {
-    const double qs = q[DIM * j + a] * S;
-    on = on && qs > -0x1p30 && qs < S + 0x1p30;
-    f.c[a] = (uint32_t)(int64_t)__builtin_floor(on ? __builtin_ldexp(qs, -k) : 0.0);
-  }
-  if (window) {
-    f.acc = (float)(R * (1.0 - 0x1p-16) - 1.0);
-    f.rej = (float)(R * (1.0 + 0x1p-16) + 1.0);
-  } else {
-    const double slack = DIM * (2.0 * (6.0 * R + 10.0) + 1.0);
-    f.acc = (float)(R * R * (1.0 - 0x1p-16) - slack);
-    f.rej = (float)(R * R * (1.0 + 0x1p-16) + slack);
-  }
-  if (!on) {   // undecided for every candidate: the exact test decides
-    f.acc = __uint_as_float(0xFFFFFFFFu);
-    f.rej = __builtin_inff();
-    f.shift = 0;
-  }
-  out[j] = f;
-}
-
-// 1: accepted, 0: rejected, -1: undecided by the cell.  SHIFTED: the cells
-// are compared f.shift bits coarser (else f.shift is 0).
+// What a query's limits are compared with, from a candidate's cell: the sum of
+// the squared offsets, or (WINDOW) the largest.  SHIFTED: the cells are
+// compared f.shift bits coarser (else f.shift is 0).
 template <int DIM, bool WINDOW, bool SHIFTED>
-__device__ __forceinline__ int cell_check(uint64_t cell, const QueryFilter& f) {
+__device__ __forceinline__ float cell_distance(uint64_t cell, const QueryFilter& f) {
   constexpr int B = DIM == 2 ? 32 : 21;
   const uint64_t mask = (1ull << B) - 1;
   float e[DIM];
@@ -751,18 +1032,15 @@ __device__ __forceinline__ int cell_check(uint64_t cell, const QueryFilter& f) {
     e[a] = (float)(int32_t)(u - f.c[a]);
   }
   if (WINDOW) {
-    bool in = true, out = false;
+    float v = fabsf(e[0]);
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-      in = in && fabsf(e[a]) <= f.acc;
-      out = out || fabsf(e[a]) > f.rej;
-    }
-    return in ? 1 : out ? 0 : -1;
+    for (int a = 1; a < DIM; ++a) v = fmaxf(v, fabsf(e[a]));
+    return v;
   }
-  float d2 = e[0] * e[0];
+  float v = e[0] * e[0];
 #pragma unroll
-  for (int a = 1; a < DIM; ++a) d2 = d2 + e[a] * e[a];
-  return d2 <= f.acc ? 1 : d2 > f.rej ? 0 : -1;
+  for (int a = 1; a < DIM; ++a) v = __fmaf_rn(e[a], e[a], v);
+  return v;
 }
 
 // The exact test of candidate pos against query qs (the point and the query
@@ -787,281 +1065,520 @@ __device__ __forceinline__ bool exact_hit(const double* __restrict__ q,
                 : within3(pp[0], pp[1], pp[2], qp[0], qp[1], qp[2], d);
 }
 
+// A predicate for this lane from a mask that is the same in every lane.
+__device__ __forceinline__ bool lane_of(uint64_t mask) {
+  return __builtin_amdgcn_inverse_ballot_w64(mask);
+}
+
+// Lane R's words of (lo, hi) replaced by those of v (the same in every lane).
+// A vector instruction may read a scalar that another wrote (the compares that
+// made v) only two wait states later, which the compiler does not see to in
+// inline assembly: hence the s_nop.
+template <int R>
+__device__ __forceinline__ void write_lane64(uint64_t v, uint32_t& lo, uint32_t& hi) {
+  asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+      : "+v"(lo), "+v"(hi)
+      : "s"(__builtin_amdgcn_readfirstlane((uint32_t)v)),
+        "s"(__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32))), "n"(R));
+}
+
+// f(0), f(1), ..., f(N - 1) with the index a constant of its type.
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_each(std::make_integer_sequence<int, N>{}, f);
+}
+
+// Set bits of a mask below this lane.
+__device__ __forceinline__ uint32_t below_in(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+
+// Lane R's word, as a scalar.
+template <int R>
+__device__ __forceinline__ uint32_t read_lane(uint32_t v) {
+  return __builtin_amdgcn_readlane(v, R);
+}
+template <int R>
+__device__ __forceinline__ uint64_t read_lane64(uint64_t v) {
+  return (uint64_t)read_lane<R>((uint32_t)(v >> 32)) << 32 | read_lane<R>((uint32_t)v);
+}
+
+// The value `offset` bytes past an address in device memory that is the same in
+// every lane (a global access at a scalar base plus a 32-bit lane offset).
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+template <typename T>
+__device__ __forceinline__ T global_at(uint64_t base, uint32_t offset) {
+  typedef const __attribute__((address_space(1))) char* Bytes;
+  typedef const __attribute__((address_space(1))) T* Ptr;
+  return *(Ptr)((Bytes)base + offset);
+}
+
+// Rows of a wave's unit that exist (row0: its first row within the chunk of
+// `have` rows).
+__device__ __forceinline__ uint32_t unit_rows(uint64_t have, uint64_t row0) {
+  return have <= row0 ? 0u : (uint32_t)(have - row0 < kWaveRows ? have - row0 : kWaveRows);
+}
+
 // Pass 1: the exact test of every candidate; per row the 64-bit mask of the
-// accepted lanes, per tile their number.  Each wave handles 16 consecutive
-// rows as ITERS groups of ROWS rows whose point loads are in flight together,
-// writes its 16 masks with one store (lane j: row j) and adds its count to
-// the tile's (zeroed before the launch), so that the waves of a workgroup
-// never wait for each other.
+// accepted lanes and the number of accepted ones in the unit's rows before it,
+// per unit (a wave's 16 rows) their number.  A wave writes its masks, prefixes
+// and count with one store each (lane j: row j), so that the waves of a
+// workgroup never wait for each other and nothing is cleared beforehand.
 // EPOCH: a candidate that passes the test also has to be visible at the
 // query's epoch (ins <= e < era); only those lanes read the epochs.
 // window: the square-window test instead of the Euclidean one.
+//
+// The pass is bound by the instructions of a row (a vector one for 64 lanes and
+// a scalar one both take an issue slot in four cycles) and by the latency of its
+// chain of loads (descriptor, record, candidates).  So lane j holds row j's
+// descriptor and record, loaded for all 16 rows at once and one unit ahead; what
+// can be computed for the rows in their lanes is (their addresses, their valid
+// lanes), and a row's words are read from there as scalars; its candidates are
+// read at a scalar base plus the lane's offset, ROWS rows at a time, a group's
+// loads leaving before the previous group is tested; the two verdicts are masks
+// straight from the compares.  21 vector instructions a row, the vector units
+// four fifths busy: 0.282 ms for the 6.6 * 10^6 rows of 2 * 10^5 windows (0.450
+// with a workgroup's barriers, a descriptor and a record read row by row and
+// rows in query order), 0.47 ms for 8 * 10^6 rows in query order (0.50).
 template <int ROWS, int ITERS, bool EPOCH, int DIM, bool CELLS, bool WINDOW, bool SHIFTS>
 __global__ __launch_bounds__(256) void compact_test(
     const double* __restrict__ q, const double* __restrict__ delta, uint64_t m,
     const double* __restrict__ pts, const uint32_t* __restrict__ via,
-    const uint64_t* __restrict__ cells,
-    const QueryFilter* __restrict__ qfilt, uint64_t npts, const uint4* __restrict__ row_meta,
-    const uint64_t* __restrict__ total_rows_dev, uint64_t rbase, uint64_t row_end,
-    bool flag_overflow, uint64_t* __restrict__ masks, uint32_t* __restrict__ tile_hits,
-    uint32_t* counters, const uint32_t* __restrict__ ins, const uint32_t* __restrict__ era,
-    const uint32_t* __restrict__ qepoch, uint32_t epoch) {
+    const uint64_t* __restrict__ cells, const void* __restrict__ rec,
+    const uint4* __restrict__ row_meta, const uint64_t* __restrict__ total_rows_dev,
+    uint64_t rbase, uint64_t row_end, bool only_whole, uint64_t* __restrict__ masks,
+    uint16_t* __restrict__ unit_pre, uint32_t* __restrict__ unit_hits, BatchStatus* status,
+    const uint32_t* __restrict__ ins, const uint32_t* __restrict__ era) {
   static_assert(ROWS * ITERS == (int)kWaveRows, "a wave's groups cover its rows");
-  const uint32_t tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  // SHIFTS: the batch may hold queries with coarser cells (flag_coarse)
-  const bool any_shifted = SHIFTS && CELLS && counters[kShiftWord] != 0u;
+  static_assert(!(EPOCH && CELLS), "an index with epochs keeps no cells");
+  const uint32_t lane = lane_id();
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr uint32_t kEntry = CELLS ? 8 : 8 * DIM;   // bytes per candidate
+  const uint32_t offset = kEntry * lane;
+  // SHIFTS: the batch may hold queries with coarser cells
+  const bool any_shifted = SHIFTS && CELLS && status->coarse != 0u;
   const uint64_t total_all = *total_rows_dev;
   const uint64_t total_rows = total_all < row_end ? total_all : row_end;
-  const uint64_t ntiles = total_rows > rbase ? (total_rows - rbase + kTileRows - 1) / kTileRows : 0;
-  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint64_t wrow0 = rbase + tile * kTileRows + (uint64_t)w * kWaveRows;
-    uint32_t cnt = 0;
-    uint64_t mrow = 0;   // lane j < 16: the mask of the wave's row j
-    // The records of the wave's rows, one per lane, in one load.
-    uint4 mdw = make_uint4(0, 0, 0, 0);
-    if (lane < (uint32_t)kWaveRows && wrow0 + lane < total_rows)
-      mdw = row_meta[wrow0 + lane - rbase];
-#pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-      const uint4 md = mdw;   // rows it * ROWS .. it * ROWS + ROWS - 1 of the wave
-      uint32_t pos[ROWS];
-      uint32_t qrow[ROWS];
-      bool act[ROWS];
-#pragma unroll
-      for (int jr = 0; jr < ROWS; ++jr) {
-        const uint32_t pb = __builtin_amdgcn_readlane(md.x, it * ROWS + jr);
-        const uint32_t nv = __builtin_amdgcn_readlane(md.y, it * ROWS + jr);
-        const uint32_t qi = __builtin_amdgcn_readlane(md.z, it * ROWS + jr);
-        const uint64_t p64 = (uint64_t)pb + lane;
-        act[jr] = lane < nv && p64 < npts && qi < m;
-        pos[jr] = act[jr] ? (uint32_t)p64 : 0u;
-        qrow[jr] = qi < m ? qi : 0u;
-      }
-      bool hit[ROWS];
-      if constexpr (CELLS) {
-        // Decide from the cells; the coordinates only for undecided lanes.
-        // The rows' filter records (uniform loads) and cells are all
-        // requested before any is used.
-        // (the plane needs the record's first 16 bytes: limits and x, y; the
-        // cell shifts only in a batch with coarser cells)
-        QueryFilter qf[ROWS];
-#pragma unroll
-        for (int jr = 0; jr < ROWS; ++jr) {
-          const uint4 a = ((const uint4*)qfilt)[2 * (uint64_t)qrow[jr]];
-          qf[jr].acc = __uint_as_float(a.x);
-          qf[jr].rej = __uint_as_float(a.y);
-          qf[jr].c[0] = a.z;
-          qf[jr].c[1] = a.w;
-          qf[jr].c[2] = DIM == 3 ? qfilt[qrow[jr]].c[2] : 0u;
-          qf[jr].shift = 0;
-        }
-        uint64_t cv[ROWS];
-#pragma unroll
-        for (int jr = 0; jr < ROWS; ++jr) cv[jr] = cells[pos[jr]];   // pos 0 when inactive
-        bool und[ROWS];
-        bool any = false;
-        // A batch with coarser cells (radii past the shift limit) takes the
-        // shifting check.
-        if (!any_shifted) {
-#pragma unroll
-          for (int jr = 0; jr < ROWS; ++jr) {
-            const int vd = act[jr] ? cell_check<DIM, WINDOW, false>(cv[jr], qf[jr]) : 0;
-            hit[jr] = vd == 1;
-            und[jr] = vd < 0;
-            any = any || und[jr];
-          }
-        } else {
-#pragma unroll
-          for (int jr = 0; jr < ROWS; ++jr) {
-            qf[jr].shift = qfilt[qrow[jr]].shift;
-            const int vd = act[jr] ? cell_check<DIM, WINDOW, true>(cv[jr], qf[jr]) : 0;
-            hit[jr] = vd == 1;
-            und[jr] = vd < 0;
-            any = any || und[jr];
-          }
-        }
-        // The candidates their cells leave undecided (rare) take the exact
-        // test, behind one branch for the whole group.
-        if (__ballot(any) != 0) {
-#pragma unroll
-          for (int jr = 0; jr < ROWS; ++jr)
-            if (und[jr]) hit[jr] = exact_hit<DIM>(q, delta, pts, via, qrow[jr], pos[jr], WINDOW);
-        }
-      } else {
-        double qx[ROWS], qy[ROWS], qz[ROWS], dd[ROWS];
-#pragma unroll
-        for (int jr = 0; jr < ROWS; ++jr) {
-          const uint32_t qs = qrow[jr];
-          if (DIM == 2) {
-            const double2 qq = ((const double2*)q)[qs];
-            qx[jr] = qq.x;
-            qy[jr] = qq.y;
-          } else {
-            qx[jr] = q[3 * (uint64_t)qs];
-            qy[jr] = q[3 * (uint64_t)qs + 1];
-            qz[jr] = q[3 * (uint64_t)qs + 2];
-          }
-          dd[jr] = delta[qs];
-        }
-        double2 pv[ROWS];
-        double pz[ROWS];
-#pragma unroll
-        for (int jr = 0; jr < ROWS; ++jr) {
-          if (act[jr]) {
-            if (DIM == 2) {
-              pv[jr] = ((const double2*)pts)[pos[jr]];
-            } else {
-              pv[jr].x = pts[3 * (uint64_t)pos[jr]];
-              pv[jr].y = pts[3 * (uint64_t)pos[jr] + 1];
-              pz[jr] = pts[3 * (uint64_t)pos[jr] + 2];
-            }
-          }
-        }
-#pragma unroll
-        for (int jr = 0; jr < ROWS; ++jr) {
-          if (DIM == 2)
-            hit[jr] = act[jr] &&
-                      (WINDOW ? within_window(pv[jr].x, pv[jr].y, qx[jr], qy[jr], dd[jr])
-                              : within(pv[jr].x, pv[jr].y, qx[jr], qy[jr], dd[jr]));
-          else
-            hit[jr] = act[jr] && (WINDOW ? within_window3(pv[jr].x, pv[jr].y, pz[jr], qx[jr],
-                                                          qy[jr], qz[jr], dd[jr])
-                                         : within3(pv[jr].x, pv[jr].y, pz[jr], qx[jr], qy[jr],
-                                                   qz[jr], dd[jr]));
-        }
-      }
-#pragma unroll
-      for (int jr = 0; jr < ROWS; ++jr) {
-        bool h = hit[jr];
-        if (EPOCH && h) {
-          const uint32_t qe = qepoch ? qepoch[qrow[jr]] : epoch;
-          h = ins[pos[jr]] <= qe && qe < era[pos[jr]];
-        }
-        const uint64_t bal = __ballot(h);
-        cnt += (uint32_t)__popcll(bal);
-        if (lane == (uint32_t)(it * ROWS + jr)) mrow = bal;
-      }
-    }
-    if (lane < (uint32_t)kWaveRows)
-      masks[tile * kTileRows + (uint64_t)w * kWaveRows + lane] = mrow;
-    if (lane == 0 && cnt) atomicAdd(&tile_hits[tile], cnt);
-  }
-  if (blockIdx.x == 0 && tid == 0) {
-    counters[12] = (uint32_t)ntiles;   // tile count for the scan that follows
-    if (flag_overflow && total_all > row_end) atomicOr(&counters[2], kErrOverflow);
-  }
-}
-
-// Pass 2: the ids of the accepted candidates at the tile's output offset, in
-// row order (= curve order per query), and the absolute output position of
-// every row of the tile (row_pre, chunk-relative index; the entry one past a
-// tile's last row is the next tile's first, and the one at the batch's last
-// row + 1 is the total).  Output-driven: one lane per reported id rather than
-// one per candidate.  The waves first map every output o of the tile to its
-// row and its candidate within the row (one 16-bit map in LDS, written by the
-// lanes whose bit is set); the output's id is then read at the row's first
-// candidate position plus that candidate.  Writes are contiguous; a tile
-// with few hits costs few lanes.
-__global__ __launch_bounds__(256) void compact_write_out(
-    const uint32_t* __restrict__ ids, uint64_t npts, const uint4* __restrict__ row_meta,
-    const uint64_t* __restrict__ total_rows_dev, uint64_t rbase, uint64_t row_end,
-    const uint64_t* __restrict__ masks, const uint64_t* __restrict__ tile_off,
-    uint64_t* __restrict__ row_pre, uint32_t* __restrict__ out_ids, uint64_t cap, bool whole) {
-  __shared__ uint64_t s_mask[kTileRows];
-  __shared__ uint32_t s_pre[kTileRows + 1];
-  __shared__ uint32_t s_base[kTileRows];
-  // Output o of the tile: its row << 8 | its candidate within the row.
-  __shared__ uint16_t s_map[kTileRows * 64];
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const uint64_t below = lanemask_lt();
-  const uint64_t total_all = *total_rows_dev;
-  const uint64_t total_rows = total_all < row_end ? total_all : row_end;
-  const uint64_t ntiles = total_rows > rbase ? (total_rows - rbase + kTileRows - 1) / kTileRows : 0;
-  const bool write_ids = !whole || ntiles == 0 || tile_off[ntiles] <= cap;
-  // The next tile's masks and first positions are loaded while this tile is
-  // written (one row per thread of the first wave).
-  uint64_t nx_mask = 0;
-  uint32_t nx_base = 0;
-  uint64_t nx_off = 0;
-  auto fetch = [&](uint64_t t) {
-    const uint64_t r0 = rbase + t * kTileRows;
-    if (t < ntiles && tid < kTileRows) {
-      nx_mask = masks[t * kTileRows + tid];
-      nx_base = r0 + tid < total_rows ? row_meta[r0 + tid - rbase].x : 0u;
-    }
-    if (t < ntiles) nx_off = tile_off[t];
+  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, only_whole);
+  const uint64_t have = total_rows - rbase;
+  // Lane j of a unit: row j's descriptor (rows past the last: candidate 0 of
+  // query 0, whose result is dropped), then the record of its query.  A record
+  // is four or eight words; the plane's cell filter needs the first four, and
+  // its shift (the sixth) only in a batch with coarser cells.
+  constexpr int kRecWords = CELLS && DIM == 2 && !SHIFTS ? 4 : 8;
+  // (Loaded words are kept as they come: arithmetic on them here would wait for
+  // them here.)
+  struct Unit {
+    uint32_t pb, nv, at;
+    uint32_t rec[kRecWords];
   };
-  fetch(blockIdx.x);
-  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint64_t trow0 = rbase + tile * kTileRows;
-    if (tid < kTileRows) {
-      s_mask[tid] = nx_mask;
-      s_base[tid] = nx_base;
+  auto fetch_rows = [&](uint64_t tile, Unit& u) {
+    u.pb = u.at = 0;
+    u.nv = 1;
+    const uint64_t row0 = tile * kTileRows + (uint64_t)w * kWaveRows;
+    if (tile != ~0ull && lane < unit_rows(have, row0)) {
+      const uint4 md = row_meta[row0 + lane];
+      u.pb = md.x;
+      u.nv = md.y;
+      u.at = md.z;
     }
-    const uint64_t prefix = nx_off;
-    __syncthreads();
-    fetch(tile + gridDim.x);
-    if (tid < 64) {   // exclusive scan of the row counts (one wave)
-      const uint32_t v = (uint32_t)__popcll(s_mask[tid]);
+  };
+  auto fetch_rec = [&](Unit& u) {
+    if (lane < (uint32_t)kWaveRows) {
+      const uint4* r = (const uint4*)rec + 2 * (uint64_t)u.at;
+#pragma unroll
+      for (int i = 0; i < kRecWords; i += 4) {
+        const uint4 v = r[i / 4];
+        u.rec[i] = v.x;
+        u.rec[i + 1] = v.y;
+        u.rec[i + 2] = v.z;
+        u.rec[i + 3] = v.w;
+      }
+    }
+  };
+  uint64_t tile = xcd_tile(blockIdx.x, gridDim.x, 0, ntiles);
+  if (tile != ~0ull) {
+    Unit u, nx;
+    fetch_rows(tile, u);
+    fetch_rec(u);
+    uint64_t next = xcd_tile(blockIdx.x, gridDim.x, 1, ntiles);
+    fetch_rows(next, nx);
+    for (uint64_t step = 2;; ++step) {
+      const uint64_t row0 = tile * kTileRows + (uint64_t)w * kWaveRows;
+      const uint64_t after = next == ~0ull ? ~0ull
+                                           : xcd_tile(blockIdx.x, gridDim.x, step, ntiles);
+      Unit nn;
+      fetch_rows(after, nn);
+      fetch_rec(nx);   // the next unit's records, its descriptors being here
+      // The rows' first candidates, and the last lanes that have one (the
+      // lanes past it repeat its candidate, and their verdicts are dropped at
+      // the end).
+      const uint32_t ulast = u.nv - 1, uend = kEntry * ulast;
+      const uint64_t ubase = CELLS ? (uint64_t)(cells + u.pb)
+                                   : (uint64_t)(pts + (uint64_t)DIM * u.pb);
+      uint32_t mlo = 0, mhi = 0;   // lane j < 16: the mask of the wave's row j
+
+      // A group's candidates: one load per row (three coordinates: three).
+      struct Group {
+        uint64_t cell[CELLS ? ROWS : 1];
+        f64x2 xy[CELLS ? 1 : ROWS];
+        double z[CELLS || DIM == 2 ? 1 : ROWS];
+      };
+      auto load = [&](auto group, Group& G) {
+        static_for<ROWS>([&](auto row) {
+          constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
+          const uint64_t base = read_lane64<r>(ubase);
+          const uint32_t last = read_lane<r>(uend);
+          const uint32_t o = offset < last ? offset : last;
+          if constexpr (CELLS) {
+            G.cell[jr] = global_at<uint64_t>(base, o);
+          } else if constexpr (DIM == 2) {
+            G.xy[jr] = global_at<f64x2>(base, o);
+          } else {
+            G.xy[jr].x = global_at<double>(base, o);
+            G.xy[jr].y = global_at<double>(base, o + 8);
+            G.z[jr] = global_at<double>(base, o + 16);
+          }
+        });
+      };
+      auto test = [&](auto group, const Group& G) {
+        uint64_t hit[ROWS], und[ROWS], any = 0;
+        static_for<ROWS>([&](auto row) {
+          constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
+          if constexpr (CELLS) {
+            // Decide from the cells.
+            QueryFilter f;
+            f.acc = __uint_as_float(read_lane<r>(u.rec[0]));
+            f.rej = __uint_as_float(read_lane<r>(u.rec[1]));
+            f.c[0] = read_lane<r>(u.rec[2]);
+            f.c[1] = read_lane<r>(u.rec[3]);
+            f.c[2] = DIM == 3 ? read_lane<r>(u.rec[kRecWords > 4 ? 4 : 0]) : 0u;
+            float v;
+            // A batch with coarser cells (radii past the shift limit) takes
+            // the shifting check.
+            if (SHIFTS && any_shifted) {
+              f.shift = read_lane<r>(u.rec[kRecWords > 4 ? 5 : 0]);
+              v = cell_distance<DIM, WINDOW, true>(G.cell[jr], f);
+            } else {
+              f.shift = 0;
+              v = cell_distance<DIM, WINDOW, false>(G.cell[jr], f);
+            }
+            const uint64_t in = __ballot(v <= f.acc), out = __ballot(v > f.rej);
+            hit[jr] = in;
+            und[jr] = ~(in | out);
+            any |= und[jr];
+          } else {
+            auto word = [&](auto i) {
+              constexpr int k = decltype(i)::value;
+              return __longlong_as_double((long long)((uint64_t)read_lane<r>(u.rec[k + 1]) << 32 |
+                                                      read_lane<r>(u.rec[k])));
+            };
+            const double qx = word(std::integral_constant<int, 0>{});
+            const double qy = word(std::integral_constant<int, 2>{});
+            const double third = word(std::integral_constant<int, 4>{});
+            bool h;
+            if constexpr (DIM == 2) {
+              h = WINDOW ? within_window(G.xy[jr].x, G.xy[jr].y, qx, qy, third)
+                         : within(G.xy[jr].x, G.xy[jr].y, qx, qy, third);
+            } else {
+              const double d = word(std::integral_constant<int, 6>{});
+              h = WINDOW ? within_window3(G.xy[jr].x, G.xy[jr].y, G.z[jr], qx, qy, third, d)
+                         : within3(G.xy[jr].x, G.xy[jr].y, G.z[jr], qx, qy, third, d);
+            }
+            hit[jr] = __ballot(h);
+          }
+        });
+        if constexpr (CELLS) {
+          // The candidates their cells leave undecided (rare) take the exact
+          // test, behind one branch for the whole group.
+          if (any != 0)
+            static_for<ROWS>([&](auto row) {
+              constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
+              const uint32_t last = read_lane<r>(ulast);
+              bool h = false;
+              if (lane_of(und[jr]))
+                h = exact_hit<DIM>(q, delta, pts, via, read_lane<r>(u.at),
+                                   read_lane<r>(u.pb) + (lane < last ? lane : last), WINDOW);
+              hit[jr] |= __ballot(h);
+            });
+        }
+        if constexpr (EPOCH)
+          static_for<ROWS>([&](auto row) {
+            constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
+            const uint32_t last = read_lane<r>(ulast);
+            bool h = false;
+            if (lane_of(hit[jr])) {
+              const uint64_t pos = (uint64_t)read_lane<r>(u.pb) + (lane < last ? lane : last);
+              const uint32_t qe = read_lane<r>(u.rec[kRecWords > 4 ? 7 : 0]);
+              h = ins[pos] <= qe && qe < era[pos];
+            }
+            hit[jr] = __ballot(h);
+          });
+        static_for<ROWS>([&](auto row) {
+          constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
+          write_lane64<r>(hit[jr], mlo, mhi);
+        });
+      };
+      Group G[2];
+      load(std::integral_constant<int, 0>{}, G[0]);
+      static_for<ITERS>([&](auto group) {
+        constexpr int g = decltype(group)::value;
+        if constexpr (g + 1 < ITERS) load(std::integral_constant<int, g + 1>{}, G[(g + 1) & 1]);
+        test(group, G[g & 1]);
+      });
+
+      // Lanes 0..15: the rows' valid hits, and the unit's up to the lane's row.
+      const uint64_t mask = lane < unit_rows(have, row0)
+                                ? ((uint64_t)mhi << 32 | mlo) & (~0ull >> (63 - ulast))
+                                : 0;
+      const uint32_t v = (uint32_t)__popcll(mask);
       uint32_t x = v;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
+      for (int o = 1; o < (int)kWaveRows; o <<= 1) {
         const uint32_t y = __shfl_up(x, o, 64);
         if (lane >= (uint32_t)o) x += y;
       }
-      s_pre[tid] = x - v;
-      if (tid == 63) s_pre[kTileRows] = x;
-    }
-    __syncthreads();
-    if (tid <= kTileRows && trow0 + tid <= total_rows)
-      row_pre[tile * kTileRows + tid] = prefix + s_pre[tid];
-    const uint32_t hits = s_pre[kTileRows];
-    if (write_ids) {
-      // Each wave maps the outputs of 16 rows (lane l of row r, if its bit
-      // is set, is output s_pre[r] + the set bits below it), then every
-      // output finds its row and candidate with one read of each map.
-      for (uint32_t k = 0; k < kTileRows / 4; ++k) {
-        const uint32_t r = wv * (kTileRows / 4) + k;
-        const uint64_t mk = s_mask[r];
-        if ((mk >> lane) & 1ull) {
-          const uint32_t o = s_pre[r] + (uint32_t)__popcll(mk & below);
-          s_map[o] = (uint16_t)((r << 8) | lane);
-        }
+      if (lane < (uint32_t)kWaveRows) {
+        masks[row0 + lane] = mask;
+        unit_pre[row0 + lane] = (uint16_t)(x - v);
+        if (lane == kWaveRows - 1) unit_hits[tile * kTileUnits + w] = x;
       }
-      __syncthreads();
-      for (uint32_t o = tid; o < hits; o += 256) {
-        const uint32_t mp = s_map[o];
-        const uint64_t p64 = (uint64_t)s_base[mp >> 8] + (mp & 0xFFu);
-        const uint64_t opos = prefix + o;
-        if (p64 < npts && opos < cap) out_ids[opos] = ids[p64];
+      if (next == ~0ull) break;
+      u = nx;
+      nx = nn;
+      tile = next;
+      next = after;
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) status->units = (uint32_t)(ntiles * kTileUnits);
+}
+
+// Hits before the unit: of every unit (of `units`), and at [units] all hits,
+// in LDS, from the units' hits (FUSED compaction: at most kFusedUnits).
+constexpr uint32_t kFusedUnits = 4096;
+
+__device__ __forceinline__ void units_to_lds(const uint32_t* __restrict__ unit_hits,
+                                             uint32_t units, uint32_t* s_off, uint64_t* s_w) {
+  constexpr uint32_t kPer = kFusedUnits / 256;
+  const uint32_t f = threadIdx.x * kPer;
+  uint32_t v[kPer], sum = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) v[i] = f + i < units ? unit_hits[f + i] : 0u;
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) sum += v[i];
+  uint64_t total;
+  uint32_t run = (uint32_t)scan256_u64(sum, s_w, &total);
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    s_off[f + i] = run;
+    run += v[i];
+  }
+  if (threadIdx.x == 255) s_off[kFusedUnits] = run;
+  __syncthreads();
+}
+
+// Pass 2: the ids of the accepted candidates.  A wave takes a unit of 16 rows:
+// the lanes of a row's mask read their ids and write them one after another
+// from the row's place in the output.  ORDERED (rows in curve order): that is
+// the query's output offset plus the query's hits before the row,
+// out_base[query] + P(row) with P(row) the hits of all rows before it; else
+// rows follow the output, P(row) is the place, and the workgroups past
+// `tile_grid` write the queries' CSR offsets, P of each query's first row.
+// FUSED (at most kFusedUnits units): every workgroup scans the units' hits
+// itself, so that a small batch takes no scan launch.  The batch's final
+// counters go to *host (host memory) and its error bits to *flags_out, if not
+// null.  As in the test pass a row's mask, first position and place are scalar;
+// the lanes only count the mask's bits below them.  Bound by memory: 0.373 ms for
+// 0.81 GB of ids from 6.6 * 10^6 rows, 3.4 TB/s with what is read (0.43 ms with a
+// workgroup's hits listed in LDS).  Listing a wave's hits in LDS, for loads and
+// stores of 64 lanes, takes a third of the memory instructions and 0.414 ms;
+// non-temporal stores 0.355 ms here but 0.406 instead of 0.360 where a query
+// reports 170 ids.
+template <bool ORDERED, bool FUSED>
+__global__ __launch_bounds__(256) void compact_write_out(
+    const uint32_t* __restrict__ ids, const uint4* __restrict__ row_meta,
+    const uint64_t* __restrict__ row_off, uint64_t m, uint64_t rbase, uint64_t rend,
+    uint64_t row_end, bool only_whole, const uint64_t* __restrict__ masks,
+    const uint16_t* __restrict__ unit_pre, const uint32_t* __restrict__ unit_hits,
+    const uint64_t* __restrict__ unit_off, const uint64_t* __restrict__ out_base, uint32_t tile_grid, uint32_t* __restrict__ out_ids,
+    uint64_t cap, bool whole, uint64_t* __restrict__ offsets, const BatchStatus* status,
+    BatchStatus* host, uint32_t* flags_out) {
+  __shared__ uint32_t s_off[FUSED ? kFusedUnits + 1 : 1];
+  __shared__ uint64_t s_w[4];
+  static_assert(!(ORDERED && FUSED), "small batches are not ordered");
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t total_all = row_off[m];
+  const uint64_t total_rows = total_all < row_end ? total_all : row_end;
+  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, only_whole);
+  const uint64_t units = ntiles * kTileUnits;
+  // A workgroup without a tile (and not the first, which reports) is done.
+  if (blockIdx.x > 0 && blockIdx.x < tile_grid &&
+      xcd_tile(blockIdx.x, tile_grid, 0, ntiles) == ~0ull)
+    return;
+  if (FUSED) units_to_lds(unit_hits, (uint32_t)units, s_off, s_w);
+  // All hits up to the end of this chunk; without rows in it there are none
+  // to write (and, in the first chunk, none at all).
+  const uint64_t hits_end = FUSED ? s_off[units] : ntiles ? unit_off[units] : 0;
+  // The chunk owns rows [rbase, rend) below the total and, if the total falls
+  // in (rbase, rend], the total itself.
+  const bool owns_total = total_rows == 0 ? rbase == 0 : (rbase < total_rows && total_rows <= rend);
+  if (blockIdx.x == 0 && tid == 0) {
+    if (host && owns_total) {
+      host->rows = status->rows;
+      host->total = ORDERED ? offsets[m] : hits_end;
+      host->candidates = status->candidates;
+      host->endpoints = status->endpoints;
+      host->fallbacks = status->fallbacks;
+      host->pruned = status->pruned;
+      host->err = status->err;
+      host->coarse = status->coarse;
+    }
+    if (flags_out) *flags_out = status->err;
+  }
+  if (only_whole && total_all > row_end) return;   // nothing was tested
+  if (!ORDERED && blockIdx.x >= tile_grid) {
+    // The CSR offsets of the queries whose first row lies in this chunk (a
+    // query with no rows takes the position of the next row, trailing ones
+    // the total).
+    const uint64_t stride = (uint64_t)(gridDim.x - tile_grid) * 256;
+    for (uint64_t j = (uint64_t)(blockIdx.x - tile_grid) * 256 + tid; j <= m; j += stride) {
+      uint64_t r = row_off[j];
+      if (r > total_rows) r = total_rows;   // past the capacity (flagged as overflow)
+      if (r == total_rows) {
+        if (owns_total) offsets[j] = hits_end;
+      } else if (r >= rbase && r < rend) {
+        const uint64_t lr = r - rbase;
+        offsets[j] = (FUSED ? (uint64_t)s_off[lr >> kUnitShift] : unit_off[lr >> kUnitShift]) +
+                     unit_pre[lr];
       }
     }
-    __syncthreads();
+    return;
+  }
+  const bool write_ids = !whole || ntiles == 0 || (ORDERED ? offsets[m] : hits_end) <= cap;
+  if (!write_ids) return;
+  const uint64_t have = total_rows - rbase;
+  // Lane j of a unit: row j's mask and first position, and the terms of its
+  // place in the output (kept as they come, not to wait for them here).
+  struct Unit {
+    uint64_t mask, unit, base;
+    uint32_t pb, at;
+  };
+  auto fetch_rows = [&](uint64_t tile, Unit& u) {
+    u.mask = u.unit = u.base = 0;
+    u.pb = u.at = 0;
+    const uint64_t row0 = tile * kTileRows + (uint64_t)w * kWaveRows;
+    if (tile != ~0ull && lane < unit_rows(have, row0)) {
+      const uint64_t lr = row0 + lane;
+      u.mask = masks[lr];
+      const uint4 md = row_meta[lr];
+      u.pb = md.x;
+      u.at = md.z;
+      u.unit = FUSED ? (uint64_t)s_off[lr >> kUnitShift] : unit_off[lr >> kUnitShift];
+    }
+  };
+  auto fetch_base = [&](Unit& u) {
+    if (ORDERED && lane < (uint32_t)kWaveRows) u.base = out_base[u.at];
+  };
+  uint64_t tile = xcd_tile(blockIdx.x, tile_grid, 0, ntiles);
+  if (tile == ~0ull) return;
+  Unit u, nx;
+  fetch_rows(tile, u);
+  fetch_base(u);
+  uint64_t next = xcd_tile(blockIdx.x, tile_grid, 1, ntiles);
+  fetch_rows(next, nx);
+  for (uint64_t step = 2;; ++step) {
+    const uint64_t after = next == ~0ull ? ~0ull : xcd_tile(blockIdx.x, tile_grid, step, ntiles);
+    Unit nn;
+    fetch_rows(after, nn);
+    fetch_base(nx);
+    // Addresses in the rows' lanes, read as scalars; the capacity checked once
+    // for the unit.
+    const uint32_t hits = (uint32_t)__popcll(u.mask);
+    uint32_t upto = hits;   // the unit's hits up to the row
+#pragma unroll
+    for (int o = 1; o < (int)kWaveRows; o <<= 1) {
+      const uint32_t y = __shfl_up(upto, o, 64);
+      if (lane >= (uint32_t)o) upto += y;
+    }
+    const uint64_t place = u.unit + u.base + (upto - hits);
+    const uint64_t from = (uint64_t)(ids + u.pb), to = (uint64_t)(out_ids + place);
+    const bool fits = __ballot(lane < (uint32_t)kWaveRows && place + 64 > cap) == 0;
+    // Lanes past a row's last hit read that one again.  All the ids are waited
+    // for at once: a wait for one of them after a store would wait for stores
+    // too (they share a counter).
+    const uint32_t end = u.mask ? 4 * (63 - (uint32_t)__clzll(u.mask)) : 0u;
+    const uint32_t offset = 4 * lane;
+    uint32_t id[kWaveRows];
+    static_for<(int)kWaveRows>([&](auto row) {
+      constexpr int r = decltype(row)::value;
+      const uint32_t last = read_lane<r>(end);
+      id[r] = global_at<uint32_t>(read_lane64<r>(from), offset < last ? offset : last);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+    auto store = [&](auto row, bool on, uint32_t k) {
+      constexpr int r = decltype(row)::value;
+      typedef __attribute__((address_space(1))) char* Bytes;
+      typedef __attribute__((address_space(1))) uint32_t* Ptr;
+      if (on) *(Ptr)((Bytes)read_lane64<r>(to) + 4 * k) = id[r];
+    };
+    if (fits) {
+      static_for<(int)kWaveRows>([&](auto row) {
+        const uint64_t mk = read_lane64<decltype(row)::value>(u.mask);
+        store(row, lane_of(mk), below_in(mk));
+      });
+    } else {
+      static_for<(int)kWaveRows>([&](auto row) {
+        constexpr int r = decltype(row)::value;
+        const uint64_t mk = read_lane64<r>(u.mask);
+        const uint32_t k = below_in(mk);
+        store(row, lane_of(mk) && read_lane64<r>(place) + k < cap, k);
+      });
+    }
+    if (next == ~0ull) break;
+    u = nx;
+    nx = nn;
+    next = after;
   }
 }
 
-// The CSR offsets of the queries whose first row lies in this chunk: query
-// j's offset is the output position of row row_off[j] (a query with no
-// rows takes the position of the next row, trailing ones the total).  One
-// thread per query; the chunk owns rows [rbase, rend) below the total and,
-// if the total falls in (rbase, rend], the total itself.
-__global__ __launch_bounds__(256) void query_offsets(
-    const uint64_t* __restrict__ row_off, int ss, uint64_t m,
-    const uint64_t* __restrict__ total_rows_dev, uint64_t rbase, uint64_t rend, uint64_t row_end,
-    const uint64_t* __restrict__ row_pre, uint64_t* __restrict__ offsets) {
-  const uint64_t total_all = *total_rows_dev;
-  const uint64_t total = total_all < row_end ? total_all : row_end;
-  const bool owns_total = total == 0 ? rbase == 0 : (rbase < total && total <= rend);
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j <= m; j += stride) {
-    uint64_t r = row_off[j];
-    if (r > total) r = total;   // past the capacity (flagged as overflow)
-    if (r == total) {
-      if (owns_total) offsets[j] = total == 0 ? 0 : row_pre[r - rbase];
-    } else if (r >= rbase && r < rend) {
-      offsets[j] = row_pre[r - rbase];
-    }
-  }
+// Ordered rows: the hits of every query, and in out_base the hits P of all
+// rows before its first.  One thread per place.
+__global__ __launch_bounds__(256) void query_hits(const uint64_t* __restrict__ row_off, uint64_t m,
+                                                  uint64_t row_end,
+                                                  const uint16_t* __restrict__ unit_pre,
+                                                  const uint64_t* __restrict__ unit_off,
+                                                  const uint32_t* __restrict__ perm,
+                                                  uint32_t* __restrict__ qhits,
+                                                  uint64_t* __restrict__ out_base) {
+  const uint64_t at = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (at >= m) return;
+  const uint64_t total_all = row_off[m];
+  const uint64_t total = total_all <= row_end ? total_all : 0;   // past a capacity: not tested
+  const uint64_t units = (total + kTileRows - 1) / kTileRows * kTileUnits;
+  auto before = [&](uint64_t r) -> uint64_t {
+    if (r >= total) return total ? unit_off[units] : 0;
+    return unit_off[r >> kUnitShift] + unit_pre[r];
+  };
+  const uint64_t p0 = before(row_off[at]), p1 = before(row_off[at + 1]);
+  const uint32_t j = perm[at];
+  qhits[j] = (uint32_t)(p1 - p0);
+  out_base[j] = p0;
+}
+
+// out_base: from P of the query's first row to what added to P(row) gives the
+// row's place in the output.
+__global__ __launch_bounds__(256) void place_rows(const uint64_t* __restrict__ offsets, uint64_t m,
+                                                  uint64_t* __restrict__ out_base) {
+  const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j < m) out_base[j] = offsets[j] - out_base[j];
 }
 
 __global__ void fill64_kernel(uint64_t* p, uint64_t v, uint64_t count) {
@@ -1081,9 +1598,9 @@ std::atomic<uint64_t> g_chunk_tiles{kCompactChunkTiles};
 // Shape of the test kernel's row groups, rows x iterations: 0: 16 x 1,
 // 1: 4 x 4, 2: 8 x 2, 3: 2 x 8, 4: 1 x 16 (same results for all).  The
 // environment variable SFC_TEST_VARIANT overrides; else the autotuner's choice
-// for this number of rows; else 1 (measured fastest: 0.531 ms vs 0.541 ms for
-// 8 x 2 and 0.614 ms for 16 x 1 at 8 * 10^6 rows; the 256-set batch 1.96 vs
-// 2.09 ms).
+// for this number of rows; else 1 (8 * 10^6 rows in the plane: 0.366 ms, 0.370
+// for 16 x 1, 0.365 for 8 x 2 and 0.393 for 1 x 16; in three dimensions 0.810,
+// 0.918, 0.847 and 1.026 ms).
 int test_variant(uint64_t rows) {
   static const int env = [] {
     const char* e = std::getenv("SFC_TEST_VARIANT");
@@ -1121,6 +1638,9 @@ hipError_t fill_u32(uint32_t* p, uint32_t value, uint64_t count, hipStream_t s) 
   return hipGetLastError();
 }
 
+// The sizes callers plan with (sfc_query_scratch_size, the fixed scratch of
+// sfc_query_batch_static): they stay as published, and the layouts below use
+// less (checked where they are carved).
 size_t query_scratch_bytes(uint64_t m, uint32_t slots) {
   const uint64_t nseg = slots * m;
   return align256(nseg * 4) * 3 + align256((nseg + 1) * 8) + scan_scratch_bytes(nseg) +
@@ -1128,21 +1648,45 @@ size_t query_scratch_bytes(uint64_t m, uint32_t slots) {
          order_scratch_bytes(m) + align256(m * 4);
 }
 
-void query_scratch_carve(void* base, uint64_t m, QueryScratch* qs, uint32_t slots) {
+bool query_scratch_carve(void* base, uint64_t m, QueryScratch* qs, uint32_t slots) {
   const uint64_t nseg = slots * m;
+  const uint64_t nblk = (m + 31) / 32;           // search workgroups (32 or 64 queries each)
+  const uint64_t npack = (m + 255) / 256;        // cells_pack workgroups
   char* p = (char*)base;
-  qs->slot_begin = (uint32_t*)p;  p += align256(nseg * 4);
-  qs->slot_count = (uint32_t*)p;  p += align256(nseg * 4);
-  qs->slot_rows = (uint32_t*)p;   p += align256(nseg * 4);
-  qs->row_off = (uint64_t*)p;     p += align256((nseg + 1) * 8);
-  qs->scan_tmp = (uint64_t*)p;    p += scan_scratch_bytes(nseg);
-  qs->counters = (uint32_t*)p;    p += align256(64);
-  qs->pairs = (uint64_t*)p;       p += align256(4 * m * 8);
-  qs->qfilt = p;                  p += align256(m * 32);
+  qs->m = m;
+  qs->status = (BatchStatus*)p;   p += align256(sizeof(BatchStatus));
+  qs->slots = (uint2*)p;          p += align256(nseg * 8);
+  qs->row_off = (uint64_t*)p;     p += align256((m + 1) * 8);
+  qs->blk_rows = (uint64_t*)p;
+  qs->blk_off = qs->blk_rows + nblk;
+  qs->blk_stat = qs->blk_off + nblk;
+  qs->blk_learned = (uint32_t*)(qs->blk_stat + nblk);
+  p += align256(nblk * 28);
+  qs->rec = p;                    p += align256(m * 32);
   qs->perm = (uint32_t*)p;        p += align256(m * 4);
-  qs->qrows = (uint32_t*)p;       p += align256(m * 4);
-  qs->order_scratch = p;
+  qs->out_base = (uint64_t*)p;    p += align256(m * 8);
+  qs->qhits = (uint32_t*)p;       p += align256(m * 4);
+  qs->scan_tmp = (uint64_t*)p;    p += scan_scratch_bytes(m);
+  // One region for what is needed in turn: the ordering's buffers and the work
+  // list of early termination.
+  char* aux = p;
+  qs->order_scratch = aux;
+  const size_t order_end = order_scratch_bytes(m);
+  char* e = aux;
+  qs->pairs = (uint64_t*)e;       e += align256(4 * m * 8);
+  qs->regions = (uint64_t*)e;     e += align256(4 * m * 8);
+  qs->pack_flags = (uint64_t*)e;
+  qs->pack_cnt = (uint32_t*)(qs->pack_flags + npack);
+  qs->pack_pruned = qs->pack_cnt + npack;
+  qs->pack_pre = qs->pack_pruned + npack;
+  e += align256(npack * 20 + 4);
+  p += (size_t)(e - aux) > order_end ? (size_t)(e - aux) : order_end;
   qs->ss = 2;
+  qs->perm_made = false;
+  qs->fused = false;
+  qs->stats_ns = qs->stats_np = 0;
+  qs->learned = false;
+  return (size_t)(p - (char*)base) <= query_scratch_bytes(m, slots);
 }
 
 size_t compact_scratch_bytes(uint64_t total_rows) {
@@ -1154,72 +1698,153 @@ size_t compact_scratch_bytes(uint64_t total_rows) {
          scan_scratch_bytes(tiles);
 }
 
-// Every query's first row (row_off[j], and the total at row_off[m]): its
-// slots' rows summed, then scanned over the queries.
-hipError_t scan_query_rows(QueryScratch& qs, uint64_t m, hipStream_t s) {
-  {
-    ProfScope ps("scan", s);
-    query_rows<<<(uint32_t)(((m << qs.ss) + 255) / 256), 256, 0, s>>>(qs.slot_rows, m << qs.ss,
-                                                                       qs.ss, qs.qrows);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return scan_excl(qs.qrows, qs.row_off, m, nullptr, qs.scan_tmp, s);
+namespace {
+
+struct CompactScratch {
+  uint64_t* masks;       // per row
+  uint4* meta;           // per row
+  uint16_t* unit_pre;    // per row
+  uint32_t* unit_hits;   // per unit
+  uint64_t* unit_off[2]; // per unit, and the total; two, for the chunks in turn
+  uint64_t* scan_tmp;
+};
+
+// Lays out the scratch of a chunk of `tiles` tiles; false if it needs more
+// than compact_scratch_bytes gives.
+bool compact_carve(void* base, uint64_t tiles, CompactScratch* c) {
+  char* p = (char*)base;
+  const uint64_t units = tiles * kTileUnits;
+  c->masks = (uint64_t*)p;       p += align256(tiles * kTileRows * 8);
+  c->meta = (uint4*)p;           p += align256(tiles * kTileRows * 16);
+  c->unit_pre = (uint16_t*)p;    p += align256(tiles * kTileRows * 2);
+  c->unit_hits = (uint32_t*)p;   p += align256(units * 4);
+  c->unit_off[0] = (uint64_t*)p; p += align256((units + 1) * 8);
+  c->unit_off[1] = (uint64_t*)p; p += align256((units + 1) * 8);
+  c->scan_tmp = (uint64_t*)p;    p += scan_dev_scratch_bytes(units);
+  return (size_t)(p - (char*)base) <= compact_scratch_bytes(tiles * kCompactTileRows);
 }
 
-// Batches from this size on are ordered along the curve before the search.
-constexpr uint64_t kOrderMin = 1u << 14;
+// Query slots per thread of the kernels over slots: a workgroup holds the
+// queries of one workgroup of the search (64, or 32 in three dimensions).
+int slots_per_thread(const QueryScratch& qs) { return (qs.block_queries << qs.ss) / 256; }
 
-hipError_t launch_ranges(const double* q, const double* delta, uint64_t m, const uint64_t* keys,
-                         uint64_t n, int curve, bool refine, uint32_t refine_min, bool ball,
-                         const LearnedView* lview, const StreeView* sview, const uint32_t* occ,
-                         const uint32_t* qset, const uint64_t* set_off, uint32_t n_sets,
-                         QueryScratch& qs, uint64_t* dbg_lo, uint64_t* dbg_hi, uint64_t* dbg_b,
-                         uint64_t* dbg_e, uint32_t* dbg_nr, hipStream_t s) {
+uint32_t query_blocks(const QueryScratch& qs) {
+  return (uint32_t)((qs.m + qs.block_queries - 1) / qs.block_queries);
+}
+
+BatchStats stats_of(const QueryScratch& qs) {
+  return BatchStats{qs.blk_stat, qs.learned ? qs.blk_learned : nullptr, qs.stats_ns,
+                    qs.pack_flags, qs.pack_pruned, qs.stats_np};
+}
+
+hipError_t launch_slot_rows(const QueryScratch& qs, const uint32_t* perm, hipStream_t s) {
+  const uint64_t nseg = qs.m << qs.ss;
+  const uint32_t g = query_blocks(qs);
+  switch (slots_per_thread(qs)) {
+    case 1: slot_rows<1><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, qs.blk_rows); break;
+    case 2: slot_rows<2><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, qs.blk_rows); break;
+    default: slot_rows<4><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, qs.blk_rows); break;
+  }
+  return hipGetLastError();
+}
+
+// After the search: the rows' scan over the search's workgroups and the
+// batch's counters, unless expand_rows does both (fused).
+hipError_t finish_ranges(QueryScratch& qs, bool need_rows, BatchStatus* host, hipStream_t s) {
+  const uint32_t nblk = query_blocks(qs);
+  qs.fused = !need_rows && nblk <= kFusedBlocks && qs.stats_np == 0;
+  if (qs.fused) return hipSuccess;
+  ProfScope ps("scan", s);
+  batch_scan<<<1, 1024, 0, s>>>(qs.blk_rows, nblk, qs.blk_off, qs.row_off + qs.m, stats_of(qs),
+                                true, qs.status, host);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Whether a batch's search takes its queries in curve order.  Only the binary
+// search gains (its probes of a workgroup then meet in the same lines), and
+// only if the order (23 us for 2 * 10^5 queries, 33 for 10^6) costs less: 2^20
+// queries over 2^24 points 0.76 ms against 0.88 (c 1 to 100; 10^3: 1.39 against
+// 1.79), 2^18 0.29 against 0.30 (0.46 against 0.53), 2^17 0.188 against 0.182
+// (0.288 against 0.299), 2^17 over 2^20 0.160 against 0.147.  The learned
+// index and the search tree probe less (2^22 queries over 2^26 points: learned
+// search 0.63 ms against 0.67, the order 0.08), batches of point sets are grouped
+// by set as a rule, and early termination leaves too few cells (2^20 windows over
+// 2^24 points: 0.41 ms in order, 0.31 without).
+constexpr uint64_t kOrderMin = (1u << 17) + 1;
+constexpr uint64_t kOrderPoints = 1u << 20;
+bool search_ordered(const RangePlan& P, bool binary, uint64_t m) {
+  return binary && !P.occ && !P.qset && m >= kOrderMin && P.n >= kOrderPoints;
+}
+
+// Whether a batch's rows are processed in curve order: the test pass gains a
+// third (0.46 -> 0.29 ms for the 6.6 * 10^6 rows of 2 * 10^5 windows), but the
+// queries' offsets then take a scan of their hits (0.03 ms; 2^22 queries 0.2 ms),
+// so only with many rows a query: at 33 the windows' batch takes 0.91 ms against
+// 1.01, at 8 (2^20 queries over 2^24 points) 2.22 against 2.20.
+constexpr uint64_t kOrderRows = 16;
+bool rows_ordered(const CompactPlan& P, uint64_t m) {
+  return P.keys && m >= kOrderMin && P.n >= kOrderPoints && P.max_rows > kOrderRows * m;
+}
+
+hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
+  const uint64_t m = qs.m;
   if (m == 0) return hipSuccess;
-  const uint32_t blocks = (uint32_t)((4 * m + 255) / 256);
+  const bool dbg = P.dbg_lo != nullptr;
+  const bool refine = P.refine && !dbg;   // the inspected ranges are the method's merged ranges
+  const bool d3 = P.dim == 3;
   hipError_t e;
-  if ((e = fill_u32(qs.counters, 0, 16, s)) != hipSuccess) return e;
-  flag_coarse<<<(uint32_t)((m + 255) / 256), 256, 0, s>>>(delta, m, 4294967296.0, 0x1p28,
-                                                           qs.counters);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (dbg_lo) refine = false;   // the inspected ranges are the method's merged ranges
-  qs.ss = refine ? 3 : 2;
-  const bool learned = lview != nullptr && qset == nullptr;
-  const bool stree = !learned && sview != nullptr && qset == nullptr;
-  const LearnedView lv = learned ? *lview : LearnedView{};
-  const StreeView sv = stree ? *sview : StreeView{};
-  unsigned long long* cand = (unsigned long long*)(qs.counters + 4);
-  // With early termination (and no inspected ranges) the search runs one
-  // lane per surviving cell, from a dense list of (query, cell) pairs.
-  const bool dense = occ != nullptr && dbg_lo == nullptr;
-  unsigned long long* total = (unsigned long long*)(qs.counters + 14);   // cleared above
-  const uint64_t* pairs = nullptr;
-  const uint64_t* pair_total = nullptr;
-  // Large batches over the whole array are searched in curve order (with
-  // early termination: listed in that order).
+  qs.ss = d3 ? (refine ? 5 : 3) : (refine ? 3 : 2);
+  qs.block_queries = d3 ? 32 : 64;
+  qs.stats_ns = query_blocks(qs);
+  qs.stats_np = 0;
+  const bool learned = P.lview != nullptr && P.qset == nullptr;
+  const bool stree = !learned && P.sview != nullptr && P.qset == nullptr;
+  qs.learned = learned;
+  const LearnedView lv = learned ? *P.lview : LearnedView{};
+  const StreeView sv = stree ? *P.sview : StreeView{};
+  RecordPlan rec = P.record;
+  rec.rec = qs.rec;
+  if (dbg) rec = RecordPlan{};
   const uint32_t* perm = nullptr;
-  if (!dbg_lo && !qset && m >= kOrderMin) {
-    if ((e = order_queries(q, m, curve, qs.perm, qs.order_scratch, qs.counters + 2, s)) !=
-        hipSuccess)
+  qs.perm_made = !dbg && search_ordered(P, !learned && !stree, m);
+  if (qs.perm_made) {
+    if ((e = order_queries(P.q, m, d3 ? SFC_CURVE_MORTON3 : P.curve, P.keys, P.n, qs.perm,
+                           qs.order_scratch, s)) != hipSuccess)
       return e;
     perm = qs.perm;
   }
+  if (d3) {
+    ProfScope ps(stree ? "ranges_stree3" : "ranges_search3", s);
+#define SFC_R3(S, R)                                                                         \
+  ranges_search3<S, R><<<query_blocks(qs), 256, 0, s>>>(P.q, P.delta, m, P.keys, P.n, lv, sv, \
+                                                        P.refine_min, perm, rec, qs.slots,   \
+                                                        qs.blk_rows, qs.blk_stat)
+    if (stree) {
+      if (refine) SFC_R3(2, true);
+      else SFC_R3(2, false);
+    } else {
+      if (refine) SFC_R3(0, true);
+      else SFC_R3(0, false);
+    }
+#undef SFC_R3
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (perm && (e = launch_slot_rows(qs, nullptr, s)) != hipSuccess) return e;
+    return finish_ranges(qs, P.need_rows, P.host, s);
+  }
+  // With early termination (and no inspected ranges) the search runs one
+  // lane per surviving cell, from a dense list of (query, cell) pairs.
+  const bool dense = P.occ != nullptr && !dbg;
+  const uint64_t* pairs = nullptr;
+  const uint32_t* pair_total = nullptr;
   if (dense) {
     const uint32_t qb = (uint32_t)((m + 255) / 256);
-    // Until the row scan (after the search) fills them: the row offsets hold
-    // each block's region of pairs (4m entries at most), and the query row
-    // counts the blocks' counts, pruned cells and exclusive prefixes.
-    uint64_t* regions = qs.row_off;
-    uint32_t* blk_cnt = qs.qrows;
-    uint32_t* blk_pruned = qs.qrows + qb;
-    uint32_t* blk_pre = qs.qrows + 2 * (uint64_t)qb;
     ProfScope ps("cells_pack", s);
 #define SFC_CELLS(C, R)                                                                    \
-  cells_pack<C, R><<<qb, 256, 0, s>>>((const double2*)q, delta, m, occ, qset, n_sets,       \
-                                      regions, blk_cnt, qs.slot_rows, qs.counters,          \
-                                      blk_pruned, perm)
-    if (curve == SFC_CURVE_HILBERT) {
+  cells_pack<C, R><<<qb, 256, 0, s>>>((const double2*)P.q, P.delta, m, P.occ, qs.regions,  \
+                                      qs.pack_cnt, qs.pack_pruned, qs.pack_flags, rec, qs.slots)
+    if (P.curve == SFC_CURVE_HILBERT) {
       if (refine) SFC_CELLS(SFC_CURVE_HILBERT, true);
       else SFC_CELLS(SFC_CURVE_HILBERT, false);
     } else {
@@ -1228,21 +1853,22 @@ hipError_t launch_ranges(const double* q, const double* delta, uint64_t m, const
     }
 #undef SFC_CELLS
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    pack_scan<<<1, 1024, 0, s>>>(blk_cnt, blk_pruned, qb, blk_pre, total, cand + 3);
+    pack_scan<<<1, 1024, 0, s>>>(qs.pack_cnt, qb, qs.pack_pre, qs.pack_pre + qb);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    pack_move<<<qb, 256, 0, s>>>(regions, blk_cnt, blk_pre, qs.pairs);
+    pack_move<<<qb, 256, 0, s>>>(qs.regions, qs.pack_cnt, qs.pack_pre, qs.pairs);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     pairs = qs.pairs;
-    pair_total = (const uint64_t*)total;
+    pair_total = qs.pack_pre + qb;
+    qs.stats_np = qb;
   }
   {
     ProfScope ps(learned ? "ranges_learned" : stree ? "ranges_stree" : "ranges_search", s);
 #define SFC_RANGES(C, R, S)                                                                  \
-  ranges_search<C, R, S><<<blocks, 256, 0, s>>>(                                              \
-      (const double2*)q, delta, m, keys, n, lv, sv, refine_min, ball, dbg_lo ? nullptr : occ, \
-      pairs, pair_total, qset, set_off, n_sets, qs.slot_begin,                                \
-      qs.slot_count, qs.slot_rows, qs.counters, cand, dense ? nullptr : perm, dbg_lo, dbg_hi, \
-      dbg_b, dbg_e, dbg_nr)
+  ranges_search<C, R, S><<<query_blocks(qs), 256, 0, s>>>(                                    \
+      (const double2*)P.q, P.delta, m, P.keys, P.n, lv, sv, P.refine_min, P.ball,             \
+      dbg ? nullptr : P.occ, pairs, pair_total, P.qset, P.set_off, P.n_sets, perm, rec,       \
+      qs.slots, qs.blk_rows, qs.blk_stat, qs.blk_learned, P.dbg_lo, P.dbg_hi, P.dbg_b,        \
+      P.dbg_e, P.dbg_nr)
 #define SFC_RANGES_R(C, R)                      \
   if (learned) SFC_RANGES(C, R, 1);             \
   else if (stree) SFC_RANGES(C, R, 2);          \
@@ -1253,7 +1879,7 @@ hipError_t launch_ranges(const double* q, const double* delta, uint64_t m, const
   } else {                                      \
     SFC_RANGES_R(C, false)                      \
   }
-    if (curve == SFC_CURVE_HILBERT) {
+    if (P.curve == SFC_CURVE_HILBERT) {
       SFC_RANGES_C(SFC_CURVE_HILBERT)
     } else {
       SFC_RANGES_C(SFC_CURVE_MORTON)
@@ -1263,177 +1889,160 @@ hipError_t launch_ranges(const double* q, const double* delta, uint64_t m, const
 #undef SFC_RANGES
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  return scan_query_rows(qs, m, s);
+  if ((dense || perm) && (e = launch_slot_rows(qs, nullptr, s)) != hipSuccess) return e;
+  return finish_ranges(qs, P.need_rows, P.host, s);
 }
 
-// Blocks of the compaction kernels (grid-stride over tiles beyond this):
-// 16384, 64 per CU, measured best of 4096 to 32768 (the 2^24 batch's test
-// and write passes 0.968 -> 0.958 ms against 8192).
+// Blocks of the compaction kernels (a loop over tiles beyond this): 16384,
+// 64 per CU, measured best of 4096 to 32768 (the 2^24 batch's test and write
+// passes 0.968 -> 0.958 ms against 8192).
 constexpr uint64_t kCompactGrid = 16384;
 
-hipError_t launch_ranges3(const double* q, const double* delta, uint64_t m, const uint64_t* keys,
-                          uint64_t n, bool refine, uint32_t refine_min, const StreeView* sview,
-                          QueryScratch& qs, hipStream_t s) {
-  if (m == 0) return hipSuccess;
+hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStream_t s) {
   hipError_t e;
-  if ((e = fill_u32(qs.counters, 0, 16, s)) != hipSuccess) return e;
-  flag_coarse<<<(uint32_t)((m + 255) / 256), 256, 0, s>>>(delta, m, 2097152.0, 0x1p17,
-                                                           qs.counters);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  qs.ss = refine ? 5 : 3;
-  const uint32_t blocks = (uint32_t)((8 * m + 255) / 256);
-  unsigned long long* cand = (unsigned long long*)(qs.counters + 4);
-  const LearnedView lv{};
-  const StreeView sv = sview ? *sview : StreeView{};
-  {
-    ProfScope ps(sview ? "ranges_stree3" : "ranges_search3", s);
-#define SFC_R3(S, R)                                                                         \
-  ranges_search3<S, R><<<blocks, 256, 0, s>>>(q, delta, m, keys, n, lv, sv, refine_min,      \
-                                              qs.slot_begin, qs.slot_count, qs.slot_rows,    \
-                                              qs.counters, cand)
-    if (sview) {
-      if (refine) SFC_R3(2, true);
-      else SFC_R3(2, false);
-    } else {
-      if (refine) SFC_R3(0, true);
-      else SFC_R3(0, false);
-    }
-#undef SFC_R3
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  return scan_query_rows(qs, m, s);
-}
-
-hipError_t launch_compact(const double* q, const double* delta, uint64_t m, const double* pts,
-                          const double* pts_in, const uint64_t* cells, const uint32_t* ids,
-                          uint64_t npts, const QueryScratch& qs,
-                          uint64_t max_rows, bool device_sized, void* cscratch,
-                          uint64_t* offsets, uint32_t* out_ids, uint64_t cap, bool window,
-                          int dim, hipStream_t s, const EpochView* ev, bool write_only,
-                          int coarse) {
-  hipError_t e;
-  if (m == 0) return fill_u64(offsets, 0, 1, s);
+  QueryScratch qs = qs0;
+  const uint64_t m = qs.m;
+  if (m == 0) return fill_u64(P.offsets, 0, 1, s);
   // Whether the test pass may meet queries with coarser cells: known (0, 1)
   // when the caller read the batch's flag, else (-1) the pass reads it.
-  const bool shifts = coarse != 0;
-  const uint64_t nseg = m << qs.ss;
-  const uint64_t* total_dev = qs.row_off + m;
+  const bool shifts = P.coarse != 0;
   // Rows are processed in chunks of at most kCompactChunkTiles tiles.
   // Host-sized: max_rows is the exact number of rows.  Device-sized: max_rows
   // is a capacity; each kernel reads the row count on the device, chunks past
   // it do no work, and a count above the capacity is flagged as overflow.
-  const uint64_t tiles_all = (max_rows + kCompactTileRows - 1) / kCompactTileRows;
-  if (!device_sized && max_rows == 0) return fill_u64(offsets, 0, m + 1, s);
+  const uint64_t tiles_all = (P.max_rows + kCompactTileRows - 1) / kCompactTileRows;
   const uint64_t chunk = compact_chunk_tiles();
   const uint64_t ch_tiles = tiles_all < chunk ? (tiles_all ? tiles_all : 1) : chunk;
-  char* p = (char*)cscratch;
-  uint64_t* masks = (uint64_t*)p;     p += align256(ch_tiles * kTileRows * 8);
-  uint32_t* hits = (uint32_t*)p;      p += align256(ch_tiles * 4);
-  uint64_t* toff[2];
-  toff[0] = (uint64_t*)p;             p += align256((ch_tiles + 1) * 8);
-  toff[1] = (uint64_t*)p;             p += align256((ch_tiles + 1) * 8);
-  uint4* meta = (uint4*)p;            p += align256(ch_tiles * kTileRows * 16);
-  uint64_t* rpre = (uint64_t*)p;      p += align256((ch_tiles * kTileRows + 1) * 8);
-  uint64_t* stmp = (uint64_t*)p;
+  const uint64_t chunks = tiles_all ? (tiles_all + chunk - 1) / chunk : 1;
+  CompactScratch c;
+  if (!compact_carve(P.scratch, ch_tiles, &c)) return hipErrorInvalidValue;
+  // write_only: the masks and unit offsets of an earlier call on the same
+  // batch are still in scratch (one chunk only); run the write pass again.
+  if (P.write_only && chunks != 1) return hipErrorInvalidValue;
+  // Rows in curve order: only one chunk's hits are kept, so many chunks are
+  // processed in query order.
+  const bool ordered = chunks == 1 && rows_ordered(P, m);
+  const uint32_t* perm = ordered ? qs.perm : nullptr;
+  if (ordered && !P.write_only) {
+    if (!qs.perm_made &&
+        (e = order_queries(P.q, m, P.dim == 3 ? SFC_CURVE_MORTON3 : P.curve, P.keys, P.n,
+                           qs.perm, qs.order_scratch, s)) != hipSuccess)
+      return e;
+    ProfScope ps("expand_rows", s);
+    if ((e = launch_slot_rows(qs, perm, s)) != hipSuccess) return e;
+    batch_scan<<<1, 1024, 0, s>>>(qs.blk_rows, query_blocks(qs), qs.blk_off, qs.row_off + m,
+                                  stats_of(qs), qs.fused, qs.status, nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    qs.fused = false;
+  }
+  const bool fused_units = !ordered && chunks == 1 && ch_tiles * kTileUnits <= kFusedUnits;
+  const uint64_t* total_dev = qs.row_off + m;
   const uint64_t* carry = nullptr;
   int buf = 0;
-  const uint64_t chunks = tiles_all ? (tiles_all + chunk - 1) / chunk : 1;
-  // write_only: the masks and tile offsets of an earlier call on the same
-  // batch are still in cscratch (one chunk only); run the write pass again.
-  if (write_only && (chunks != 1 || device_sized)) return hipErrorInvalidValue;
-  if (cells && !write_only) {
-    ProfScope ps("query_filters", s);
-    const uint32_t qb = (uint32_t)((m + 255) / 256);
-    if (dim == 3)
-      query_filters<3><<<qb, 256, 0, s>>>(q, delta, m, window, (QueryFilter*)qs.qfilt);
-    else
-      query_filters<2><<<qb, 256, 0, s>>>(q, delta, m, window, (QueryFilter*)qs.qfilt);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  for (uint64_t c = 0; c < chunks; ++c, buf ^= 1) {
-    const uint64_t rbase = c * chunk * kCompactTileRows;
-    const uint64_t nt = tiles_all - c * chunk < chunk ? (tiles_all ? tiles_all - c * chunk : 1)
-                                                      : chunk;
+  for (uint64_t ci = 0; ci < chunks; ++ci, buf ^= 1) {
+    const uint64_t rbase = ci * chunk * kCompactTileRows;
+    const uint64_t nt = tiles_all - ci * chunk < chunk ? (tiles_all ? tiles_all - ci * chunk : 1)
+                                                       : chunk;
+    const uint64_t rend = rbase + nt * kCompactTileRows;
     // A full chunk ends at its last tile; the last chunk at the capacity
     // (device-sized) or at the exact count (host-sized, a multiple of 64 rows
     // past it is never read because the kernels clamp to the count).
-    const uint64_t row_end = c + 1 < chunks ? rbase + nt * kCompactTileRows
-                             : device_sized ? max_rows : rbase + nt * kCompactTileRows;
-    const bool flag = device_sized && c + 1 == chunks;
-    const uint32_t grid = (uint32_t)(nt < kCompactGrid ? (nt ? nt : 1) : kCompactGrid);
-    if (!write_only) {
+    const uint64_t row_end = ci + 1 == chunks && P.device_sized ? P.max_rows : rend;
+    const bool flag = P.device_sized && ci + 1 == chunks;
+    // A multiple of eight workgroups, so that each XCD gets its share.
+    const uint32_t grid = (uint32_t)(((nt < kCompactGrid ? nt : kCompactGrid) + 7) / 8 * 8);
+    uint64_t* unit_off = c.unit_off[buf];
+    if (!P.write_only) {
       ProfScope ps("expand_rows", s);
-      expand_rows<<<(uint32_t)((nseg + 255) / 256), 256, 0, s>>>(
-          qs.row_off, qs.slot_rows, qs.slot_begin, qs.slot_count, nseg, qs.ss, rbase, row_end,
-          meta);
+#define SFC_EXPAND(K, F)                                                                     \
+  expand_rows<K, F><<<query_blocks(qs), 256, 0, s>>>(qs.row_off, qs.slots, perm, qs.blk_rows, \
+                                                     qs.blk_off, stats_of(qs), qs.status, m, qs.ss, rbase,  \
+                                                     row_end, flag, c.meta)
+      switch (slots_per_thread(qs)) {
+        case 1: if (qs.fused) SFC_EXPAND(1, true); else SFC_EXPAND(1, false); break;
+        case 2: if (qs.fused) SFC_EXPAND(2, true); else SFC_EXPAND(2, false); break;
+        default: if (qs.fused) SFC_EXPAND(4, true); else SFC_EXPAND(4, false); break;
+      }
+#undef SFC_EXPAND
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (!write_only) {
-      if ((e = fill_u32(hits, 0, nt, s)) != hipSuccess) return e;
+    if (!P.write_only) {
       ProfScope ps("compact_test", s);
 #define SFC_TEST_K(R, I, E, D, C, W, K)                                                    \
   compact_test<R, I, E, D, C, W, K><<<grid, 256, 0, s>>>(                                  \
-      q, delta, m, pts ? pts : pts_in, pts ? nullptr : ids, cells,                         \
-      (const QueryFilter*)qs.qfilt, npts, meta,                                            \
-      total_dev, rbase, row_end, flag, masks, hits, qs.counters,                           \
-      ev ? ev->ins : nullptr, ev ? ev->era : nullptr,                                      \
-      ev ? ev->qepoch : nullptr, ev ? ev->epoch : 0u)
+      P.q, P.delta, m, P.pts ? P.pts : P.pts_in, P.pts ? nullptr : P.ids, P.cells, qs.rec, \
+      c.meta, total_dev, rbase, row_end, flag, c.masks, c.unit_pre, c.unit_hits, qs.status, \
+      P.ins, P.era)
 #define SFC_TEST_W(R, I, E, D, C, W)                                                       \
   if (C && shifts) SFC_TEST_K(R, I, E, D, C, W, C);                                        \
   else SFC_TEST_K(R, I, E, D, C, W, false)
-#define SFC_TEST_D(R, I, E, D, C)                                                          \
-  if (window) SFC_TEST_W(R, I, E, D, C, true);                                             \
+#define SFC_TEST(R, I, E, D, C)                                                            \
+  if (P.window) SFC_TEST_W(R, I, E, D, C, true);                                           \
   else SFC_TEST_W(R, I, E, D, C, false)
-#define SFC_TEST(R, I, E)                                                                  \
-  if (dim == 3) {                                                                          \
-    if (cells) SFC_TEST_D(R, I, E, 3, true);                                               \
-    else SFC_TEST_D(R, I, E, 3, false);                                                    \
-  } else {                                                                                 \
-    if (cells) SFC_TEST_D(R, I, E, 2, true);                                               \
-    else SFC_TEST_D(R, I, E, 2, false);                                                    \
+#define SFC_TEST_SHAPES(E, D, C)              \
+  switch (test_variant(P.max_rows)) {         \
+    case 1: SFC_TEST(4, 4, E, D, C); break;   \
+    case 2: SFC_TEST(8, 2, E, D, C); break;   \
+    case 3: SFC_TEST(2, 8, E, D, C); break;   \
+    case 4: SFC_TEST(1, 16, E, D, C); break;  \
+    default: SFC_TEST(16, 1, E, D, C); break; \
   }
-#define SFC_TEST_SHAPES(E)                  \
-  switch (test_variant(max_rows)) {         \
-    case 1: SFC_TEST(4, 4, E); break;       \
-    case 2: SFC_TEST(8, 2, E); break;       \
-    case 3: SFC_TEST(2, 8, E); break;       \
-    case 4: SFC_TEST(1, 16, E); break;      \
-    default: SFC_TEST(16, 1, E); break;     \
-  }
-      if (ev && ev->ins) {
-        SFC_TEST_SHAPES(true)
+      if (P.ins && (P.cells || P.dim == 3)) return hipErrorInvalidValue;   // never kept together
+      if (P.dim == 3) {
+        if (P.cells) {
+          SFC_TEST_SHAPES(false, 3, true)
+        } else {
+          SFC_TEST_SHAPES(false, 3, false)
+        }
+      } else if (P.cells) {
+        SFC_TEST_SHAPES(false, 2, true)
+      } else if (P.ins) {
+        SFC_TEST_SHAPES(true, 2, false)
       } else {
-        SFC_TEST_SHAPES(false)
+        SFC_TEST_SHAPES(false, 2, false)
       }
 #undef SFC_TEST_SHAPES
 #undef SFC_TEST
-#undef SFC_TEST_D
 #undef SFC_TEST_W
 #undef SFC_TEST_K
       if ((e = hipGetLastError()) != hipSuccess) return e;
+      if (!fused_units &&
+          (e = scan_excl_dev(c.unit_hits, unit_off, &qs.status->units, nt * kTileUnits, carry,
+                             c.scan_tmp, s)) != hipSuccess)
+        return e;
     }
-    if (!write_only &&
-        (e = scan_excl_dev(hits, toff[buf], qs.counters + 12, nt, carry, stmp, s)) != hipSuccess)
-      return e;
+    if (ordered) {
+      ProfScope ps("query_offsets", s);
+      const uint32_t qb = (uint32_t)((m + 255) / 256);
+      if (!P.write_only) {
+        query_hits<<<qb, 256, 0, s>>>(qs.row_off, m, row_end, c.unit_pre, unit_off, qs.perm,
+                                      qs.qhits, qs.out_base);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+      }
+      if ((e = scan_excl(qs.qhits, P.offsets, m, nullptr, qs.scan_tmp, s)) != hipSuccess) return e;
+      if (!P.write_only) {
+        place_rows<<<qb, 256, 0, s>>>(P.offsets, m, qs.out_base);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+      }
+    }
     {
       ProfScope ps("compact_write", s);
-      // One lane per output (0.64 ms at 1.7e8 outputs from 6.3e8 candidates;
-      // the candidate-driven version with eight-row groups took 0.72 ms).
-      compact_write_out<<<grid, 256, 0, s>>>(ids, npts, meta, total_dev, rbase, row_end, masks,
-                                             toff[buf], rpre, out_ids, cap, chunks == 1);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    {
-      ProfScope ps("query_offsets", s);
-      query_offsets<<<fill_blocks(m + 1), 256, 0, s>>>(qs.row_off, qs.ss, m, total_dev, rbase,
-                                                        rbase + nt * kCompactTileRows, row_end,
-                                                        rpre, offsets);
+      const uint32_t extra = ordered ? 0 : fill_blocks(m + 1);
+#define SFC_WRITE(O, F)                                                                      \
+  compact_write_out<O, F><<<grid + extra, 256, 0, s>>>(                                       \
+      P.ids, c.meta, qs.row_off, m, rbase, rend, row_end, flag, c.masks, c.unit_pre,  \
+      c.unit_hits, unit_off, qs.out_base, grid, P.out_ids, P.cap, chunks == 1, P.offsets,     \
+      qs.status, P.host, P.flags_out)
+      if (ordered) SFC_WRITE(true, false);
+      else if (fused_units) SFC_WRITE(false, true);
+      else SFC_WRITE(false, false);
+#undef SFC_WRITE
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // The chunk's total, read by the next chunk's scan.  A chunk has tiles
     // only when every chunk before it was full, so this slot is always
     // written when it is consumed.
-    carry = toff[buf] + nt;
+    carry = unit_off + nt * kTileUnits;
   }
   return hipSuccess;
 }

@@ -167,6 +167,33 @@ __global__ __launch_bounds__(kScanThreads) void scan_dev_blocks(const uint32_t* 
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[count] = partial[gridDim.x];
 }
 
+// One workgroup scans all: for up to kScanOne elements (the count in device
+// memory, or given) one launch of a few rounds is shorter than three.
+constexpr uint64_t kScanOne = 1u << 15;
+
+__global__ __launch_bounds__(1024) void scan_one(const uint32_t* __restrict__ in, uint64_t count,
+                                                 const uint32_t* __restrict__ count_dev,
+                                                 const uint64_t* __restrict__ carry_in,
+                                                 uint64_t* __restrict__ out) {
+  __shared__ uint64_t s_tmp[16];
+  if (count_dev) count = *count_dev;
+  uint64_t carry = carry_in ? carry_in[0] : 0;
+  for (uint64_t b = 0; b < count; b += 1024 * kScanItems) {
+    uint32_t v[kScanItems];
+    const uint64_t f = b + (uint64_t)threadIdx.x * kScanItems;
+    const uint64_t s = load_items(in, count, f, v);
+    uint64_t tot;
+    uint64_t run = carry + block_scan_u64(s, s_tmp, &tot);
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+      if (f + i < count) out[f + i] = run;
+      run += v[i];
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) out[count] = carry;
+}
+
 }  // namespace
 
 uint32_t scan_dev_blocks_for(uint64_t max_count) {
@@ -180,10 +207,18 @@ hipError_t scan_excl_dev(const uint32_t* in, uint64_t* out, const uint32_t* coun
                          hipStream_t s) {
   const uint32_t nb = scan_dev_blocks_for(max_count);
   ProfScope ps("scan", s);
+  if (max_count <= kScanOne) {
+    scan_one<<<1, 1024, 0, s>>>(in, 0, count_dev, carry_in, out);
+    return hipGetLastError();
+  }
   scan_dev_sums<<<nb, kScanThreads, 0, s>>>(in, count_dev, partial);
   scan_partials<<<1, 1024, 0, s>>>(partial, nb, carry_in);
   scan_dev_blocks<<<nb, kScanThreads, 0, s>>>(in, count_dev, partial, out);
   return hipGetLastError();
+}
+
+size_t scan_dev_scratch_bytes(uint64_t max_count) {
+  return align256(((uint64_t)scan_dev_blocks_for(max_count) + 1) * 8);
 }
 
 size_t scan_scratch_bytes(uint64_t count) {
@@ -199,6 +234,10 @@ hipError_t scan_excl(const uint32_t* in, uint64_t* out, uint64_t count, const ui
   }
   const uint64_t nb = (count + kScanBlock - 1) / kScanBlock;
   ProfScope ps("scan", s);
+  if (count <= kScanOne) {
+    scan_one<<<1, 1024, 0, s>>>(in, count, nullptr, carry_in, out);
+    return hipGetLastError();
+  }
   scan_block_sums<<<(uint32_t)nb, kScanThreads, 0, s>>>(in, count, partial);
   scan_partials<<<1, 1024, 0, s>>>(partial, nb, carry_in);
   scan_blocks<<<(uint32_t)nb, kScanThreads, 0, s>>>(in, count, partial, out);

@@ -239,14 +239,6 @@ __global__ __launch_bounds__(kThreads) void iota_u32(uint32_t* __restrict__ out,
   if (j < k) out[j] = first + (uint32_t)j;
 }
 
-__global__ __launch_bounds__(kThreads) void check_epochs(const uint32_t* __restrict__ qe,
-                                                         uint64_t m, uint32_t oldest,
-                                                         uint32_t epoch, uint32_t* err) {
-  const uint64_t j = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
-  const bool bad = j < m && (qe[j] < oldest || qe[j] > epoch);
-  if (__ballot(bad) && __lane_id() == 0) atomicOr(err, kErrInvalidQuery);
-}
-
 uint32_t grid_for(uint64_t count, uint64_t per_block) {
   return (uint32_t)((count + per_block - 1) / per_block);
 }
@@ -322,13 +314,6 @@ hipError_t compact_entries(const Run& stored, uint64_t n, uint32_t oldest, const
 hipError_t fill_iota(uint32_t* out, uint64_t k, uint32_t first, hipStream_t s) {
   if (k == 0) return hipSuccess;
   iota_u32<<<grid_for(k, kThreads), kThreads, 0, s>>>(out, k, first);
-  return hipGetLastError();
-}
-
-hipError_t validate_epochs(const uint32_t* qe, uint64_t m, uint32_t oldest, uint32_t epoch,
-                           uint32_t* err, hipStream_t s) {
-  if (m == 0) return hipSuccess;
-  check_epochs<<<grid_for(m, kThreads), kThreads, 0, s>>>(qe, m, oldest, epoch, err);
   return hipGetLastError();
 }
 

@@ -1,0 +1,139 @@
+"""Batches at the sizes where their processing changes: the fused small batch,
+the search and the rows in curve order, many chunks (rows in query order), more
+rows than a batch is expected to have, the kept batch's write-only retry; every
+result against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2508_19891_amd import sfc, workload
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def dev(a, dtype=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=dtype).to(DEV)
+
+
+def same(got, want):
+    off, ids = got
+    assert torch.equal(off, dev(want[0].view(np.int64), torch.int64))
+    assert torch.equal(ids, dev(want[1].view(np.int32), torch.int32))
+
+
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 1024, 1025, 4097, 65536, 65537])
+@pytest.mark.parametrize("curve,refine", [(sfc.MORTON, False), (sfc.HILBERT, True)])
+def test_batch_sizes(m, curve, refine):
+    wl = workload.clustered_loguniform(n=30_011, m=m, curve=curve, seed=m, c_hi=60.0)
+    idx = sfc.Index(dev(wl.points), curve, refine=refine)
+    want = oracle.query(oracle.build(wl.points, curve), wl.queries, wl.delta, curve, nthreads=8)
+    same(idx.query(dev(wl.queries), dev(wl.delta)), want)
+    idx.close()
+
+
+N, M = (1 << 20) + 3, (1 << 17) + 1   # the least that is processed in curve order
+FORMS = [("hilbert", sfc.BINARY, True, False), ("morton", sfc.BINARY, False, False),
+         ("morton", sfc.LEARNED, True, False), ("hilbert", sfc.BINARY, True, True),
+         ("morton3", sfc.BINARY, False, False), ("morton3", sfc.STREE, True, False)]
+
+
+@pytest.mark.parametrize("many_rows", [False, True])
+@pytest.mark.parametrize("curve,search,refine,early_term", FORMS)
+def test_curve_order(curve, search, refine, early_term, many_rows):
+    """Few rows a query: the search alone in curve order; many: the rows too.
+    Some centres lie outside the domain and on its border."""
+    # (3-D cubes, not refined, hold many more candidates: one chunk of rows.)
+    c = 4.0 if not many_rows else 600.0 if refine or curve != "morton3" else 100.0
+    if curve == "morton3":
+        wl = workload.clustered3(n=N, m=M, seed=7, c_lo=c, c_hi=c)
+        code, built, ask = sfc.MORTON3, oracle.build3(wl.points), oracle.query3
+    else:
+        code = {"hilbert": sfc.HILBERT, "morton": sfc.MORTON}[curve]
+        wl = workload.clustered_loguniform(n=N, m=M, curve=code, seed=7, c_lo=c, c_hi=c)
+        built = oracle.build(wl.points, code)
+
+        def ask(index, q, d, nthreads):
+            return oracle.query(index, q, d, code, nthreads=nthreads)
+    queries = wl.queries.copy()
+    queries[::1000, 0] = -0.01
+    queries[1::1000, 1] = 1.0
+    queries[2::1000, 0] = 1.0 + 1e-9
+    want = ask(built, queries, wl.delta, nthreads=8)
+    idx = sfc.Index(dev(wl.points), code, search=search, refine=refine, early_term=early_term)
+    q, d = dev(queries), dev(wl.delta)
+    same(idx.query(q, d), want)
+    rows, total = idx.last_stats()["rows"], len(want[1])
+    assert (rows > 16 * M) == many_rows
+    # the kept batch, written once its buffer is large enough
+    off = torch.empty(M + 1, dtype=torch.int64, device=DEV)
+    ids = torch.full((total,), -1, dtype=torch.int32, device=DEV)
+    with pytest.raises(sfc.CapacityError):
+        idx.query(q, d, out_ids=ids[:total - 1], out_offsets=off)
+    assert (ids == -1).all()
+    off.fill_(-1)
+    assert idx.query_retry(off, ids) == total
+    same((off, ids), want)
+    # recorded
+    g = sfc.Graph.query(idx, q, d, max_rows=rows + 100, ids_cap=total)
+    for _ in range(3):
+        g.ids.fill_(-1)
+        g.launch()
+        same(g.result(), want)
+        idx.query(q[:100].contiguous(), d[:100].contiguous())
+    g.close()
+    # in many chunks: the rows in query order
+    try:
+        sfc.debug_chunk_tiles(1 << 12)
+        same(idx.query(q, d), want)
+    finally:
+        sfc.debug_chunk_tiles(0)
+    # an invalid query among them
+    bad = d.clone()
+    bad[M // 2] = float("nan")
+    with pytest.raises(sfc.SfcError):
+        idx.query(q, bad)
+    same(idx.query(q, d), want)
+    idx.close()
+
+
+@pytest.mark.parametrize("m", [64, 1500])
+def test_more_rows_than_expected(m):
+    """Every query covers the square: far more rows than a batch of m is
+    sized for, on a fresh handle (compacted again) and on one that has seen
+    such a batch."""
+    n = 200_000 if m == 64 else 40_000
+    pts = workload.uniform_points(n, 3)
+    keys, ids, _ = oracle.build(pts, sfc.MORTON)
+    idx = sfc.Index(dev(pts), sfc.MORTON)
+    q = torch.full((m, 2), 0.5, dtype=torch.float64, device=DEV)
+    d = torch.full((m,), 2.0, dtype=torch.float64, device=DEV)
+    for _ in range(2):
+        off, got = idx.query(q, d)
+        assert np.array_equal(off.cpu().numpy(), np.arange(m + 1, dtype=np.int64) * n)
+        assert np.array_equal(got.cpu().numpy().view(np.uint32).reshape(m, n)[m - 1], ids)
+        assert (got.reshape(m, n) == got[:n]).all()
+    small = idx.query(q[:3].contiguous(), torch.zeros(3, dtype=torch.float64, device=DEV))
+    assert int(small[0][-1]) == 0
+    idx.close()
+
+
+def test_retry_after_capacity():
+    m = 500
+    wl = workload.clustered_loguniform(n=20_000, m=m, curve=0, seed=9, c_hi=40.0)
+    want = oracle.query(oracle.build(wl.points, 0), wl.queries, wl.delta, 0, nthreads=8)
+    total = len(want[1])
+    idx = sfc.Index(dev(wl.points), sfc.MORTON, refine=True)
+    off = torch.empty(m + 1, dtype=torch.int64, device=DEV)
+    small = torch.full((total - 1,), -1, dtype=torch.int32, device=DEV)
+    with pytest.raises(sfc.CapacityError) as err:
+        idx.query(dev(wl.queries), dev(wl.delta), out_ids=small, out_offsets=off)
+    assert err.value.total == total
+    assert (small == -1).all()
+    assert np.array_equal(off.cpu().numpy().view(np.uint64), want[0])
+    off.fill_(-1)
+    ids = torch.empty(total, dtype=torch.int32, device=DEV)
+    assert idx.query_retry(off, ids) == total
+    same((off, ids), want)
+    idx.close()
