@@ -137,9 +137,11 @@ struct QueryScratch {
   BatchStatus* status;
   uint2* slots;            // per query and slot: first sorted index, candidates
   uint64_t* row_off;       // per place: its first row (+ the total at [m])
-  uint64_t* blk_rows;      // per workgroup of places: its rows,
+  uint64_t* blk_rows;      // per workgroup of queries: its rows,
   uint64_t* blk_off;       //   its first row,
   uint64_t* blk_stat;      // per search workgroup: its candidates and flags,
+  uint64_t* blk_rows64;    //   its rows of 64 candidates,
+  uint64_t* blk_place;     //   (queries in curve order) its rows,
   uint32_t* blk_learned;   //   its learned endpoints and fallbacks
   void* rec;               // per query: the test pass's record (32 B)
   uint32_t* perm;          // the queries in curve order

@@ -17,10 +17,10 @@
 //                  counters (small batches: inside expand_rows).
 //   expand_rows    rows -> (slot, first candidate) tiles, and every query's
 //                  first row.
-//   compact_test   a wave tests 16 rows of 64 candidates each with the exact
-//                  distance test: a hit mask per row, the rows' hits before
-//                  it among the 16, and the 16 rows' hits, which are scanned
-//                  on the device.
+//   compact_test   a wave tests 32 rows of 32 candidates each with the exact
+//                  distance test, two rows at a time: a hit mask per row, the
+//                  hits before it among the 32, and the 32 rows' hits, which
+//                  are scanned on the device.
 //   compact_write  the same tiles again: the ids of the hits at the scanned
 //                  positions, in candidate order; and the CSR offset of every
 //                  query, from its first row.
@@ -82,7 +82,7 @@ namespace {
 struct QueryFilter {
   float acc, rej;   // limits on sum e^2 (or per-axis |e|); filter off: acc = not a number
                     // and rej = +inf, so that neither comparison decides a candidate
-  uint32_t c[3];    // the query's cell per axis (low 32 bits), 2^shift quanta wide
+  uint32_t minus[3];   // minus the query's cell per axis (low 32 bits), 2^shift quanta wide
   uint32_t shift;   // cells are compared 2^shift quanta wide
   uint32_t pad[2];
 };
@@ -119,7 +119,7 @@ __device__ __forceinline__ QueryFilter query_filter(const double (&q)[DIM], doub
   for (int a = 0; a < DIM; ++a) {
     const double qs = q[a] * S;
     on = on && qs > -0x1p30 && qs < S + 0x1p30;
-    f.c[a] = (uint32_t)(int64_t)__builtin_floor(on ? __builtin_ldexp(qs, -k) : 0.0);
+    f.minus[a] = 0u - (uint32_t)(int64_t)__builtin_floor(on ? __builtin_ldexp(qs, -k) : 0.0);
   }
   if (window) {
     f.acc = (float)(R * (1.0 - 0x1p-16) - 1.0);
@@ -157,6 +157,15 @@ constexpr int kStatShift = 48;
 constexpr uint64_t kStatInvalid = 1ull << kStatShift;         // an invalid query
 constexpr uint64_t kStatCoarse = 1ull << (kStatShift + 1);    // a radius past the filter limit
 
+// Candidates are processed in rows of 32 (the last of a range partly filled);
+// the batch's row count, which capacities refer to, counts rows of 64, of which
+// a range has at least half as many.
+constexpr int kRowShift = 5;
+__device__ __forceinline__ uint64_t rows_of(uint64_t count) {
+  return (count + (1u << kRowShift) - 1) >> kRowShift;
+}
+__device__ __forceinline__ uint64_t rows64_of(uint64_t count) { return (count + 63) >> 6; }
+
 // One lane per (query, slot): four slots per query (the method's ranges),
 // or eight (REFINE: two runs per cell of cells(Q)); the lane's work is the
 // body in query_lane.inc.  perm non-null: the queries in curve order, so that
@@ -176,7 +185,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     const uint32_t* __restrict__ qset, const uint64_t* __restrict__ set_off, uint32_t n_sets,
     const uint32_t* __restrict__ perm, RecordPlan record, uint2* __restrict__ slots,
     uint64_t* __restrict__ blk_rows, uint64_t* __restrict__ blk_stat,
-    uint32_t* __restrict__ blk_learned, uint64_t* __restrict__ dbg_lo,
+    uint64_t* __restrict__ blk_rows64, uint32_t* __restrict__ blk_learned,
+    uint64_t* __restrict__ dbg_lo,
     uint64_t* __restrict__ dbg_hi, uint64_t* __restrict__ dbg_b, uint64_t* __restrict__ dbg_e,
     uint32_t* __restrict__ dbg_nr) {
   constexpr bool LEARNED = SEARCH == 1;
@@ -185,6 +195,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   if (pairs && (uint64_t)blockIdx.x * 256 >= *pair_total) {
     if (threadIdx.x == 0) {
       blk_stat[blockIdx.x] = 0;
+      blk_rows64[blockIdx.x] = 0;
       if (LEARNED) blk_learned[blockIdx.x] = 0;
     }
     return;
@@ -233,10 +244,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   (void)pruned;   // counted where the work list is made
   // Candidates, rows, flags (and learned-index endpoints and fallbacks) of
   // the workgroup.
-  __shared__ uint64_t s_cand[4], s_rows[4];
+  __shared__ uint64_t s_cand[4], s_rows[4], s_rows64[4];
   __shared__ uint32_t s_learned[4];
-  const uint32_t r0 = (uint32_t)((e0 - b0 + 63) >> 6), r1 = (uint32_t)((e1 - b1 + 63) >> 6);
-  uint64_t wc = (e0 - b0) + (e1 - b1), wr = (uint64_t)r0 + r1;
+  uint64_t wc = (e0 - b0) + (e1 - b1), wr = rows_of(e0 - b0) + rows_of(e1 - b1);
+  uint64_t wr64 = rows64_of(e0 - b0) + rows64_of(e1 - b1);
   uint32_t wl = (ends << 16) | fb;
   const uint64_t flags = (__ballot(bad) != 0 ? kStatInvalid : 0) |
                          (__ballot(coarse) != 0 ? kStatCoarse : 0);
@@ -244,12 +255,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   for (int o = 32; o >= 1; o >>= 1) {
     wc += __shfl_xor(wc, o, 64);
     wr += __shfl_xor(wr, o, 64);
+    wr64 += __shfl_xor(wr64, o, 64);
     if (LEARNED) wl += __shfl_xor(wl, o, 64);
   }
   const uint32_t wv = threadIdx.x >> 6;
   if (lane_id() == 0) {
     s_cand[wv] = wc | flags;
     s_rows[wv] = wr;
+    s_rows64[wv] = wr64;
     if (LEARNED) s_learned[wv] = wl;
   }
   __syncthreads();
@@ -260,7 +273,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
       f |= s_cand[w] & ~(kStatInvalid - 1);
     }
     blk_stat[blockIdx.x] = c | f;
-    if (!pairs && !perm) blk_rows[blockIdx.x] = s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3];
+    blk_rows64[blockIdx.x] = s_rows64[0] + s_rows64[1] + s_rows64[2] + s_rows64[3];
+    if (!pairs) blk_rows[blockIdx.x] = s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3];
     if (LEARNED)
       blk_learned[blockIdx.x] = s_learned[0] + s_learned[1] + s_learned[2] + s_learned[3];
   }
@@ -453,7 +467,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     const uint64_t* __restrict__ keys, uint64_t n, LearnedView lv, StreeView sv,
     uint32_t refine_min, const uint32_t* __restrict__ perm, RecordPlan record,
     uint2* __restrict__ slots, uint64_t* __restrict__ blk_rows,
-    uint64_t* __restrict__ blk_stat) {
+    uint64_t* __restrict__ blk_stat, uint64_t* __restrict__ blk_rows64) {
   const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   const uint64_t j = (g >> 3) < m ? (perm ? perm[g >> 3] : g >> 3) : m;
   const int r = (int)(g & 7);
@@ -549,12 +563,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     }
   }
   // Candidates, rows and flags of the workgroup (32 queries).
-  __shared__ uint64_t s_cand[4], s_rows[4];
-  uint64_t wc = 0, wr = 0;
+  __shared__ uint64_t s_cand[4], s_rows[4], s_rows64[4];
+  uint64_t wc = 0, wr = 0, wr64 = 0;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     wc += E[t] - B[t];
-    wr += (E[t] - B[t] + 63) >> 6;
+    wr += rows_of(E[t] - B[t]);
+    wr64 += rows64_of(E[t] - B[t]);
   }
   const uint64_t flags = (__ballot(bad) != 0 ? kStatInvalid : 0) |
                          (__ballot(coarse) != 0 ? kStatCoarse : 0);
@@ -562,10 +577,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   for (int o = 32; o >= 1; o >>= 1) {
     wc += __shfl_xor(wc, o, 64);
     wr += __shfl_xor(wr, o, 64);
+    wr64 += __shfl_xor(wr64, o, 64);
   }
   if (lane_id() == 0) {
     s_cand[threadIdx.x >> 6] = wc | flags;
     s_rows[threadIdx.x >> 6] = wr;
+    s_rows64[threadIdx.x >> 6] = wr64;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -575,7 +592,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
       f |= s_cand[w] & ~(kStatInvalid - 1);
     }
     blk_stat[blockIdx.x] = c | f;
-    if (!perm) blk_rows[blockIdx.x] = s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3];
+    blk_rows64[blockIdx.x] = s_rows64[0] + s_rows64[1] + s_rows64[2] + s_rows64[3];
+    blk_rows[blockIdx.x] = s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3];
   }
   if (j < m) {
     const uint64_t sidx = 8 * j + r;
@@ -711,27 +729,24 @@ __global__ __launch_bounds__(256) void pack_move(const uint64_t* __restrict__ pa
     pairs_out[at + i] = pairs_in[(uint64_t)blockIdx.x * 1024 + i];
 }
 
-// The candidates are laid out in rows of 64: each query slot (segment) s
+// The candidates are laid out in rows of 32: each query slot (segment) s
 // owns rows [row_off[s], row_off[s+1]), row k of s holding its candidates
-// 64k .. 64k+63 (the last row partly filled).  So every row belongs to one
-// slot and one query, found by a scalar walk, and the query's data are
-// wave-uniform.  A tile is 64 consecutive rows: four waves of kIters x kRows.
-constexpr int kRows = 8;                                  // rows per iteration
-constexpr int kIters = 2;                                 // iterations per wave
-constexpr int kTileRows = 4 * kRows * kIters;             // 64 rows per tile
-constexpr uint64_t kWaveRows = (uint64_t)kRows * kIters;  // rows per wave
-static_assert(kCompactTileRows == (uint64_t)kTileRows, "tile shape");
-// A wave's 16 rows: the unit whose hits are scanned.  Row r's hits come after
-// unit_off[r / 16] + unit_pre[r] others.
+// 32k .. 32k+31 (the last row partly filled).  So every row belongs to one slot
+// and one query.  A wave takes two rows at a time (short ranges are the rule:
+// 19 candidates a range for 10 reports aimed at, so that a row of 64 would leave
+// two lanes of three idle), 32 rows in all, its unit; a tile is four waves' rows.
+constexpr uint32_t kUnitRows = 32;
+constexpr int kUnitShift = 5;
+constexpr int kUnitSteps = 16;                         // pairs of rows
 constexpr uint32_t kTileUnits = 4;
-constexpr int kUnitShift = 4;
-static_assert(kWaveRows == 1u << kUnitShift, "a unit is a wave's rows");
+constexpr uint64_t kTileRows = kTileUnits * kUnitRows; // rows of 32
+static_assert(kTileRows == 2 * kCompactTileRows, "a tile holds 64 rows of 64 candidates");
 
 // Tiles of a chunk's rows [rbase, row_end); none when the batch has more rows
-// than a capacity (only_whole): it is compacted again, or reported.
+// than a capacity (over): it is compacted again, or reported.
 __device__ __forceinline__ uint64_t chunk_tiles(uint64_t total_all, uint64_t rbase,
-                                                uint64_t row_end, bool only_whole) {
-  if (only_whole && total_all > row_end) return 0;
+                                                uint64_t row_end, bool over) {
+  if (over) return 0;
   const uint64_t total = total_all < row_end ? total_all : row_end;
   return total > rbase ? (total - rbase + kTileRows - 1) / kTileRows : 0;
 }
@@ -748,12 +763,13 @@ __device__ __forceinline__ uint64_t xcd_tile(uint64_t b, uint64_t grid, uint64_t
   return k < per && t < ntiles ? t : ~0ull;
 }
 
-// The batch's counters, from those of the workgroups: stat (ns words:
-// candidates and flags), learned (ns words or null: endpoints << 16 |
+// The batch's counters, from those of the workgroups: stat and rows64 (ns words
+// each: candidates and flags; rows of 64), learned (ns words or null: endpoints << 16 |
 // fallbacks), and with early termination flags and pruned (np words each, or
 // null).  Every thread of the workgroup calls it; thread 0 holds the result.
 struct BatchStats {
   const uint64_t* stat;
+  const uint64_t* rows64;
   const uint32_t* learned;
   uint32_t ns;
   const uint64_t* flags;
@@ -762,54 +778,56 @@ struct BatchStats {
 };
 
 template <int WAVES>
-__device__ __forceinline__ void sum_stats(const BatchStats& B, uint64_t rows,
-                                          BatchStatus* status, BatchStatus* host) {
-  __shared__ uint64_t s_v[5][WAVES];
-  uint64_t v[5] = {0, 0, 0, 0, 0};   // candidates, endpoints, fallbacks, pruned, flags
+__device__ __forceinline__ void sum_stats(const BatchStats& B, BatchStatus* status,
+                                          BatchStatus* host) {
+  __shared__ uint64_t s_v[6][WAVES];
+  uint64_t v[6] = {0, 0, 0, 0, 0, 0};   // candidates, endpoints, fallbacks, pruned, rows, flags
   // Eight words in flight per thread: those past the end load the last one
   // and are not added.
   for (uint32_t i0 = threadIdx.x; i0 < B.ns; i0 += WAVES * 64 * 8) {
-    uint64_t w[8];
+    uint64_t w[8], rw[8];
     uint32_t l[8];
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) {
       const uint32_t i = i0 + k * WAVES * 64, ic = i < B.ns ? i : B.ns - 1;
       w[k] = B.stat[ic];
+      rw[k] = B.rows64[ic];
       l[k] = B.learned ? B.learned[ic] : 0u;
     }
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k)
       if (i0 + k * WAVES * 64 < B.ns) {
         v[0] += w[k] & (kStatInvalid - 1);
-        v[4] |= w[k] >> kStatShift;
+        v[5] |= w[k] >> kStatShift;
+        v[4] += rw[k];
         v[1] += l[k] >> 16;
         v[2] += l[k] & 0xFFFFu;
       }
   }
   for (uint32_t i = threadIdx.x; i < B.np; i += WAVES * 64) {
     v[3] += B.pruned[i];
-    v[4] |= B.flags[i] >> kStatShift;
+    v[5] |= B.flags[i] >> kStatShift;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] += __shfl_xor(v[k], o, 64);
-    v[4] |= __shfl_xor(v[4], o, 64);
+    for (int k = 0; k < 5; ++k) v[k] += __shfl_xor(v[k], o, 64);
+    v[5] |= __shfl_xor(v[5], o, 64);
   }
   if (lane_id() == 0)
 #pragma unroll
-    for (int k = 0; k < 5; ++k) s_v[k][threadIdx.x >> 6] = v[k];
+    for (int k = 0; k < 6; ++k) s_v[k][threadIdx.x >> 6] = v[k];
   __syncthreads();
   if (threadIdx.x == 0) {
     BatchStatus st{};
-    st.rows = rows;
     for (int w = 0; w < WAVES; ++w) {
       st.candidates += s_v[0][w];
       st.endpoints += s_v[1][w];
       st.fallbacks += s_v[2][w];
       st.pruned += s_v[3][w];
-      if (s_v[4][w] & 1) st.err |= kErrInvalidQuery;
-      if (s_v[4][w] & 2) st.coarse = 1;
+      st.rows += s_v[4][w];
+      if (s_v[5][w] & 1) st.err |= kErrInvalidQuery;
+      if (s_v[5][w] & 2) st.coarse = 1;
     }
     *status = st;
     if (host) *host = st;
@@ -818,7 +836,7 @@ __device__ __forceinline__ void sum_stats(const BatchStats& B, uint64_t rows,
 
 // One workgroup: the exclusive scan of the workgroups' rows (blk_off, the
 // total in *rows_out), and the batch's counters in *status (and *host, host
-// memory, if not null); stats false: the counters stay, but for the rows.
+// memory, if not null); stats false: the counters stay.
 __global__ __launch_bounds__(1024) void batch_scan(const uint64_t* __restrict__ blk_rows,
                                                    uint32_t nblk, uint64_t* __restrict__ blk_off,
                                                    uint64_t* __restrict__ rows_out,
@@ -862,10 +880,7 @@ __global__ __launch_bounds__(1024) void batch_scan(const uint64_t* __restrict__ 
     __syncthreads();
   }
   if (tid == 0) *rows_out = carry;
-  if (stats)
-    sum_stats<16>(B, carry, status, host);
-  else if (tid == 0)
-    status->rows = carry;
+  if (stats) sum_stats<16>(B, status, host);
 }
 
 // The K consecutive slots from `first` on, in the order of the places (perm:
@@ -892,8 +907,6 @@ __device__ __forceinline__ void load_slots(const uint2* __restrict__ slots,
     for (int i = 0; i < K; ++i) v[i] = make_uint2(0, 0);
   }
 }
-
-__device__ __forceinline__ uint64_t rows_of(uint32_t count) { return ((uint64_t)count + 63) >> 6; }
 
 // Exclusive scan of one uint64 per thread over 256 threads; *total gets the
 // sum.
@@ -930,9 +943,9 @@ __global__ __launch_bounds__(256) void slot_rows(const uint2* __restrict__ slots
   if (threadIdx.x == 0) blk_rows[blockIdx.x] = total;
 }
 
-// Row descriptors of a launch's rows [rbase, rend): for row r of slot s,
-// (first sorted index of the row, number of valid lanes, the query), and the
-// first row of every place (row_off).  One block per K * 256 slots (whole
+// Row descriptors of a launch's rows [rbase, rend): for row r of slot s, the
+// first sorted index of the row and the query (row_meta) and the number of its
+// candidates (row_info), and the first row of every place (row_off).  One block per K * 256 slots (whole
 // queries: 2^ss slots each), a thread's K slots consecutive; the block's
 // rows are spread over its threads and each finds its slot by a binary search
 // in LDS.  FUSED (at most kFusedBlocks blocks): the block sums the rows of the
@@ -945,10 +958,12 @@ template <int K, bool FUSED>
 __global__ __launch_bounds__(256) void expand_rows(
     uint64_t* __restrict__ row_off, const uint2* __restrict__ slots,
     const uint32_t* __restrict__ perm, const uint64_t* __restrict__ blk_rows, const uint64_t* __restrict__ blk_off, BatchStats B,
-    BatchStatus* status, uint64_t m, int ss, uint64_t rbase, uint64_t row_end, bool flag_overflow,
-    uint4* __restrict__ row_meta) {
+    BatchStatus* status, uint64_t m, int ss, uint64_t rbase, uint64_t row_end, uint64_t max_rows64,
+    uint2* __restrict__ row_meta, uint16_t* __restrict__ row_info) {
   __shared__ uint64_t st[256 * K + 1];
   __shared__ uint2 s_slot[256 * K];
+  __shared__ uint16_t s_mark[4][kWave];
+  __shared__ uint32_t s_query[64];   // of the block's places (at most 64)
   __shared__ uint64_t s_w[4];
   const uint64_t nseg = m << ss;
   const uint32_t tid = threadIdx.x;
@@ -963,21 +978,22 @@ __global__ __launch_bounds__(256) void expand_rows(
     scan256_u64(before, s_w, &row0);
     scan256_u64(all, s_w, &total);
     if (blockIdx.x == 0) {
-      sum_stats<4>(B, total, status, nullptr);
+      sum_stats<4>(B, status, nullptr);
       if (tid == 0) {
         row_off[m] = total;
-        if (flag_overflow && total > row_end) status->err |= kErrOverflow;
+        if (status->rows > max_rows64) status->err |= kErrOverflow;
       }
     }
   } else {
     row0 = blk_off[blockIdx.x];
     total = row_off[m];
-    if (blockIdx.x == 0 && tid == 0 && flag_overflow && total > row_end)
-      status->err |= kErrOverflow;
+    if (blockIdx.x == 0 && tid == 0 && status->rows > max_rows64) status->err |= kErrOverflow;
   }
   const uint64_t rend = total < row_end ? total : row_end;
   const uint64_t s0 = (uint64_t)blockIdx.x * 256 * K;
   const uint64_t first = s0 + (uint64_t)tid * K;
+  const uint64_t place = (s0 >> ss) + tid;   // s0 is a multiple of 2^ss
+  if (tid < ((256u * K) >> ss) && place < m) s_query[tid] = perm ? perm[place] : (uint32_t)place;
   uint2 v[K];
   load_slots<K>(slots, perm, ss, first, nseg, v);
   uint64_t mine = 0, here;
@@ -995,25 +1011,48 @@ __global__ __launch_bounds__(256) void expand_rows(
   __syncthreads();
   const uint64_t r0 = st[0] > rbase ? st[0] : rbase;
   const uint64_t r1 = st[256 * K] < rend ? st[256 * K] : rend;
-  for (uint64_t r = r0 + tid; r < r1; r += 256) {
-    uint32_t lo = 0, len = 256 * K;   // largest k with st[k] <= r
-    while (len > 0) {
-      const uint32_t h = len >> 1;
-      if (st[lo + h] <= r) {
-        lo += h + 1;
-        len -= h + 1;
-      } else {
-        len = h;
+  if (r1 <= r0) return;
+  // Each wave takes a quarter of the rows, 64 at a time (by slots, with fewer
+  // steps before the first row, one wave often has most of the rows).
+  const uint32_t lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t per = ((r1 - r0 + 255) >> 8) << 6;
+  const uint64_t first_row = r0 + wv * per;
+  const uint64_t last_row = first_row + per < r1 ? first_row + per : r1;
+  if (first_row >= last_row) return;   // the whole wave; no barrier follows
+  // The last slot that starts at or before the first row.
+  uint32_t k0 = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < 4 * K; ++i)
+    k0 += (uint32_t)__popcll(__ballot(st[i * kWave + lane] <= first_row));
+  k0 -= 1;
+  uint16_t* mark = s_mark[wv];
+  for (uint64_t base = first_row; base < last_row; base += kWave) {
+    // The slots that start in these rows leave their number at their first row;
+    // a row's slot is that of the last such row up to it, or the first row's.
+    mark[lane] = 0xFFFFu;
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t k = k0 + 1; k < 256 * K && st[k] < base + kWave; k += kWave) {
+      const uint32_t mine = k + lane;
+      if (mine < 256 * K && s_slot[mine].y != 0) {
+        const uint64_t at = st[mine] - base;   // (a slot before the base wraps)
+        if (at < kWave) mark[at] = (uint16_t)mine;
       }
     }
-    const uint32_t k = lo - 1;
-    const uint64_t local = (r - st[k]) * kWave;
-    const uint2 sl = s_slot[k];
-    const uint64_t left = sl.y - local;
-    row_meta[r - rbase] = make_uint4((uint32_t)(sl.x + local),
-                                     (uint32_t)(left < (uint64_t)kWave ? left : (uint64_t)kWave),
-                                     perm ? perm[(s0 + k) >> ss] : (uint32_t)((s0 + k) >> ss),
-                                     0u);
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t own = mark[lane];
+    const uint64_t starts = __ballot(own != 0xFFFFu) & (~0ull >> (63 - lane));
+    const uint32_t k = starts ? mark[63 - __clzll(starts)] : k0;
+    __builtin_amdgcn_wave_barrier();
+    const uint64_t r = base + lane;
+    if (r < last_row) {
+      const uint64_t local = (r - st[k]) << kRowShift;
+      const uint2 sl = s_slot[k];
+      const uint64_t left = sl.y - local;
+      row_meta[r - rbase] = make_uint2((uint32_t)(sl.x + local),
+                                       s_query[k >> ss]);
+      row_info[r - rbase] = (uint16_t)(left < 32 ? left : 32);
+    }
+    k0 = __builtin_amdgcn_readlane(k, 63);
   }
 }
 
@@ -1029,7 +1068,7 @@ __device__ __forceinline__ float cell_distance(uint64_t cell, const QueryFilter&
   for (int a = 0; a < DIM; ++a) {
     uint32_t u = (uint32_t)((cell >> (B * a)) & mask);
     if (SHIFTED) u >>= f.shift;
-    e[a] = (float)(int32_t)(u - f.c[a]);
+    e[a] = (float)(int32_t)(u + f.minus[a]);
   }
   if (WINDOW) {
     float v = fabsf(e[0]);
@@ -1070,16 +1109,16 @@ __device__ __forceinline__ bool lane_of(uint64_t mask) {
   return __builtin_amdgcn_inverse_ballot_w64(mask);
 }
 
-// Lane R's words of (lo, hi) replaced by those of v (the same in every lane).
-// A vector instruction may read a scalar that another wrote (the compares that
-// made v) only two wait states later, which the compiler does not see to in
-// inline assembly: hence the s_nop.
+// Lane R's word replaced by v's low word and lane R + 32's by its high one (v the
+// same in every lane).  A vector instruction may read a scalar that another
+// wrote (the compares that made v) only two wait states later, which the
+// compiler does not see to in inline assembly: hence the s_nop.
 template <int R>
-__device__ __forceinline__ void write_lane64(uint64_t v, uint32_t& lo, uint32_t& hi) {
-  asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
-      : "+v"(lo), "+v"(hi)
+__device__ __forceinline__ void write_pair(uint64_t v, uint32_t& w) {
+  asm("s_nop 1\n\tv_writelane_b32 %0, %1, %3\n\tv_writelane_b32 %0, %2, %4"
+      : "+v"(w)
       : "s"(__builtin_amdgcn_readfirstlane((uint32_t)v)),
-        "s"(__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32))), "n"(R));
+        "s"(__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32))), "n"(R), "n"(R + 32));
 }
 
 // f(0), f(1), ..., f(N - 1) with the index a constant of its type.
@@ -1103,73 +1142,96 @@ template <int R>
 __device__ __forceinline__ uint32_t read_lane(uint32_t v) {
   return __builtin_amdgcn_readlane(v, R);
 }
-template <int R>
-__device__ __forceinline__ uint64_t read_lane64(uint64_t v) {
-  return (uint64_t)read_lane<R>((uint32_t)(v >> 32)) << 32 | read_lane<R>((uint32_t)v);
+
+// In every row of 16 lanes, the word of its lane T: a lane permutation that the
+// compiler may make an operand modifier of the instruction using the word.
+// Measured: in the instructions with reversed operands (v_subrev, v_lshrrev) the
+// hardware then permutes the other operand.  So bcast16_operand is for operands
+// of additions, minima and the like alone; bcast16 keeps the word in a register
+// of its own.
+template <int T>
+__device__ __forceinline__ uint32_t bcast16_operand(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + T, 0xF, 0xF, true);
+}
+template <int T>
+__device__ __forceinline__ uint32_t bcast16(uint32_t v) {
+  uint32_t x = bcast16_operand<T>(v);
+  asm("" : "+v"(x));
+  return x;
+}
+template <int T>
+__device__ __forceinline__ uint64_t bcast16(uint64_t v) {
+  return (uint64_t)bcast16<T>((uint32_t)(v >> 32)) << 32 | bcast16<T>((uint32_t)v);
+}
+// Every lane's word plus those of the lanes below it in its row of 16.
+__device__ __forceinline__ uint32_t scan16(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // 1 lane up
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);   // 2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);   // 4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);   // 8
+  return v;
 }
 
-// The value `offset` bytes past an address in device memory that is the same in
-// every lane (a global access at a scalar base plus a 32-bit lane offset).
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-template <typename T>
-__device__ __forceinline__ T global_at(uint64_t base, uint32_t offset) {
-  typedef const __attribute__((address_space(1))) char* Bytes;
-  typedef const __attribute__((address_space(1))) T* Ptr;
-  return *(Ptr)((Bytes)base + offset);
+// Rows of a wave's unit: step t takes rows 2t (lanes 0..31) and 2t + 1, and
+// lane l holds what belongs to row 2 (l % 16) + l / 32 (lanes with bit 4 set
+// what those 16 below hold), so that in step t bcast16<t> gives each lane what
+// belongs to its row.
+__device__ __forceinline__ uint32_t unit_row(uint32_t lane) {
+  return 2 * (lane & 15) + (lane >> 5);
 }
+
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // Rows of a wave's unit that exist (row0: its first row within the chunk of
 // `have` rows).
 __device__ __forceinline__ uint32_t unit_rows(uint64_t have, uint64_t row0) {
-  return have <= row0 ? 0u : (uint32_t)(have - row0 < kWaveRows ? have - row0 : kWaveRows);
+  return have <= row0 ? 0u : (uint32_t)(have - row0 < kUnitRows ? have - row0 : kUnitRows);
 }
 
-// Pass 1: the exact test of every candidate; per row the 64-bit mask of the
-// accepted lanes and the number of accepted ones in the unit's rows before it,
-// per unit (a wave's 16 rows) their number.  A wave writes its masks, prefixes
-// and count with one store each (lane j: row j), so that the waves of a
-// workgroup never wait for each other and nothing is cleared beforehand.
-// EPOCH: a candidate that passes the test also has to be visible at the
-// query's epoch (ins <= e < era); only those lanes read the epochs.
+// Pass 1: the exact test of every candidate; per row the 32-bit mask of the
+// accepted ones (masks) and the number of accepted ones in the unit's rows before
+// it (row_info, which held the row's candidates), per unit (a wave's 32 rows) their
+// number.  A wave writes its masks, prefixes and count with one store each, so
+// that the waves of a workgroup never wait for each other and nothing is cleared
+// beforehand.  EPOCH: a candidate that passes the test also has to be visible at
+// the query's epoch (ins <= e < era); only those lanes read the epochs.
 // window: the square-window test instead of the Euclidean one.
 //
-// The pass is bound by the instructions of a row (a vector one for 64 lanes and
-// a scalar one both take an issue slot in four cycles) and by the latency of its
-// chain of loads (descriptor, record, candidates).  So lane j holds row j's
-// descriptor and record, loaded for all 16 rows at once and one unit ahead; what
-// can be computed for the rows in their lanes is (their addresses, their valid
-// lanes), and a row's words are read from there as scalars; its candidates are
-// read at a scalar base plus the lane's offset, ROWS rows at a time, a group's
-// loads leaving before the previous group is tested; the two verdicts are masks
-// straight from the compares.  21 vector instructions a row, the vector units
-// four fifths busy: 0.282 ms for the 6.6 * 10^6 rows of 2 * 10^5 windows (0.450
-// with a workgroup's barriers, a descriptor and a record read row by row and
-// rows in query order), 0.47 ms for 8 * 10^6 rows in query order (0.50).
-template <int ROWS, int ITERS, bool EPOCH, int DIM, bool CELLS, bool WINDOW, bool SHIFTS>
+// The pass is bound by the vector instructions of a step (two rows) and by the
+// latency of its chain of loads (descriptor, record, candidates).  So the lanes
+// hold the 32 rows' descriptors and records, loaded for all rows at once and one
+// unit ahead, and a step's lanes get their row's words by a broadcast in each row
+// of 16 lanes, an operand modifier of the instruction that uses the word; STEPS
+// steps' candidates are read at a time, a group's loads leaving before the
+// previous group is tested; the two verdicts are masks straight from the compares.
+// Measured (rows of 64, one at a time, before): 0.302 ms for the 4 * 10^8
+// candidates of 2 * 10^5 windows in curve order (0.282), the caches' 12 TB/s its
+// limit; 0.32 ms for 3.7 * 10^8 of 2^20 queries over 2^24 points (0.365); 0.508
+// ms for 2.4 * 10^8 of 2^22 queries in no order, 19 a range (0.677), memory's
+// 6.5 TB/s.
+template <int STEPS, int ITERS, bool EPOCH, int DIM, bool CELLS, bool WINDOW, bool SHIFTS>
 __global__ __launch_bounds__(256) void compact_test(
     const double* __restrict__ q, const double* __restrict__ delta, uint64_t m,
     const double* __restrict__ pts, const uint32_t* __restrict__ via,
     const uint64_t* __restrict__ cells, const void* __restrict__ rec,
-    const uint4* __restrict__ row_meta, const uint64_t* __restrict__ total_rows_dev,
-    uint64_t rbase, uint64_t row_end, bool only_whole, uint64_t* __restrict__ masks,
-    uint16_t* __restrict__ unit_pre, uint32_t* __restrict__ unit_hits, BatchStatus* status,
+    const uint2* __restrict__ row_meta, const uint64_t* __restrict__ total_rows_dev,
+    uint64_t rbase, uint64_t row_end, uint64_t max_rows64, uint32_t* __restrict__ masks,
+    uint16_t* __restrict__ row_info, uint32_t* __restrict__ unit_hits, BatchStatus* status,
     const uint32_t* __restrict__ ins, const uint32_t* __restrict__ era) {
-  static_assert(ROWS * ITERS == (int)kWaveRows, "a wave's groups cover its rows");
+  static_assert(STEPS * ITERS == kUnitSteps, "a wave's groups cover its rows");
   static_assert(!(EPOCH && CELLS), "an index with epochs keeps no cells");
-  const uint32_t lane = lane_id();
+  const uint32_t lane = lane_id(), row = unit_row(lane), lane32 = lane & 31;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  constexpr uint32_t kEntry = CELLS ? 8 : 8 * DIM;   // bytes per candidate
-  const uint32_t offset = kEntry * lane;
   // SHIFTS: the batch may hold queries with coarser cells
   const bool any_shifted = SHIFTS && CELLS && status->coarse != 0u;
   const uint64_t total_all = *total_rows_dev;
   const uint64_t total_rows = total_all < row_end ? total_all : row_end;
-  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, only_whole);
+  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, status->rows > max_rows64);
   const uint64_t have = total_rows - rbase;
-  // Lane j of a unit: row j's descriptor (rows past the last: candidate 0 of
-  // query 0, whose result is dropped), then the record of its query.  A record
-  // is four or eight words; the plane's cell filter needs the first four, and
-  // its shift (the sixth) only in a batch with coarser cells.
+  // What belongs to a lane's row: its descriptor (rows past the last: candidate 0
+  // of query 0, whose result is dropped), then the record of its query.  A
+  // record is four or eight words; the plane's cell filter needs the first four,
+  // and its shift (the sixth) only in a batch with coarser cells.
   constexpr int kRecWords = CELLS && DIM == 2 && !SHIFTS ? 4 : 8;
   // (Loaded words are kept as they come: arithmetic on them here would wait for
   // them here.)
@@ -1180,25 +1242,23 @@ __global__ __launch_bounds__(256) void compact_test(
   auto fetch_rows = [&](uint64_t tile, Unit& u) {
     u.pb = u.at = 0;
     u.nv = 1;
-    const uint64_t row0 = tile * kTileRows + (uint64_t)w * kWaveRows;
-    if (tile != ~0ull && lane < unit_rows(have, row0)) {
-      const uint4 md = row_meta[row0 + lane];
+    const uint64_t row0 = tile * kTileRows + (uint64_t)w * kUnitRows;
+    if (tile != ~0ull && row < unit_rows(have, row0)) {
+      const uint2 md = row_meta[row0 + row];
       u.pb = md.x;
-      u.nv = md.y;
-      u.at = md.z;
+      u.at = md.y;
+      u.nv = row_info[row0 + row];
     }
   };
   auto fetch_rec = [&](Unit& u) {
-    if (lane < (uint32_t)kWaveRows) {
-      const uint4* r = (const uint4*)rec + 2 * (uint64_t)u.at;
+    const uint4* r = (const uint4*)rec + 2 * (uint64_t)u.at;
 #pragma unroll
-      for (int i = 0; i < kRecWords; i += 4) {
-        const uint4 v = r[i / 4];
-        u.rec[i] = v.x;
-        u.rec[i + 1] = v.y;
-        u.rec[i + 2] = v.z;
-        u.rec[i + 3] = v.w;
-      }
+    for (int i = 0; i < kRecWords; i += 4) {
+      const uint4 v = r[i / 4];
+      u.rec[i] = v.x;
+      u.rec[i + 1] = v.y;
+      u.rec[i + 2] = v.z;
+      u.rec[i + 3] = v.w;
     }
   };
   uint64_t tile = xcd_tile(blockIdx.x, gridDim.x, 0, ntiles);
@@ -1209,119 +1269,116 @@ __global__ __launch_bounds__(256) void compact_test(
     uint64_t next = xcd_tile(blockIdx.x, gridDim.x, 1, ntiles);
     fetch_rows(next, nx);
     for (uint64_t step = 2;; ++step) {
-      const uint64_t row0 = tile * kTileRows + (uint64_t)w * kWaveRows;
+      const uint64_t row0 = tile * kTileRows + (uint64_t)w * kUnitRows;
       const uint64_t after = next == ~0ull ? ~0ull
                                            : xcd_tile(blockIdx.x, gridDim.x, step, ntiles);
       Unit nn;
       fetch_rows(after, nn);
       fetch_rec(nx);   // the next unit's records, its descriptors being here
-      // The rows' first candidates, and the last lanes that have one (the
-      // lanes past it repeat its candidate, and their verdicts are dropped at
-      // the end).
-      const uint32_t ulast = u.nv - 1, uend = kEntry * ulast;
-      const uint64_t ubase = CELLS ? (uint64_t)(cells + u.pb)
-                                   : (uint64_t)(pts + (uint64_t)DIM * u.pb);
-      uint32_t mlo = 0, mhi = 0;   // lane j < 16: the mask of the wave's row j
+      // The last of the row's lanes that has a candidate (the lanes past it
+      // repeat its candidate, and their verdicts are dropped at the end).
+      const uint32_t ulast = u.nv - 1;
+      uint32_t mk = 0;   // the mask of the lane's row (lanes without bit 4)
 
-      // A group's candidates: one load per row (three coordinates: three).
+      // The sorted index of the lane's candidate in step t.
+      auto position = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        const uint32_t last = bcast16_operand<T>(ulast);
+        return bcast16_operand<T>(u.pb) + (lane32 < last ? lane32 : last);
+      };
+      // A group's candidates: one load per step (three coordinates: three).
       struct Group {
-        uint64_t cell[CELLS ? ROWS : 1];
-        f64x2 xy[CELLS ? 1 : ROWS];
-        double z[CELLS || DIM == 2 ? 1 : ROWS];
+        uint64_t cell[CELLS ? STEPS : 1];
+        f64x2 xy[CELLS ? 1 : STEPS];
+        double z[CELLS || DIM == 2 ? 1 : STEPS];
       };
       auto load = [&](auto group, Group& G) {
-        static_for<ROWS>([&](auto row) {
-          constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
-          const uint64_t base = read_lane64<r>(ubase);
-          const uint32_t last = read_lane<r>(uend);
-          const uint32_t o = offset < last ? offset : last;
+        static_for<STEPS>([&](auto i) {
+          constexpr int g = decltype(i)::value, t = decltype(group)::value * STEPS + g;
+          const uint64_t pos = position(std::integral_constant<int, t>{});
           if constexpr (CELLS) {
-            G.cell[jr] = global_at<uint64_t>(base, o);
+            G.cell[g] = cells[pos];
           } else if constexpr (DIM == 2) {
-            G.xy[jr] = global_at<f64x2>(base, o);
+            G.xy[g] = ((const f64x2*)pts)[pos];
           } else {
-            G.xy[jr].x = global_at<double>(base, o);
-            G.xy[jr].y = global_at<double>(base, o + 8);
-            G.z[jr] = global_at<double>(base, o + 16);
+            G.xy[g].x = pts[3 * pos];
+            G.xy[g].y = pts[3 * pos + 1];
+            G.z[g] = pts[3 * pos + 2];
           }
         });
       };
       auto test = [&](auto group, const Group& G) {
-        uint64_t hit[ROWS], und[ROWS], any = 0;
-        static_for<ROWS>([&](auto row) {
-          constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
+        uint64_t hit[STEPS], und[STEPS], any = 0;
+        static_for<STEPS>([&](auto i) {
+          constexpr int g = decltype(i)::value, t = decltype(group)::value * STEPS + g;
           if constexpr (CELLS) {
             // Decide from the cells.
             QueryFilter f;
-            f.acc = __uint_as_float(read_lane<r>(u.rec[0]));
-            f.rej = __uint_as_float(read_lane<r>(u.rec[1]));
-            f.c[0] = read_lane<r>(u.rec[2]);
-            f.c[1] = read_lane<r>(u.rec[3]);
-            f.c[2] = DIM == 3 ? read_lane<r>(u.rec[kRecWords > 4 ? 4 : 0]) : 0u;
+            f.acc = __uint_as_float(bcast16<t>(u.rec[0]));
+            f.rej = __uint_as_float(bcast16<t>(u.rec[1]));
+            f.minus[0] = bcast16_operand<t>(u.rec[2]);
+            f.minus[1] = bcast16_operand<t>(u.rec[3]);
+            f.minus[2] = DIM == 3 ? bcast16_operand<t>(u.rec[kRecWords > 4 ? 4 : 0]) : 0u;
             float v;
             // A batch with coarser cells (radii past the shift limit) takes
             // the shifting check.
             if (SHIFTS && any_shifted) {
-              f.shift = read_lane<r>(u.rec[kRecWords > 4 ? 5 : 0]);
-              v = cell_distance<DIM, WINDOW, true>(G.cell[jr], f);
+              f.shift = bcast16<t>(u.rec[kRecWords > 4 ? 5 : 0]);
+              v = cell_distance<DIM, WINDOW, true>(G.cell[g], f);
             } else {
               f.shift = 0;
-              v = cell_distance<DIM, WINDOW, false>(G.cell[jr], f);
+              v = cell_distance<DIM, WINDOW, false>(G.cell[g], f);
             }
             const uint64_t in = __ballot(v <= f.acc), out = __ballot(v > f.rej);
-            hit[jr] = in;
-            und[jr] = ~(in | out);
-            any |= und[jr];
+            hit[g] = in;
+            und[g] = ~(in | out);
+            any |= und[g];
           } else {
-            auto word = [&](auto i) {
-              constexpr int k = decltype(i)::value;
-              return __longlong_as_double((long long)((uint64_t)read_lane<r>(u.rec[k + 1]) << 32 |
-                                                      read_lane<r>(u.rec[k])));
+            auto word = [&](auto k) {
+              constexpr int c = decltype(k)::value;
+              return __longlong_as_double((long long)((uint64_t)bcast16<t>(u.rec[c + 1]) << 32 |
+                                                      bcast16<t>(u.rec[c])));
             };
             const double qx = word(std::integral_constant<int, 0>{});
             const double qy = word(std::integral_constant<int, 2>{});
             const double third = word(std::integral_constant<int, 4>{});
             bool h;
             if constexpr (DIM == 2) {
-              h = WINDOW ? within_window(G.xy[jr].x, G.xy[jr].y, qx, qy, third)
-                         : within(G.xy[jr].x, G.xy[jr].y, qx, qy, third);
+              h = WINDOW ? within_window(G.xy[g].x, G.xy[g].y, qx, qy, third)
+                         : within(G.xy[g].x, G.xy[g].y, qx, qy, third);
             } else {
               const double d = word(std::integral_constant<int, 6>{});
-              h = WINDOW ? within_window3(G.xy[jr].x, G.xy[jr].y, G.z[jr], qx, qy, third, d)
-                         : within3(G.xy[jr].x, G.xy[jr].y, G.z[jr], qx, qy, third, d);
+              h = WINDOW ? within_window3(G.xy[g].x, G.xy[g].y, G.z[g], qx, qy, third, d)
+                         : within3(G.xy[g].x, G.xy[g].y, G.z[g], qx, qy, third, d);
             }
-            hit[jr] = __ballot(h);
+            hit[g] = __ballot(h);
           }
         });
         if constexpr (CELLS) {
           // The candidates their cells leave undecided (rare) take the exact
           // test, behind one branch for the whole group.
           if (any != 0)
-            static_for<ROWS>([&](auto row) {
-              constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
-              const uint32_t last = read_lane<r>(ulast);
+            static_for<STEPS>([&](auto i) {
+              constexpr int g = decltype(i)::value, t = decltype(group)::value * STEPS + g;
+              const uint32_t pos = position(std::integral_constant<int, t>{});
+              const uint32_t at = bcast16<t>(u.at);
               bool h = false;
-              if (lane_of(und[jr]))
-                h = exact_hit<DIM>(q, delta, pts, via, read_lane<r>(u.at),
-                                   read_lane<r>(u.pb) + (lane < last ? lane : last), WINDOW);
-              hit[jr] |= __ballot(h);
+              if (lane_of(und[g])) h = exact_hit<DIM>(q, delta, pts, via, at, pos, WINDOW);
+              hit[g] |= __ballot(h);
             });
         }
         if constexpr (EPOCH)
-          static_for<ROWS>([&](auto row) {
-            constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
-            const uint32_t last = read_lane<r>(ulast);
+          static_for<STEPS>([&](auto i) {
+            constexpr int g = decltype(i)::value, t = decltype(group)::value * STEPS + g;
+            const uint32_t pos = position(std::integral_constant<int, t>{});
+            const uint32_t qe = bcast16<t>(u.rec[kRecWords > 4 ? 7 : 0]);
             bool h = false;
-            if (lane_of(hit[jr])) {
-              const uint64_t pos = (uint64_t)read_lane<r>(u.pb) + (lane < last ? lane : last);
-              const uint32_t qe = read_lane<r>(u.rec[kRecWords > 4 ? 7 : 0]);
-              h = ins[pos] <= qe && qe < era[pos];
-            }
-            hit[jr] = __ballot(h);
+            if (lane_of(hit[g])) h = ins[pos] <= qe && qe < era[pos];
+            hit[g] = __ballot(h);
           });
-        static_for<ROWS>([&](auto row) {
-          constexpr int jr = decltype(row)::value, r = decltype(group)::value * ROWS + jr;
-          write_lane64<r>(hit[jr], mlo, mhi);
+        static_for<STEPS>([&](auto i) {
+          constexpr int g = decltype(i)::value, t = decltype(group)::value * STEPS + g;
+          write_pair<t>(hit[g], mk);
         });
       };
       Group G[2];
@@ -1329,24 +1386,21 @@ __global__ __launch_bounds__(256) void compact_test(
       static_for<ITERS>([&](auto group) {
         constexpr int g = decltype(group)::value;
         if constexpr (g + 1 < ITERS) load(std::integral_constant<int, g + 1>{}, G[(g + 1) & 1]);
+        // (Every load of the group first: else a wait for one comes before the next.)
+        __builtin_amdgcn_sched_barrier(0);
         test(group, G[g & 1]);
+        __builtin_amdgcn_sched_barrier(0);
       });
 
-      // Lanes 0..15: the rows' valid hits, and the unit's up to the lane's row.
-      const uint64_t mask = lane < unit_rows(have, row0)
-                                ? ((uint64_t)mhi << 32 | mlo) & (~0ull >> (63 - ulast))
-                                : 0;
-      const uint32_t v = (uint32_t)__popcll(mask);
-      uint32_t x = v;
-#pragma unroll
-      for (int o = 1; o < (int)kWaveRows; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= (uint32_t)o) x += y;
-      }
-      if (lane < (uint32_t)kWaveRows) {
-        masks[row0 + lane] = mask;
-        unit_pre[row0 + lane] = (uint16_t)(x - v);
-        if (lane == kWaveRows - 1) unit_hits[tile * kTileUnits + w] = x;
+      // The rows' valid hits, and the unit's before the row: those of the pairs
+      // of rows before, and of the pair's first row before its second.
+      const uint32_t mask = row < unit_rows(have, row0) ? mk & (~0u >> (31 - ulast)) : 0;
+      const uint32_t v = __popc(mask), other = __shfl_xor(v, 32, 64);
+      const uint32_t upto = scan16(v + other);
+      if ((lane & 16) == 0) {
+        masks[row0 + row] = mask;
+        row_info[row0 + row] = (uint16_t)(upto - (lane < 32 ? v + other : v));
+        if (lane == 15) unit_hits[tile * kTileUnits + w] = upto;
       }
       if (next == ~0ull) break;
       u = nx;
@@ -1382,29 +1436,28 @@ __device__ __forceinline__ void units_to_lds(const uint32_t* __restrict__ unit_h
   __syncthreads();
 }
 
-// Pass 2: the ids of the accepted candidates.  A wave takes a unit of 16 rows:
-// the lanes of a row's mask read their ids and write them one after another
-// from the row's place in the output.  ORDERED (rows in curve order): that is
-// the query's output offset plus the query's hits before the row,
-// out_base[query] + P(row) with P(row) the hits of all rows before it; else
-// rows follow the output, P(row) is the place, and the workgroups past
+// Pass 2: the ids of the accepted candidates.  A wave takes a unit of 32 rows, two
+// at a time as in the test pass: the lanes of a row's mask read their ids and write
+// them one after another from the row's place in the output.  ORDERED (rows in
+// curve order): that is the query's output offset plus the query's hits before
+// the row, out_base[query] + P(row) with P(row) the hits of all rows before it;
+// else rows follow the output, P(row) is the place, and the workgroups past
 // `tile_grid` write the queries' CSR offsets, P of each query's first row.
 // FUSED (at most kFusedUnits units): every workgroup scans the units' hits
 // itself, so that a small batch takes no scan launch.  The batch's final
 // counters go to *host (host memory) and its error bits to *flags_out, if not
-// null.  As in the test pass a row's mask, first position and place are scalar;
-// the lanes only count the mask's bits below them.  Bound by memory: 0.373 ms for
-// 0.81 GB of ids from 6.6 * 10^6 rows, 3.4 TB/s with what is read (0.43 ms with a
-// workgroup's hits listed in LDS).  Listing a wave's hits in LDS, for loads and
-// stores of 64 lanes, takes a third of the memory instructions and 0.414 ms;
-// non-temporal stores 0.355 ms here but 0.406 instead of 0.360 where a query
-// reports 170 ids.
+// null.  Bound by memory: 0.362 ms for 0.81 GB of ids of 4 * 10^8 candidates, 3.5
+// TB/s with what is read (0.378 for rows of 64, 0.43 with a workgroup's hits
+// listed in LDS first; 0.245 ms, 0.313 for rows of 64, for 0.17 GB of 2.4 * 10^8).
+// Listing a wave's hits in LDS, for loads and stores of 64 lanes, takes a third of
+// the memory instructions but a tenth more time; non-temporal stores are better
+// (0.355) only where a query reports a thousand ids (0.41 for 0.36 at 170).
 template <bool ORDERED, bool FUSED>
 __global__ __launch_bounds__(256) void compact_write_out(
-    const uint32_t* __restrict__ ids, const uint4* __restrict__ row_meta,
+    const uint32_t* __restrict__ ids, const uint2* __restrict__ row_meta,
     const uint64_t* __restrict__ row_off, uint64_t m, uint64_t rbase, uint64_t rend,
-    uint64_t row_end, bool only_whole, const uint64_t* __restrict__ masks,
-    const uint16_t* __restrict__ unit_pre, const uint32_t* __restrict__ unit_hits,
+    uint64_t row_end, uint64_t max_rows64, const uint32_t* __restrict__ masks,
+    const uint16_t* __restrict__ row_info, const uint32_t* __restrict__ unit_hits,
     const uint64_t* __restrict__ unit_off, const uint64_t* __restrict__ out_base, uint32_t tile_grid, uint32_t* __restrict__ out_ids,
     uint64_t cap, bool whole, uint64_t* __restrict__ offsets, const BatchStatus* status,
     BatchStatus* host, uint32_t* flags_out) {
@@ -1415,7 +1468,8 @@ __global__ __launch_bounds__(256) void compact_write_out(
   const uint32_t w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint64_t total_all = row_off[m];
   const uint64_t total_rows = total_all < row_end ? total_all : row_end;
-  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, only_whole);
+  const bool over = status->rows > max_rows64;
+  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, over);
   const uint64_t units = ntiles * kTileUnits;
   // A workgroup without a tile (and not the first, which reports) is done.
   if (blockIdx.x > 0 && blockIdx.x < tile_grid &&
@@ -1441,7 +1495,7 @@ __global__ __launch_bounds__(256) void compact_write_out(
     }
     if (flags_out) *flags_out = status->err;
   }
-  if (only_whole && total_all > row_end) return;   // nothing was tested
+  if (over) return;   // nothing was tested
   if (!ORDERED && blockIdx.x >= tile_grid) {
     // The CSR offsets of the queries whose first row lies in this chunk (a
     // query with no rows takes the position of the next row, trailing ones
@@ -1455,7 +1509,7 @@ __global__ __launch_bounds__(256) void compact_write_out(
       } else if (r >= rbase && r < rend) {
         const uint64_t lr = r - rbase;
         offsets[j] = (FUSED ? (uint64_t)s_off[lr >> kUnitShift] : unit_off[lr >> kUnitShift]) +
-                     unit_pre[lr];
+                     row_info[lr];
       }
     }
     return;
@@ -1463,27 +1517,28 @@ __global__ __launch_bounds__(256) void compact_write_out(
   const bool write_ids = !whole || ntiles == 0 || (ORDERED ? offsets[m] : hits_end) <= cap;
   if (!write_ids) return;
   const uint64_t have = total_rows - rbase;
-  // Lane j of a unit: row j's mask and first position, and the terms of its
-  // place in the output (kept as they come, not to wait for them here).
+  // What belongs to a lane's row: its mask and first position, and the terms of
+  // its place in the output (kept as they come, not to wait for them here).
+  const uint32_t row = unit_row(lane), lane32 = lane & 31;
   struct Unit {
-    uint64_t mask, unit, base;
-    uint32_t pb, at;
+    uint64_t unit, base;
+    uint32_t mask, pb, at;
   };
   auto fetch_rows = [&](uint64_t tile, Unit& u) {
-    u.mask = u.unit = u.base = 0;
-    u.pb = u.at = 0;
-    const uint64_t row0 = tile * kTileRows + (uint64_t)w * kWaveRows;
-    if (tile != ~0ull && lane < unit_rows(have, row0)) {
-      const uint64_t lr = row0 + lane;
+    u.unit = u.base = 0;
+    u.mask = u.pb = u.at = 0;
+    const uint64_t row0 = tile * kTileRows + (uint64_t)w * kUnitRows;
+    if (tile != ~0ull && row < unit_rows(have, row0)) {
+      const uint64_t lr = row0 + row;
       u.mask = masks[lr];
-      const uint4 md = row_meta[lr];
+      const uint2 md = row_meta[lr];
       u.pb = md.x;
-      u.at = md.z;
+      u.at = md.y;
       u.unit = FUSED ? (uint64_t)s_off[lr >> kUnitShift] : unit_off[lr >> kUnitShift];
     }
   };
   auto fetch_base = [&](Unit& u) {
-    if (ORDERED && lane < (uint32_t)kWaveRows) u.base = out_base[u.at];
+    if (ORDERED) u.base = out_base[u.at];
   };
   uint64_t tile = xcd_tile(blockIdx.x, tile_grid, 0, ntiles);
   if (tile == ~0ull) return;
@@ -1497,51 +1552,35 @@ __global__ __launch_bounds__(256) void compact_write_out(
     Unit nn;
     fetch_rows(after, nn);
     fetch_base(nx);
-    // Addresses in the rows' lanes, read as scalars; the capacity checked once
-    // for the unit.
-    const uint32_t hits = (uint32_t)__popcll(u.mask);
-    uint32_t upto = hits;   // the unit's hits up to the row
-#pragma unroll
-    for (int o = 1; o < (int)kWaveRows; o <<= 1) {
-      const uint32_t y = __shfl_up(upto, o, 64);
-      if (lane >= (uint32_t)o) upto += y;
-    }
-    const uint64_t place = u.unit + u.base + (upto - hits);
-    const uint64_t from = (uint64_t)(ids + u.pb), to = (uint64_t)(out_ids + place);
-    const bool fits = __ballot(lane < (uint32_t)kWaveRows && place + 64 > cap) == 0;
-    // Lanes past a row's last hit read that one again.  All the ids are waited
+    // The row's place; the capacity checked once for the unit.
+    const uint32_t v = __popc(u.mask), other = __shfl_xor(v, 32, 64);
+    const uint32_t upto = scan16(v + other);
+    const uint64_t place = u.unit + u.base + (upto - (lane < 32 ? v + other : v));
+    const bool fits = __ballot(place + 32 > cap) == 0;
+    // A step's hits are counted over both rows: the second row's start counts
+    // the first one's hits off.
+    const uint64_t to = place - (lane < 32 ? 0 : other);
+    // Lanes past a row's last hit read that one again, and a row without hits the
+    // index's first id, which is at hand (not a line of its own).  All the ids are waited
     // for at once: a wait for one of them after a store would wait for stores
     // too (they share a counter).
-    const uint32_t end = u.mask ? 4 * (63 - (uint32_t)__clzll(u.mask)) : 0u;
-    const uint32_t offset = 4 * lane;
-    uint32_t id[kWaveRows];
-    static_for<(int)kWaveRows>([&](auto row) {
-      constexpr int r = decltype(row)::value;
-      const uint32_t last = read_lane<r>(end);
-      id[r] = global_at<uint32_t>(read_lane64<r>(from), offset < last ? offset : last);
+    const uint32_t end = u.mask ? 31 - (uint32_t)__clz(u.mask) : 0u;
+    const uint32_t pb = u.mask ? u.pb : 0u;
+    uint32_t id[kUnitSteps];
+    static_for<kUnitSteps>([&](auto t) {
+      constexpr int T = decltype(t)::value;
+      const uint32_t last = bcast16_operand<T>(end);
+      id[T] = ids[(uint64_t)(bcast16_operand<T>(pb) + (lane32 < last ? lane32 : last))];
     });
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     __builtin_amdgcn_sched_barrier(0);
-    auto store = [&](auto row, bool on, uint32_t k) {
-      constexpr int r = decltype(row)::value;
-      typedef __attribute__((address_space(1))) char* Bytes;
-      typedef __attribute__((address_space(1))) uint32_t* Ptr;
-      if (on) *(Ptr)((Bytes)read_lane64<r>(to) + 4 * k) = id[r];
-    };
-    if (fits) {
-      static_for<(int)kWaveRows>([&](auto row) {
-        const uint64_t mk = read_lane64<decltype(row)::value>(u.mask);
-        store(row, lane_of(mk), below_in(mk));
-      });
-    } else {
-      static_for<(int)kWaveRows>([&](auto row) {
-        constexpr int r = decltype(row)::value;
-        const uint64_t mk = read_lane64<r>(u.mask);
-        const uint32_t k = below_in(mk);
-        store(row, lane_of(mk) && read_lane64<r>(place) + k < cap, k);
-      });
-    }
+    static_for<kUnitSteps>([&](auto t) {
+      constexpr int T = decltype(t)::value;
+      const uint64_t mk = (uint64_t)read_lane<T + 32>(u.mask) << 32 | read_lane<T>(u.mask);
+      const uint64_t at = bcast16<T>(to) + below_in(mk);
+      if (lane_of(mk) && (fits || at < cap)) out_ids[at] = id[T];
+    });
     if (next == ~0ull) break;
     u = nx;
     nx = nn;
@@ -1552,8 +1591,8 @@ __global__ __launch_bounds__(256) void compact_write_out(
 // Ordered rows: the hits of every query, and in out_base the hits P of all
 // rows before its first.  One thread per place.
 __global__ __launch_bounds__(256) void query_hits(const uint64_t* __restrict__ row_off, uint64_t m,
-                                                  uint64_t row_end,
-                                                  const uint16_t* __restrict__ unit_pre,
+                                                  uint64_t max_rows64, const BatchStatus* status,
+                                                  const uint16_t* __restrict__ row_info,
                                                   const uint64_t* __restrict__ unit_off,
                                                   const uint32_t* __restrict__ perm,
                                                   uint32_t* __restrict__ qhits,
@@ -1561,11 +1600,11 @@ __global__ __launch_bounds__(256) void query_hits(const uint64_t* __restrict__ r
   const uint64_t at = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   if (at >= m) return;
   const uint64_t total_all = row_off[m];
-  const uint64_t total = total_all <= row_end ? total_all : 0;   // past a capacity: not tested
+  const uint64_t total = status->rows <= max_rows64 ? total_all : 0;   // past it: not tested
   const uint64_t units = (total + kTileRows - 1) / kTileRows * kTileUnits;
   auto before = [&](uint64_t r) -> uint64_t {
     if (r >= total) return total ? unit_off[units] : 0;
-    return unit_off[r >> kUnitShift] + unit_pre[r];
+    return unit_off[r >> kUnitShift] + row_info[r];
   };
   const uint64_t p0 = before(row_off[at]), p1 = before(row_off[at + 1]);
   const uint32_t j = perm[at];
@@ -1595,12 +1634,11 @@ __global__ void fill32_kernel(uint32_t* p, uint32_t v, uint64_t count) {
 // Tiles per compaction chunk (lowered only by the test hook).
 std::atomic<uint64_t> g_chunk_tiles{kCompactChunkTiles};
 
-// Shape of the test kernel's row groups, rows x iterations: 0: 16 x 1,
-// 1: 4 x 4, 2: 8 x 2, 3: 2 x 8, 4: 1 x 16 (same results for all).  The
-// environment variable SFC_TEST_VARIANT overrides; else the autotuner's choice
-// for this number of rows; else 1 (8 * 10^6 rows in the plane: 0.366 ms, 0.370
-// for 16 x 1, 0.365 for 8 x 2 and 0.393 for 1 x 16; in three dimensions 0.810,
-// 0.918, 0.847 and 1.026 ms).
+// Shape of the test kernel's groups, steps x iterations: 0: 16 x 1, 1: 4 x 4,
+// 2: 8 x 2, 3: 2 x 8, 4: 1 x 16 (same results for all).  The environment
+// variable SFC_TEST_VARIANT overrides; else the autotuner's choice for this number
+// of rows; else 1 (2^20 queries over 2^24 points: 0.322 ms, 0.322 for 16 x 1,
+// 0.321 for 8 x 2 and 0.331 for 2 x 8).
 int test_variant(uint64_t rows) {
   static const int env = [] {
     const char* e = std::getenv("SFC_TEST_VARIANT");
@@ -1660,8 +1698,10 @@ bool query_scratch_carve(void* base, uint64_t m, QueryScratch* qs, uint32_t slot
   qs->blk_rows = (uint64_t*)p;
   qs->blk_off = qs->blk_rows + nblk;
   qs->blk_stat = qs->blk_off + nblk;
-  qs->blk_learned = (uint32_t*)(qs->blk_stat + nblk);
-  p += align256(nblk * 28);
+  qs->blk_rows64 = qs->blk_stat + nblk;
+  qs->blk_place = qs->blk_rows64 + nblk;
+  qs->blk_learned = (uint32_t*)(qs->blk_place + nblk);
+  p += align256(nblk * 44);
   qs->rec = p;                    p += align256(m * 32);
   qs->perm = (uint32_t*)p;        p += align256(m * 4);
   qs->out_base = (uint64_t*)p;    p += align256(m * 8);
@@ -1693,17 +1733,17 @@ size_t compact_scratch_bytes(uint64_t total_rows) {
   uint64_t tiles = (total_rows + kCompactTileRows - 1) / kCompactTileRows;
   if (tiles > kCompactChunkTiles) tiles = kCompactChunkTiles;
   if (tiles == 0) tiles = 1;
-  return align256(tiles * kTileRows * 8) + align256(tiles * 4) + 2 * align256((tiles + 1) * 8) +
-         align256(tiles * kTileRows * 16) + align256((tiles * kTileRows + 1) * 8) +
-         scan_scratch_bytes(tiles);
+  const uint64_t rows = tiles * kCompactTileRows;
+  return align256(rows * 8) + align256(tiles * 4) + 2 * align256((tiles + 1) * 8) +
+         align256(rows * 16) + align256((rows + 1) * 8) + scan_scratch_bytes(tiles);
 }
 
 namespace {
 
 struct CompactScratch {
-  uint64_t* masks;       // per row
-  uint4* meta;           // per row
-  uint16_t* unit_pre;    // per row
+  uint32_t* masks;       // per row
+  uint2* meta;           // per row
+  uint16_t* info;        // per row
   uint32_t* unit_hits;   // per unit
   uint64_t* unit_off[2]; // per unit, and the total; two, for the chunks in turn
   uint64_t* scan_tmp;
@@ -1714,9 +1754,9 @@ struct CompactScratch {
 bool compact_carve(void* base, uint64_t tiles, CompactScratch* c) {
   char* p = (char*)base;
   const uint64_t units = tiles * kTileUnits;
-  c->masks = (uint64_t*)p;       p += align256(tiles * kTileRows * 8);
-  c->meta = (uint4*)p;           p += align256(tiles * kTileRows * 16);
-  c->unit_pre = (uint16_t*)p;    p += align256(tiles * kTileRows * 2);
+  c->meta = (uint2*)p;           p += align256(tiles * kTileRows * 8);
+  c->masks = (uint32_t*)p;       p += align256(tiles * kTileRows * 4);
+  c->info = (uint16_t*)p;        p += align256(tiles * kTileRows * 2);
   c->unit_hits = (uint32_t*)p;   p += align256(units * 4);
   c->unit_off[0] = (uint64_t*)p; p += align256((units + 1) * 8);
   c->unit_off[1] = (uint64_t*)p; p += align256((units + 1) * 8);
@@ -1733,17 +1773,18 @@ uint32_t query_blocks(const QueryScratch& qs) {
 }
 
 BatchStats stats_of(const QueryScratch& qs) {
-  return BatchStats{qs.blk_stat, qs.learned ? qs.blk_learned : nullptr, qs.stats_ns,
+  return BatchStats{qs.blk_stat, qs.blk_rows64, qs.learned ? qs.blk_learned : nullptr, qs.stats_ns,
                     qs.pack_flags, qs.pack_pruned, qs.stats_np};
 }
 
-hipError_t launch_slot_rows(const QueryScratch& qs, const uint32_t* perm, hipStream_t s) {
+hipError_t launch_slot_rows(const QueryScratch& qs, const uint32_t* perm, uint64_t* blk_rows,
+                            hipStream_t s) {
   const uint64_t nseg = qs.m << qs.ss;
   const uint32_t g = query_blocks(qs);
   switch (slots_per_thread(qs)) {
-    case 1: slot_rows<1><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, qs.blk_rows); break;
-    case 2: slot_rows<2><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, qs.blk_rows); break;
-    default: slot_rows<4><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, qs.blk_rows); break;
+    case 1: slot_rows<1><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, blk_rows); break;
+    case 2: slot_rows<2><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, blk_rows); break;
+    default: slot_rows<4><<<g, 256, 0, s>>>(qs.slots, perm, qs.ss, nseg, blk_rows); break;
   }
   return hipGetLastError();
 }
@@ -1752,11 +1793,11 @@ hipError_t launch_slot_rows(const QueryScratch& qs, const uint32_t* perm, hipStr
 // batch's counters, unless expand_rows does both (fused).
 hipError_t finish_ranges(QueryScratch& qs, bool need_rows, BatchStatus* host, hipStream_t s) {
   const uint32_t nblk = query_blocks(qs);
-  qs.fused = !need_rows && nblk <= kFusedBlocks && qs.stats_np == 0;
+  qs.fused = !need_rows && nblk <= kFusedBlocks && qs.stats_np == 0 && !qs.perm_made;
   if (qs.fused) return hipSuccess;
   ProfScope ps("scan", s);
-  batch_scan<<<1, 1024, 0, s>>>(qs.blk_rows, nblk, qs.blk_off, qs.row_off + qs.m, stats_of(qs),
-                                true, qs.status, host);
+  batch_scan<<<1, 1024, 0, s>>>(qs.perm_made ? qs.blk_place : qs.blk_rows, nblk, qs.blk_off,
+                                qs.row_off + qs.m, stats_of(qs), true, qs.status, host);
   return hipGetLastError();
 }
 
@@ -1779,13 +1820,16 @@ bool search_ordered(const RangePlan& P, bool binary, uint64_t m) {
 }
 
 // Whether a batch's rows are processed in curve order: the test pass gains a
-// third (0.46 -> 0.29 ms for the 6.6 * 10^6 rows of 2 * 10^5 windows), but the
-// queries' offsets then take a scan of their hits (0.03 ms; 2^22 queries 0.2 ms),
-// so only with many rows a query: at 33 the windows' batch takes 0.91 ms against
-// 1.01, at 8 (2^20 queries over 2^24 points) 2.22 against 2.20.
-constexpr uint64_t kOrderRows = 16;
-bool rows_ordered(const CompactPlan& P, uint64_t m) {
-  return P.keys && m >= kOrderMin && P.n >= kOrderPoints && P.max_rows > kOrderRows * m;
+// third (0.46 -> 0.30 ms for the 4 * 10^8 candidates of 2 * 10^5 windows), but
+// the queries' offsets then take a scan of their hits (0.03 ms; 2^20 queries 0.07
+// and 2^22 0.2 ms), and the order 0.03 ms unless the search has made it.  So only
+// with many rows of 64 a query: at 33 the windows' batch takes 0.91 ms against
+// 1.01; at 8 and with the order made (2^20 queries over 2^24 points) 2.13 against
+// 2.19; 2^20 queries over 2^24 points in space (search tree) 3.44 against 3.33.
+constexpr uint64_t kOrderRows = 16, kOrderRowsMade = 6;
+bool rows_ordered(const CompactPlan& P, const QueryScratch& qs) {
+  return P.keys && qs.m >= kOrderMin && P.n >= kOrderPoints &&
+         P.max_rows > (qs.perm_made ? kOrderRowsMade : kOrderRows) * qs.m;
 }
 
 hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
@@ -1815,12 +1859,14 @@ hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
       return e;
     perm = qs.perm;
   }
+  uint64_t* blk_rows = perm ? qs.blk_place : qs.blk_rows;
   if (d3) {
     ProfScope ps(stree ? "ranges_stree3" : "ranges_search3", s);
 #define SFC_R3(S, R)                                                                         \
   ranges_search3<S, R><<<query_blocks(qs), 256, 0, s>>>(P.q, P.delta, m, P.keys, P.n, lv, sv, \
                                                         P.refine_min, perm, rec, qs.slots,   \
-                                                        qs.blk_rows, qs.blk_stat)
+                                                        blk_rows, qs.blk_stat,               \
+                                                        qs.blk_rows64)
     if (stree) {
       if (refine) SFC_R3(2, true);
       else SFC_R3(2, false);
@@ -1830,7 +1876,6 @@ hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
     }
 #undef SFC_R3
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (perm && (e = launch_slot_rows(qs, nullptr, s)) != hipSuccess) return e;
     return finish_ranges(qs, P.need_rows, P.host, s);
   }
   // With early termination (and no inspected ranges) the search runs one
@@ -1867,8 +1912,8 @@ hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
   ranges_search<C, R, S><<<query_blocks(qs), 256, 0, s>>>(                                    \
       (const double2*)P.q, P.delta, m, P.keys, P.n, lv, sv, P.refine_min, P.ball,             \
       dbg ? nullptr : P.occ, pairs, pair_total, P.qset, P.set_off, P.n_sets, perm, rec,       \
-      qs.slots, qs.blk_rows, qs.blk_stat, qs.blk_learned, P.dbg_lo, P.dbg_hi, P.dbg_b,        \
-      P.dbg_e, P.dbg_nr)
+      qs.slots, blk_rows, qs.blk_stat, qs.blk_rows64, qs.blk_learned, P.dbg_lo, P.dbg_hi,  \
+      P.dbg_b, P.dbg_e, P.dbg_nr)
 #define SFC_RANGES_R(C, R)                      \
   if (learned) SFC_RANGES(C, R, 1);             \
   else if (stree) SFC_RANGES(C, R, 2);          \
@@ -1889,7 +1934,7 @@ hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
 #undef SFC_RANGES
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((dense || perm) && (e = launch_slot_rows(qs, nullptr, s)) != hipSuccess) return e;
+  if (dense && (e = launch_slot_rows(qs, nullptr, qs.blk_rows, s)) != hipSuccess) return e;
   return finish_ranges(qs, P.need_rows, P.host, s);
 }
 
@@ -1921,43 +1966,45 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
   if (P.write_only && chunks != 1) return hipErrorInvalidValue;
   // Rows in curve order: only one chunk's hits are kept, so many chunks are
   // processed in query order.
-  const bool ordered = chunks == 1 && rows_ordered(P, m);
+  const bool ordered = chunks == 1 && rows_ordered(P, qs);
   const uint32_t* perm = ordered ? qs.perm : nullptr;
-  if (ordered && !P.write_only) {
-    if (!qs.perm_made &&
-        (e = order_queries(P.q, m, P.dim == 3 ? SFC_CURVE_MORTON3 : P.curve, P.keys, P.n,
-                           qs.perm, qs.order_scratch, s)) != hipSuccess)
+  const uint64_t* blk_rows = ordered ? qs.blk_place : qs.blk_rows;
+  if (!P.write_only && ordered != qs.perm_made) {
+    // The rows' scan so far is over the other order's workgroups.
+    if (ordered && (e = order_queries(P.q, m, P.dim == 3 ? SFC_CURVE_MORTON3 : P.curve, P.keys, P.n,
+                                      qs.perm, qs.order_scratch, s)) != hipSuccess)
       return e;
-    ProfScope ps("expand_rows", s);
-    if ((e = launch_slot_rows(qs, perm, s)) != hipSuccess) return e;
-    batch_scan<<<1, 1024, 0, s>>>(qs.blk_rows, query_blocks(qs), qs.blk_off, qs.row_off + m,
+    ProfScope ps("scan", s);
+    uint64_t* rows = ordered ? qs.blk_place : qs.blk_rows;
+    if ((e = launch_slot_rows(qs, perm, rows, s)) != hipSuccess) return e;
+    batch_scan<<<1, 1024, 0, s>>>(rows, query_blocks(qs), qs.blk_off, qs.row_off + m,
                                   stats_of(qs), qs.fused, qs.status, nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     qs.fused = false;
   }
   const bool fused_units = !ordered && chunks == 1 && ch_tiles * kTileUnits <= kFusedUnits;
   const uint64_t* total_dev = qs.row_off + m;
+  // A batch with more rows is flagged, and none of its rows is tested.
+  const uint64_t max_rows64 = P.device_sized ? P.max_rows : ~0ull;
   const uint64_t* carry = nullptr;
   int buf = 0;
   for (uint64_t ci = 0; ci < chunks; ++ci, buf ^= 1) {
-    const uint64_t rbase = ci * chunk * kCompactTileRows;
+    const uint64_t rbase = ci * chunk * kTileRows;
     const uint64_t nt = tiles_all - ci * chunk < chunk ? (tiles_all ? tiles_all - ci * chunk : 1)
                                                        : chunk;
-    const uint64_t rend = rbase + nt * kCompactTileRows;
-    // A full chunk ends at its last tile; the last chunk at the capacity
-    // (device-sized) or at the exact count (host-sized, a multiple of 64 rows
-    // past it is never read because the kernels clamp to the count).
-    const uint64_t row_end = ci + 1 == chunks && P.device_sized ? P.max_rows : rend;
-    const bool flag = P.device_sized && ci + 1 == chunks;
+    const uint64_t rend = rbase + nt * kTileRows;
+    // A full chunk ends at its last tile; the last chunk at the capacity: at
+    // most two rows of 32 for one of 64.
+    const uint64_t row_end = ci + 1 == chunks && P.device_sized ? 2 * P.max_rows : rend;
     // A multiple of eight workgroups, so that each XCD gets its share.
     const uint32_t grid = (uint32_t)(((nt < kCompactGrid ? nt : kCompactGrid) + 7) / 8 * 8);
     uint64_t* unit_off = c.unit_off[buf];
     if (!P.write_only) {
       ProfScope ps("expand_rows", s);
 #define SFC_EXPAND(K, F)                                                                     \
-  expand_rows<K, F><<<query_blocks(qs), 256, 0, s>>>(qs.row_off, qs.slots, perm, qs.blk_rows, \
+  expand_rows<K, F><<<query_blocks(qs), 256, 0, s>>>(qs.row_off, qs.slots, perm, blk_rows, \
                                                      qs.blk_off, stats_of(qs), qs.status, m, qs.ss, rbase,  \
-                                                     row_end, flag, c.meta)
+                                                     row_end, max_rows64, c.meta, c.info)
       switch (slots_per_thread(qs)) {
         case 1: if (qs.fused) SFC_EXPAND(1, true); else SFC_EXPAND(1, false); break;
         case 2: if (qs.fused) SFC_EXPAND(2, true); else SFC_EXPAND(2, false); break;
@@ -1971,7 +2018,7 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
 #define SFC_TEST_K(R, I, E, D, C, W, K)                                                    \
   compact_test<R, I, E, D, C, W, K><<<grid, 256, 0, s>>>(                                  \
       P.q, P.delta, m, P.pts ? P.pts : P.pts_in, P.pts ? nullptr : P.ids, P.cells, qs.rec, \
-      c.meta, total_dev, rbase, row_end, flag, c.masks, c.unit_pre, c.unit_hits, qs.status, \
+      c.meta, total_dev, rbase, row_end, max_rows64, c.masks, c.info, c.unit_hits, qs.status, \
       P.ins, P.era)
 #define SFC_TEST_W(R, I, E, D, C, W)                                                       \
   if (C && shifts) SFC_TEST_K(R, I, E, D, C, W, C);                                        \
@@ -2015,8 +2062,8 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
       ProfScope ps("query_offsets", s);
       const uint32_t qb = (uint32_t)((m + 255) / 256);
       if (!P.write_only) {
-        query_hits<<<qb, 256, 0, s>>>(qs.row_off, m, row_end, c.unit_pre, unit_off, qs.perm,
-                                      qs.qhits, qs.out_base);
+        query_hits<<<qb, 256, 0, s>>>(qs.row_off, m, max_rows64, qs.status, c.info, unit_off,
+                                      qs.perm, qs.qhits, qs.out_base);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
       if ((e = scan_excl(qs.qhits, P.offsets, m, nullptr, qs.scan_tmp, s)) != hipSuccess) return e;
@@ -2030,7 +2077,7 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
       const uint32_t extra = ordered ? 0 : fill_blocks(m + 1);
 #define SFC_WRITE(O, F)                                                                      \
   compact_write_out<O, F><<<grid + extra, 256, 0, s>>>(                                       \
-      P.ids, c.meta, qs.row_off, m, rbase, rend, row_end, flag, c.masks, c.unit_pre,  \
+      P.ids, c.meta, qs.row_off, m, rbase, rend, row_end, max_rows64, c.masks, c.info, \
       c.unit_hits, unit_off, qs.out_base, grid, P.out_ids, P.cap, chunks == 1, P.offsets,     \
       qs.status, P.host, P.flags_out)
       if (ordered) SFC_WRITE(true, false);

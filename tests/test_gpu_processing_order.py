@@ -137,3 +137,34 @@ def test_retry_after_capacity():
     assert idx.query_retry(off, ids) == total
     same((off, ids), want)
     idx.close()
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 96, 1023, 1024, 1025, 4095, 4097])
+def test_row_edges(n):
+    """One range of n candidates for each of 1, 2 and 40 queries: rows, pairs of
+    rows, units and tiles partly filled; the row count of rows of 64, and a
+    capacity of just that and of one less."""
+    pts = workload.uniform_points(n, 5)
+    idx = sfc.Index(dev(pts), sfc.MORTON)
+    built = oracle.build(pts, sfc.MORTON)
+    rng = np.random.default_rng(n)
+    for m in (1, 2, 40):
+        q, d = rng.random((m, 2)), np.full(m, 0.6)   # the box's cells cover the square
+        d[::3] = 3.0
+        want = oracle.query(built, q, d, sfc.MORTON)
+        same(idx.query(dev(q), dev(d)), want)
+        rows = idx.last_stats()["rows"]
+        assert rows == m * ((n + 63) // 64)
+        for cap, fits in ((rows, True), (rows - 1, False)):
+            if cap == 0:
+                continue
+            g = sfc.Graph.query(idx, dev(q), dev(d), max_rows=cap, ids_cap=len(want[1]))
+            for _ in range(2):
+                g.launch()
+                if fits:
+                    same(g.result(), want)
+                else:
+                    with pytest.raises(sfc.CapacityError):
+                        g.result()
+            g.close()
+    idx.close()
