@@ -856,6 +856,9 @@ sfc_status build_impl(const double* xy, uint64_t n, const uint64_t* set_off_host
               ? sfc::sort_build_sets_chunked(xy, n, h->curve, h->keys, h->ids, nullptr, scratch,
                                              err, h->stream, h->set_off, h->n_sets, h->cells,
                                              h->xy_in, false)
+          : n <= sfc::kSmallSort
+              ? sfc::sort_build_small(xy, n, h->curve, h->keys, h->ids, nullptr, scratch, err,
+                                      h->stream, h->cells, h->xy_in)
               : sfc::sort_build_chunked(xy, n, h->curve, h->keys, h->ids, scratch, err, h->stream,
                                         h->cells, h->xy_in);
     uint64_t w = 0;
@@ -1547,6 +1550,9 @@ sfc_status sfc_graph_build(sfc_index* h, const double* xy, sfc_graph** out) {
       e = g_force_plain_sort
               ? sfc::sort_build(xy, h->n, h->curve, h->keys, h->ids, h->xy, g->scratch, g->err,
                                 s, h->set_off, h->n_sets, h->cells, h->xy_in)
+          : !h->set_off && h->n <= sfc::kSmallSort
+              ? sfc::sort_build_small(xy, h->n, h->curve, h->keys, h->ids, h->xy, g->scratch,
+                                      g->err, s, h->cells, h->xy_in)
               : sfc::sort_build_sets_chunked(xy, h->n, h->curve, h->keys, h->ids, h->xy,
                                              g->scratch, g->err, s, h->set_off, h->n_sets,
                                              h->cells, h->xy_in, true);
@@ -2041,7 +2047,10 @@ sfc_status insert_impl(sfc_index* h, const double* xy, uint64_t k, const uint64_
   if (e == hipSuccess && roff)
     e = hipMemcpyAsync(roff, run_off, (runs + 1) * 8, hipMemcpyHostToDevice, h->stream);
   if (e == hipSuccess)
-    e = sfc::sort_build(xy, k, h->curve, bkeys, bids, bxy, scratch, err, h->stream);
+    e = k <= sfc::kSmallSort && !g_force_plain_sort
+            ? sfc::sort_build_small(xy, k, h->curve, bkeys, bids, bxy, scratch, err, h->stream,
+                                    nullptr, nullptr)
+            : sfc::sort_build(xy, k, h->curve, bkeys, bids, bxy, scratch, err, h->stream);
   if (e == hipSuccess)
     e = sfc::merge_runs(current_run(h), h->n, bkeys, bids, bxy, k, h->next_id, ep, h->spare,
                         h->key_of, h->stream, roff, runs > 1 ? runs : 0);

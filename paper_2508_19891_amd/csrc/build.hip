@@ -15,6 +15,7 @@
 //                  base(digit) + scan(digit, tile).  The first pass takes ids
 //                  from the position (iota); the last pass also gathers the
 //                  points into key order.
+// Up to 2^16 points are sorted in two launches instead (small_runs, small_merge).
 // No workgroup waits on another.  Tiles are assigned so that each XCD (the
 // hardware deals workgroups to the eight XCDs in turn) scatters a contiguous
 // range of tiles: the runs that consecutive tiles write for one digit are
@@ -25,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
+#include <type_traits>
 
 #include "common.h"
 #include "curve.h"
@@ -716,17 +718,106 @@ __device__ __forceinline__ uint64_t chunk_bound(const uint64_t* first, uint64_t 
   return ~0ull;
 }
 
+// A workgroup's items in LDS, or the waves' digit counts.
+template <int WAVES>
+union ChunkLds {
+  uint32_t wave_hist[WAVES][kRadix];
+  struct {
+    uint64_t k[kChunkCap];
+    uint32_t v[kChunkCap];
+  } st;
+};
+
+// Stable LSD passes over the bytes from bit `low` up of the workgroup's keys
+// that vary (vmask).  Each wave holds a contiguous stretch of `slots` rows of 64
+// positions, so that (wave, slot, lane) order is position order.  A barrier
+// comes before (the items are in registers) and after.
+template <int WAVES, int SLOTS>
+__device__ __forceinline__ void lds_passes(ChunkLds<WAVES>& sm, uint32_t* s_local, uint32_t* s_tmp,
+                                           uint32_t slots, uint64_t (&key)[SLOTS],
+                                           uint32_t (&val)[SLOTS], uint64_t vmask, int low) {
+  const uint32_t tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const uint32_t wbase = w * slots * kWave;
+  const uint64_t below_mask = lanemask_lt();
+  for (int shift = low; shift < 64; shift += 8) {
+    if (((vmask >> shift) & 255u) == 0) continue;   // the byte is the same for every key
+    uint32_t* wh = sm.wave_hist[w];
+    for (uint32_t i = l; i < kRadix; i += kWave) wh[i] = 0;
+    uint32_t dig[SLOTS], rank[SLOTS];
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) {
+      if (i >= (int)slots) continue;
+      const uint32_t dg = (uint32_t)(key[i] >> shift) & 255u;
+      uint64_t match = ~0ull;
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const bool bit = (dg >> b) & 1u;
+        const uint64_t bal = __ballot(bit);
+        match &= bit ? bal : ~bal;
+      }
+      const uint32_t cnt = (uint32_t)__popcll(match);
+      const uint32_t below = (uint32_t)__popcll(match & below_mask);
+      const uint32_t pre = wh[dg];
+      if (below == 0) wh[dg] = pre + cnt;
+      dig[i] = dg;
+      rank[i] = pre + below;
+    }
+    __syncthreads();
+    // Digit d (threads 0..255): per-wave exclusive bases and the chunk's
+    // exclusive count of smaller digits.
+    if (tid < kRadix) {
+      uint32_t tot = 0;
+#pragma unroll
+      for (int ww = 0; ww < WAVES; ++ww) {
+        const uint32_t cw = sm.wave_hist[ww][tid];
+        sm.wave_hist[ww][tid] = tot;
+        tot += cw;
+      }
+      uint32_t x = tot;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (l >= (uint32_t)o) x += y;
+      }
+      if (l == 63) s_tmp[w] = x;
+      s_local[tid] = x - tot;
+    }
+    __syncthreads();
+    uint32_t lpos[SLOTS];
+    {
+      const uint32_t add1 = s_tmp[0], add2 = add1 + s_tmp[1], add3 = add2 + s_tmp[2];
+#pragma unroll
+      for (int i = 0; i < SLOTS; ++i) {
+        if (i >= (int)slots) continue;
+        const uint32_t dg = dig[i], q = dg >> 6;
+        const uint32_t wadd = q == 0 ? 0u : (q == 1 ? add1 : (q == 2 ? add2 : add3));
+        lpos[i] = s_local[dg] + wadd + sm.wave_hist[w][dg] + rank[i];
+      }
+    }
+    __syncthreads();   // every histogram read is done before the items overwrite it
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) {
+      if (i >= (int)slots) continue;
+      sm.st.k[lpos[i]] = key[i];
+      sm.st.v[lpos[i]] = val[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) {
+      if (i >= (int)slots) continue;
+      const uint32_t pos = wbase + i * kWave + l;
+      key[i] = sm.st.k[pos];
+      val[i] = sm.st.v[pos];
+    }
+    __syncthreads();   // every item is read back before the next pass's histograms
+  }
+}
+
 __global__ __launch_bounds__(kChunkThreads) void chunk_sort(
     uint64_t* __restrict__ keys, uint32_t* __restrict__ ids, uint64_t n,
     const uint64_t* __restrict__ first, uint64_t chunks, uint64_t* __restrict__ cells_out,
     int cell_curve, uint32_t* err) {
-  __shared__ union {
-    uint32_t wave_hist[kChunkWaves][kRadix];
-    struct {
-      uint64_t k[kChunkCap];
-      uint32_t v[kChunkCap];
-    } st;
-  } sm;
+  __shared__ ChunkLds<kChunkWaves> sm;
   __shared__ uint32_t s_local[kRadix];
   __shared__ uint32_t s_tmp[kChunkWaves];
   __shared__ uint64_t s_bound[2];
@@ -843,79 +934,7 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_sort(
       }
     }
     __syncthreads();   // the items are in registers before the histograms reuse LDS
-    const uint64_t below_mask = lanemask_lt();
-    for (int shift = 0; shift < 64; shift += 8) {
-      if (((vmask >> shift) & 255u) == 0) continue;   // the byte is the same for every key
-      uint32_t* wh = sm.wave_hist[w];
-      for (uint32_t i = l; i < kRadix; i += kWave) wh[i] = 0;
-      uint32_t dig[kChunkSlots], rank[kChunkSlots];
-#pragma unroll
-      for (int i = 0; i < kChunkSlots; ++i) {
-        if (i >= (int)slots) continue;
-        const uint32_t dg = (uint32_t)(key[i] >> shift) & 255u;
-        uint64_t match = ~0ull;
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-          const bool bit = (dg >> b) & 1u;
-          const uint64_t bal = __ballot(bit);
-          match &= bit ? bal : ~bal;
-        }
-        const uint32_t cnt = (uint32_t)__popcll(match);
-        const uint32_t below = (uint32_t)__popcll(match & below_mask);
-        const uint32_t pre = wh[dg];
-        if (below == 0) wh[dg] = pre + cnt;
-        dig[i] = dg;
-        rank[i] = pre + below;
-      }
-      __syncthreads();
-      // Digit d (threads 0..255): per-wave exclusive bases and the chunk's
-      // exclusive count of smaller digits.
-      if (tid < kRadix) {
-        uint32_t tot = 0;
-#pragma unroll
-        for (int ww = 0; ww < kChunkWaves; ++ww) {
-          const uint32_t cw = sm.wave_hist[ww][tid];
-          sm.wave_hist[ww][tid] = tot;
-          tot += cw;
-        }
-        uint32_t x = tot;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint32_t y = __shfl_up(x, o, 64);
-          if (l >= (uint32_t)o) x += y;
-        }
-        if (l == 63) s_tmp[w] = x;
-        s_local[tid] = x - tot;
-      }
-      __syncthreads();
-      uint32_t lpos[kChunkSlots];
-      {
-        const uint32_t add1 = s_tmp[0], add2 = add1 + s_tmp[1], add3 = add2 + s_tmp[2];
-#pragma unroll
-        for (int i = 0; i < kChunkSlots; ++i) {
-          if (i >= (int)slots) continue;
-          const uint32_t dg = dig[i], q = dg >> 6;
-          const uint32_t wadd = q == 0 ? 0u : (q == 1 ? add1 : (q == 2 ? add2 : add3));
-          lpos[i] = s_local[dg] + wadd + sm.wave_hist[w][dg] + rank[i];
-        }
-      }
-      __syncthreads();   // every histogram read is done before the items overwrite it
-#pragma unroll
-      for (int i = 0; i < kChunkSlots; ++i) {
-        if (i >= (int)slots) continue;
-        sm.st.k[lpos[i]] = key[i];
-        sm.st.v[lpos[i]] = val[i];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < kChunkSlots; ++i) {
-        if (i >= (int)slots) continue;
-        const uint32_t pos = wbase + i * kWave + l;
-        key[i] = sm.st.k[pos];
-        val[i] = sm.st.v[pos];
-      }
-      __syncthreads();   // every item is read back before the next pass's histograms
-    }
+    lds_passes(sm, s_local, s_tmp, slots, key, val, vmask, 0);
 #pragma unroll
     for (int i = 0; i < kChunkSlots; ++i) {
       if (i >= (int)slots) continue;
@@ -932,6 +951,208 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_sort(
     keys[start + j] = k;
     ids[start + j] = sm.st.v[j];
     if (cells_out) cells_out[start + j] = cell_of_key_lut(cell_curve, k, s_inv);
+  }
+}
+
+// ---- construction of up to kSmallSort points: two launches --------------------
+//
+// With so few points the passes' launches are the cost (24 of 5 to 10 us each,
+// 14 with the chunked sort).  So each workgroup keys and sorts one run of
+// consecutive points in LDS, and an element's place is then its place in its run
+// plus its rank in every other one: elements not after it in earlier runs,
+// elements before it in later ones, so that equal keys keep their order.  At most
+// 16 runs, of up to a workgroup's LDS each: with more the ranks would cost more
+// than the passes' launches.  2^16 points: 22 and 26 us (chains of LDS steps;
+// scattered writes), where the chunked sort's launches took 85; 20003 points of an
+// insertion, sorted by whole keys: 16 and 18 us for 200.
+constexpr uint32_t kSmallRuns = 16;
+static_assert(kSmallSort == kSmallRuns * kChunkCap, "a run fits a workgroup");
+// (Sixteen waves to a run: a pass is a chain of LDS steps per slot.)
+constexpr int kSmallWaves = 16;
+constexpr int kSmallThreads = kSmallWaves * kWave;
+constexpr int kSmallSlots = kChunkCap / kSmallThreads;
+constexpr uint32_t kSmallSamples = 64;   // keys of each run that the merge holds in LDS
+// Points per run: as short as the runs allow, in whole rows of a workgroup.
+uint32_t small_run(uint64_t n) {
+  const uint64_t per = (n + kSmallRuns - 1) / kSmallRuns;
+  return (uint32_t)((per + kSmallThreads - 1) / kSmallThreads * kSmallThreads);
+}
+
+template <int CURVE>
+__global__ __launch_bounds__(kSmallThreads) void small_runs(
+    const double* __restrict__ xy, uint32_t n, uint32_t run, uint64_t* __restrict__ keys,
+    uint32_t* __restrict__ ids, uint32_t* err, double* __restrict__ xy_copy) {
+  constexpr int DIM = CURVE == SFC_CURVE_MORTON3 ? 3 : 2;
+  __shared__ ChunkLds<kSmallWaves> sm;
+  __shared__ uint32_t s_local[kRadix];
+  __shared__ uint32_t s_tmp[kSmallWaves];
+  __shared__ uint16_t lut[CURVE == SFC_CURVE_HILBERT ? 1024 : 1];
+  const uint32_t tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const uint32_t start = blockIdx.x * run, len = n - start < run ? n - start : run;
+  if (CURVE == SFC_CURVE_HILBERT)
+    for (uint32_t i = tid; i < 1024; i += kSmallThreads) lut[i] = kHilbertLutConst.v[i];
+  __syncthreads();
+  const uint32_t slots = run / kSmallThreads, wbase = w * slots * kWave;
+  uint64_t key[kSmallSlots];
+  uint32_t val[kSmallSlots];
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < kSmallSlots; ++i) {
+    key[i] = ~0ull;   // padding sorts after every key of the run
+    val[i] = 0xFFFFFFFFu;
+    const uint32_t pos = wbase + i * kWave + l;
+    if (i < (int)slots && pos < len) {
+      double p[DIM];
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) {
+        const uint64_t at = (uint64_t)DIM * (start + pos) + a;
+        p[a] = xy[at];
+        if (xy_copy) xy_copy[at] = p[a];
+      }
+      uint64_t k = 0;
+      if constexpr (DIM == 3) {
+        if (in_unit(p[0]) && in_unit(p[1]) && in_unit(p[2]))
+          k = morton3_key(quantize3(p[0]), quantize3(p[1]), quantize3(p[2]));
+        else
+          bad = true;
+      } else if (in_unit(p[0]) && in_unit(p[1])) {
+        const uint32_t ux = quantize(p[0]), uy = quantize(p[1]);
+        k = CURVE == SFC_CURVE_HILBERT ? hilbert_key_lut(lut, ux, uy) : morton_key(ux, uy);
+      } else {
+        bad = true;
+      }
+      key[i] = k;
+      val[i] = start + pos;
+    }
+  }
+  if (__ballot(bad) != 0 && l == 0) atomicOr(err, kErrDomain);
+  // By the top 16 bits, or if that leaves many keys equal the top 32; then, as in
+  // chunk_sort, by counting within the runs of equal top bits.  (Stable passes
+  // from an order that keeps equal keys in theirs end in the same order.)
+  for (int top = 48; top >= kTopShift; top -= 16) {
+    lds_passes(sm, s_local, s_tmp, slots, key, val, ~0ull, top);
+#pragma unroll
+    for (int i = 0; i < kSmallSlots; ++i) {
+      if (i >= (int)slots) continue;
+      const uint32_t pos = wbase + i * kWave + l;
+      sm.st.k[pos] = key[i];
+      sm.st.v[pos] = val[i];
+    }
+    __syncthreads();
+    bool is_long = false;
+    for (uint32_t j = tid; j < len; j += kSmallThreads)
+      if (j >= kShortRun && (sm.st.k[j - kShortRun] >> top) == (sm.st.k[j] >> top)) is_long = true;
+    if (__syncthreads_or(is_long)) continue;
+    for (uint32_t j = tid; j < len; j += kSmallThreads) {
+      const uint64_t kj = sm.st.k[j];
+      const uint64_t t = kj >> top;
+      uint32_t b = j;
+      while (b > 0 && (sm.st.k[b - 1] >> top) == t) --b;
+      uint32_t r = 0;
+      for (uint32_t q = b; q < len; ++q) {
+        const uint64_t kq = sm.st.k[q];
+        if ((kq >> top) != t) break;
+        r += (kq < kj || (kq == kj && q < j)) ? 1u : 0u;
+      }
+      keys[start + b + r] = kj;
+      ids[start + b + r] = sm.st.v[j];
+    }
+    return;
+  }
+  lds_passes(sm, s_local, s_tmp, slots, key, val, ~0ull, 0);
+#pragma unroll
+  for (int i = 0; i < kSmallSlots; ++i) {
+    const uint32_t pos = wbase + i * kWave + l;
+    if (i < (int)slots && pos < len) {
+      keys[start + pos] = key[i];
+      ids[start + pos] = val[i];
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void small_merge(
+    const uint64_t* __restrict__ rkeys, const uint32_t* __restrict__ rids, uint32_t n, uint32_t run,
+    uint64_t* __restrict__ keys, uint32_t* __restrict__ ids, uint64_t* __restrict__ cells,
+    int curve, const double* __restrict__ xy, double* __restrict__ xy_out) {
+  // Every stride-th key of each run, so that a search's first steps are in LDS and
+  // its others within a window of `stride` keys (a step in memory that another
+  // XCD has just written takes most of a microsecond).
+  __shared__ uint64_t s_key[kSmallRuns][kSmallSamples];
+  __shared__ uint16_t s_inv[1024];
+  const uint32_t tid = threadIdx.x, base = blockIdx.x * 256;
+  // A workgroup's elements belong to one run (a run holds whole workgroups' worth).
+  const uint32_t mine = base / run, runs = (n + run - 1) / run;
+  const uint32_t run_end = n - mine * run < run ? n : (mine + 1) * run;
+  const uint32_t end = base + 256 < run_end ? base + 256 : run_end;
+  if (cells && curve == SFC_CURVE_HILBERT)
+    for (uint32_t i = tid; i < 1024; i += 256) s_inv[i] = kHilbertInvLutConst.v[i];
+  const uint32_t stride = run / kSmallSamples;
+  for (uint32_t i = tid; i < runs * kSmallSamples; i += 256) {
+    const uint32_t p = i / kSmallSamples * run + i % kSmallSamples * stride;
+    s_key[i / kSmallSamples][i % kSmallSamples] = p < n ? rkeys[p] : ~0ull;
+  }
+  const uint32_t i = base + tid;
+  const uint64_t k = i < end ? rkeys[i] : 0;
+  const uint32_t id = i < end ? rids[i] : 0;
+  __syncthreads();
+  if (i >= end) return;
+  uint32_t at = i - mine * run;
+  // In run r: the first entry not before k, past those equal to it in the runs
+  // before this one; kAtOnce runs at a time, their loads independent.
+  constexpr int kAtOnce = 8;
+  for (uint32_t r0 = 0; r0 < runs; r0 += kAtOnce) {
+    uint32_t lo[kAtOnce], len[kAtOnce];
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      const uint32_t r = r0 + j;
+      lo[j] = len[j] = 0;
+      if (r >= runs || r == mine) continue;   // its own run: counted above
+      const uint64_t* sk = s_key[r];
+      uint32_t c = 0;   // samples before k's place
+#pragma unroll
+      for (uint32_t h = kSmallSamples / 2; h > 0; h >>= 1) {
+        const uint64_t v = sk[c + h - 1];
+        c += (v < k || (v == k && r < mine)) ? h : 0u;
+      }
+      {
+        const uint64_t v = sk[c];
+        c += (v < k || (v == k && r < mine)) ? 1u : 0u;
+      }
+      // The place lies past sample c - 1 and not past sample c.
+      const uint32_t size = n - r * run < run ? n - r * run : run;
+      const uint32_t a = c > 0 ? (c - 1) * stride + 1 : 0, b = c > 0 ? c * stride : 0;
+      lo[j] = r * run + (a < size ? a : size);
+      len[j] = (b < size ? b : size) - (a < size ? a : size);
+    }
+    for (uint32_t most = stride - 1; most > 0; most >>= 1) {
+      uint64_t v[kAtOnce];
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j) {
+        const uint32_t p = lo[j] + (len[j] >> 1);
+        v[j] = rkeys[p < n ? p : n - 1];
+      }
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j) {
+        const uint32_t h = len[j] >> 1;
+        const bool up = len[j] > 0 && (v[j] < k || (v[j] == k && r0 + j < mine));
+        lo[j] += up ? h + 1 : 0u;
+        len[j] = up ? len[j] - h - 1 : h;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j)
+      if (r0 + j < runs && r0 + j != mine) at += lo[j] - (r0 + j) * run;
+  }
+  keys[at] = k;
+  ids[at] = id;
+  if (cells) cells[at] = cell_of_key_lut(curve, k, s_inv);
+  if (xy_out) {
+    if (curve == SFC_CURVE_MORTON3) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) xy_out[3 * (uint64_t)at + a] = xy[3 * (uint64_t)id + a];
+    } else {
+      ((double2*)xy_out)[at] = ((const double2*)xy)[id];
+    }
   }
 }
 
@@ -1115,6 +1336,32 @@ hipError_t sort_build(const double* xy, uint64_t n, int curve, uint64_t* keys_ou
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t sort_build_small(const double* xy, uint64_t n, int curve, uint64_t* keys_out,
+                            uint32_t* ids_out, double* xy_out, void* scratch, uint32_t* err,
+                            hipStream_t s, uint64_t* cells_out, double* xy_copy) {
+  if (n == 0) return hipSuccess;
+  if (n > kSmallSort) return hipErrorInvalidValue;
+  char* p = (char*)scratch;
+  uint64_t* rkeys = (uint64_t*)p;   p += align256(n * 8);
+  uint32_t* rids = (uint32_t*)p;
+  const uint32_t run = small_run(n), runs = (uint32_t)((n + run - 1) / run);
+  hipError_t e;
+  {
+    ProfScope ps("small_runs", s);
+#define SFC_RUNS(C) \
+  small_runs<C><<<runs, kSmallThreads, 0, s>>>(xy, (uint32_t)n, run, rkeys, rids, err, xy_copy)
+    if (curve == SFC_CURVE_MORTON3) SFC_RUNS(SFC_CURVE_MORTON3);
+    else if (curve == SFC_CURVE_HILBERT) SFC_RUNS(SFC_CURVE_HILBERT);
+    else SFC_RUNS(SFC_CURVE_MORTON);
+#undef SFC_RUNS
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  ProfScope ps("small_merge", s);
+  small_merge<<<(uint32_t)((n + 255) / 256), 256, 0, s>>>(rkeys, rids, (uint32_t)n, run, keys_out,
+                                                          ids_out, cells_out, curve, xy, xy_out);
+  return hipGetLastError();
 }
 
 namespace {

@@ -59,6 +59,11 @@ hipError_t sort_build(const double* xy, uint64_t n, int curve, uint64_t* keys_ou
                       hipStream_t s, const uint64_t* set_off = nullptr, uint32_t n_sets = 0,
                       uint64_t* cells_out = nullptr, double* xy_copy = nullptr,
                       SortGuard guard = {});
+// sort_build without point sets, of up to kSmallSort points, in two launches.
+constexpr uint64_t kSmallSort = 1u << 16;
+hipError_t sort_build_small(const double* xy, uint64_t n, int curve, uint64_t* keys_out,
+                            uint32_t* ids_out, double* xy_out, void* scratch, uint32_t* err,
+                            hipStream_t s, uint64_t* cells_out, double* xy_copy);
 // sort_build without point sets or xy_out, by four radix passes over the
 // top 32 key bits and an LDS sort of each chunk of whole runs of equal top
 // bits (same results).  A run too long for a chunk raises kErrOversized in
