@@ -382,73 +382,35 @@ __device__ int query_ranges3(double qx, double qy, double qz, double d, uint64_t
   return r;
 }
 
-// The level-l cubes meeting the widened box, unmerged and sorted by key, with
-// their coordinates at level l (for the refinement); *L gets l, b the box.
-__device__ __forceinline__ void cube_cas(uint64_t* lo, uint32_t* cx, uint32_t* cy, uint32_t* cz,
-                                         int i, int j) {
-  if (lo[j] < lo[i]) {
-    const uint64_t k = lo[i];
-    lo[i] = lo[j];
-    lo[j] = k;
-    uint32_t t = cx[i];
-    cx[i] = cx[j];
-    cx[j] = t;
-    t = cy[i];
-    cy[i] = cy[j];
-    cy[j] = t;
-    t = cz[i];
-    cz[i] = cz[j];
-    cz[j] = t;
-  }
+// The value of the lane whose number differs in the bits of X (1..7) from this
+// one's; the eight lanes of a group are active together.
+template <int CTRL>
+__device__ __forceinline__ uint32_t permute_lanes(uint32_t v) {
+  uint32_t x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+  asm("" : "+v"(x));   // (never an operand modifier; see bcast16)
+  return x;
 }
-
-__device__ __forceinline__ int query_cubes3(double qx, double qy, double qz, double d,
-                                            uint64_t lo[8], uint32_t cx[8], uint32_t cy[8],
-                                            uint32_t cz[8], int* L, int64_t b[6]) {
-  if (!axis_box3(qx, d, b[0], b[1]) || !axis_box3(qy, d, b[2], b[3]) ||
-      !axis_box3(qz, d, b[4], b[5]))
-    return 0;
-  uint64_t side = (uint64_t)(b[1] - b[0] + 1);
-  side = (uint64_t)(b[3] - b[2] + 1) > side ? (uint64_t)(b[3] - b[2] + 1) : side;
-  side = (uint64_t)(b[5] - b[4] + 1) > side ? (uint64_t)(b[5] - b[4] + 1) : side;
-  const int l = side <= 1 ? 0 : 64 - __clzll(side - 1);
-  if (l >= 21) {
-    *L = 21;
-    lo[0] = 0;
-    cx[0] = cy[0] = cz[0] = 0;
-    return 1;
+template <int X>
+__device__ __forceinline__ uint64_t across(uint64_t v) {
+  constexpr int kQuad[4] = {0xE4, 0xB1, 0x4E, 0x1B};   // lanes of four exchanged by xor
+  uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  constexpr int kIn = X & 4 ? X ^ 7 : X;   // mirrored in eight: xor 7
+  if constexpr (X & 4) {
+    lo = permute_lanes<0x141>(lo);
+    hi = permute_lanes<0x141>(hi);
   }
-  *L = l;
-  // A box of side at most 2^l meets at most two level-l cells per axis: the
-  // eight candidates (x0 + dx, y0 + dy, z0 + dz), those outside the box keyed
-  // past every cube, then sorted by key with a fixed network (Batcher's
-  // odd-even merge, 19 exchanges), every array index static so that the
-  // arrays stay in registers.
-  const uint32_t x0 = (uint32_t)(b[0] >> l), x1 = (uint32_t)(b[1] >> l);
-  const uint32_t y0 = (uint32_t)(b[2] >> l), y1 = (uint32_t)(b[3] >> l);
-  const uint32_t z0 = (uint32_t)(b[4] >> l), z1 = (uint32_t)(b[5] >> l);
-  int k = 0;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const uint32_t x = x0 + (c & 1), y = y0 + ((c >> 1) & 1), z = z0 + (c >> 2);
-    const bool in = x <= x1 && y <= y1 && z <= z1;
-    lo[c] = in ? morton3_key(x << l, y << l, z << l) : ~0ull;
-    cx[c] = x;
-    cy[c] = y;
-    cz[c] = z;
-    k += in ? 1 : 0;
+  if constexpr (kIn != 0) {
+    lo = permute_lanes<kQuad[kIn]>(lo);
+    hi = permute_lanes<kQuad[kIn]>(hi);
   }
-  cube_cas(lo, cx, cy, cz, 0, 1); cube_cas(lo, cx, cy, cz, 2, 3);
-  cube_cas(lo, cx, cy, cz, 4, 5); cube_cas(lo, cx, cy, cz, 6, 7);
-  cube_cas(lo, cx, cy, cz, 0, 2); cube_cas(lo, cx, cy, cz, 1, 3);
-  cube_cas(lo, cx, cy, cz, 4, 6); cube_cas(lo, cx, cy, cz, 5, 7);
-  cube_cas(lo, cx, cy, cz, 1, 2); cube_cas(lo, cx, cy, cz, 5, 6);
-  cube_cas(lo, cx, cy, cz, 0, 4); cube_cas(lo, cx, cy, cz, 1, 5);
-  cube_cas(lo, cx, cy, cz, 2, 6); cube_cas(lo, cx, cy, cz, 3, 7);
-  cube_cas(lo, cx, cy, cz, 2, 4); cube_cas(lo, cx, cy, cz, 3, 5);
-  cube_cas(lo, cx, cy, cz, 1, 2); cube_cas(lo, cx, cy, cz, 3, 4);
-  cube_cas(lo, cx, cy, cz, 5, 6);
-  return k;
+  return (uint64_t)hi << 32 | lo;
+}
+// 1 if the key of that lane comes before this lane's (equal keys by lane).
+template <int X>
+__device__ __forceinline__ uint32_t before(uint64_t key, int lane) {
+  constexpr int kTop = X & 4 ? 4 : X & 2 ? 2 : 1;
+  const uint64_t other = across<X>(key);
+  return other < key || (other == key && (lane & kTop)) ? 1u : 0u;
 }
 
 // One lane per (query, slot): eight slots per query, each a merged interval
@@ -458,10 +420,10 @@ __device__ __forceinline__ int query_cubes3(double qx, double qy, double qz, dou
 // (four slots per cube, 32 per query), each found by two searches inside the
 // cube's index range.  The reported ids and their order do not change.
 template <int SEARCH, bool REFINE>
-// Five waves per SIMD or more (the cubes sorted by a fixed network, so that
-// their arrays stay in registers): 1.71 ms binary, 1.16 ms with the static
-// search tree for 2^20 queries over 2^24 keys, against 1.89 and 1.39 ms with
-// the arrays in scratch memory.
+// Refined, a lane works out its own cube and its place among the eight lanes'
+// (all eight cubes in every lane, sorted by a network of 19 exchanges, took 71
+// registers for 54 and a quarter more instructions: 1.00 ms for 0.98 with the
+// static search tree, 2^20 queries over 2^24 keys; the lines of memory bound both).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void ranges_search3(
     const double* __restrict__ q, const double* __restrict__ delta, uint64_t m,
     const uint64_t* __restrict__ keys, uint64_t n, LearnedView lv, StreeView sv,
@@ -471,6 +433,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   const uint64_t j = (g >> 3) < m ? (perm ? perm[g >> 3] : g >> 3) : m;
   const int r = (int)(g & 7);
+  int slot = r;
   uint64_t B[4] = {0, 0, 0, 0}, E[4] = {0, 0, 0, 0};
   uint32_t fb = 0;
   bool bad = false, coarse = false;
@@ -500,24 +463,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
         }
       if (r < nr) find_range<SEARCH>(keys, n, lv, sv, mlo, mhi, B[0], E[0], fb);
     } else {
-      uint64_t lo[8];
-      uint32_t cx[8], cy[8], cz[8];
-      int64_t b[6];
-      int L = 0;
-      const int nr = query_cubes3(qx, qy, qz, d, lo, cx, cy, cz, &L, b);
-      // The lane's cube, taken with static indexes (a runtime index into the
-      // arrays would put them in scratch memory).
-      uint64_t mlo = 0;
-      uint32_t mx = 0, my = 0, mz = 0;
-#pragma unroll
-      for (int c = 0; c < 8; ++c)
-        if (c == r) {
-          mlo = lo[c];
-          mx = cx[c];
-          my = cy[c];
-          mz = cz[c];
-        }
-      if (r < nr) {
+      // A box of side at most 2^L meets at most two level-L cells per axis:
+      // lane r takes the cube at offsets (r, r / 2, r / 4) mod 2, and its slot
+      // is its key's place among the eight lanes' (those without a cube last).
+      int64_t b[6] = {0, -1, 0, -1, 0, -1};
+      const bool some = axis_box3(qx, d, b[0], b[1]) && axis_box3(qy, d, b[2], b[3]) &&
+                        axis_box3(qz, d, b[4], b[5]);
+      uint64_t side = (uint64_t)(b[1] - b[0] + 1);
+      side = (uint64_t)(b[3] - b[2] + 1) > side ? (uint64_t)(b[3] - b[2] + 1) : side;
+      side = (uint64_t)(b[5] - b[4] + 1) > side ? (uint64_t)(b[5] - b[4] + 1) : side;
+      const int L = side <= 1 ? 0 : 64 - __clzll(side - 1) < 21 ? 64 - __clzll(side - 1) : 21;
+      const uint32_t mx = (uint32_t)(b[0] >> L) + (r & 1);
+      const uint32_t my = (uint32_t)(b[2] >> L) + ((r >> 1) & 1);
+      const uint32_t mz = (uint32_t)(b[4] >> L) + (r >> 2);
+      const bool in = some && mx <= (uint32_t)(b[1] >> L) && my <= (uint32_t)(b[3] >> L) &&
+                      mz <= (uint32_t)(b[5] >> L);
+      const uint64_t key = morton3_key(mx << L, my << L, mz << L);
+      const uint64_t mlo = in ? key : ~0ull;
+      slot = (int)(before<1>(mlo, r) + before<2>(mlo, r) + before<3>(mlo, r) + before<4>(mlo, r) +
+                   before<5>(mlo, r) + before<6>(mlo, r) + before<7>(mlo, r));
+      if (in) {
         const uint64_t span = L >= 21 ? (1ull << 63) - 1 : (1ull << (3 * L)) - 1;
         find_range<SEARCH>(keys, n, lv, sv, mlo, mlo | span, B[0], E[0], fb);
         if (E[0] - B[0] > refine_min && L >= 1 && L < 21) {
@@ -596,7 +561,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     blk_rows[blockIdx.x] = s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3];
   }
   if (j < m) {
-    const uint64_t sidx = 8 * j + r;
+    const uint64_t sidx = 8 * j + slot;
     if (!REFINE) {
       slots[sidx] = make_uint2((uint32_t)B[0], (uint32_t)(E[0] - B[0]));
     } else {
