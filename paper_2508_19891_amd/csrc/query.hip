@@ -166,9 +166,42 @@ __device__ __forceinline__ uint64_t rows_of(uint64_t count) {
 }
 __device__ __forceinline__ uint64_t rows64_of(uint64_t count) { return (count + 63) >> 6; }
 
+// The value of the lane whose number differs in the bits of X (1..7) from this
+// one's; the lanes of a query are active together.
+template <int CTRL>
+__device__ __forceinline__ uint32_t permute_lanes(uint32_t v) {
+  uint32_t x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+  asm("" : "+v"(x));   // (never an operand modifier; see bcast16)
+  return x;
+}
+template <int X>
+__device__ __forceinline__ uint64_t across(uint64_t v) {
+  constexpr int kQuad[4] = {0xE4, 0xB1, 0x4E, 0x1B};   // lanes of four exchanged by xor
+  uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  constexpr int kIn = X & 4 ? X ^ 7 : X;   // mirrored in eight: xor 7
+  if constexpr (X & 4) {
+    lo = permute_lanes<0x141>(lo);
+    hi = permute_lanes<0x141>(hi);
+  }
+  if constexpr (kIn != 0) {
+    lo = permute_lanes<kQuad[kIn]>(lo);
+    hi = permute_lanes<kQuad[kIn]>(hi);
+  }
+  return (uint64_t)hi << 32 | lo;
+}
+// 1 if the key of that lane comes before this lane's (equal keys by lane).
+template <int X>
+__device__ __forceinline__ uint32_t before(uint64_t key, int lane) {
+  constexpr int kTop = X & 4 ? 4 : X & 2 ? 2 : 1;
+  const uint64_t other = across<X>(key);
+  return other < key || (other == key && (lane & kTop)) ? 1u : 0u;
+}
+
 // One lane per (query, slot): four slots per query (the method's ranges),
-// or eight (REFINE: two runs per cell of cells(Q)); the lane's work is the
-// body in query_lane.inc.  perm non-null: the queries in curve order, so that
+// or eight (REFINE: two runs per cell of cells(Q)).  QUAD: a lane works out its
+// own cell of the query's box alone, and the query's four lanes exchange keys to
+// order and merge them; else (early termination's list, inspected ranges) the
+// lane's work is the body in query_lane.inc.  perm non-null: the queries in curve order, so that
 // the searches of a workgroup meet in the same lines of the key array; slots
 // and records are laid out by query.  Each workgroup (64 queries) also sums
 // its counters, and its candidate rows if it holds 64 consecutive queries: one
@@ -176,7 +209,7 @@ __device__ __forceinline__ uint64_t rows64_of(uint64_t count) { return (count + 
 // serialise across the XCDs), and nothing to clear beforehand.
 // At least five waves per SIMD (at most 102 registers): the chains of
 // dependent probes need waves in flight.
-template <int CURVE, bool REFINE, int SEARCH>
+template <int CURVE, bool REFINE, int SEARCH, bool QUAD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void ranges_search(
     const double2* __restrict__ q, const double* __restrict__ delta, uint64_t m,
     const uint64_t* __restrict__ keys, uint64_t n, LearnedView lv, StreeView sv,
@@ -211,7 +244,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   const uint64_t pair = pairs ? (act ? pairs[g] : 0) : g;   // 4 * query + cell
   const int r = (int)(pair & 3);
   const uint64_t j = act ? (perm ? perm[pair >> 2] : pair >> 2) : m;
-  const uint64_t sidx = 4 * j + r;
+  uint64_t sidx = 4 * j + r;
 
   uint64_t b0 = 0, e0 = 0, b1 = 0, e1 = 0, klo = 0, khi = 0;
   int nr = 0;
@@ -240,8 +273,81 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
       nn = set_off[sj + 1] - base;
     }
   }
+  if constexpr (QUAD) {
+    if (j < m && !bad) {
+      const double2 qq = q[j];
+      const double d = delta[j];
+      if (!(finite64(qq.x) && finite64(qq.y) && finite64(d) && d >= 0.0)) {
+        bad = true;
+      } else {
+        // A box of side at most 2^L meets at most two level-L cells per axis:
+        // lane r takes the cell at offsets (r / 2, r mod 2).
+        int64_t box[4] = {0, -1, 0, -1};
+        const bool some = axis_box(qq.x, d, box[0], box[1]) && axis_box(qq.y, d, box[2], box[3]);
+        const uint64_t sx = (uint64_t)(box[1] - box[0] + 1), sy = (uint64_t)(box[3] - box[2] + 1);
+        const uint64_t side = sx > sy ? sx : sy;
+        const int L = side <= 1 ? 0 : 64 - __clzll(side - 1);   // ceil(log2 side)
+        const bool whole = L >= 32;
+        const int l = whole ? 0 : L;
+        const uint32_t x0 = (uint32_t)(box[0] >> l), y0 = (uint32_t)(box[2] >> l);
+        const uint32_t cx = whole ? 0 : x0 + (r >> 1), cy = whole ? 0 : y0 + (r & 1);
+        const bool in = some && (whole ? r == 0
+                                       : (uint32_t)(r >> 1) <= (uint32_t)(box[1] >> l) - x0 &&
+                                             (uint32_t)(r & 1) <= (uint32_t)(box[3] >> l) - y0);
+        const uint64_t span = whole ? ~0ull : (1ull << (2 * l)) - 1;
+        const uint64_t lo = in ? cell_key<CURVE>(lut, cx << l, cy << l) & ~span : ~0ull;
+        if constexpr (REFINE) {
+          // (A key is 2^64 - 1 only on level 0, where lane 0 has the one cell.)
+          sidx = 4 * j + before<1>(lo, r) + before<2>(lo, r) + before<3>(lo, r);
+          if (in) {
+            find_range<SEARCH>(keys + base, nn, lv, sv, lo, lo | span, b0, e0, fb);
+            b0 += base;
+            e0 += base;
+            ends += 2;
+            refine_cell<CURVE, SEARCH>(lut, keys, nn, lv, sv, refine_min, ball, lo, lo | span, cx,
+                                       cy, L, box, qq.x, qq.y, d, b0, e0, b1, e1, fb, ends);
+          }
+        } else {
+          // Cells next to each other in key order are one range: of the first of
+          // them, whose lane takes the place of its key among the first ones.
+          const uint32_t q0 = lane_id() & ~3u;
+          const uint32_t present = (uint32_t)(__ballot(in) >> q0) & 15u;
+          const uint64_t other[3] = {across<1>(lo), across<2>(lo), across<3>(lo)};
+          const uint64_t next = span + 1;
+          bool after[3] = {false, false, false}, first = in;
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            // (The comparison first: on level 31 the differences wrap.)
+            const bool there = (present >> (r ^ (x + 1))) & 1u;
+            const bool above = there && other[x] > lo, below = there && other[x] < lo;
+            const uint64_t up = other[x] - lo;
+            after[0] |= above && up == next;
+            after[1] |= above && up == 2 * next;
+            after[2] |= above && up == 3 * next;
+            first = first && !(below && lo - other[x] == next);
+          }
+          const uint32_t firsts = (uint32_t)(__ballot(first) >> q0) & 15u;
+          uint32_t at = 0;
+#pragma unroll
+          for (int x = 0; x < 3; ++x)
+            at += ((firsts >> (r ^ (x + 1))) & 1u) && other[x] < lo ? 1u : 0u;
+          if (!first)   // the other lanes' places, empty, come last
+            at = (uint32_t)__popc(firsts) + (uint32_t)__popc(~firsts & ((1u << r) - 1));
+          sidx = 4 * j + at;
+          if (first) {
+            const uint32_t cells = !after[0] ? 1u : !after[1] ? 2u : !after[2] ? 3u : 4u;
+            find_range<SEARCH>(keys + base, nn, lv, sv, lo, lo + cells * next - 1, b0, e0, fb);
+            b0 += base;
+            e0 += base;
+            ends += 2;
+          }
+        }
+      }
+    }
+  } else {
 #include "query_lane.inc"
-  (void)pruned;   // counted where the work list is made
+    (void)pruned;   // counted where the work list is made
+  }
   // Candidates, rows, flags (and learned-index endpoints and fallbacks) of
   // the workgroup.
   __shared__ uint64_t s_cand[4], s_rows[4], s_rows64[4];
@@ -380,37 +486,6 @@ __device__ int query_ranges3(double qx, double qy, double qz, double d, uint64_t
     }
   }
   return r;
-}
-
-// The value of the lane whose number differs in the bits of X (1..7) from this
-// one's; the eight lanes of a group are active together.
-template <int CTRL>
-__device__ __forceinline__ uint32_t permute_lanes(uint32_t v) {
-  uint32_t x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-  asm("" : "+v"(x));   // (never an operand modifier; see bcast16)
-  return x;
-}
-template <int X>
-__device__ __forceinline__ uint64_t across(uint64_t v) {
-  constexpr int kQuad[4] = {0xE4, 0xB1, 0x4E, 0x1B};   // lanes of four exchanged by xor
-  uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-  constexpr int kIn = X & 4 ? X ^ 7 : X;   // mirrored in eight: xor 7
-  if constexpr (X & 4) {
-    lo = permute_lanes<0x141>(lo);
-    hi = permute_lanes<0x141>(hi);
-  }
-  if constexpr (kIn != 0) {
-    lo = permute_lanes<kQuad[kIn]>(lo);
-    hi = permute_lanes<kQuad[kIn]>(hi);
-  }
-  return (uint64_t)hi << 32 | lo;
-}
-// 1 if the key of that lane comes before this lane's (equal keys by lane).
-template <int X>
-__device__ __forceinline__ uint32_t before(uint64_t key, int lane) {
-  constexpr int kTop = X & 4 ? 4 : X & 2 ? 2 : 1;
-  const uint64_t other = across<X>(key);
-  return other < key || (other == key && (lane & kTop)) ? 1u : 0u;
 }
 
 // One lane per (query, slot): eight slots per query, each a merged interval
@@ -1874,15 +1949,22 @@ hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
   {
     ProfScope ps(learned ? "ranges_learned" : stree ? "ranges_stree" : "ranges_search", s);
 #define SFC_RANGES(C, R, S)                                                                  \
-  ranges_search<C, R, S><<<query_blocks(qs), 256, 0, s>>>(                                    \
+  if (dense || dbg) SFC_RANGES_Q(C, R, S, false);                                            \
+  else SFC_RANGES_Q(C, R, S, true)
+#define SFC_RANGES_Q(C, R, S, Q)                                                             \
+  ranges_search<C, R, S, Q><<<query_blocks(qs), 256, 0, s>>>(                                 \
       (const double2*)P.q, P.delta, m, P.keys, P.n, lv, sv, P.refine_min, P.ball,             \
       dbg ? nullptr : P.occ, pairs, pair_total, P.qset, P.set_off, P.n_sets, perm, rec,       \
       qs.slots, blk_rows, qs.blk_stat, qs.blk_rows64, qs.blk_learned, P.dbg_lo, P.dbg_hi,  \
       P.dbg_b, P.dbg_e, P.dbg_nr)
 #define SFC_RANGES_R(C, R)                      \
-  if (learned) SFC_RANGES(C, R, 1);             \
-  else if (stree) SFC_RANGES(C, R, 2);          \
-  else SFC_RANGES(C, R, 0);
+  if (learned) {                                \
+    SFC_RANGES(C, R, 1);                        \
+  } else if (stree) {                           \
+    SFC_RANGES(C, R, 2);                        \
+  } else {                                      \
+    SFC_RANGES(C, R, 0);                        \
+  }
 #define SFC_RANGES_C(C)                         \
   if (refine) {                                 \
     SFC_RANGES_R(C, true)                       \
@@ -1897,6 +1979,7 @@ hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
 #undef SFC_RANGES_C
 #undef SFC_RANGES_R
 #undef SFC_RANGES
+#undef SFC_RANGES_Q
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (dense && (e = launch_slot_rows(qs, nullptr, qs.blk_rows, s)) != hipSuccess) return e;

@@ -499,4 +499,47 @@ __device__ __forceinline__ CellRuns cell_runs(const uint16_t* lut, uint64_t lo, 
   return cr;
 }
 
+// A cell of cells(Q) (level L, grid cell (cx, cy), keys [lo, hi], index range
+// [b0, e0)) that holds more than refine_min keys: the index ranges [b0, e0) and
+// [b1, e1) of the key runs of its kept sub-cells instead.
+template <int CURVE, int SEARCH>
+__device__ __forceinline__ void refine_cell(const uint16_t* lut, const uint64_t* __restrict__ keys,
+                                            uint64_t nn, const LearnedView& lv,
+                                            const StreeView& sv, uint32_t refine_min, bool ball,
+                                            uint64_t lo, uint64_t hi, uint32_t cx, uint32_t cy,
+                                            int L, const int64_t (&box)[4], double qx, double qy,
+                                            double d, uint64_t& b0, uint64_t& e0, uint64_t& b1,
+                                            uint64_t& e1, uint32_t& fb, uint32_t& ends) {
+  if (e0 - b0 <= refine_min) return;
+  const CellRuns cr = cell_runs<CURVE>(lut, lo, hi, cx, cy, L, box, ball, qx, qy, d);
+  if (cr.kind == 0) {
+    e0 = b0;   // no point of the cell can be reported
+  } else if (cr.kind > 0) {
+    if (SEARCH == 1) {
+      // The learned index locates the runs too (it serves whole arrays only,
+      // so positions are absolute); its windows are narrower than the cell's
+      // index range.
+      find_range<1>(keys, nn, lv, sv, cr.lo0, cr.hi0, b0, e0, fb);
+      ends += 2;
+      if (cr.kind == 2) {
+        find_range<1>(keys, nn, lv, sv, cr.lo1, cr.hi1, b1, e1, fb);
+        ends += 2;
+      }
+    } else {
+      // Both runs lie in the cell's index range: searched there, together.
+      const uint64_t pb = b0;
+      const uint64_t kl[2] = {cr.lo0, cr.lo1}, kh[2] = {cr.hi0, cr.hi1};
+      const bool use[2] = {true, cr.kind == 2};
+      uint64_t sb[2], se[2];
+      search_lockstep<2>(keys + pb, e0 - pb, kl, kh, use, sb, se);
+      b0 = pb + sb[0];
+      e0 = pb + se[0];
+      if (cr.kind == 2) {
+        b1 = pb + sb[1];
+        e1 = pb + se[1];
+      }
+    }
+  }
+}
+
 }  // namespace sfc

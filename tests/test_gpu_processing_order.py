@@ -168,3 +168,29 @@ def test_row_edges(n):
                         g.result()
             g.close()
     idx.close()
+
+
+@pytest.mark.parametrize("refine", [False, True])
+@pytest.mark.parametrize("curve", [sfc.MORTON, sfc.HILBERT, sfc.MORTON3])
+def test_box_levels(curve, refine):
+    """Boxes of every level, from one cell of the grid to the whole square (or
+    cube), about all its corners and edges: one to four (eight) cells, next to
+    each other in key order or not."""
+    rng = np.random.default_rng(17 + curve)
+    dim = 3 if curve == sfc.MORTON3 else 2
+    pts = rng.random((3000, dim))
+    pts[:200] = np.round(pts[:200] * 8) / 8 * (1 - 2.0 ** -40)
+    q = rng.random((4000, dim))
+    q[::4] = np.round(q[::4] * 4) / 4            # corners and centres of the top cells
+    q[1::4] = pts[rng.integers(0, 3000, 1000)]
+    d = 2.0 ** rng.uniform(-34, 1, 4000)
+    d[::3] = 2.0 ** rng.uniform(-4, 0.5, len(d[::3]))
+    if dim == 3:
+        want = oracle.query3(oracle.build3(pts), q, d, nthreads=8)
+    else:
+        want = oracle.query(oracle.build(pts, curve), q, d, curve, nthreads=8)
+    for search in (sfc.BINARY, sfc.STREE) + ((sfc.LEARNED,) if dim == 2 else ()):
+        for early_term in (False, True)[:1 if dim == 3 else 2]:
+            idx = sfc.Index(dev(pts), curve, search=search, refine=refine, early_term=early_term)
+            same(idx.query(dev(q), dev(d)), want)
+            idx.close()
