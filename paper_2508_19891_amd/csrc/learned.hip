@@ -54,8 +54,11 @@ __device__ __forceinline__ float inside01(float v) { return (v > 0.f && v < 1.f)
 // the weight gradient, whose sum runs over the samples, goes through LDS:
 // waves 0..3 take one 16x16 tile of it each, waves 4..6 the column sums, and
 // each lane updates (Adam) the parameters whose gradients it holds.
-// 256 steps over 2^16 samples take 0.94 ms; 26.1 ms with one sample per lane
-// and every weight read from LDS for each multiply-add.
+// 256 steps over 2^16 samples take 0.82 ms (0.94 with the lanes' four updates one
+// after another, each behind branches); 26.1 ms with one sample per lane and every
+// weight read from LDS for each multiply-add.  A step's 7600 cycles are 3600 of
+// matrix instructions and 3300 of vector ones a SIMD, in phases that follow from
+// each other.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWStride = 36;             // LDS row of 32 weights
@@ -128,11 +131,14 @@ __device__ __forceinline__ void store_param(TrainLds& S, int at, float v) {
 // Gradient of the mean squared error over samples 0..cnt - 1 of a batch for
 // the parameters in S: G[r] is that of owned_param(r).  x, t: the sample of
 // this lane, 16 w + l % 16 (zeros from cnt on).  Returns the sample's error
-// y - t.  One barrier; the caller's next one ends the reads of S.
-__device__ __forceinline__ float batch_gradient(TrainLds& S, float x, float t, int cnt,
+// y - t.  One barrier; the caller's next one ends the reads of S.  FULL: cnt is
+// kBatch.
+template <bool FULL>
+__device__ __forceinline__ float batch_gradient(TrainLds& S, float x, float t, int count,
                                                 float G[kOwned]) {
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, c = l & 15, grp = l >> 4;
-  const bool mine = 16 * w + c < cnt;
+  const int cnt = FULL ? kBatch : count;
+  const bool mine = FULL || 16 * w + c < cnt;
   // Forward.  Row r of tile t stands for unit 16 t + 4 (r % 4) + r / 4.
   const int row0 = 4 * (c & 3) + (c >> 2);
   float w1[8], b1[8], w3[8], a1[8], h1[8], a2[8], h2[8];
@@ -234,7 +240,7 @@ __global__ __launch_bounds__(kTrainThreads) void learned_grad_kernel(const float
   const int b = 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
   const float x = b < cnt ? xs[b] : 0.f, t = b < cnt ? ts[b] : 0.f;
   float G[kOwned];
-  const float err = batch_gradient(S, x, t, cnt, G);
+  const float err = batch_gradient<false>(S, x, t, cnt, G);
 #pragma unroll
   for (int r = 0; r < kOwned; ++r) {
     const int at = owned_param(r);
@@ -301,14 +307,15 @@ __global__ __launch_bounds__(256) void learned_loss(const float* __restrict__ sq
                                                     float* __restrict__ loss) {
   __shared__ float s_red[256];
   float acc = 0.f;
-  // Eight loads in flight per thread, added in order (positions past the end
-  // load the last one and add nothing).
-  for (uint32_t s0 = threadIdx.x; s0 < S; s0 += 256 * 8) {
-    float v[8];
+  // Many loads in flight per thread (a round of them is a round trip to memory),
+  // added in order; positions past the end load the last one and add nothing.
+  constexpr int kAtOnce = 64;
+  for (uint32_t s0 = threadIdx.x; s0 < S; s0 += 256 * kAtOnce) {
+    float v[kAtOnce];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = sq[s0 + 256 * k < S ? s0 + 256 * k : S - 1];
+    for (int k = 0; k < kAtOnce; ++k) v[k] = sq[s0 + 256 * k < S ? s0 + 256 * k : S - 1];
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
+    for (int k = 0; k < kAtOnce; ++k)
       if (s0 + 256 * k < S) acc += v[k];
   }
   s_red[threadIdx.x] = acc;
@@ -343,30 +350,57 @@ __global__ __launch_bounds__(kTrainThreads) void learned_train(const float* __re
   // A step's samples are loaded during the step before it.
   uint32_t s = (uint32_t)((uint64_t)b * 2654435761ull) & mask;
   float x = xs[s], t = ts[s];
-  const int owned = (threadIdx.x >> 6) < 4 ? kOwned : (threadIdx.x >> 6) < 7 ? 1 : 0;
+  // Where the lane's parameters lie in LDS, and whether they stay nonnegative (the
+  // second layer's weights twice, as its transpose holds them too).
+  const int w = threadIdx.x >> 6, at0 = owned_param(0);
+  // (As numbers of words: pointers would be followed as generic ones.)
+  float* const lds = (float*)&L;
+  int to[kOwned] = {}, tt[kOwned] = {};
+  bool nonneg = false;
+  if (w < 4) {
+#pragma unroll
+    for (int r = 0; r < kOwned; ++r) {
+      const int e = owned_param(r) - kOffW2, i = e / kHidden, k = e % kHidden;
+      to[r] = (int)(L.w2 - lds) + i * kWStride + unit_pos(k);
+      tt[r] = (int)(L.w2t - lds) + k * kWStride + unit_pos(i);
+    }
+  } else if (at0 >= 0) {
+    to[0] = at0 >= kOffB3   ? (int)(L.b3 - lds)
+            : at0 >= kOffW3 ? (int)(L.w3 - lds) + unit_pos(at0 - kOffW3)
+            : at0 >= kOffB2 ? (int)(L.b2 - lds) + unit_pos(at0 - kOffB2)
+            : at0 >= kOffB1 ? (int)(L.b1 - lds) + unit_pos(at0 - kOffB1)
+                            : (int)(L.w1 - lds) + unit_pos(at0);
+    nonneg = at0 < kOffB1 || (at0 >= kOffW3 && at0 < kOffB3);
+  }
   __syncthreads();
   for (uint32_t st = 0; st < steps; ++st) {
     s = (uint32_t)(((uint64_t)(st + 1) * kBatch + b) * 2654435761ull) & mask;
     const float nx = xs[s], nt = ts[s];
     float G[kOwned] = {0.f, 0.f, 0.f, 0.f};
-    batch_gradient(L, x, t, kBatch, G);
+    batch_gradient<true>(L, x, t, kBatch, G);
     b1t *= b1;
     b2t *= b2;
-#pragma unroll
-    for (int r = 0; r < kOwned; ++r) {
-      if (r >= owned) break;
-      const int at = owned_param(r);
-      if (at < 0) break;
+    const float c1 = 1.f - b1t, c2 = 1.f - b2t;
+    auto adam = [&](int r) {
       const float gi = G[r];
       Mo[r] = b1 * Mo[r] + (1.f - b1) * gi;
       Vo[r] = b2 * Vo[r] + (1.f - b2) * gi * gi;
-      const float mh = Mo[r] / (1.f - b1t), vh = Vo[r] / (1.f - b2t);
-      float v = P[r] - lr * mh / (sqrtf(vh) + eps);
-      const bool nonneg =
-          (at < kOffB1) || (at >= kOffW2 && at < kOffB2) || (at >= kOffW3 && at < kOffB3);
-      if (nonneg) v = fmaxf(v, 0.f);
-      P[r] = v;
-      store_param(L, at, v);
+      const float mh = Mo[r] / c1, vh = Vo[r] / c2;
+      return P[r] - lr * mh / (sqrtf(vh) + eps);
+    };
+    // (No branch between a lane's four: their chains of divisions run together.)
+    if (w < 4) {
+#pragma unroll
+      for (int r = 0; r < kOwned; ++r) P[r] = fmaxf(adam(r), 0.f);
+#pragma unroll
+      for (int r = 0; r < kOwned; ++r) {
+        lds[to[r]] = P[r];
+        lds[tt[r]] = P[r];
+      }
+    } else if (at0 >= 0) {
+      const float v = adam(0);
+      P[0] = nonneg ? fmaxf(v, 0.f) : v;
+      lds[to[0]] = P[0];
     }
     x = nx;
     t = nt;
