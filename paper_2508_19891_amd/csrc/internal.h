@@ -148,6 +148,7 @@ struct QueryScratch {
   uint64_t* blk_rows64;    //   its rows of 64 candidates,
   uint64_t* blk_place;     //   (queries in curve order) its rows,
   uint32_t* blk_learned;   //   its learned endpoints and fallbacks
+  void* groups;            // per group of workgroups: its rows and counters
   void* rec;               // per query: the test pass's record (32 B)
   uint32_t* perm;          // the queries in curve order
   uint64_t* out_base;      // per query: added to the hits before a row gives its output

@@ -803,6 +803,25 @@ __device__ __forceinline__ uint64_t xcd_tile(uint64_t b, uint64_t grid, uint64_t
   return k < per && t < ntiles ? t : ~0ull;
 }
 
+// Exclusive scan of one uint64 per thread over 256 threads; *total gets the
+// sum.
+__device__ __forceinline__ uint64_t scan256_u64(uint64_t v, uint64_t* s_w, uint64_t* total) {
+  const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
+  uint64_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_up(x, o, 64);
+    if (lane >= (uint32_t)o) x += y;
+  }
+  if (lane == 63) s_w[wv] = x;
+  __syncthreads();
+  uint64_t before = 0;
+  for (uint32_t w = 0; w < wv; ++w) before += s_w[w];
+  *total = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+  __syncthreads();
+  return before + x - v;
+}
+
 // The batch's counters, from those of the workgroups: stat and rows64 (ns words
 // each: candidates and flags; rows of 64), learned (ns words or null: endpoints << 16 |
 // fallbacks), and with early termination flags and pruned (np words each, or
@@ -817,26 +836,25 @@ struct BatchStats {
   uint32_t np;
 };
 
-template <int WAVES>
-__device__ __forceinline__ void sum_stats(const BatchStats& B, BatchStatus* status,
-                                          BatchStatus* host) {
-  __shared__ uint64_t s_v[6][WAVES];
-  uint64_t v[6] = {0, 0, 0, 0, 0, 0};   // candidates, endpoints, fallbacks, pruned, rows, flags
+// Adds the counters of entries [first, ns) in steps of `step` (np likewise) to v:
+// candidates, endpoints, fallbacks, pruned, rows, flags.
+__device__ __forceinline__ void add_stats(const BatchStats& B, uint32_t first, uint32_t step,
+                                          uint32_t ns, uint32_t np, uint64_t (&v)[6]) {
   // Eight words in flight per thread: those past the end load the last one
   // and are not added.
-  for (uint32_t i0 = threadIdx.x; i0 < B.ns; i0 += WAVES * 64 * 8) {
+  for (uint32_t i0 = first; i0 < ns; i0 += step * 8) {
     uint64_t w[8], rw[8];
     uint32_t l[8];
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) {
-      const uint32_t i = i0 + k * WAVES * 64, ic = i < B.ns ? i : B.ns - 1;
+      const uint32_t i = i0 + k * step, ic = i < ns ? i : ns - 1;
       w[k] = B.stat[ic];
       rw[k] = B.rows64[ic];
       l[k] = B.learned ? B.learned[ic] : 0u;
     }
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k)
-      if (i0 + k * WAVES * 64 < B.ns) {
+      if (i0 + k * step < ns) {
         v[0] += w[k] & (kStatInvalid - 1);
         v[5] |= w[k] >> kStatShift;
         v[4] += rw[k];
@@ -844,10 +862,16 @@ __device__ __forceinline__ void sum_stats(const BatchStats& B, BatchStatus* stat
         v[2] += l[k] & 0xFFFFu;
       }
   }
-  for (uint32_t i = threadIdx.x; i < B.np; i += WAVES * 64) {
+  for (uint32_t i = first; i < np; i += step) {
     v[3] += B.pruned[i];
     v[5] |= B.flags[i] >> kStatShift;
   }
+}
+
+// The workgroup's sums of v, in thread 0.
+template <int WAVES>
+__device__ __forceinline__ void sum_over_waves(uint64_t (&v)[6]) {
+  __shared__ uint64_t s_v[6][WAVES];
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
 #pragma unroll
@@ -858,19 +882,108 @@ __device__ __forceinline__ void sum_stats(const BatchStats& B, BatchStatus* stat
 #pragma unroll
     for (int k = 0; k < 6; ++k) s_v[k][threadIdx.x >> 6] = v[k];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    BatchStatus st{};
-    for (int w = 0; w < WAVES; ++w) {
-      st.candidates += s_v[0][w];
-      st.endpoints += s_v[1][w];
-      st.fallbacks += s_v[2][w];
-      st.pruned += s_v[3][w];
-      st.rows += s_v[4][w];
-      if (s_v[5][w] & 1) st.err |= kErrInvalidQuery;
-      if (s_v[5][w] & 2) st.coarse = 1;
+  if (threadIdx.x == 0)
+    for (int w = 1; w < WAVES; ++w) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) v[k] += s_v[k][w];
+      v[5] |= s_v[5][w];
     }
-    *status = st;
-    if (host) *host = st;
+}
+
+__device__ __forceinline__ void put_stats(const uint64_t (&v)[6], BatchStatus* status,
+                                          BatchStatus* host) {
+  BatchStatus st{};
+  st.candidates = v[0];
+  st.endpoints = v[1];
+  st.fallbacks = v[2];
+  st.pruned = v[3];
+  st.rows = v[4];
+  if (v[5] & 1) st.err |= kErrInvalidQuery;
+  if (v[5] & 2) st.coarse = 1;
+  *status = st;
+  if (host) *host = st;
+}
+
+// The same by one workgroup alone.
+template <int WAVES>
+__device__ __forceinline__ void sum_stats(const BatchStats& B, BatchStatus* status,
+                                          BatchStatus* host) {
+  uint64_t v[6] = {0, 0, 0, 0, 0, 0};
+  add_stats(B, threadIdx.x, WAVES * 64, B.ns, B.np, v);
+  sum_over_waves<WAVES>(v);
+  if (threadIdx.x == 0) put_stats(v, status, host);
+}
+
+// Batches of more search workgroups than this sum their rows and counters in two
+// launches: group_sums by groups of kGroupBlocks, then one workgroup over the
+// groups.  (One workgroup over all is a chain of rounds of loads: 83 us at 2^16
+// workgroups and 21 at 2^14, by groups 12 and 9; at 2^12 both take about 9.)
+constexpr uint32_t kOneScan = 4096;
+constexpr uint32_t kGroupBlocks = 1024;
+struct GroupSums {
+  uint64_t rows;     // of the group; then of the groups before it
+  uint64_t v[6];     // the counters of its entries
+  uint64_t pad;
+};
+
+// Group g: its rows and counters, and the exclusive scan of its workgroups' rows.
+__global__ __launch_bounds__(256) void group_sums(const uint64_t* __restrict__ blk_rows,
+                                                  uint32_t nblk, uint64_t* __restrict__ blk_off,
+                                                  BatchStats B, bool stats,
+                                                  GroupSums* __restrict__ groups) {
+  __shared__ uint64_t s_w[4];
+  const uint32_t first = blockIdx.x * kGroupBlocks, tid = threadIdx.x;
+  constexpr uint32_t kPer = kGroupBlocks / 256;
+  const uint32_t f = first + tid * kPer;
+  uint64_t v[kPer], sum = 0, total;
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) v[i] = f + i < nblk ? blk_rows[f + i] : 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) sum += v[i];
+  uint64_t run = scan256_u64(sum, s_w, &total);
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    if (f + i < nblk) blk_off[f + i] = run;
+    run += v[i];
+  }
+  uint64_t c[6] = {0, 0, 0, 0, 0, 0};
+  if (stats) {
+    const uint32_t end = first + kGroupBlocks;
+    add_stats(B, first + tid, 256, B.ns < end ? B.ns : end, B.np < end ? B.np : end, c);
+    sum_over_waves<4>(c);
+  }
+  if (tid == 0) {
+    groups[blockIdx.x].rows = total;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) groups[blockIdx.x].v[k] = c[k];
+  }
+}
+
+// One workgroup: the groups' rows -> the rows before each; the total and the
+// counters as batch_scan gives them.
+__global__ __launch_bounds__(256) void group_scan(GroupSums* __restrict__ groups, uint32_t count,
+                                                  uint64_t* __restrict__ rows_out, bool stats,
+                                                  BatchStatus* status, BatchStatus* host) {
+  __shared__ uint64_t s_w[4];
+  const uint32_t tid = threadIdx.x;
+  uint64_t carry = 0, c[6] = {0, 0, 0, 0, 0, 0};
+  for (uint32_t g0 = 0; g0 < count; g0 += 256) {
+    const uint32_t g = g0 + tid;
+    uint64_t rows = 0, total;
+    if (g < count) {
+      rows = groups[g].rows;
+#pragma unroll
+      for (int k = 0; k < 5; ++k) c[k] += groups[g].v[k];
+      c[5] |= groups[g].v[5];
+    }
+    const uint64_t before = scan256_u64(rows, s_w, &total);
+    if (g < count) groups[g].rows = carry + before;
+    carry += total;
+  }
+  if (tid == 0) *rows_out = carry;
+  if (stats) {
+    sum_over_waves<4>(c);
+    if (tid == 0) put_stats(c, status, host);
   }
 }
 
@@ -948,25 +1061,6 @@ __device__ __forceinline__ void load_slots(const uint2* __restrict__ slots,
   }
 }
 
-// Exclusive scan of one uint64 per thread over 256 threads; *total gets the
-// sum.
-__device__ __forceinline__ uint64_t scan256_u64(uint64_t v, uint64_t* s_w, uint64_t* total) {
-  const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
-  uint64_t x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t y = __shfl_up(x, o, 64);
-    if (lane >= (uint32_t)o) x += y;
-  }
-  if (lane == 63) s_w[wv] = x;
-  __syncthreads();
-  uint64_t before = 0;
-  for (uint32_t w = 0; w < wv; ++w) before += s_w[w];
-  *total = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-  __syncthreads();
-  return before + x - v;
-}
-
 // Rows of each workgroup's K * 256 slots, from the slots (where the search
 // kernel's workgroups do not hold the queries of as many consecutive places).
 template <int K>
@@ -997,7 +1091,8 @@ constexpr uint32_t kFusedBlocks = 1024;
 template <int K, bool FUSED>
 __global__ __launch_bounds__(256) void expand_rows(
     uint64_t* __restrict__ row_off, const uint2* __restrict__ slots,
-    const uint32_t* __restrict__ perm, const uint64_t* __restrict__ blk_rows, const uint64_t* __restrict__ blk_off, BatchStats B,
+    const uint32_t* __restrict__ perm, const uint64_t* __restrict__ blk_rows,
+    const uint64_t* __restrict__ blk_off, const GroupSums* __restrict__ groups, BatchStats B,
     BatchStatus* status, uint64_t m, int ss, uint64_t rbase, uint64_t row_end, uint64_t max_rows64,
     uint2* __restrict__ row_meta, uint16_t* __restrict__ row_info) {
   __shared__ uint64_t st[256 * K + 1];
@@ -1025,7 +1120,7 @@ __global__ __launch_bounds__(256) void expand_rows(
       }
     }
   } else {
-    row0 = blk_off[blockIdx.x];
+    row0 = blk_off[blockIdx.x] + (groups ? groups[blockIdx.x / kGroupBlocks].rows : 0);
     total = row_off[m];
     if (blockIdx.x == 0 && tid == 0 && status->rows > max_rows64) status->err |= kErrOverflow;
   }
@@ -1742,6 +1837,7 @@ bool query_scratch_carve(void* base, uint64_t m, QueryScratch* qs, uint32_t slot
   qs->blk_place = qs->blk_rows64 + nblk;
   qs->blk_learned = (uint32_t*)(qs->blk_place + nblk);
   p += align256(nblk * 44);
+  qs->groups = p;                 p += align256((nblk + kGroupBlocks - 1) / kGroupBlocks * sizeof(GroupSums));
   qs->rec = p;                    p += align256(m * 32);
   qs->perm = (uint32_t*)p;        p += align256(m * 4);
   qs->out_base = (uint64_t*)p;    p += align256(m * 8);
@@ -1829,16 +1925,37 @@ hipError_t launch_slot_rows(const QueryScratch& qs, const uint32_t* perm, uint64
   return hipGetLastError();
 }
 
+// The groups of a batch whose rows are scanned by groups, or null.
+GroupSums* scan_groups(const QueryScratch& qs) {
+  return query_blocks(qs) > kOneScan ? (GroupSums*)qs.groups : nullptr;
+}
+
+// The scan of the workgroups' rows (blk_off within their groups), and with stats
+// the batch's counters.
+hipError_t launch_rows_scan(const QueryScratch& qs, const uint64_t* blk_rows, bool stats,
+                            BatchStatus* host, hipStream_t s) {
+  ProfScope ps("scan", s);
+  const uint32_t nblk = query_blocks(qs);
+  if (GroupSums* groups = scan_groups(qs)) {
+    const uint32_t count = (nblk + kGroupBlocks - 1) / kGroupBlocks;
+    group_sums<<<count, 256, 0, s>>>(blk_rows, nblk, qs.blk_off, stats_of(qs), stats, groups);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    group_scan<<<1, 256, 0, s>>>(groups, count, qs.row_off + qs.m, stats, qs.status, host);
+    return hipGetLastError();
+  }
+  batch_scan<<<1, 1024, 0, s>>>(blk_rows, nblk, qs.blk_off, qs.row_off + qs.m, stats_of(qs), stats,
+                                qs.status, host);
+  return hipGetLastError();
+}
+
 // After the search: the rows' scan over the search's workgroups and the
 // batch's counters, unless expand_rows does both (fused).
 hipError_t finish_ranges(QueryScratch& qs, bool need_rows, BatchStatus* host, hipStream_t s) {
   const uint32_t nblk = query_blocks(qs);
   qs.fused = !need_rows && nblk <= kFusedBlocks && qs.stats_np == 0 && !qs.perm_made;
   if (qs.fused) return hipSuccess;
-  ProfScope ps("scan", s);
-  batch_scan<<<1, 1024, 0, s>>>(qs.perm_made ? qs.blk_place : qs.blk_rows, nblk, qs.blk_off,
-                                qs.row_off + qs.m, stats_of(qs), true, qs.status, host);
-  return hipGetLastError();
+  return launch_rows_scan(qs, qs.perm_made ? qs.blk_place : qs.blk_rows, true, host, s);
 }
 
 }  // namespace
@@ -2022,14 +2139,12 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
     if (ordered && (e = order_queries(P.q, m, P.dim == 3 ? SFC_CURVE_MORTON3 : P.curve, P.keys, P.n,
                                       qs.perm, qs.order_scratch, s)) != hipSuccess)
       return e;
-    ProfScope ps("scan", s);
     uint64_t* rows = ordered ? qs.blk_place : qs.blk_rows;
     if ((e = launch_slot_rows(qs, perm, rows, s)) != hipSuccess) return e;
-    batch_scan<<<1, 1024, 0, s>>>(rows, query_blocks(qs), qs.blk_off, qs.row_off + m,
-                                  stats_of(qs), qs.fused, qs.status, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_rows_scan(qs, rows, qs.fused, nullptr, s)) != hipSuccess) return e;
     qs.fused = false;
   }
+  const GroupSums* groups = scan_groups(qs);
   const bool fused_units = !ordered && chunks == 1 && ch_tiles * kTileUnits <= kFusedUnits;
   const uint64_t* total_dev = qs.row_off + m;
   // A batch with more rows is flagged, and none of its rows is tested.
@@ -2051,7 +2166,8 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
       ProfScope ps("expand_rows", s);
 #define SFC_EXPAND(K, F)                                                                     \
   expand_rows<K, F><<<query_blocks(qs), 256, 0, s>>>(qs.row_off, qs.slots, perm, blk_rows, \
-                                                     qs.blk_off, stats_of(qs), qs.status, m, qs.ss, rbase,  \
+                                                     qs.blk_off, groups, stats_of(qs), qs.status, m, \
+                                                     qs.ss, rbase,                           \
                                                      row_end, max_rows64, c.meta, c.info)
       switch (slots_per_thread(qs)) {
         case 1: if (qs.fused) SFC_EXPAND(1, true); else SFC_EXPAND(1, false); break;

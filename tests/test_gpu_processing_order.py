@@ -23,7 +23,7 @@ def same(got, want):
     assert torch.equal(ids, dev(want[1].view(np.int32), torch.int32))
 
 
-@pytest.mark.parametrize("m", [1, 63, 64, 65, 1024, 1025, 4097, 65536, 65537])
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 1024, 1025, 4097, 65536, 65537, 262_145])
 @pytest.mark.parametrize("curve,refine", [(sfc.MORTON, False), (sfc.HILBERT, True)])
 def test_batch_sizes(m, curve, refine):
     wl = workload.clustered_loguniform(n=30_011, m=m, curve=curve, seed=m, c_hi=60.0)
@@ -194,3 +194,33 @@ def test_box_levels(curve, refine):
             idx = sfc.Index(dev(pts), curve, search=search, refine=refine, early_term=early_term)
             same(idx.query(dev(q), dev(d)), want)
             idx.close()
+
+
+@pytest.mark.parametrize("early_term", [False, True])
+@pytest.mark.parametrize("m", [262_144, 262_145, 400_001, 16_800_001])
+def test_many_queries(m, early_term):
+    """The rows' scan in one workgroup and by groups (one and more than one round
+    of them): a few queries among many that lie outside the domain, one of them
+    invalid in the end."""
+    n, k = 20_000, 1000
+    pts = workload.uniform_points(n, 8)
+    rng = np.random.default_rng(m)
+    at = np.unique(np.concatenate([[0, m - 1], rng.integers(0, m, k)]))
+    qs, ds = rng.random((len(at), 2)), 10.0 ** rng.uniform(-4, -1, len(at))
+    want = oracle.query(oracle.build(pts, sfc.MORTON), qs, ds, sfc.MORTON, nthreads=8)
+    q = torch.full((m, 2), 5.0, dtype=torch.float64, device=DEV)
+    d = torch.full((m,), 0.5, dtype=torch.float64, device=DEV)
+    where = torch.as_tensor(at, device=DEV)
+    q[where], d[where] = dev(qs), dev(ds)
+    idx = sfc.Index(dev(pts), sfc.MORTON, early_term=early_term)
+    off, ids = idx.query(q, d)
+    assert torch.equal(ids, dev(want[1].view(np.int32), torch.int32))
+    assert torch.equal(off[where], dev(want[0][:-1].view(np.int64), torch.int64))
+    assert torch.equal(off[where + 1], dev(want[0][1:].view(np.int64), torch.int64))
+    counts = off[1:] - off[:-1]
+    counts[where] = 0
+    assert int(counts.abs().sum()) == 0
+    d[m - 2] = -1.0
+    with pytest.raises(sfc.SfcError):
+        idx.query(q, d)
+    idx.close()
