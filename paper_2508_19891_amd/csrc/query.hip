@@ -166,14 +166,15 @@ __device__ __forceinline__ uint64_t rows_of(uint64_t count) {
 }
 __device__ __forceinline__ uint64_t rows64_of(uint64_t count) { return (count + 63) >> 6; }
 
-// The value of the lane whose number differs in the bits of X (1..7) from this
-// one's; the lanes of a query are active together.
+// Every lane's word as the lane permutation CTRL gives it (0 where it has no lane).
 template <int CTRL>
 __device__ __forceinline__ uint32_t permute_lanes(uint32_t v) {
   uint32_t x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-  asm("" : "+v"(x));   // (never an operand modifier; see bcast16)
+  asm("" : "+v"(x));   // (a register of its own, never an operand modifier: see bcast16)
   return x;
 }
+// The value of the lane whose number differs in the bits of X (1..7) from this
+// one's; the lanes of a query are active together.
 template <int X>
 __device__ __forceinline__ uint64_t across(uint64_t v) {
   constexpr int kQuad[4] = {0xE4, 0xB1, 0x4E, 0x1B};   // lanes of four exchanged by xor
@@ -1290,9 +1291,7 @@ __device__ __forceinline__ uint32_t bcast16_operand(uint32_t v) {
 }
 template <int T>
 __device__ __forceinline__ uint32_t bcast16(uint32_t v) {
-  uint32_t x = bcast16_operand<T>(v);
-  asm("" : "+v"(x));
-  return x;
+  return permute_lanes<0x150 + T>(v);
 }
 template <int T>
 __device__ __forceinline__ uint64_t bcast16(uint64_t v) {
@@ -1300,10 +1299,10 @@ __device__ __forceinline__ uint64_t bcast16(uint64_t v) {
 }
 // Every lane's word plus those of the lanes below it in its row of 16.
 __device__ __forceinline__ uint32_t scan16(uint32_t v) {
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // 1 lane up
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);   // 2
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);   // 4
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);   // 8
+  v += permute_lanes<0x111>(v);   // of the lane 1 below, 0 for none
+  v += permute_lanes<0x112>(v);   // 2
+  v += permute_lanes<0x114>(v);   // 4
+  v += permute_lanes<0x118>(v);   // 8
   return v;
 }
 
