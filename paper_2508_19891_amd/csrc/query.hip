@@ -1441,7 +1441,7 @@ __global__ __launch_bounds__(256) void compact_test(
           }
         });
       };
-      auto test = [&](auto group, const Group& G) {
+      auto test = [&](auto group, const Group& G, auto shifted) {
         uint64_t hit[STEPS], und[STEPS], any = 0;
         static_for<STEPS>([&](auto i) {
           constexpr int g = decltype(i)::value, t = decltype(group)::value * STEPS + g;
@@ -1453,16 +1453,9 @@ __global__ __launch_bounds__(256) void compact_test(
             f.minus[0] = bcast16_operand<t>(u.rec[2]);
             f.minus[1] = bcast16_operand<t>(u.rec[3]);
             f.minus[2] = DIM == 3 ? bcast16_operand<t>(u.rec[kRecWords > 4 ? 4 : 0]) : 0u;
-            float v;
-            // A batch with coarser cells (radii past the shift limit) takes
-            // the shifting check.
-            if (SHIFTS && any_shifted) {
-              f.shift = bcast16<t>(u.rec[kRecWords > 4 ? 5 : 0]);
-              v = cell_distance<DIM, WINDOW, true>(G.cell[g], f);
-            } else {
-              f.shift = 0;
-              v = cell_distance<DIM, WINDOW, false>(G.cell[g], f);
-            }
+            constexpr bool kShifted = decltype(shifted)::value;
+            f.shift = kShifted ? bcast16<t>(u.rec[kRecWords > 4 ? 5 : 0]) : 0u;
+            const float v = cell_distance<DIM, WINDOW, kShifted>(G.cell[g], f);
             const uint64_t in = __ballot(v <= f.acc), out = __ballot(v > f.rej);
             hit[g] = in;
             und[g] = ~(in | out);
@@ -1515,16 +1508,23 @@ __global__ __launch_bounds__(256) void compact_test(
           write_pair<t>(hit[g], mk);
         });
       };
-      Group G[2];
-      load(std::integral_constant<int, 0>{}, G[0]);
-      static_for<ITERS>([&](auto group) {
-        constexpr int g = decltype(group)::value;
-        if constexpr (g + 1 < ITERS) load(std::integral_constant<int, g + 1>{}, G[(g + 1) & 1]);
-        // (Every load of the group first: else a wait for one comes before the next.)
-        __builtin_amdgcn_sched_barrier(0);
-        test(group, G[g & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-      });
+      auto groups = [&](auto shifted) {
+        Group G[2];
+        load(std::integral_constant<int, 0>{}, G[0]);
+        static_for<ITERS>([&](auto group) {
+          constexpr int g = decltype(group)::value;
+          if constexpr (g + 1 < ITERS) load(std::integral_constant<int, g + 1>{}, G[(g + 1) & 1]);
+          // (Every load of the group first: else a wait for one comes before the next.)
+          __builtin_amdgcn_sched_barrier(0);
+          test(group, G[g & 1], shifted);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      };
+      // A batch with coarser cells (radii past the shift limit) takes the shifting
+      // check throughout (one branch per unit: with one per step the steps' loads
+      // and compares did not overlap).
+      if (SHIFTS && CELLS && any_shifted) groups(std::integral_constant<bool, SHIFTS && CELLS>{});
+      else groups(std::integral_constant<bool, false>{});
 
       // The rows' valid hits, and the unit's before the row: those of the pairs
       // of rows before, and of the pair's first row before its second.
