@@ -193,16 +193,18 @@ __device__ __forceinline__ uint64_t across(uint64_t v) {
 // 1 if the key of that lane comes before this lane's (equal keys by lane).
 template <int X>
 __device__ __forceinline__ uint32_t before(uint64_t key, int lane) {
-  constexpr int kTop = X & 4 ? 4 : X & 2 ? 2 : 1;
-  const uint64_t other = across<X>(key);
-  return other < key || (other == key && (lane & kTop)) ? 1u : 0u;
+  return comes_before<X>(key, across<X>(key), lane);
+}
+// The lanes of this lane's query (four, bit r for lane r) for which p holds.
+__device__ __forceinline__ uint32_t quad_ballot(bool p) {
+  return (uint32_t)(__ballot(p) >> (lane_id() & ~3u)) & 15u;
 }
 
 // One lane per (query, slot): four slots per query (the method's ranges),
-// or eight (REFINE: two runs per cell of cells(Q)).  QUAD: a lane works out its
-// own cell of the query's box alone, and the query's four lanes exchange keys to
-// order and merge them; else (early termination's list, inspected ranges) the
-// lane's work is the body in query_lane.inc.  perm non-null: the queries in curve order, so that
+// or eight (REFINE: two runs per cell of cells(Q)).  QUAD: the lane's work is the
+// body in query_quad.inc (its own cell alone; the query's four lanes exchange keys
+// to order and merge them); else (early termination's list, inspected ranges) the
+// one in query_lane.inc.  perm non-null: the queries in curve order, so that
 // the searches of a workgroup meet in the same lines of the key array; slots
 // and records are laid out by query.  Each workgroup (64 queries) also sums
 // its counters, and its candidate rows if it holds 64 consecutive queries: one
@@ -256,10 +258,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     const double c[2] = {qq.x, qq.y}, d = delta[j];
     put_record<2>(record, j, c, d);
     coarse = d * grid_side<2>() > filter_limit<2>();
-    if (record.qepoch) {
-      const uint32_t qe = record.qepoch[j];
-      bad = qe < record.oldest || qe > record.epoch;
-    }
   }
   // With point sets, a query searches only its own set's keys: positions
   // [base, base + nn) of the sorted arrays.
@@ -275,76 +273,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     }
   }
   if constexpr (QUAD) {
-    if (j < m && !bad) {
-      const double2 qq = q[j];
-      const double d = delta[j];
-      if (!(finite64(qq.x) && finite64(qq.y) && finite64(d) && d >= 0.0)) {
-        bad = true;
-      } else {
-        // A box of side at most 2^L meets at most two level-L cells per axis:
-        // lane r takes the cell at offsets (r / 2, r mod 2).
-        int64_t box[4] = {0, -1, 0, -1};
-        const bool some = axis_box(qq.x, d, box[0], box[1]) && axis_box(qq.y, d, box[2], box[3]);
-        const uint64_t sx = (uint64_t)(box[1] - box[0] + 1), sy = (uint64_t)(box[3] - box[2] + 1);
-        const uint64_t side = sx > sy ? sx : sy;
-        const int L = side <= 1 ? 0 : 64 - __clzll(side - 1);   // ceil(log2 side)
-        const bool whole = L >= 32;
-        const int l = whole ? 0 : L;
-        const uint32_t x0 = (uint32_t)(box[0] >> l), y0 = (uint32_t)(box[2] >> l);
-        const uint32_t cx = whole ? 0 : x0 + (r >> 1), cy = whole ? 0 : y0 + (r & 1);
-        const bool in = some && (whole ? r == 0
-                                       : (uint32_t)(r >> 1) <= (uint32_t)(box[1] >> l) - x0 &&
-                                             (uint32_t)(r & 1) <= (uint32_t)(box[3] >> l) - y0);
-        const uint64_t span = whole ? ~0ull : (1ull << (2 * l)) - 1;
-        const uint64_t lo = in ? cell_key<CURVE>(lut, cx << l, cy << l) & ~span : ~0ull;
-        if constexpr (REFINE) {
-          // (A key is 2^64 - 1 only on level 0, where lane 0 has the one cell.)
-          sidx = 4 * j + before<1>(lo, r) + before<2>(lo, r) + before<3>(lo, r);
-          if (in) {
-            find_range<SEARCH>(keys + base, nn, lv, sv, lo, lo | span, b0, e0, fb);
-            b0 += base;
-            e0 += base;
-            ends += 2;
-            refine_cell<CURVE, SEARCH>(lut, keys, nn, lv, sv, refine_min, ball, lo, lo | span, cx,
-                                       cy, L, box, qq.x, qq.y, d, b0, e0, b1, e1, fb, ends);
-          }
-        } else {
-          // Cells next to each other in key order are one range: of the first of
-          // them, whose lane takes the place of its key among the first ones.
-          const uint32_t q0 = lane_id() & ~3u;
-          const uint32_t present = (uint32_t)(__ballot(in) >> q0) & 15u;
-          const uint64_t other[3] = {across<1>(lo), across<2>(lo), across<3>(lo)};
-          const uint64_t next = span + 1;
-          bool after[3] = {false, false, false}, first = in;
-#pragma unroll
-          for (int x = 0; x < 3; ++x) {
-            // (The comparison first: on level 31 the differences wrap.)
-            const bool there = (present >> (r ^ (x + 1))) & 1u;
-            const bool above = there && other[x] > lo, below = there && other[x] < lo;
-            const uint64_t up = other[x] - lo;
-            after[0] |= above && up == next;
-            after[1] |= above && up == 2 * next;
-            after[2] |= above && up == 3 * next;
-            first = first && !(below && lo - other[x] == next);
-          }
-          const uint32_t firsts = (uint32_t)(__ballot(first) >> q0) & 15u;
-          uint32_t at = 0;
-#pragma unroll
-          for (int x = 0; x < 3; ++x)
-            at += ((firsts >> (r ^ (x + 1))) & 1u) && other[x] < lo ? 1u : 0u;
-          if (!first)   // the other lanes' places, empty, come last
-            at = (uint32_t)__popc(firsts) + (uint32_t)__popc(~firsts & ((1u << r) - 1));
-          sidx = 4 * j + at;
-          if (first) {
-            const uint32_t cells = !after[0] ? 1u : !after[1] ? 2u : !after[2] ? 3u : 4u;
-            find_range<SEARCH>(keys + base, nn, lv, sv, lo, lo + cells * next - 1, b0, e0, fb);
-            b0 += base;
-            e0 += base;
-            ends += 2;
-          }
-        }
-      }
-    }
+#include "query_quad.inc"
   } else {
 #include "query_lane.inc"
     (void)pruned;   // counted where the work list is made
@@ -520,9 +449,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
       put_record<3>(record, j, c, d);
       coarse = d * grid_side<3>() > filter_limit<3>();
     }
-    const bool bad_epoch = record.qepoch && (record.qepoch[j] < record.oldest ||
-                                             record.qepoch[j] > record.epoch);
-    if (bad_epoch ||
+    if (epoch_rejected(record, j) ||
         !(finite64(qx) && finite64(qy) && finite64(qz) && finite64(d) && d >= 0.0)) {
       bad = true;
     } else if (!REFINE) {
@@ -681,9 +608,8 @@ __global__ __launch_bounds__(256) void cells_pack(
     const double c[2] = {qq.x, qq.y};
     put_record<2>(record, j, c, d);
     coarse = d * grid_side<2>() > filter_limit<2>();
-    if (record.qepoch)
-      bad = record.qepoch[j] < record.oldest || record.qepoch[j] > record.epoch;
-    if (!(finite64(qq.x) && finite64(qq.y) && finite64(d) && d >= 0.0)) {
+    if (epoch_rejected(record, j) ||
+        !(finite64(qq.x) && finite64(qq.y) && finite64(d) && d >= 0.0)) {
       bad = true;
     } else if (REFINE) {
       uint64_t lo[4], hi[4];

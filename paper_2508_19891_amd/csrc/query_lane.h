@@ -1,7 +1,8 @@
 // The per-lane pieces of the search (Alg. 1 with the Observation and the
 // definition of cells(Q)): a query's widened box, its cells and their key
 // intervals, the searches of an interval, and the helpers of the refinement
-// of a crowded cell; query_lane.inc puts them together for one lane.  Plain
+// of a crowded cell; query_quad.inc puts them together for a query's four lanes,
+// query_lane.inc for a lane by itself.  Plain
 // per-lane code with no cross-lane operation, so that the same source also
 // compiles as host C++ (a C++ compiler other than the HIP one sees
 // __device__ and __forceinline__ as plain inline functions), where the tests
@@ -50,6 +51,19 @@ __device__ __forceinline__ bool within_window(double px, double py, double qx, d
 }
 
 __device__ __forceinline__ bool finite64(double v) { return __builtin_isfinite(v); }
+
+// Whether query j asks for an epoch that the index does not hold.
+__device__ __forceinline__ bool epoch_rejected(const RecordPlan& R, uint64_t j) {
+  return R.qepoch && (R.qepoch[j] < R.oldest || R.qepoch[j] > R.epoch);
+}
+
+// 1 if `other`, the key of the lane whose number differs from this one's in the
+// bits of X (1..7), comes before this lane's key (equal keys by lane).
+template <int X>
+__device__ __forceinline__ uint32_t comes_before(uint64_t key, uint64_t other, int lane) {
+  constexpr int kTop = X & 4 ? 4 : X & 2 ? 2 : 1;
+  return other < key || (other == key && (lane & kTop)) ? 1u : 0u;
+}
 
 __device__ __forceinline__ int64_t floor_clamped(double v) {
   v = v < -kTwo33 ? -kTwo33 : v;
