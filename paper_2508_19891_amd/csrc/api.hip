@@ -1000,6 +1000,7 @@ sfc_status query_impl(sfc_index* h, const double* q, const double* delta, const 
     cp.max_rows = cap_rows;
     cp.device_sized = true;
     cp.scratch = h->cws;
+    cp.reject = sfc::kErrInvalidQuery;   // (the caller gets the error, and keeps its outputs)
     SFC_TRY(sfc::launch_compact(cp, qs, h->stream));
   }
   SFC_TRY(hipStreamSynchronize(h->stream));

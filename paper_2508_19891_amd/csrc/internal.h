@@ -237,6 +237,8 @@ struct CompactPlan {
   const uint32_t* ins = nullptr;     // with both: only entries with ins <= e < era are
   const uint32_t* era = nullptr;     // visible to a query at epoch e
   bool write_only = false;           // the write pass alone, on a batch still in scratch
+  uint32_t reject = 0;               // kErr* bits: a batch with one of them is left alone, its
+                                     // offsets and ids as they were
   int coarse = -1;                   // BatchStatus::coarse if the caller read it (1, 0), else
                                      // -1; with 0 the test pass takes its shortest form
   BatchStatus* host = nullptr;       // host memory: the final counters, if not null

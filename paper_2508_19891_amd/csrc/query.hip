@@ -709,8 +709,15 @@ constexpr uint32_t kTileUnits = 4;
 constexpr uint64_t kTileRows = kTileUnits * kUnitRows; // rows of 32
 static_assert(kTileRows == 2 * kCompactTileRows, "a tile holds 64 rows of 64 candidates");
 
-// Tiles of a chunk's rows [rbase, row_end); none when the batch has more rows
-// than a capacity (over): it is compacted again, or reported.
+// Whether a batch is not tested and nothing of it written: it has more rows than
+// a capacity (then it is compacted again, or reported), or it holds what the caller
+// rejects it for (error bits `reject`).
+__device__ __forceinline__ bool batch_over(const BatchStatus* status, uint64_t max_rows64,
+                                           uint32_t reject) {
+  return status->rows > max_rows64 || (status->err & reject) != 0;
+}
+
+// Tiles of a chunk's rows [rbase, row_end); none of a batch that is not tested.
 __device__ __forceinline__ uint64_t chunk_tiles(uint64_t total_all, uint64_t rbase,
                                                 uint64_t row_end, bool over) {
   if (over) return 0;
@@ -1275,9 +1282,9 @@ __global__ __launch_bounds__(256) void compact_test(
     const double* __restrict__ pts, const uint32_t* __restrict__ via,
     const uint64_t* __restrict__ cells, const void* __restrict__ rec,
     const uint2* __restrict__ row_meta, const uint64_t* __restrict__ total_rows_dev,
-    uint64_t rbase, uint64_t row_end, uint64_t max_rows64, uint32_t* __restrict__ masks,
-    uint16_t* __restrict__ row_info, uint32_t* __restrict__ unit_hits, BatchStatus* status,
-    const uint32_t* __restrict__ ins, const uint32_t* __restrict__ era) {
+    uint64_t rbase, uint64_t row_end, uint64_t max_rows64, uint32_t reject,
+    uint32_t* __restrict__ masks, uint16_t* __restrict__ row_info,
+    uint32_t* __restrict__ unit_hits, BatchStatus* status, const uint32_t* __restrict__ ins, const uint32_t* __restrict__ era) {
   static_assert(STEPS * ITERS == kUnitSteps, "a wave's groups cover its rows");
   static_assert(!(EPOCH && CELLS), "an index with epochs keeps no cells");
   const uint32_t lane = lane_id(), row = unit_row(lane), lane32 = lane & 31;
@@ -1286,7 +1293,8 @@ __global__ __launch_bounds__(256) void compact_test(
   const bool any_shifted = SHIFTS && CELLS && status->coarse != 0u;
   const uint64_t total_all = *total_rows_dev;
   const uint64_t total_rows = total_all < row_end ? total_all : row_end;
-  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, status->rows > max_rows64);
+  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end,
+                                      batch_over(status, max_rows64, reject));
   const uint64_t have = total_rows - rbase;
   // What belongs to a lane's row: its descriptor (rows past the last: candidate 0
   // of query 0, whose result is dropped), then the record of its query.  A
@@ -1516,9 +1524,10 @@ template <bool ORDERED, bool FUSED>
 __global__ __launch_bounds__(256) void compact_write_out(
     const uint32_t* __restrict__ ids, const uint2* __restrict__ row_meta,
     const uint64_t* __restrict__ row_off, uint64_t m, uint64_t rbase, uint64_t rend,
-    uint64_t row_end, uint64_t max_rows64, const uint32_t* __restrict__ masks,
+    uint64_t row_end, uint64_t max_rows64, uint32_t reject, const uint32_t* __restrict__ masks,
     const uint16_t* __restrict__ row_info, const uint32_t* __restrict__ unit_hits,
-    const uint64_t* __restrict__ unit_off, const uint64_t* __restrict__ out_base, uint32_t tile_grid, uint32_t* __restrict__ out_ids,
+    const uint64_t* __restrict__ unit_off, const uint64_t* __restrict__ out_base,
+    uint32_t tile_grid, uint32_t* __restrict__ out_ids,
     uint64_t cap, bool whole, uint64_t* __restrict__ offsets, const BatchStatus* status,
     BatchStatus* host, uint32_t* flags_out) {
   __shared__ uint32_t s_off[FUSED ? kFusedUnits + 1 : 1];
@@ -1528,7 +1537,7 @@ __global__ __launch_bounds__(256) void compact_write_out(
   const uint32_t w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint64_t total_all = row_off[m];
   const uint64_t total_rows = total_all < row_end ? total_all : row_end;
-  const bool over = status->rows > max_rows64;
+  const bool over = batch_over(status, max_rows64, reject);
   const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, over);
   const uint64_t units = ntiles * kTileUnits;
   // A workgroup without a tile (and not the first, which reports) is done.
@@ -1651,7 +1660,8 @@ __global__ __launch_bounds__(256) void compact_write_out(
 // Ordered rows: the hits of every query, and in out_base the hits P of all
 // rows before its first.  One thread per place.
 __global__ __launch_bounds__(256) void query_hits(const uint64_t* __restrict__ row_off, uint64_t m,
-                                                  uint64_t max_rows64, const BatchStatus* status,
+                                                  uint64_t max_rows64, uint32_t reject,
+                                                  const BatchStatus* status,
                                                   const uint16_t* __restrict__ row_info,
                                                   const uint64_t* __restrict__ unit_off,
                                                   const uint32_t* __restrict__ perm,
@@ -1660,7 +1670,7 @@ __global__ __launch_bounds__(256) void query_hits(const uint64_t* __restrict__ r
   const uint64_t at = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   if (at >= m) return;
   const uint64_t total_all = row_off[m];
-  const uint64_t total = status->rows <= max_rows64 ? total_all : 0;   // past it: not tested
+  const uint64_t total = batch_over(status, max_rows64, reject) ? 0 : total_all;
   const uint64_t units = (total + kTileRows - 1) / kTileRows * kTileUnits;
   auto before = [&](uint64_t r) -> uint64_t {
     if (r >= total) return total ? unit_off[units] : 0;
@@ -2107,8 +2117,8 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
 #define SFC_TEST_K(R, I, E, D, C, W, K)                                                    \
   compact_test<R, I, E, D, C, W, K><<<grid, 256, 0, s>>>(                                  \
       P.q, P.delta, m, P.pts ? P.pts : P.pts_in, P.pts ? nullptr : P.ids, P.cells, qs.rec, \
-      c.meta, total_dev, rbase, row_end, max_rows64, c.masks, c.info, c.unit_hits, qs.status, \
-      P.ins, P.era)
+      c.meta, total_dev, rbase, row_end, max_rows64, P.reject, c.masks, c.info, c.unit_hits, \
+      qs.status, P.ins, P.era)
 #define SFC_TEST_W(R, I, E, D, C, W)                                                       \
   if (C && shifts) SFC_TEST_K(R, I, E, D, C, W, C);                                        \
   else SFC_TEST_K(R, I, E, D, C, W, false)
@@ -2151,8 +2161,8 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
       ProfScope ps("query_offsets", s);
       const uint32_t qb = (uint32_t)((m + 255) / 256);
       if (!P.write_only) {
-        query_hits<<<qb, 256, 0, s>>>(qs.row_off, m, max_rows64, qs.status, c.info, unit_off,
-                                      qs.perm, qs.qhits, qs.out_base);
+        query_hits<<<qb, 256, 0, s>>>(qs.row_off, m, max_rows64, P.reject, qs.status, c.info,
+                                      unit_off, qs.perm, qs.qhits, qs.out_base);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
       if ((e = scan_excl(qs.qhits, P.offsets, m, nullptr, qs.scan_tmp, s)) != hipSuccess) return e;
@@ -2166,7 +2176,7 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
       const uint32_t extra = ordered ? 0 : fill_blocks(m + 1);
 #define SFC_WRITE(O, F)                                                                      \
   compact_write_out<O, F><<<grid + extra, 256, 0, s>>>(                                       \
-      P.ids, c.meta, qs.row_off, m, rbase, rend, row_end, max_rows64, c.masks, c.info, \
+      P.ids, c.meta, qs.row_off, m, rbase, rend, row_end, max_rows64, P.reject, c.masks, c.info, \
       c.unit_hits, unit_off, qs.out_base, grid, P.out_ids, P.cap, chunks == 1, P.offsets,     \
       qs.status, P.host, P.flags_out)
       if (ordered) SFC_WRITE(true, false);
