@@ -170,7 +170,7 @@ __device__ __forceinline__ uint64_t rows64_of(uint64_t count) { return (count + 
 template <int CTRL>
 __device__ __forceinline__ uint32_t permute_lanes(uint32_t v) {
   uint32_t x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-  asm("" : "+v"(x));   // (a register of its own, never an operand modifier: see bcast16)
+  asm("" : "+v"(x));   // (a register of its own, never an operand modifier: see plus_bcast16)
   return x;
 }
 // The value of the lane whose number differs in the bits of X (1..7) from this
@@ -1125,20 +1125,13 @@ __global__ __launch_bounds__(256) void expand_rows(
   }
 }
 
-// What a query's limits are compared with, from a candidate's cell: the sum of
-// the squared offsets, or (WINDOW) the largest.  SHIFTED: the cells are
-// compared f.shift bits coarser (else f.shift is 0).
-template <int DIM, bool WINDOW, bool SHIFTED>
-__device__ __forceinline__ float cell_distance(uint64_t cell, const QueryFilter& f) {
-  constexpr int B = DIM == 2 ? 32 : 21;
-  const uint64_t mask = (1ull << B) - 1;
+// What a query's limits are compared with, from the quanta between its cell and a
+// candidate's on each axis: the sum of their squares, or (WINDOW) the largest.
+template <int DIM, bool WINDOW>
+__device__ __forceinline__ float cell_distance(const int32_t (&off)[3]) {
   float e[DIM];
 #pragma unroll
-  for (int a = 0; a < DIM; ++a) {
-    uint32_t u = (uint32_t)((cell >> (B * a)) & mask);
-    if (SHIFTED) u >>= f.shift;
-    e[a] = (float)(int32_t)(u + f.minus[a]);
-  }
+  for (int a = 0; a < DIM; ++a) e[a] = (float)off[a];
   if (WINDOW) {
     float v = fabsf(e[0]);
 #pragma unroll
@@ -1212,16 +1205,7 @@ __device__ __forceinline__ uint32_t read_lane(uint32_t v) {
   return __builtin_amdgcn_readlane(v, R);
 }
 
-// In every row of 16 lanes, the word of its lane T: a lane permutation that the
-// compiler may make an operand modifier of the instruction using the word.
-// Measured: in the instructions with reversed operands (v_subrev, v_lshrrev) the
-// hardware then permutes the other operand.  So bcast16_operand is for operands
-// of additions, minima and the like alone; bcast16 keeps the word in a register
-// of its own.
-template <int T>
-__device__ __forceinline__ uint32_t bcast16_operand(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + T, 0xF, 0xF, true);
-}
+// In every row of 16 lanes, the word of its lane T, in a register of its own.
 template <int T>
 __device__ __forceinline__ uint32_t bcast16(uint32_t v) {
   return permute_lanes<0x150 + T>(v);
@@ -1229,6 +1213,29 @@ __device__ __forceinline__ uint32_t bcast16(uint32_t v) {
 template <int T>
 __device__ __forceinline__ uint64_t bcast16(uint64_t v) {
   return (uint64_t)bcast16<T>((uint32_t)(v >> 32)) << 32 | bcast16<T>((uint32_t)v);
+}
+// x plus that word, and the smaller of the two, in one instruction: the permutation
+// is the modifier of its first operand.  Spelled out, since the compiler, which may
+// fold a permutation into any instruction that uses it, must not choose one of
+// reversed operands here (measured: v_subrev and v_lshrrev then permute the other
+// operand).  A lane permutation reads a register that a vector instruction wrote only
+// two wait states later, which the compiler does not see to in inline assembly: hence
+// the s_nop.
+template <int T>
+__device__ __forceinline__ uint32_t plus_bcast16(uint32_t x, uint32_t v) {
+  uint32_t r;
+  asm("s_nop 1\n\tv_add_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+      : "=v"(r)
+      : "v"(v), "v"(x), "n"(T));
+  return r;
+}
+template <int T>
+__device__ __forceinline__ uint32_t min_bcast16(uint32_t x, uint32_t v) {
+  uint32_t r;
+  asm("s_nop 1\n\tv_min_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+      : "=v"(r)
+      : "v"(v), "v"(x), "n"(T));
+  return r;
 }
 // Every lane's word plus those of the lanes below it in its row of 16.
 __device__ __forceinline__ uint32_t scan16(uint32_t v) {
@@ -1351,8 +1358,7 @@ __global__ __launch_bounds__(256) void compact_test(
       // The sorted index of the lane's candidate in step t.
       auto position = [&](auto t) {
         constexpr int T = decltype(t)::value;
-        const uint32_t last = bcast16_operand<T>(ulast);
-        return bcast16_operand<T>(u.pb) + (lane32 < last ? lane32 : last);
+        return plus_bcast16<T>(min_bcast16<T>(lane32, ulast), u.pb);
       };
       // A group's candidates: one load per step (three coordinates: three).
       struct Group {
@@ -1381,16 +1387,23 @@ __global__ __launch_bounds__(256) void compact_test(
           constexpr int g = decltype(i)::value, t = decltype(group)::value * STEPS + g;
           if constexpr (CELLS) {
             // Decide from the cells.
-            QueryFilter f;
-            f.acc = __uint_as_float(bcast16<t>(u.rec[0]));
-            f.rej = __uint_as_float(bcast16<t>(u.rec[1]));
-            f.minus[0] = bcast16_operand<t>(u.rec[2]);
-            f.minus[1] = bcast16_operand<t>(u.rec[3]);
-            f.minus[2] = DIM == 3 ? bcast16_operand<t>(u.rec[kRecWords > 4 ? 4 : 0]) : 0u;
+            // (A shifted query's cells are compared 2^shift quanta wide.)
+            const float acc = __uint_as_float(bcast16<t>(u.rec[0]));
+            const float rej = __uint_as_float(bcast16<t>(u.rec[1]));
             constexpr bool kShifted = decltype(shifted)::value;
-            f.shift = kShifted ? bcast16<t>(u.rec[kRecWords > 4 ? 5 : 0]) : 0u;
-            const float v = cell_distance<DIM, WINDOW, kShifted>(G.cell[g], f);
-            const uint64_t in = __ballot(v <= f.acc), out = __ballot(v > f.rej);
+            const uint32_t shift = kShifted ? bcast16<t>(u.rec[kRecWords > 4 ? 5 : 0]) : 0u;
+            constexpr int B = DIM == 2 ? 32 : 21;
+            auto axis = [&](auto k) {
+              constexpr int a = decltype(k)::value;
+              uint32_t c = (uint32_t)((G.cell[g] >> (B * a)) & ((1ull << B) - 1));
+              if (kShifted) c >>= shift;
+              return (int32_t)plus_bcast16<t>(c, u.rec[kRecWords > 4 || a < 2 ? 2 + a : 0]);
+            };
+            int32_t off[3] = {axis(std::integral_constant<int, 0>{}),
+                              axis(std::integral_constant<int, 1>{}), 0};
+            if constexpr (DIM == 3) off[2] = axis(std::integral_constant<int, 2>{});
+            const float v = cell_distance<DIM, WINDOW>(off);
+            const uint64_t in = __ballot(v <= acc), out = __ballot(v > rej);
             hit[g] = in;
             und[g] = ~(in | out);
             any |= und[g];
@@ -1638,8 +1651,7 @@ __global__ __launch_bounds__(256) void compact_write_out(
     uint32_t id[kUnitSteps];
     static_for<kUnitSteps>([&](auto t) {
       constexpr int T = decltype(t)::value;
-      const uint32_t last = bcast16_operand<T>(end);
-      id[T] = ids[(uint64_t)(bcast16_operand<T>(pb) + (lane32 < last ? lane32 : last))];
+      id[T] = ids[(uint64_t)plus_bcast16<T>(min_bcast16<T>(lane32, end), pb)];
     });
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
