@@ -1011,12 +1011,22 @@ __global__ __launch_bounds__(256) void slot_rows(const uint2* __restrict__ slots
   if (threadIdx.x == 0) blk_rows[blockIdx.x] = total;
 }
 
+// What a wave's lanes stored to LDS before, its lanes load after.  (The barrier alone
+// holds the instructions' order; the fences also keep a lane from taking what it
+// stored itself for what is there.)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Row descriptors of a launch's rows [rbase, rend): for row r of slot s, the
 // first sorted index of the row and the query (row_meta) and the number of its
 // candidates (row_info), and the first row of every place (row_off).  One block per K * 256 slots (whole
 // queries: 2^ss slots each), a thread's K slots consecutive; the block's
-// rows are spread over its threads and each finds its slot by a binary search
-// in LDS.  FUSED (at most kFusedBlocks blocks): the block sums the rows of the
+// rows are spread over its waves, 64 at a time: the slots that start among them
+// mark their first row in LDS, and a row's slot is that of the last mark up to it.
+// FUSED (at most kFusedBlocks blocks): the block sums the rows of the
 // blocks before it itself and block 0 gathers the batch's counters, so that a
 // small batch takes no batch_scan launch (5 us; with more blocks the repeated
 // sums would cost more).
@@ -1099,7 +1109,7 @@ __global__ __launch_bounds__(256) void expand_rows(
     // The slots that start in these rows leave their number at their first row;
     // a row's slot is that of the last such row up to it, or the first row's.
     mark[lane] = 0xFFFFu;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (uint32_t k = k0 + 1; k < 256 * K && st[k] < base + kWave; k += kWave) {
       const uint32_t mine = k + lane;
       if (mine < 256 * K && s_slot[mine].y != 0) {
@@ -1107,11 +1117,11 @@ __global__ __launch_bounds__(256) void expand_rows(
         if (at < kWave) mark[at] = (uint16_t)mine;
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     const uint32_t own = mark[lane];
     const uint64_t starts = __ballot(own != 0xFFFFu) & (~0ull >> (63 - lane));
     const uint32_t k = starts ? mark[63 - __clzll(starts)] : k0;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     const uint64_t r = base + lane;
     if (r < last_row) {
       const uint64_t local = (r - st[k]) << kRowShift;
