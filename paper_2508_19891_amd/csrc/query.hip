@@ -170,7 +170,7 @@ __device__ __forceinline__ uint64_t rows64_of(uint64_t count) { return (count + 
 template <int CTRL>
 __device__ __forceinline__ uint32_t permute_lanes(uint32_t v) {
   uint32_t x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-  asm("" : "+v"(x));   // (a register of its own, never an operand modifier: see plus_bcast16)
+  asm("" : "+v"(x));   // (a register of its own, never an operand modifier: see bcast16)
   return x;
 }
 // The value of the lane whose number differs in the bits of X (1..7) from this
@@ -1215,7 +1215,12 @@ __device__ __forceinline__ uint32_t read_lane(uint32_t v) {
   return __builtin_amdgcn_readlane(v, R);
 }
 
-// In every row of 16 lanes, the word of its lane T, in a register of its own.
+// In every row of 16 lanes, the word of its lane T, in a register of its own: the
+// compiler would fold the permutation into the instruction using the word, and in
+// those of reversed operands (v_subrev, v_lshrrev) the hardware then permutes the
+// other operand (measured).  The moves cost the passes nothing that shows: they wait
+// for memory (2^20 queries over 2^24 points 2091 and 2094 us a step without and with
+// the three that were folded before, 2^22 over 2^26 1547 and 1550).
 template <int T>
 __device__ __forceinline__ uint32_t bcast16(uint32_t v) {
   return permute_lanes<0x150 + T>(v);
@@ -1223,29 +1228,6 @@ __device__ __forceinline__ uint32_t bcast16(uint32_t v) {
 template <int T>
 __device__ __forceinline__ uint64_t bcast16(uint64_t v) {
   return (uint64_t)bcast16<T>((uint32_t)(v >> 32)) << 32 | bcast16<T>((uint32_t)v);
-}
-// x plus that word, and the smaller of the two, in one instruction: the permutation
-// is the modifier of its first operand.  Spelled out, since the compiler, which may
-// fold a permutation into any instruction that uses it, must not choose one of
-// reversed operands here (measured: v_subrev and v_lshrrev then permute the other
-// operand).  A lane permutation reads a register that a vector instruction wrote only
-// two wait states later, which the compiler does not see to in inline assembly: hence
-// the s_nop.
-template <int T>
-__device__ __forceinline__ uint32_t plus_bcast16(uint32_t x, uint32_t v) {
-  uint32_t r;
-  asm("s_nop 1\n\tv_add_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-      : "=v"(r)
-      : "v"(v), "v"(x), "n"(T));
-  return r;
-}
-template <int T>
-__device__ __forceinline__ uint32_t min_bcast16(uint32_t x, uint32_t v) {
-  uint32_t r;
-  asm("s_nop 1\n\tv_min_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-      : "=v"(r)
-      : "v"(v), "v"(x), "n"(T));
-  return r;
 }
 // Every lane's word plus those of the lanes below it in its row of 16.
 __device__ __forceinline__ uint32_t scan16(uint32_t v) {
@@ -1285,7 +1267,7 @@ __device__ __forceinline__ uint32_t unit_rows(uint64_t have, uint64_t row0) {
 // latency of its chain of loads (descriptor, record, candidates).  So the lanes
 // hold the 32 rows' descriptors and records, loaded for all rows at once and one
 // unit ahead, and a step's lanes get their row's words by a broadcast in each row
-// of 16 lanes, an operand modifier of the instruction that uses the word; STEPS
+// of 16 lanes; STEPS
 // steps' candidates are read at a time, a group's loads leaving before the
 // previous group is tested; the two verdicts are masks straight from the compares.
 // Measured (rows of 64, one at a time, before): 0.302 ms for the 4 * 10^8
@@ -1368,7 +1350,8 @@ __global__ __launch_bounds__(256) void compact_test(
       // The sorted index of the lane's candidate in step t.
       auto position = [&](auto t) {
         constexpr int T = decltype(t)::value;
-        return plus_bcast16<T>(min_bcast16<T>(lane32, ulast), u.pb);
+        const uint32_t last = bcast16<T>(ulast);
+        return bcast16<T>(u.pb) + (lane32 < last ? lane32 : last);
       };
       // A group's candidates: one load per step (three coordinates: three).
       struct Group {
@@ -1407,7 +1390,7 @@ __global__ __launch_bounds__(256) void compact_test(
               constexpr int a = decltype(k)::value;
               uint32_t c = (uint32_t)((G.cell[g] >> (B * a)) & ((1ull << B) - 1));
               if (kShifted) c >>= shift;
-              return (int32_t)plus_bcast16<t>(c, u.rec[kRecWords > 4 || a < 2 ? 2 + a : 0]);
+              return (int32_t)(c + bcast16<t>(u.rec[kRecWords > 4 || a < 2 ? 2 + a : 0]));
             };
             int32_t off[3] = {axis(std::integral_constant<int, 0>{}),
                               axis(std::integral_constant<int, 1>{}), 0};
@@ -1661,7 +1644,8 @@ __global__ __launch_bounds__(256) void compact_write_out(
     uint32_t id[kUnitSteps];
     static_for<kUnitSteps>([&](auto t) {
       constexpr int T = decltype(t)::value;
-      id[T] = ids[(uint64_t)plus_bcast16<T>(min_bcast16<T>(lane32, end), pb)];
+      const uint32_t last = bcast16<T>(end);
+      id[T] = ids[(uint64_t)(bcast16<T>(pb) + (lane32 < last ? lane32 : last))];
     });
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
