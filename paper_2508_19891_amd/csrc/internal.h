@@ -119,7 +119,7 @@ struct BatchStatus {
   uint32_t err;          // kErr* bits
   uint32_t coarse;       // some radius lies past the cell filter's shift limit
   uint32_t units;        // compaction units of the current chunk
-  uint32_t pad;
+  uint32_t left;         // the compaction leaves the batch alone (expand_rows decides)
 };
 
 // What the search leaves of each query for the test pass: nothing, the cell

@@ -709,14 +709,6 @@ constexpr uint32_t kTileUnits = 4;
 constexpr uint64_t kTileRows = kTileUnits * kUnitRows; // rows of 32
 static_assert(kTileRows == 2 * kCompactTileRows, "a tile holds 64 rows of 64 candidates");
 
-// Whether a batch is not tested and nothing of it written: it has more rows than
-// a capacity (then it is compacted again, or reported), or it holds what the caller
-// rejects it for (error bits `reject`).
-__device__ __forceinline__ bool batch_over(const BatchStatus* status, uint64_t max_rows64,
-                                           uint32_t reject) {
-  return status->rows > max_rows64 || (status->err & reject) != 0;
-}
-
 // Tiles of a chunk's rows [rbase, row_end); none of a batch that is not tested.
 __device__ __forceinline__ uint64_t chunk_tiles(uint64_t total_all, uint64_t rbase,
                                                 uint64_t row_end, bool over) {
@@ -1020,6 +1012,17 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Whether the batch is left alone, not tested and nothing of it written: it has more
+// rows than a capacity (flagged; it is compacted again, or reported), or one of the
+// error bits that its caller rejects it for.
+__device__ __forceinline__ void put_verdict(BatchStatus* status, uint64_t max_rows64,
+                                            uint32_t reject) {
+  const bool over = status->rows > max_rows64;
+  const uint32_t err = status->err;
+  if (over) status->err = err | kErrOverflow;
+  status->left = over || (err & reject) != 0 ? 1u : 0u;
+}
+
 // Row descriptors of a launch's rows [rbase, rend): for row r of slot s, the
 // first sorted index of the row and the query (row_meta) and the number of its
 // candidates (row_info), and the first row of every place (row_off).  One block per K * 256 slots (whole
@@ -1038,7 +1041,7 @@ __global__ __launch_bounds__(256) void expand_rows(
     const uint32_t* __restrict__ perm, const uint64_t* __restrict__ blk_rows,
     const uint64_t* __restrict__ blk_off, const GroupSums* __restrict__ groups, BatchStats B,
     BatchStatus* status, uint64_t m, int ss, uint64_t rbase, uint64_t row_end, uint64_t max_rows64,
-    uint2* __restrict__ row_meta, uint16_t* __restrict__ row_info) {
+    uint32_t reject, uint2* __restrict__ row_meta, uint16_t* __restrict__ row_info) {
   __shared__ uint64_t st[256 * K + 1];
   __shared__ uint2 s_slot[256 * K];
   __shared__ uint16_t s_mark[4][kWave];
@@ -1060,13 +1063,13 @@ __global__ __launch_bounds__(256) void expand_rows(
       sum_stats<4>(B, status, nullptr);
       if (tid == 0) {
         row_off[m] = total;
-        if (status->rows > max_rows64) status->err |= kErrOverflow;
+        put_verdict(status, max_rows64, reject);
       }
     }
   } else {
     row0 = blk_off[blockIdx.x] + (groups ? groups[blockIdx.x / kGroupBlocks].rows : 0);
     total = row_off[m];
-    if (blockIdx.x == 0 && tid == 0 && status->rows > max_rows64) status->err |= kErrOverflow;
+    if (blockIdx.x == 0 && tid == 0) put_verdict(status, max_rows64, reject);
   }
   const uint64_t rend = total < row_end ? total : row_end;
   const uint64_t s0 = (uint64_t)blockIdx.x * 256 * K;
@@ -1281,9 +1284,9 @@ __global__ __launch_bounds__(256) void compact_test(
     const double* __restrict__ pts, const uint32_t* __restrict__ via,
     const uint64_t* __restrict__ cells, const void* __restrict__ rec,
     const uint2* __restrict__ row_meta, const uint64_t* __restrict__ total_rows_dev,
-    uint64_t rbase, uint64_t row_end, uint64_t max_rows64, uint32_t reject,
-    uint32_t* __restrict__ masks, uint16_t* __restrict__ row_info,
-    uint32_t* __restrict__ unit_hits, BatchStatus* status, const uint32_t* __restrict__ ins, const uint32_t* __restrict__ era) {
+    uint64_t rbase, uint64_t row_end, uint32_t* __restrict__ masks,
+    uint16_t* __restrict__ row_info, uint32_t* __restrict__ unit_hits, BatchStatus* status,
+    const uint32_t* __restrict__ ins, const uint32_t* __restrict__ era) {
   static_assert(STEPS * ITERS == kUnitSteps, "a wave's groups cover its rows");
   static_assert(!(EPOCH && CELLS), "an index with epochs keeps no cells");
   const uint32_t lane = lane_id(), row = unit_row(lane), lane32 = lane & 31;
@@ -1292,8 +1295,7 @@ __global__ __launch_bounds__(256) void compact_test(
   const bool any_shifted = SHIFTS && CELLS && status->coarse != 0u;
   const uint64_t total_all = *total_rows_dev;
   const uint64_t total_rows = total_all < row_end ? total_all : row_end;
-  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end,
-                                      batch_over(status, max_rows64, reject));
+  const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, status->left != 0);
   const uint64_t have = total_rows - rbase;
   // What belongs to a lane's row: its descriptor (rows past the last: candidate 0
   // of query 0, whose result is dropped), then the record of its query.  A
@@ -1530,7 +1532,7 @@ template <bool ORDERED, bool FUSED>
 __global__ __launch_bounds__(256) void compact_write_out(
     const uint32_t* __restrict__ ids, const uint2* __restrict__ row_meta,
     const uint64_t* __restrict__ row_off, uint64_t m, uint64_t rbase, uint64_t rend,
-    uint64_t row_end, uint64_t max_rows64, uint32_t reject, const uint32_t* __restrict__ masks,
+    uint64_t row_end, const uint32_t* __restrict__ masks,
     const uint16_t* __restrict__ row_info, const uint32_t* __restrict__ unit_hits,
     const uint64_t* __restrict__ unit_off, const uint64_t* __restrict__ out_base,
     uint32_t tile_grid, uint32_t* __restrict__ out_ids,
@@ -1543,7 +1545,7 @@ __global__ __launch_bounds__(256) void compact_write_out(
   const uint32_t w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint64_t total_all = row_off[m];
   const uint64_t total_rows = total_all < row_end ? total_all : row_end;
-  const bool over = batch_over(status, max_rows64, reject);
+  const bool over = status->left != 0;
   const uint64_t ntiles = chunk_tiles(total_all, rbase, row_end, over);
   const uint64_t units = ntiles * kTileUnits;
   // A workgroup without a tile (and not the first, which reports) is done.
@@ -1666,7 +1668,6 @@ __global__ __launch_bounds__(256) void compact_write_out(
 // Ordered rows: the hits of every query, and in out_base the hits P of all
 // rows before its first.  One thread per place.
 __global__ __launch_bounds__(256) void query_hits(const uint64_t* __restrict__ row_off, uint64_t m,
-                                                  uint64_t max_rows64, uint32_t reject,
                                                   const BatchStatus* status,
                                                   const uint16_t* __restrict__ row_info,
                                                   const uint64_t* __restrict__ unit_off,
@@ -1676,7 +1677,7 @@ __global__ __launch_bounds__(256) void query_hits(const uint64_t* __restrict__ r
   const uint64_t at = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   if (at >= m) return;
   const uint64_t total_all = row_off[m];
-  const uint64_t total = batch_over(status, max_rows64, reject) ? 0 : total_all;
+  const uint64_t total = status->left ? 0 : total_all;
   const uint64_t units = (total + kTileRows - 1) / kTileRows * kTileUnits;
   auto before = [&](uint64_t r) -> uint64_t {
     if (r >= total) return total ? unit_off[units] : 0;
@@ -2109,7 +2110,7 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
   expand_rows<K, F><<<query_blocks(qs), 256, 0, s>>>(qs.row_off, qs.slots, perm, blk_rows, \
                                                      qs.blk_off, groups, stats_of(qs), qs.status, m, \
                                                      qs.ss, rbase,                           \
-                                                     row_end, max_rows64, c.meta, c.info)
+                                                     row_end, max_rows64, P.reject, c.meta, c.info)
       switch (slots_per_thread(qs)) {
         case 1: if (qs.fused) SFC_EXPAND(1, true); else SFC_EXPAND(1, false); break;
         case 2: if (qs.fused) SFC_EXPAND(2, true); else SFC_EXPAND(2, false); break;
@@ -2123,8 +2124,7 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
 #define SFC_TEST_K(R, I, E, D, C, W, K)                                                    \
   compact_test<R, I, E, D, C, W, K><<<grid, 256, 0, s>>>(                                  \
       P.q, P.delta, m, P.pts ? P.pts : P.pts_in, P.pts ? nullptr : P.ids, P.cells, qs.rec, \
-      c.meta, total_dev, rbase, row_end, max_rows64, P.reject, c.masks, c.info, c.unit_hits, \
-      qs.status, P.ins, P.era)
+      c.meta, total_dev, rbase, row_end, c.masks, c.info, c.unit_hits, qs.status, P.ins, P.era)
 #define SFC_TEST_W(R, I, E, D, C, W)                                                       \
   if (C && shifts) SFC_TEST_K(R, I, E, D, C, W, C);                                        \
   else SFC_TEST_K(R, I, E, D, C, W, false)
@@ -2167,8 +2167,8 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
       ProfScope ps("query_offsets", s);
       const uint32_t qb = (uint32_t)((m + 255) / 256);
       if (!P.write_only) {
-        query_hits<<<qb, 256, 0, s>>>(qs.row_off, m, max_rows64, P.reject, qs.status, c.info,
-                                      unit_off, qs.perm, qs.qhits, qs.out_base);
+        query_hits<<<qb, 256, 0, s>>>(qs.row_off, m, qs.status, c.info, unit_off, qs.perm,
+                                      qs.qhits, qs.out_base);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
       if ((e = scan_excl(qs.qhits, P.offsets, m, nullptr, qs.scan_tmp, s)) != hipSuccess) return e;
@@ -2182,9 +2182,9 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
       const uint32_t extra = ordered ? 0 : fill_blocks(m + 1);
 #define SFC_WRITE(O, F)                                                                      \
   compact_write_out<O, F><<<grid + extra, 256, 0, s>>>(                                       \
-      P.ids, c.meta, qs.row_off, m, rbase, rend, row_end, max_rows64, P.reject, c.masks, c.info, \
-      c.unit_hits, unit_off, qs.out_base, grid, P.out_ids, P.cap, chunks == 1, P.offsets,     \
-      qs.status, P.host, P.flags_out)
+      P.ids, c.meta, qs.row_off, m, rbase, rend, row_end, c.masks, c.info, c.unit_hits,       \
+      unit_off, qs.out_base, grid, P.out_ids, P.cap, chunks == 1, P.offsets, qs.status,       \
+      P.host, P.flags_out)
       if (ordered) SFC_WRITE(true, false);
       else if (fused_units) SFC_WRITE(false, true);
       else SFC_WRITE(false, false);
