@@ -378,7 +378,9 @@ void sfc_graph_free(sfc_graph* g);   /* NULL-safe; waits for h's stream */
  * sfc_autotune_query: row groups of the exact-test kernel (5 shapes, 3 timed
  *   batches each; ms[5], *best = the chosen shape index), for the bucket of
  *   the batch's candidate rows; buffers as in sfc_query_batch (qset may be
- *   NULL).  best and ms may be NULL.  Synchronises the stream.
+ *   NULL).  best and ms may be NULL.  Synchronises the stream.  (A batch of up
+ *   to 2^17 queries is queued before its rows are known: its bucket is that of
+ *   as many rows a query as the handle's last batch had.)
  */
 sfc_status sfc_autotune_build(const double* xy, uint64_t n, const uint64_t* set_off,
                               uint32_t n_sets, const sfc_options* opt, int* best, double* ms);

@@ -181,13 +181,6 @@ int tuned(TuneOp op, uint64_t size) {
   return it == g_tune.end() ? -1 : it->second;
 }
 
-bool tuned_any(TuneOp op) {
-  std::lock_guard<std::mutex> g(g_tune_mu);
-  for (const auto& t : g_tune)
-    if (t.first.first == (int)op && t.second >= 0) return true;
-  return false;
-}
-
 void set_tuned(TuneOp op, uint64_t size, int value) {
   std::lock_guard<std::mutex> g(g_tune_mu);
   g_tune[{(int)op, bucket(size)}] = value;
@@ -961,6 +954,14 @@ bool rows_expected(const sfc_index* h, uint64_t m) {
   return l.queries == 0 ||
          (double)l.rows * (double)m <= (double)expected_rows(m) * (double)l.queries;
 }
+// The rows for which such a batch's launch shape is chosen: as many a query as the
+// handle's last batch had, its first batch's as expected.
+uint64_t likely_rows(const sfc_index* h, uint64_t m) {
+  const sfc_query_stats& l = h->last;
+  if (l.queries == 0) return expected_rows(m);
+  const uint64_t rows = (uint64_t)((double)l.rows * (double)m / (double)l.queries);
+  return rows ? rows : 1;
+}
 
 sfc_status query_impl(sfc_index* h, const double* q, const double* delta, const uint32_t* qset,
                       uint64_t m, uint64_t* offsets, uint32_t* ids, uint64_t ids_cap,
@@ -985,9 +986,9 @@ sfc_status query_impl(sfc_index* h, const double* q, const double* delta, const 
   sfc::QueryScratch qs;
   if (!sfc::query_scratch_carve(h->ws, m, &qs, slots_of(h))) return SFC_ERR_DEVICE;
   // A capacity within one chunk only (a batch of one chunk has its own
-  // contract), and no launch shape chosen by the exact row count.
+  // contract).
   uint64_t cap_rows = 0;
-  if (m <= kUnreadMax && rows_expected(h, m) && !sfc::tuned_any(sfc::kTuneTestShape)) {
+  if (m <= kUnreadMax && rows_expected(h, m)) {
     cap_rows = expected_rows(m);
     if (!sfc::compact_single_chunk(cap_rows) || ensure_cws(h, cap_rows) != SFC_OK) cap_rows = 0;
   }
@@ -1001,6 +1002,7 @@ sfc_status query_impl(sfc_index* h, const double* q, const double* delta, const 
   if (cap_rows) {
     cp.max_rows = cap_rows;
     cp.device_sized = true;
+    cp.shape_rows = likely_rows(h, m);
     cp.scratch = h->cws;
     cp.reject = sfc::kErrInvalidQuery;   // (the caller gets the error, and keeps its outputs)
     SFC_TRY(sfc::launch_compact(cp, qs, h->stream));
@@ -1011,6 +1013,7 @@ sfc_status query_impl(sfc_index* h, const double* q, const double* delta, const 
   if (host->rows > cap_rows || cap_rows == 0) {   // the exact count is known now
     cp.max_rows = host->rows;
     cp.device_sized = false;
+    cp.shape_rows = cp.max_rows;
     cp.coarse = host->coarse ? 1 : 0;
     st = ensure_cws(h, cp.max_rows);
     if (st != SFC_OK) return st;

@@ -27,7 +27,6 @@ constexpr uint64_t kOccWords = (kOccBits + 31) / 32;
 // tuned(op, size) returns -1 when the bucket has no entry.
 enum TuneOp { kTuneSortItems = 0, kTuneTestShape = 1 };
 int tuned(TuneOp op, uint64_t size);
-bool tuned_any(TuneOp op);   // whether any bucket has an entry
 void set_tuned(TuneOp op, uint64_t size, int value);
 
 // Fill kernel (used instead of hipMemsetAsync so that every step of a batch
@@ -228,6 +227,8 @@ struct CompactPlan {
   uint64_t max_rows = 0;             // device_sized false: the exact row count, processed in
   bool device_sized = false;         // chunks; true: a capacity, the count is read on the
                                      // device and more rows raise kErrOverflow
+  uint64_t shape_rows = 0;           // the test pass's launch shape is that for so many rows
+                                     // (0: for max_rows)
   void* scratch = nullptr;           // compact_scratch_bytes(max_rows)
   uint64_t* offsets = nullptr;
   uint32_t* out_ids = nullptr;

@@ -2071,6 +2071,7 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
   // write_only: the masks and unit offsets of an earlier call on the same
   // batch are still in scratch (one chunk only); run the write pass again.
   if (P.write_only && chunks != 1) return hipErrorInvalidValue;
+  const uint64_t shape_rows = P.shape_rows ? P.shape_rows : P.max_rows;
   // Rows in curve order: only one chunk's hits are kept, so many chunks are
   // processed in query order.
   const bool ordered = chunks == 1 && rows_ordered(P, qs);
@@ -2132,7 +2133,7 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
   if (P.window) SFC_TEST_W(R, I, E, D, C, true);                                           \
   else SFC_TEST_W(R, I, E, D, C, false)
 #define SFC_TEST_SHAPES(E, D, C)              \
-  switch (test_variant(P.max_rows)) {         \
+  switch (test_variant(shape_rows)) {         \
     case 1: SFC_TEST(4, 4, E, D, C); break;   \
     case 2: SFC_TEST(8, 2, E, D, C); break;   \
     case 3: SFC_TEST(2, 8, E, D, C); break;   \
