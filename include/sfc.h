@@ -538,10 +538,11 @@ sfc_status sfc_learned_params(const sfc_index* h, float* params);
    can be checked on small inputs.  Results do not depend on it. */
 sfc_status sfc_debug_chunk_tiles(uint64_t tiles);
 /* Test hook of the construction's sort (process-wide).  force_plain 1: every
-   build uses the plain eight-pass radix sort; 0: builds without point sets
-   first order the keys by their top 32 bits and sort chunks of equal top
-   bits in LDS, falling back to the plain sort when a run of equal top bits
-   is too long (results are the same either way); negative: unchanged.
+   build uses the plain eight-pass radix sort; 0: builds of more than 2^16
+   points, or of point sets, first order the keys by their top 32 bits and sort
+   chunks of equal top bits in LDS, falling back to the plain sort when a run of
+   equal top bits is too long, and smaller builds sort runs of points in LDS and
+   merge them (results are the same every way); negative: unchanged.
    *last_fallback (may be null) receives 1 if the last build fell back. */
 sfc_status sfc_debug_sort_path(int force_plain, int* last_fallback);
 /* Leaf of each key (device keys[count]) by evaluating the router network
