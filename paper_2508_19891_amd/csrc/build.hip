@@ -959,10 +959,13 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_sort(
 // consecutive points in LDS, and an element's place is then its place in its run
 // plus its rank in every other one: elements not after it in earlier runs,
 // elements before it in later ones, so that equal keys keep their order.  At most
-// 16 runs, of up to a workgroup's LDS each: with more the ranks would cost more
-// than the passes' launches.  2^16 points: 22 and 26 us (chains of LDS steps;
-// scattered writes), where the chunked sort's launches took 85; 20003 points of an
-// insertion, sorted by whole keys: 16 and 18 us for 200.
+// 16 runs, of up to a workgroup's LDS each: the ranks grow with the runs.  (Whole
+// builds: 62 us at 2^16 points, 109 for the chunked sort just past them.  With up to
+// 32 runs, half as long, 72 at 2^16 and 69 just past; 81 at 8 * 10^4 and 88 at 2^17,
+// where the chunked sort takes 109 and 110: the two cross somewhere past 2^17.)
+// 2^16 points: 22 and 26 us (chains of LDS steps; scattered writes), where the chunked
+// sort's launches took 85; 20003 points of an insertion, sorted by whole keys: 16 and
+// 18 us for 200.
 constexpr uint32_t kSmallRuns = 16;
 static_assert(kSmallSort == kSmallRuns * kChunkCap, "a run fits a workgroup");
 // (Sixteen waves to a run: a pass is a chain of LDS steps per slot.)
