@@ -534,6 +534,7 @@ sfc::RangePlan range_plan(const sfc_index* h, Views* v, const double* q, const d
   p.qset = qset;
   p.set_off = qset ? h->set_off : nullptr;
   p.n_sets = h->n_sets;
+  if (h->last.queries) p.last_candidates = (double)h->last.candidates / (double)h->last.queries;
   p.record.mode = test_cells(h) ? sfc::kRecordFilter : sfc::kRecordExact;
   p.record.window = h->metric == SFC_METRIC_LINF;
   p.record.qepoch = qepoch;

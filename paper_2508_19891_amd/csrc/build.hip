@@ -201,7 +201,8 @@ static_assert(kOrderBuckets == 1u << kOrderBits && kOrderTile <= 1u << (32 - kOr
 template <int CURVE>
 __global__ __launch_bounds__(kOrderThreads) void order_count(
     const double* __restrict__ q, uint64_t m, const uint64_t* __restrict__ keys, uint64_t n,
-    uint32_t* __restrict__ tags, uint32_t* __restrict__ counts) {
+    uint32_t* __restrict__ tags, uint32_t* __restrict__ counts, const uint32_t* wanted) {
+  if (wanted && *wanted == 0) return;
   __shared__ uint64_t s_key[kOrderBuckets];
   __shared__ uint32_t s_cnt[kOrderBuckets];
   __shared__ uint16_t lut[CURVE == SFC_CURVE_HILBERT ? 1024 : 1];
@@ -249,7 +250,9 @@ __global__ __launch_bounds__(kOrderThreads) void order_count(
 // before; total: per bucket.  A workgroup takes 32 buckets, its 32 rows of
 // threads a run of tiles each.
 __global__ __launch_bounds__(1024) void order_scan(uint32_t* __restrict__ counts, uint32_t tiles,
-                                                   uint32_t* __restrict__ total) {
+                                                   uint32_t* __restrict__ total,
+                                                   const uint32_t* wanted) {
+  if (wanted && *wanted == 0) return;
   __shared__ uint32_t s_sum[32][33];
   const uint32_t c = threadIdx.x & 31, r = threadIdx.x >> 5;
   const uint32_t per = (tiles + 31) / 32;
@@ -387,7 +390,9 @@ __global__ __launch_bounds__(kOrderThreads) void order_place(const uint32_t* __r
                                                              uint64_t m, uint32_t tiles,
                                                              const uint32_t* __restrict__ counts,
                                                              const uint32_t* __restrict__ total,
-                                                             uint32_t* __restrict__ perm) {
+                                                             uint32_t* __restrict__ perm,
+                                                             const uint32_t* wanted) {
+  if (wanted && *wanted == 0) return;
   __shared__ uint32_t s_base[kOrderBuckets];
   __shared__ uint32_t s_w[kOrderThreads / kWave];
   const uint64_t tile = xcd_tile(blockIdx.x, tiles);
@@ -1498,7 +1503,7 @@ size_t order_scratch_bytes(uint64_t m) {
 }
 
 hipError_t order_queries(const double* q, uint64_t m, int curve, const uint64_t* keys, uint64_t n,
-                         uint32_t* perm, void* scratch, hipStream_t s) {
+                         uint32_t* perm, void* scratch, hipStream_t s, const uint32_t* wanted) {
   if (m == 0 || n == 0) return hipErrorInvalidValue;
   const uint64_t tiles = (m + kOrderTile - 1) / kOrderTile;
   char* p = (char*)scratch;
@@ -1509,16 +1514,17 @@ hipError_t order_queries(const double* q, uint64_t m, int curve, const uint64_t*
   ProfScope ps("query_order", s);
   hipError_t e;
 #define SFC_COUNT(C) \
-  order_count<C><<<(uint32_t)tiles, kOrderThreads, 0, s>>>(q, m, keys, n, tags, counts)
+  order_count<C><<<(uint32_t)tiles, kOrderThreads, 0, s>>>(q, m, keys, n, tags, counts, wanted)
   if (curve == SFC_CURVE_MORTON3) SFC_COUNT(SFC_CURVE_MORTON3);
   else if (curve == SFC_CURVE_HILBERT) SFC_COUNT(SFC_CURVE_HILBERT);
   else SFC_COUNT(SFC_CURVE_MORTON);
 #undef SFC_COUNT
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  order_scan<<<kOrderBuckets / 32, 1024, 0, s>>>(counts, (uint32_t)tiles, total);
+  order_scan<<<kOrderBuckets / 32, 1024, 0, s>>>(counts, (uint32_t)tiles, total, wanted);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   order_place<<<(uint32_t)((tiles + 7) / 8 * 8), kOrderThreads, 0, s>>>(tags, m, (uint32_t)tiles,
-                                                                        counts, total, perm);
+                                                                        counts, total, perm,
+                                                                        wanted);
   return hipGetLastError();
 }
 

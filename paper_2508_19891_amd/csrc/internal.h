@@ -91,10 +91,12 @@ hipError_t gather_sorted(const uint32_t* ids, const double* xy, double* out, uin
 // Order of a batch of m queries (centres clamped into the domain) along the
 // curve, as far as the places of their keys among the n >= 1 sorted ones, taken
 // to 11 bits, tell: perm[i] = the i-th query in that order.  scratch holds
-// order_scratch_bytes(m).
+// order_scratch_bytes(m).  wanted (device, may be null): if it holds 0 when the
+// kernels run, they do nothing.
 size_t order_scratch_bytes(uint64_t m);
 hipError_t order_queries(const double* q, uint64_t m, int curve, const uint64_t* keys, uint64_t n,
-                         uint32_t* perm, void* scratch, hipStream_t s);
+                         uint32_t* perm, void* scratch, hipStream_t s,
+                         const uint32_t* wanted = nullptr);
 // Early-termination occupancy bitmap (kOccWords words) of n sorted keys.
 hipError_t build_occupancy(const uint64_t* keys, uint64_t n, uint32_t* occ, hipStream_t s);
 
@@ -158,6 +160,7 @@ struct QueryScratch {
   uint64_t* regions;       //   the same, by workgroup
   uint32_t* pack_cnt;      //   per workgroup: its pairs,
   uint32_t* pack_pre;      //   those before it (+ the total),
+  uint32_t* pack_wanted;   //   whether the queries are listed in curve order,
   uint32_t* pack_pruned;   //   its pruned cells,
   uint64_t* pack_flags;    //   its flags
   int ss;                  // log2 of the slots per query
@@ -198,6 +201,7 @@ struct RangePlan {
   const uint32_t* qset = nullptr;      // query j searches only set qset[j] (positions
   const uint64_t* set_off = nullptr;   // [set_off[s], set_off[s+1]) of the sorted arrays)
   uint32_t n_sets = 0;
+  double last_candidates = -1.0;       // a query of the handle's last batch (negative: none)
   RecordPlan record;
   bool need_rows = false;              // the caller reads the counters before the compaction
   BatchStatus* host = nullptr;         // receives them then (host memory), if not null

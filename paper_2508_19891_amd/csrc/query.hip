@@ -577,6 +577,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   }
 }
 
+// Early termination: whether many cells of a batch's queries hold points, from a
+// sample of 1024 of them (*wanted = 1 or 0).  One workgroup.
+constexpr uint32_t kSampled = 1024;
+template <int CURVE>
+__global__ __launch_bounds__(kSampled) void sample_cells(const double2* __restrict__ q,
+                                                         const double* __restrict__ delta,
+                                                         uint64_t m,
+                                                         const uint32_t* __restrict__ occ,
+                                                         uint32_t least, uint32_t* wanted) {
+  __shared__ uint16_t lut[CURVE == SFC_CURVE_HILBERT ? 1024 : 1];
+  __shared__ uint32_t s_sum[kSampled / kWave];
+  const uint32_t tid = threadIdx.x;
+  if (CURVE == SFC_CURVE_HILBERT) lut[tid] = kHilbertLutConst.v[tid];
+  __syncthreads();
+  const uint64_t j = tid * m / kSampled;
+  const double2 qq = q[j];
+  const double d = delta[j];
+  uint32_t sum = 0;
+  if (finite64(qq.x) && finite64(qq.y) && finite64(d) && d >= 0.0) {
+    uint64_t lo[4], hi[4];
+    uint32_t cx[4], cy[4], pr = 0;
+    int64_t box[4];
+    int L = 0;
+    sum = (uint32_t)query_cells<CURVE>(lut, qq.x, qq.y, d, lo, hi, cx, cy, &L, box, occ, &pr);
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if (lane_id() == 0) s_sum[tid >> 6] = sum;
+  __syncthreads();
+  if (tid == 0) {
+    for (uint32_t w = 1; w < kSampled / kWave; ++w) sum += s_sum[w];
+    *wanted = sum >= least ? 1u : 0u;
+  }
+}
+
 // The cells of every query that survive early termination, as (query, cell)
 // pairs (4 * query + cell) for the search.  One
 // thread per query; block b lists its pairs at the start of its own region
@@ -585,13 +620,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
 // query order), its flags in blk_flags[b].  No atomic on a shared word:
 // one per block, from every block of the grid, serialises across the XCDs.
 // The query's slots are cleared and its record is written here; invalid
-// queries (and epochs) raise the flag and list no cell.
+// queries (and epochs) raise the flag and list no cell.  perm (may be null): the
+// queries in the order to list them in (if *wanted, wanted given).
 template <int CURVE, bool REFINE>
 __global__ __launch_bounds__(256) void cells_pack(
     const double2* __restrict__ q, const double* __restrict__ delta, uint64_t m,
     const uint32_t* __restrict__ occ, uint64_t* __restrict__ pairs,
     uint32_t* __restrict__ blk_cnt, uint32_t* __restrict__ blk_pruned,
-    uint64_t* __restrict__ blk_flags, RecordPlan record, uint2* __restrict__ slots) {
+    uint64_t* __restrict__ blk_flags, RecordPlan record, uint2* __restrict__ slots,
+    const uint32_t* __restrict__ perm, const uint32_t* wanted) {
   __shared__ uint16_t lut[CURVE == SFC_CURVE_HILBERT ? 1024 : 1];
   __shared__ uint32_t s_cnt[4];
   __shared__ uint32_t s_pr[4];
@@ -599,7 +636,8 @@ __global__ __launch_bounds__(256) void cells_pack(
   if (CURVE == SFC_CURVE_HILBERT)
     for (int i = threadIdx.x; i < 1024; i += 256) lut[i] = kHilbertLutConst.v[i];
   __syncthreads();
-  const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  const uint64_t at = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  const uint64_t j = perm && at < m && (!wanted || *wanted) ? perm[at] : at;
   uint32_t nr = 0, pr = 0;
   bool bad = false, coarse = false;
   if (j < m) {
@@ -1797,7 +1835,8 @@ bool query_scratch_carve(void* base, uint64_t m, QueryScratch* qs, uint32_t slot
   qs->pack_cnt = (uint32_t*)(qs->pack_flags + npack);
   qs->pack_pruned = qs->pack_cnt + npack;
   qs->pack_pre = qs->pack_pruned + npack;
-  e += align256(npack * 20 + 4);
+  qs->pack_wanted = qs->pack_pre + npack + 1;
+  e += align256(npack * 20 + 8);
   p += (size_t)(e - aux) > order_end ? (size_t)(e - aux) : order_end;
   qs->ss = 2;
   qs->perm_made = false;
@@ -1902,21 +1941,43 @@ hipError_t finish_ranges(QueryScratch& qs, bool need_rows, BatchStatus* host, hi
 
 }  // namespace
 
-// Whether a batch's search takes its queries in curve order.  Only the binary
-// search gains (its probes of a workgroup then meet in the same lines), and
-// only if the order (23 us for 2 * 10^5 queries, 33 for 10^6) costs less: 2^20
-// queries over 2^24 points 0.76 ms against 0.88 (c 1 to 100; 10^3: 1.39 against
-// 1.79), 2^18 0.29 against 0.30 (0.46 against 0.53), 2^17 0.188 against 0.182
-// (0.288 against 0.299), 2^17 over 2^20 0.160 against 0.147.  The learned
-// index and the search tree probe less (2^22 queries over 2^26 points: learned
-// search 0.63 ms against 0.67, the order 0.08), batches of point sets are grouped
-// by set as a rule, and early termination leaves too few cells (2^20 windows over
-// 2^24 points: 0.41 ms in order, 0.31 without).
+// Whether a batch's search takes its queries in curve order: where the order (23 us
+// for 2 * 10^5 queries, 33 for 10^6) costs less than the lines it saves, as the
+// probes of a workgroup then meet in the same ones.
+//   Binary search: 2^20 queries over 2^24 points 0.76 ms against 0.88 (c 1 to 100;
+// 10^3: 1.39 against 1.79), 2^18 0.29 against 0.30 (0.46 against 0.53), 2^17 0.188
+// against 0.182 (0.288 against 0.299), 2^17 over 2^20 0.160 against 0.147.
+//   The learned index and the search tree probe less: only with refined ranges, whose
+// crowded cells take more searches, and many candidates a query.  How many is known
+// from the handle's last batch alone.  2^20 queries over 2^24 points, ordered against
+// not: search tree 1.47 ms against 1.95 with 360 candidates a query, 0.66 against 0.65
+// with 100, 0.25 against 0.21 with hardly any; learned index 1.39 against 1.63, 0.67
+// against 0.72, 0.25 against 0.20; 2^18 queries of 360 0.51 against 0.57 and 0.48 against
+// 0.49; not refined 1.80 against 1.82 (360), 0.64 against 0.58 (100).  A handle's first
+// batch through the search tree is ordered from 2^20 queries on.
+//   Batches of point sets are grouped by set as a rule; early termination has its own
+// rule (below).
 constexpr uint64_t kOrderMin = (1u << 17) + 1;
 constexpr uint64_t kOrderPoints = 1u << 20;
-bool search_ordered(const RangePlan& P, bool binary, uint64_t m) {
-  return binary && !P.occ && !P.qset && m >= kOrderMin && P.n >= kOrderPoints;
+constexpr uint64_t kOrderFirst = 1u << 20;
+constexpr double kOrderCandidates = 128.0;
+bool search_ordered(const RangePlan& P, bool binary, bool stree, uint64_t m) {
+  if (P.occ || P.qset || m < kOrderMin || P.n < kOrderPoints) return false;
+  if (binary) return true;
+  if (!P.refine || P.dim != 2) return false;
+  return P.last_candidates < 0.0 ? stree && m >= kOrderFirst
+                                 : P.last_candidates >= kOrderCandidates;
 }
+
+// With early termination the queries' cells are listed in curve order if the handle's
+// last batch had many candidates, and in its first batch if a sample of 1024 queries
+// has at least as many cells that hold points (then known on the device alone, which
+// orders the queries or not): 2^20 refined queries over 2^24 points where the points
+// are, 360 candidates each, 1.57 ms against 2.84, 100 each 0.77 against 0.92, 40 each
+// 0.58 against 0.64; 2^18 of them 0.53 against 0.77 and 0.30 against 0.33.  Among cells
+// that are mostly empty the search is short: 0.25 ms against 0.22 (sampled: 0.26).
+constexpr double kListedCandidates = 16.0;
+constexpr uint32_t kListedCells = 1024;
 
 // Whether a batch's rows are processed in curve order: the test pass gains a
 // third (0.46 -> 0.30 ms for the 4 * 10^8 candidates of 2 * 10^5 windows), but
@@ -1951,7 +2012,7 @@ hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
   rec.rec = qs.rec;
   if (dbg) rec = RecordPlan{};
   const uint32_t* perm = nullptr;
-  qs.perm_made = !dbg && search_ordered(P, !learned && !stree, m);
+  qs.perm_made = !dbg && search_ordered(P, !learned && !stree, stree, m);
   if (qs.perm_made) {
     if ((e = order_queries(P.q, m, d3 ? SFC_CURVE_MORTON3 : P.curve, P.keys, P.n, qs.perm,
                            qs.order_scratch, s)) != hipSuccess)
@@ -1984,10 +2045,30 @@ hipError_t launch_ranges(const RangePlan& P, QueryScratch& qs, hipStream_t s) {
   const uint32_t* pair_total = nullptr;
   if (dense) {
     const uint32_t qb = (uint32_t)((m + 255) / 256);
+    const uint32_t *listed = nullptr, *wanted = nullptr;
+    if (m >= kOrderMin && P.n >= kOrderPoints &&
+        (P.last_candidates < 0.0 || P.last_candidates >= kListedCandidates)) {
+      if (P.last_candidates < 0.0) {
+        wanted = qs.pack_wanted;
+        ProfScope ps("cells_sample", s);
+        if (P.curve == SFC_CURVE_HILBERT)
+          sample_cells<SFC_CURVE_HILBERT><<<1, kSampled, 0, s>>>(
+              (const double2*)P.q, P.delta, m, P.occ, kListedCells, qs.pack_wanted);
+        else
+          sample_cells<SFC_CURVE_MORTON><<<1, kSampled, 0, s>>>(
+              (const double2*)P.q, P.delta, m, P.occ, kListedCells, qs.pack_wanted);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+      }
+      if ((e = order_queries(P.q, m, P.curve, P.keys, P.n, qs.perm, qs.order_scratch, s,
+                             wanted)) != hipSuccess)
+        return e;
+      listed = qs.perm;
+    }
     ProfScope ps("cells_pack", s);
 #define SFC_CELLS(C, R)                                                                    \
   cells_pack<C, R><<<qb, 256, 0, s>>>((const double2*)P.q, P.delta, m, P.occ, qs.regions,  \
-                                      qs.pack_cnt, qs.pack_pruned, qs.pack_flags, rec, qs.slots)
+                                      qs.pack_cnt, qs.pack_pruned, qs.pack_flags, rec, qs.slots, \
+                                      listed, wanted)
     if (P.curve == SFC_CURVE_HILBERT) {
       if (refine) SFC_CELLS(SFC_CURVE_HILBERT, true);
       else SFC_CELLS(SFC_CURVE_HILBERT, false);
