@@ -712,7 +712,8 @@ def main():
         # test: the test kernel then reads 16 B per candidate.
         cand_q = stats["candidates"]
         ct_x = kern_qx.get("compact_test", float("nan"))
-        exact_bytes = 16 * cand_q + 24 * m + 12 * 8 * m + cand_q // 8 + 4 * math.ceil(cand_q / 4096)
+        # as compact_test's below, with 16-byte points in place of the cells
+        exact_bytes = 16 * cand_q + 32 * m + 8 * 8 * m + cand_q // 8 + 4 * math.ceil(cand_q / 1024)
         cell_filter = {
             "step": "one query batch over a built index (refined ranges, binary search)",
             "ms_per_batch_cells": ms_qb, "ms_per_batch_exact": ms_qx,
@@ -725,7 +726,7 @@ def main():
     # Algorithmic bytes per step of each kernel (what the method must move).
     cand, rep = stats["candidates"], total
     passes = round(kern["scatter_pass"][0] / args.steps)   # radix passes per build
-    tiles = math.ceil(cand / 4096)
+    units = math.ceil(cand / 1024)   # a wave's 32 rows of 32 candidates share a count of hits
     slots = 8 * m   # refined layout: eight slots (begin u32, count u32) per query
     algo = {
         "keygen_tiles": 16 * n + 8 * n + 16 * n,            # points in, keys and input-order copy out
@@ -733,10 +734,11 @@ def main():
         "scatter_pass": passes * 24 * n,                    # (key+id) in and out per pass
         # queries in; begin+count per slot and the 32-byte record per query
         "ranges_search": 24 * m + 8 * slots + 32 * m,
-        # default: each candidate's 8-byte grid cell, the 32-byte filter record
-        # of its query per row (the rare undecided candidates read 16 B more)
-        "compact_test": 8 * cand + 32 * m + 12 * slots + cand // 8 + 4 * tiles,
-        "compact_write": cand // 8 + 8 * tiles + 4 * rep + 4 * rep + 8 * (m + 1) + 12 * slots,
+        # default: each candidate's 8-byte grid cell, each query's 32-byte filter
+        # record, the slots' ranges (in rows of 32: 10 B a row), a mask bit per
+        # candidate and a count per unit (the rare undecided candidates read 16 B more)
+        "compact_test": 8 * cand + 32 * m + 8 * slots + cand // 8 + 4 * units,
+        "compact_write": cand // 8 + 8 * units + 4 * rep + 4 * rep + 8 * (m + 1) + 8 * slots,
     }
     if "chunk_sort" in kern:
         # Chunks of equal top key bits: (key+id) in and out, the grid cell out.

@@ -1063,14 +1063,14 @@ __device__ __forceinline__ void put_verdict(BatchStatus* status, uint64_t max_ro
 
 // Row descriptors of a launch's rows [rbase, rend): for row r of slot s, the
 // first sorted index of the row and the query (row_meta) and the number of its
-// candidates (row_info), and the first row of every place (row_off).  One block per K * 256 slots (whole
-// queries: 2^ss slots each), a thread's K slots consecutive; the block's
-// rows are spread over its waves, 64 at a time: the slots that start among them
-// mark their first row in LDS, and a row's slot is that of the last mark up to it.
-// FUSED (at most kFusedBlocks blocks): the block sums the rows of the
-// blocks before it itself and block 0 gathers the batch's counters, so that a
-// small batch takes no batch_scan launch (5 us; with more blocks the repeated
-// sums would cost more).
+// candidates (row_info), and the first row of every place (row_off).  One block
+// per K * 256 slots (whole queries: 2^ss slots each), a thread's K slots
+// consecutive; the block's rows are spread over its waves, 64 at a time: the slots
+// that start among them mark their first row in LDS, and a row's slot is that of
+// the last mark up to it.  FUSED (at most kFusedBlocks blocks): the block sums the
+// rows of the blocks before it itself and block 0 gathers the batch's counters, so
+// that a small batch takes no batch_scan launch (5 us; with more blocks the
+// repeated sums would cost more).
 constexpr uint32_t kFusedBlocks = 1024;
 
 template <int K, bool FUSED>
@@ -1308,9 +1308,9 @@ __device__ __forceinline__ uint32_t unit_rows(uint64_t have, uint64_t row0) {
 // latency of its chain of loads (descriptor, record, candidates).  So the lanes
 // hold the 32 rows' descriptors and records, loaded for all rows at once and one
 // unit ahead, and a step's lanes get their row's words by a broadcast in each row
-// of 16 lanes; STEPS
-// steps' candidates are read at a time, a group's loads leaving before the
-// previous group is tested; the two verdicts are masks straight from the compares.
+// of 16 lanes; STEPS steps' candidates are read at a time, a group's loads leaving
+// before the previous group is tested; the two verdicts are masks straight from the
+// compares.
 // Measured (rows of 64, one at a time, before): 0.302 ms for the 4 * 10^8
 // candidates of 2 * 10^5 windows in curve order (0.282), the caches' 12 TB/s its
 // limit; 0.32 ms for 3.7 * 10^8 of 2^20 queries over 2^24 points (0.365); 0.508
@@ -1817,7 +1817,8 @@ bool query_scratch_carve(void* base, uint64_t m, QueryScratch* qs, uint32_t slot
   qs->blk_place = qs->blk_rows64 + nblk;
   qs->blk_learned = (uint32_t*)(qs->blk_place + nblk);
   p += align256(nblk * 44);
-  qs->groups = p;                 p += align256((nblk + kGroupBlocks - 1) / kGroupBlocks * sizeof(GroupSums));
+  qs->groups = p;
+  p += align256((nblk + kGroupBlocks - 1) / kGroupBlocks * sizeof(GroupSums));
   qs->rec = p;                    p += align256(m * 32);
   qs->perm = (uint32_t*)p;        p += align256(m * 4);
   qs->out_base = (uint64_t*)p;    p += align256(m * 8);
@@ -2189,10 +2190,9 @@ hipError_t launch_compact(const CompactPlan& P, const QueryScratch& qs0, hipStre
     if (!P.write_only) {
       ProfScope ps("expand_rows", s);
 #define SFC_EXPAND(K, F)                                                                     \
-  expand_rows<K, F><<<query_blocks(qs), 256, 0, s>>>(qs.row_off, qs.slots, perm, blk_rows, \
-                                                     qs.blk_off, groups, stats_of(qs), qs.status, m, \
-                                                     qs.ss, rbase,                           \
-                                                     row_end, max_rows64, P.reject, c.meta, c.info)
+  expand_rows<K, F><<<query_blocks(qs), 256, 0, s>>>(                                        \
+      qs.row_off, qs.slots, perm, blk_rows, qs.blk_off, groups, stats_of(qs), qs.status, m,  \
+      qs.ss, rbase, row_end, max_rows64, P.reject, c.meta, c.info)
       switch (slots_per_thread(qs)) {
         case 1: if (qs.fused) SFC_EXPAND(1, true); else SFC_EXPAND(1, false); break;
         case 2: if (qs.fused) SFC_EXPAND(2, true); else SFC_EXPAND(2, false); break;
