@@ -1976,7 +1976,10 @@ bool search_ordered(const RangePlan& P, bool binary, bool stree, uint64_t m) {
 // orders the queries or not): 2^20 refined queries over 2^24 points where the points
 // are, 360 candidates each, 1.57 ms against 2.84, 100 each 0.77 against 0.92, 40 each
 // 0.58 against 0.64; 2^18 of them 0.53 against 0.77 and 0.30 against 0.33.  Among cells
-// that are mostly empty the search is short: 0.25 ms against 0.22 (sampled: 0.26).
+// that are mostly empty the search is short: 0.25 ms against 0.22.  (10^6 windows over
+// 10^7 points, mostly empty: the first batch takes 0.27 ms, 0.25 without the sample and
+// the order's launches, which do nothing then; the sample inside order_count, by every
+// workgroup, takes as long.)
 constexpr double kListedCandidates = 16.0;
 constexpr uint32_t kListedCells = 1024;
 
